@@ -340,17 +340,25 @@ int run_score_span(const void *X, int64_t M, int64_t K, int bc, const SpanGeom &
   return check_launch();
 }
 
-// Launch geometry of score_kernel for vectors of V elements; *gy = passes of the grid.
-ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int64_t *gy_out) {
+// Launch geometry of score_kernel for vectors of V elements in a launch of `tensors` tensors; *gy = passes of
+// the grid.
+ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensors, int64_t *gy_out) {
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
   ScoreGeom g;
   const int vpb = bc / V;
   g.direct = 0;
   // large matrices take the direct body: rs lanes share a vector column of a block so that the
-  // tensor has at least 64 Ki lanes, and every lane still has a few rows
+  // tensor has at least `want` lanes, and every lane still has a few rows.  A tensor on its own wants
+  // 256 Ki lanes, half of what the chip holds: with 64 Ki the loads on their way (8 x 16 bytes a lane)
+  // do not cover the latency of HBM ([25088 x 384] bf16, 32x32 blocks: 10.9 us with 64 Ki lanes, 8.5 with
+  // 128 Ki, 6.8 with 256 Ki, 7.1 with 512 Ki; [25088 x 1536]: 22.4 / 22.8 / 16.7 / 18.7).  Tensors that
+  // share a launch fill the chip together, and more lanes a block only cost exchanges there (24 tensors:
+  // 188 us with 64 Ki lanes each, 202 with 128 Ki).
   if (vpb >= 1 && vpb <= 64 && (vpb & (vpb - 1)) == 0 && vpb * V == bc) {
+    int64_t want = 262144 / tensors;
+    if (want < 65536) want = 65536;
     int rs = 1;
-    while (nbr * nbc * vpb * rs < 65536 && vpb * rs * 2 <= 64 && rs * 2 * 4 <= br) rs *= 2;
+    while (nbr * nbc * vpb * rs < want && vpb * rs * 2 <= 64 && rs * 2 * 4 <= br) rs *= 2;
     const int64_t lanes = nbr * nbc * vpb * rs;
     if (lanes >= 16384 && lanes < (int64_t(1) << 31)) {
       g.direct = 1;
@@ -390,7 +398,7 @@ int run_score(const void *X, int64_t M, int64_t K, int64_t ldx, int br, int bc, 
               hipStream_t s) {
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
   int64_t gy;
-  const ScoreGeom g = score_geometry(V, M, K, br, bc, &gy);
+  const ScoreGeom g = score_geometry(V, M, K, br, bc, 1, &gy);
   dim3 grid((unsigned)g.nchunks, (unsigned)gy, 1);
   hipLaunchKernelGGL((score_kernel<T, V>), grid, dim3(g.direct ? kScoreThreads : g.vct * g.gb * g.rb), 0, s,
                      static_cast<const T *>(X), M, K, ldx, br, bc, nbr, nbc, g, scores);
@@ -510,7 +518,7 @@ int launch_score_batched(const ScoreJob *jobs, int n, int dtype, hipStream_t s) 
         if (kind == 0) {
           ScoreItem &it = gb.it[m];
           int64_t gy;
-          it.g = score_geometry(key, j.M, j.K, j.br, j.bc, &gy);
+          it.g = score_geometry(key, j.M, j.K, j.br, j.bc, n, &gy);
           it.X = j.X;
           it.scores = j.scores;
           it.M = j.M; it.K = j.K; it.ldx = j.ldx; it.nbr = nbr; it.nbc = nbc;
