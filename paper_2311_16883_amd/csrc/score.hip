@@ -13,6 +13,7 @@ namespace bsr {
 namespace {
 
 constexpr int kScoreThreads = 256;
+constexpr int kRowClasses = 8;     // rows of a block that are eight apart are summed by one lane (score_direct_body)
 
 struct ScoreGeom {
   int jc;    // block-columns per workgroup
@@ -92,18 +93,21 @@ __device__ __forceinline__ void score_body(
   }
 }
 
-// Large matrices: bc / V * rs lanes own a block -- lane (part, u) reads vector u of the rows
-// part, part + rs, ... of the block, eight loads on their way at a time (consecutive lanes
-// read consecutive vectors of a matrix row, whole 64-byte pieces or more) -- and add their sums
-// with a butterfly of lane exchanges in a fixed order.  No LDS, no barrier, every lane busy.
-// rs (a power of two, g.gb) is chosen so that the tensor has enough lanes for the chip.
-// wg = index of the workgroup among the ceil(nbr * nbc * (bc / V) * rs / 256) of its tensor.
-template <typename T, int V>
+// Large matrices: bc / V * RS lanes own a block -- lane (part, u) reads vector u of the rows
+// part, part + RS, ... of the block, eight loads on their way at a time (consecutive lanes
+// read consecutive vectors of a matrix row, whole 64-byte pieces or more).  No LDS, no barrier,
+// every lane busy.  RS (1, 2, 4 or 8, g.gb) is chosen so that the tensor has enough lanes for the chip.
+// The sum does not depend on it: the rows r, r + 8, ... of a vector column are added top to
+// bottom, then the eight such sums pairwise (r and r + 4, r and r + 2, r and r + 1), then the vector
+// columns; a step of that is an addition inside a lane or a lane exchange, depending on RS.
+// wg = index of the workgroup among the ceil(nbr * nbc * (bc / V) * RS / 256) of its tensor.
+template <typename T, int V, int RS>
 __device__ __forceinline__ void score_direct_body(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
-    int64_t nbc, int rs, double *__restrict__ scores, uint32_t wg) {
+    int64_t nbc, double *__restrict__ scores, uint32_t wg) {
+  constexpr int kOwn = kRowClasses / RS;                   // row classes a lane owns
   const uint32_t vpb = (uint32_t)(bc / V);                 // lanes across a block row: a power of two
-  const uint32_t lpb = vpb * (uint32_t)rs;                 // lanes per block: a power of two, at most 64
+  const uint32_t lpb = vpb * (uint32_t)RS;                 // lanes per block: a power of two, at most 64
   const uint32_t per_row = (uint32_t)nbc * lpb;            // lanes per block-row
   const uint32_t gid = wg * (uint32_t)kScoreThreads + threadIdx.x;
   const uint32_t i = gid / per_row, c = gid - i * per_row;
@@ -113,37 +117,56 @@ __device__ __forceinline__ void score_direct_body(
   const int64_t m0 = (int64_t)i * br;
   const int rows = live ? (int)((M - m0) < br ? (M - m0) : br) : 0;
   const T *p = X + m0 * ldx + col;
-  double acc0 = 0.0, acc1 = 0.0;                           // even and odd elements of the vectors
+  double acc[kOwn];
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) acc[k] = 0.0;
   // (eight, not more: with sixteen the registers they need leave room for three waves per SIMD only,
   // and a workgroup has nothing in flight while it adds up)
   constexpr int kInFlight = 8;
-  for (int r0 = (int)part; r0 < rows; r0 += kInFlight * rs) {
+  for (int r0 = (int)part; r0 < rows; r0 += kInFlight * RS) {
     Vec<T, V> v[kInFlight];
 #pragma unroll
     for (int b = 0; b < kInFlight; ++b)
-      if (r0 + b * rs < rows) v[b] = load_stream(reinterpret_cast<const Vec<T, V> *>(p + (int64_t)(r0 + b * rs) * ldx));
+      if (r0 + b * RS < rows) v[b] = load_stream(reinterpret_cast<const Vec<T, V> *>(p + (int64_t)(r0 + b * RS) * ldx));
 #pragma unroll
     for (int b = 0; b < kInFlight; ++b) {
-      if (r0 + b * rs < rows) {
+      if (r0 + b * RS < rows) {
 #pragma unroll
         for (int q = 0; q < V; ++q) {
           const double x = (double)elem_to_float<T>(v[b].e[q]);
-          if (q & 1) acc1 = fma(x, x, acc1);
-          else acc0 = fma(x, x, acc0);
+          acc[b % kOwn] = fma(x, x, acc[b % kOwn]);
         }
       }
     }
   }
-  double sum = acc0 + acc1;
-  for (uint32_t o = 1; o < lpb; o <<= 1) sum += __shfl_xor(sum, (int)o);
+#pragma unroll
+  for (int half = kOwn / 2; half >= 1; half /= 2)
+#pragma unroll
+    for (int k = 0; k < half; ++k) acc[k] += acc[k + half];
+  double sum = acc[0];
+#pragma unroll
+  for (int o = RS / 2; o >= 1; o /= 2) sum += __shfl_xor(sum, o * (int)vpb);
+  for (uint32_t o = 1; o < vpb; o <<= 1) sum += __shfl_xor(sum, (int)o);
   if (live && within == 0) scores[(int64_t)i * nbc + j] = sum;
+}
+
+template <typename T, int V>
+__device__ __forceinline__ void score_direct(
+    const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
+    int64_t nbc, int rs, double *__restrict__ scores, uint32_t wg) {
+  switch (rs) {
+    case 1: score_direct_body<T, V, 1>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
+    case 2: score_direct_body<T, V, 2>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
+    case 4: score_direct_body<T, V, 4>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
+    default: score_direct_body<T, V, 8>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
+  }
 }
 
 template <typename T, int V>
 __global__ __launch_bounds__(kScoreThreads) void score_kernel(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
     int64_t nbc, ScoreGeom g, double *__restrict__ scores) {
-  if (g.direct) score_direct_body<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g.gb, scores, blockIdx.x);
+  if (g.direct) score_direct<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g.gb, scores, blockIdx.x);
   else score_body<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g, scores, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
@@ -169,7 +192,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_batched_kernel(ScoreBatch
   const ScoreItem &it = b.it[i];
   const uint32_t local = blockIdx.x - it.wg_begin;
   if (it.g.direct) {
-    score_direct_body<T, V>(static_cast<const T *>(it.X), it.M, it.K, it.ldx, it.br, it.bc, it.nbr, it.nbc, it.g.gb, it.scores,
+    score_direct<T, V>(static_cast<const T *>(it.X), it.M, it.K, it.ldx, it.br, it.bc, it.nbr, it.nbc, it.g.gb, it.scores,
                             local);
     return;
   }
@@ -358,7 +381,7 @@ ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensor
     int64_t want = 262144 / tensors;
     if (want < 65536) want = 65536;
     int rs = 1;
-    while (nbr * nbc * vpb * rs < want && vpb * rs * 2 <= 64 && rs * 2 * 4 <= br) rs *= 2;
+    while (nbr * nbc * vpb * rs < want && vpb * rs * 2 <= 64 && rs * 2 * 4 <= br && rs < kRowClasses) rs *= 2;
     const int64_t lanes = nbr * nbc * vpb * rs;
     if (lanes >= 16384 && lanes < (int64_t(1) << 31)) {
       g.direct = 1;
