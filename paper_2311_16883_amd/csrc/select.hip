@@ -17,9 +17,10 @@
 // when the caller can bracket the threshold's key (see there).
 //
 // Small inputs (<= 12288 blocks) and per-group selection: one workgroup per
-// ranking group, bracketed_select between the group's smallest and largest key.
+// ranking group.  Keys are read once, four consecutive ones per thread, and stay
+// in registers; bracketed_select between the group's smallest and largest key.
 //
-// Large inputs: two grid-wide passes and a one-workgroup finish, three launches.
+// Large inputs: two grid-wide passes, two launches.
 //   pass 1  every workgroup draws the same small sample, takes from it two order
 //           statistics lo <= hi that bracket the rank of the threshold, and
 //           counts its slice of the keys into 256 buckets: bucket 0 below lo, the
@@ -30,13 +31,16 @@
 //   pass 2  every workgroup adds up the counts, finds the bucket that holds the
 //           n_keep-th largest key, keeps the buckets above it, prunes the ones
 //           below and appends the keys inside it to a candidate list (one atomic
-//           per workgroup).
-//   finish  one workgroup stages the candidates in LDS and selects among them
-//           exactly, with the bucket's key range as a bracket: 32-bit codes linear
-//           in the key, one 8-bit radix pass as a rule, then a ranking of the
-//           handful that share the threshold's code through lane reads.  The
+//           per workgroup).  The workgroup that finishes last selects among the
+//           candidates exactly, with the bucket's key range as a bracket: 32-bit
+//           codes linear in the key, one radix pass as a rule, then a ranking of
+//           the handful that share the threshold's code through lane reads.  The
 //           general radix select remains the fallback when a bracket misses or
 //           too many keys are equal.
+//
+// What bounds it is latency: a launch, a trip to memory, a handful of barriers.
+// So lane exchanges inside a wave are DPP moves (no LDS round trips), a key is
+// read once per pass with 16-byte loads, and mask bytes leave four at a time.
 #include "common.h"
 
 namespace bsr {
@@ -46,10 +50,12 @@ namespace {
 constexpr int kDigitBits = 12;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kCap = 1024;       // candidates ranked in LDS
-constexpr int kSample = 256;
-constexpr int kGridThreads = 256;
-constexpr int kBuckets = 256;    // buckets of the grid-wide passes (one per thread)
-constexpr int kStage = 1024;     // candidates the last workgroup stages in LDS
+constexpr int kSample = 128;
+constexpr int kGridThreads = 1024;
+constexpr int kBuckets = 256;    // buckets of the grid-wide passes
+constexpr int kMaxGridWgs = 256; // workgroups of the grid-wide passes, at most
+constexpr int kFinishBits = 10;  // digit of the selection among up to kCap candidates: a bin per thread
+constexpr int kFinishKeys = 8;   // of longer lists, candidates per thread that are taken into registers
 
 typedef unsigned __int128 u128;
 
@@ -68,15 +74,95 @@ struct AllScores {
   __device__ __forceinline__ uint64_t key(uint32_t e) const { return score_key(scores[e]); }
   __device__ __forceinline__ uint32_t idx(uint32_t e) const { return e; }
 };
+// (written by workgroups of the same launch, see store_shared)
 struct Candidates {
+  const uint64_t *keys;
+  const uint32_t *idxs;
+  __device__ __forceinline__ uint64_t key(uint32_t e) const {
+    return __hip_atomic_load(&keys[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ uint32_t idx(uint32_t e) const {
+    return __hip_atomic_load(&idxs[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
+
+struct Staged {
   const uint64_t *keys;
   const uint32_t *idxs;
   __device__ __forceinline__ uint64_t key(uint32_t e) const { return keys[e]; }
   __device__ __forceinline__ uint32_t idx(uint32_t e) const { return idxs[e]; }
 };
 
+// Values that one workgroup hands to another of the same launch: relaxed agent-scope atomic stores go
+// through the L2 of their XCD to where every XCD sees them.  Once a wave has waited for its stores
+// (stores_done), a flag it raises afterwards tells a reader -- which uses agent-scope atomic loads --
+// that they are there.  A release fence would do the same by writing the whole L2 back.
+template <typename U>
+__device__ __forceinline__ void store_shared(U *p, U v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// ---- lane exchanges inside a wave by DPP: rows of 16 lanes shifted by 1, 2, 4, 8, then the last lane
+// of a row broadcast to the next row (0x142), that of lane 31 to the upper half (0x143) ----
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t identity, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, CTRL, ROWS, 0xF, false);
+}
+// inclusive prefix sum over the 64 lanes
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += dpp<0x111, 0xF>(0u, v);
+  v += dpp<0x112, 0xF>(0u, v);
+  v += dpp<0x114, 0xF>(0u, v);
+  v += dpp<0x118, 0xF>(0u, v);
+  v += dpp<0x142, 0xA>(0u, v);
+  v += dpp<0x143, 0xC>(0u, v);
+  return v;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return lane_value(wave_scan(v), 63); }
+template <bool MAX>
+__device__ __forceinline__ uint32_t pick(uint32_t a, uint32_t b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); }
+// largest / smallest of the 64 lanes, in every lane
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {
+  constexpr uint32_t id = MAX ? 0u : 0xFFFFFFFFu;
+  v = pick<MAX>(v, dpp<0x111, 0xF>(id, v));
+  v = pick<MAX>(v, dpp<0x112, 0xF>(id, v));
+  v = pick<MAX>(v, dpp<0x114, 0xF>(id, v));
+  v = pick<MAX>(v, dpp<0x118, 0xF>(id, v));
+  v = pick<MAX>(v, dpp<0x142, 0xA>(id, v));
+  v = pick<MAX>(v, dpp<0x143, 0xC>(id, v));
+  return lane_value(v, 63);
+}
+
+// Keys of elements e .. e + 3 (0 beyond n).  `wide`: scores is 16-byte aligned (e is a multiple of four).
+__device__ __forceinline__ void load_keys4(const double *__restrict__ scores, uint32_t e, uint32_t n, bool wide,
+                                           uint64_t *k) {
+  if (wide && e + 4 <= n) {
+    const double2 a = *reinterpret_cast<const double2 *>(scores + e), b = *reinterpret_cast<const double2 *>(scores + e + 2);
+    k[0] = score_key(a.x); k[1] = score_key(a.y); k[2] = score_key(b.x); k[3] = score_key(b.y);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k[q] = e + q < n ? score_key(scores[e + q]) : 0ull;
+  }
+}
+// Mask bytes of elements e .. e + 3: the bytes of `word` whose bit in `own` is set (all four leave in one
+// store when mask is 4-byte aligned, `wide`).
+__device__ __forceinline__ void store_mask4(uint8_t *__restrict__ mask, uint32_t e, bool wide, uint32_t own, uint32_t word) {
+  if (wide && own == 0xFu) {
+    *reinterpret_cast<uint32_t *>(mask + e) = word;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (own & (1u << q)) mask[e + q] = (uint8_t)(word >> (8 * q));
+  }
+}
+
 struct SelectShared {
-  uint32_t hist[kBins];
+  __attribute__((aligned(16))) uint32_t hist[kBins];
   uint64_t ckey[kCap];
   uint32_t cidx[kCap];
   uint32_t wave_tot[16];
@@ -87,16 +173,12 @@ struct SelectShared {
 template <int THREADS>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *wave_tot) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t incl = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t o = __shfl_up(incl, d, 64);
-    if (lane >= d) incl += o;
-  }
+  const uint32_t incl = wave_scan(v);
   if (lane == 63) wave_tot[wave] = incl;
   __syncthreads();
-  uint32_t base = 0;
-  for (int w = 0; w < wave; ++w) base += wave_tot[w];
+  const uint32_t tot = wave_tot[lane & (THREADS / 64 - 1)];
+  const uint32_t upto = wave_scan(lane < THREADS / 64 ? tot : 0u);
+  const uint32_t base = wave > 0 ? lane_value(upto, __builtin_amdgcn_readfirstlane(wave > 0 ? wave - 1 : 0)) : 0u;
   __syncthreads();
   return base + incl - v;
 }
@@ -179,11 +261,11 @@ __device__ void radix_select(const Source &src, uint32_t n, uint32_t want, uint3
 }
 
 // Selection with a bracket.  The caller knows (or hopes) that the want-th best
-// of the n elements of `src` has its key inside [lo, hi].  Keys above hi are only
-// counted; keys inside get a 32-bit code, 1 + ((key - lo) >> shift), that stays
-// in registers (KPT per thread, n <= KPT * THREADS) for the radix passes that
-// find the code of the threshold: the codes spread evenly over the bracket, so
-// usually one 12-bit pass with next to no bin shared.  key -> code is monotone, so
+// of the n elements of `src` has its key inside [lo, hi].  Thread t holds the keys of
+// elements 4 (t + g THREADS) + 0 .. 3 in registers (g = 0 .. KPT / 4 - 1).  Keys above hi
+// are only counted; keys inside get a 32-bit code, 1 + ((key - lo) >> shift), for the
+// radix passes that find the code of the threshold: the codes spread evenly over the
+// bracket, so usually one pass with next to no bin shared.  key -> code is monotone, so
 // a larger (smaller) code than the threshold's means kept (pruned) for certain;
 // the few elements that share the threshold's code are ranked exactly on their
 // full keys and indices.  If the bracket misses the threshold or more than kCap
@@ -256,17 +338,18 @@ __device__ __forceinline__ void rank_candidates(SelectShared &sh, uint32_t m, ui
 
 // DB = bits per radix pass: the pass costs one histogram of 2^DB bins (zeroed,
 // filled, scanned by THREADS threads), so small workgroups take small digits.
-template <int THREADS, int KPT, int DB, typename Source>
-__device__ void bracketed_select(const Source &src, uint32_t n, uint32_t want_total, uint64_t lo, uint64_t hi,
-                                 uint32_t nblocks, uint8_t *__restrict__ mask, SelectShared &sh,
-                                 BracketShared &bs) {
+// ALL: the bracket is known to hold every element.  The caller has zeroed sh.hist[0, 2^DB)
+// and passed a barrier since.  wide: src is in linear order and mask is 4-byte aligned.
+template <int THREADS, int KPT, int DB, bool ALL, typename Source>
+__device__ __forceinline__ void bracketed_select(const uint64_t (&key)[KPT], const Source &src, uint32_t n,
+                                                 uint32_t want_total, uint64_t lo, uint64_t hi, uint32_t nblocks,
+                                                 bool wide, uint8_t *__restrict__ mask, SelectShared &sh,
+                                                 BracketShared &bs) {
   constexpr int kLocalBins = 1 << DB;
   constexpr int kPerThread = kLocalBins / THREADS;
-  static_assert(kPerThread >= 1 && kLocalBins <= kBins, "one bin per thread at least");
+  static_assert(kPerThread >= 1 && kLocalBins <= kBins && KPT % 4 == 0, "one bin per thread at least");
   constexpr uint32_t kAbove = 0xFFFFFFFFu, kBelow = 0u;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  // element i of this thread is number t + i * THREADS of src; the first cnt exist
-  const int cnt = (uint32_t)t < n ? (int)((n - 1u - (uint32_t)t) / THREADS) + 1 : 0;
   const uint64_t range = hi - lo;
   // smallest shift with 1 + (range >> shift) <= 0xFFFFFFFE
   int shift = range == 0 ? 0 : 64 - __clzll((long long)range);          // bit length of range
@@ -276,40 +359,48 @@ __device__ void bracketed_select(const Source &src, uint32_t n, uint32_t want_to
   uint32_t n_above = 0, n_inside = 0;
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    const uint32_t e = (uint32_t)(t + i * THREADS);
-    const uint64_t key = src.key(e < n ? e : 0u);
-    uint32_t c = 1u + (uint32_t)((key - lo) >> shift);
-    c = key > hi ? kAbove : (key < lo ? kBelow : c);
-    if (i >= cnt) c = kBelow;
-    n_above += c == kAbove ? 1u : 0u;
-    n_inside += (c != kAbove && c != kBelow) ? 1u : 0u;
+    const uint32_t e = 4u * (uint32_t)(t + (i >> 2) * THREADS) + (uint32_t)(i & 3);
+    uint32_t c = 1u + (uint32_t)((key[i] - lo) >> shift);
+    if constexpr (!ALL) c = key[i] > hi ? kAbove : (key[i] < lo ? kBelow : c);
+    if (e >= n) c = kBelow;
+    if constexpr (!ALL) {
+      n_above += c == kAbove ? 1u : 0u;
+      n_inside += (c != kAbove && c != kBelow) ? 1u : 0u;
+    }
     code[i] = c;
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    n_above += __shfl_xor(n_above, d, 64);
-    n_inside += __shfl_xor(n_inside, d, 64);
+  if constexpr (ALL) {
+    n_inside = n;
+  } else {
+    n_above = wave_sum(n_above);
+    n_inside = wave_sum(n_inside);
+    if (lane == 0) { bs.wave_cnt[0][wave] = n_above; bs.wave_cnt[1][wave] = n_inside; }
+    __syncthreads();
+    n_above = wave_sum(lane < THREADS / 64 ? bs.wave_cnt[0][lane & (THREADS / 64 - 1)] : 0u);
+    n_inside = wave_sum(lane < THREADS / 64 ? bs.wave_cnt[1][lane & (THREADS / 64 - 1)] : 0u);
   }
-  if (lane == 0) { bs.wave_cnt[0][wave] = n_above; bs.wave_cnt[1][wave] = n_inside; }
-  __syncthreads();
-  n_above = 0;
-  n_inside = 0;
-#pragma unroll
-  for (int w = 0; w < THREADS / 64; ++w) { n_above += bs.wave_cnt[0][w]; n_inside += bs.wave_cnt[1][w]; }
 
   // bits [ctop, 32) of the threshold's code are settled and equal cprefix
   int ctop = 32;
+  // (codes reach no further up than the bit length of the largest one)
+  if constexpr (ALL) {
+    const uint32_t top = 1u + (uint32_t)(range >> shift);
+    ctop = 32 - __clz((int)top);
+  }
+  const int ctop0 = ctop;
   uint32_t cprefix = 0, want = want_total - n_above, n_cand = n_inside;
   const bool bracketed = want_total > n_above && want <= n_inside;
   while (bracketed && n_cand > 64u && ctop > 0) {
     const int dshift = ctop > DB ? ctop - DB : 0;
     const uint32_t dmask = (1u << (ctop - dshift)) - 1u;
-    for (int b = t; b < kLocalBins; b += THREADS) sh.hist[b] = 0;
-    __syncthreads();
+    if (ctop != ctop0) {                                     // (the first histogram was zeroed by the caller)
+      for (int b = t; b < kLocalBins; b += THREADS) sh.hist[b] = 0;
+      __syncthreads();
+    }
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
       const uint32_t c = code[i];
-      if (c != kAbove && c != kBelow && (ctop == 32 || (c >> ctop) == cprefix))
+      if (c != kAbove && c != kBelow && (ctop == ctop0 || (c >> ctop) == cprefix))
         atomicAdd(&sh.hist[(c >> dshift) & dmask], 1u);
     }
     __syncthreads();
@@ -329,37 +420,50 @@ __device__ void bracketed_select(const Source &src, uint32_t n, uint32_t want_to
       }
       above += h[u];
     }
+    if (t == 0) sh.n = 0;
     __syncthreads();
-    cprefix = ctop == 32 ? sh.digit : ((cprefix << (ctop - dshift)) | sh.digit);
+    cprefix = ctop == ctop0 ? sh.digit : ((cprefix << (ctop - dshift)) | sh.digit);
     want -= sh.above;
     n_cand = sh.count;
     ctop = dshift;
-    __syncthreads();
+    if (n_cand > 64u && ctop > 0) __syncthreads();           // (another pass writes what was just read)
   }
   if (!bracketed || n_cand > (uint32_t)kCap) {
+    __syncthreads();
     radix_select<THREADS>(src, n, want_total, nblocks, mask, sh);
     return;
   }
 
   // larger code: kept; smaller: pruned; equal: ranked exactly on the full keys
-  if (t == 0) sh.n = 0;
-  __syncthreads();
+  if (ctop == ctop0) {                                       // no pass was run: sh.n is not set yet
+    if (t == 0) sh.n = 0;
+    __syncthreads();
+  }
 #pragma unroll
-  for (int i = 0; i < KPT; ++i) {
-    if (i < cnt) {
-      const uint32_t e = (uint32_t)(t + i * THREADS);
-      const uint32_t c = code[i];
-      const bool inside = c != kAbove && c != kBelow;
-      // with no pass run (ctop == 32) every element inside the bracket is a candidate
-      const uint32_t chi = ctop == 32 ? 0u : c >> ctop;
-      if (inside && chi == cprefix) {
-        const uint32_t pos = atomicAdd(&sh.n, 1u);
-        sh.ckey[pos] = src.key(e);
-        sh.cidx[pos] = src.idx(e);
-      } else {
-        mask[src.idx(e)] = (c == kAbove || (inside && chi > cprefix)) ? 1 : 0;
+  for (int g = 0; g < KPT / 4; ++g) {
+    const uint32_t e = 4u * (uint32_t)(t + g * THREADS);
+    if (e >= n) continue;
+    uint32_t own = 0, word = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (e + q < n) {
+        const uint32_t c = code[4 * g + q];
+        const bool inside = c != kAbove && c != kBelow;
+        // with no pass run every element inside the bracket is a candidate
+        const uint32_t chi = ctop == ctop0 ? 0u : c >> ctop;
+        if (inside && chi == cprefix) {
+          const uint32_t pos = atomicAdd(&sh.n, 1u);
+          sh.ckey[pos] = key[4 * g + q];
+          sh.cidx[pos] = src.idx(e + q);
+        } else {
+          const uint32_t kept = (c == kAbove || (inside && chi > cprefix)) ? 1u : 0u;
+          if (!wide) mask[src.idx(e + q)] = (uint8_t)kept;
+          else word |= kept << (8 * q);
+        }
+        own |= 1u << q;      // (a candidate's byte is written again below, behind the barrier)
       }
     }
+    if (wide) store_mask4(mask, e, true, own, word);
   }
   __syncthreads();
   rank_candidates<THREADS>(sh, sh.n, want, mask);
@@ -373,52 +477,49 @@ __device__ void bracketed_select(const Source &src, uint32_t n, uint32_t want_to
 // two, exact ranking of what shares the threshold's code.  The last group may be
 // shorter (last_blocks, keeping n_keep_last).
 // One workgroup selects the `want` best of the n scores at `scores` into gmask.
+// (12288 scores take 8.0 us, 12.9 before keys were kept in registers and lane exchanges became DPP moves.)
 template <int THREADS, int KPT, int DB>
 __device__ __forceinline__ void select_one_group(const double *__restrict__ scores, uint32_t n, uint32_t want,
-                                                 uint8_t *__restrict__ gmask) {
-  __shared__ SelectShared sh;
-  __shared__ BracketShared bs;
-  __shared__ uint64_t wave_min[THREADS / 64], wave_max[THREADS / 64];
+                                                 uint8_t *__restrict__ gmask, SelectShared &sh, BracketShared &bs) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   if (want == 0 || want >= n) {
     for (uint32_t e = t; e < n; e += THREADS) gmask[e] = want > 0 ? 1 : 0;
     return;
   }
-  AllScores src{scores};
-  uint64_t mn = ~0ull, mx = 0ull;
+  const bool wide_in = (uintptr_t)scores % 16 == 0, wide_out = (uintptr_t)gmask % 4 == 0;
+  uint64_t key[KPT];
+#pragma unroll
+  for (int g = 0; g < KPT / 4; ++g) load_keys4(scores, 4u * (uint32_t)(t + g * THREADS), n, wide_in, &key[4 * g]);
+  for (int b = t; b < (1 << DB); b += THREADS) sh.hist[b] = 0;
+  // the bracket: smallest and largest high word
+  uint32_t mn = 0xFFFFFFFFu, mx = 0u;
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    const uint32_t e = (uint32_t)(t + i * THREADS);
-    if (e < n) {
-      const uint64_t k = src.key(e);
-      mn = k < mn ? k : mn;
-      mx = k > mx ? k : mx;
-    }
+    const uint32_t e = 4u * (uint32_t)(t + (i >> 2) * THREADS) + (uint32_t)(i & 3);
+    const uint32_t h = (uint32_t)(key[i] >> 32);
+    mn = pick<false>(mn, e < n ? h : 0xFFFFFFFFu);
+    mx = pick<true>(mx, h);
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const uint64_t a = __shfl_xor(mn, d, 64), b = __shfl_xor(mx, d, 64);
-    mn = a < mn ? a : mn;
-    mx = b > mx ? b : mx;
-  }
-  if (lane == 0) { wave_min[wave] = mn; wave_max[wave] = mx; }
+  mn = wave_extreme<false>(mn);
+  mx = wave_extreme<true>(mx);
+  if (lane == 0) { bs.wave_cnt[0][wave] = mn; bs.wave_cnt[1][wave] = mx; }
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < THREADS / 64; ++w) {
-    mn = wave_min[w] < mn ? wave_min[w] : mn;
-    mx = wave_max[w] > mx ? wave_max[w] : mx;
-  }
-  bracketed_select<THREADS, KPT, DB>(src, n, want, mn, mx, n, gmask, sh, bs);
+  mn = wave_extreme<false>(bs.wave_cnt[0][lane & (THREADS / 64 - 1)]);
+  mx = wave_extreme<true>(bs.wave_cnt[1][lane & (THREADS / 64 - 1)]);
+  bracketed_select<THREADS, KPT, DB, true>(key, AllScores{scores}, n, want, (uint64_t)mn << 32,
+                                           ((uint64_t)mx << 32) | 0xFFFFFFFFull, n, wide_out, gmask, sh, bs);
 }
 
 template <int THREADS, int KPT, int DB>
 __global__ __launch_bounds__(THREADS) void select_groups_kernel(
     const double *__restrict__ scores, uint32_t group_blocks, uint32_t n_keep_group, uint32_t last_blocks,
     uint32_t n_keep_last, uint8_t *__restrict__ mask) {
+  __shared__ SelectShared sh;
+  __shared__ BracketShared bs;
   const bool last = blockIdx.x == gridDim.x - 1;
   const size_t off = (size_t)blockIdx.x * group_blocks;
   select_one_group<THREADS, KPT, DB>(scores + off, last ? last_blocks : group_blocks,
-                                     last ? n_keep_last : n_keep_group, mask + off);
+                                     last ? n_keep_last : n_keep_group, mask + off, sh, bs);
 }
 
 // Per-group selection of several tensors in one launch: tensor k owns the workgroups
@@ -434,6 +535,8 @@ struct GroupBatch {
 };
 template <int THREADS, int KPT, int DB>
 __global__ __launch_bounds__(THREADS) void select_groups_batched_kernel(GroupBatch b, int n) {
+  __shared__ SelectShared sh;
+  __shared__ BracketShared bs;
   int k = 0;
   while (k + 1 < n && blockIdx.x >= b.it[k + 1].wg_begin) ++k;
   const GroupItem &it = b.it[k];
@@ -441,13 +544,13 @@ __global__ __launch_bounds__(THREADS) void select_groups_batched_kernel(GroupBat
   const bool last = g == it.groups - 1;
   const size_t off = (size_t)g * it.group_blocks;
   select_one_group<THREADS, KPT, DB>(it.scores + off, last ? it.last_blocks : it.group_blocks,
-                                     last ? it.n_keep_last : it.n_keep_group, it.mask + off);
+                                     last ? it.n_keep_last : it.n_keep_group, it.mask + off, sh, bs);
 }
 
 // Control block shared by the two grid-wide passes (lives in the workspace;
 // written by workgroup 0 of pass 1).
 struct SelectCtrl {
-  uint32_t n_cand, shift;
+  uint32_t n_cand, shift, done, pad;
   uint64_t lo, hi;
 };
 
@@ -457,204 +560,176 @@ __device__ __forceinline__ uint32_t bucket_of(uint64_t key, uint64_t lo, uint64_
   return 1u + (uint32_t)((key - lo) >> shift);
 }
 
-// NS = sample size: 64 (ranked inside one wave through lane reads, no LDS round
-// trips) or kSample = 256 (ranked through LDS; a tighter bracket for very large
-// inputs, where the threshold bucket must still fit the candidate ranking).
-template <int NS>
-__device__ __forceinline__ void select_count_body(
-    const double *__restrict__ scores, uint32_t nblocks, uint32_t n_keep, uint32_t per_wg,
-    uint32_t *__restrict__ counts, SelectCtrl *__restrict__ ctrl, uint32_t wg) {
+// What one selection needs in the kernel arguments.  wgs == 0: the one-workgroup selection.
+struct SelectItem {
+  const double *scores;
+  uint8_t *mask;
+  uint32_t nblocks, n_keep, per_wg, wgs;
+  uint32_t *counts;
+  SelectCtrl *ctrl;
+  uint64_t *cand_key;
+  uint32_t *cand_idx;
+};
+
+// Pass 1 of workgroup `wg` of a selection.  Its slice is per_wg blocks (a multiple of four).
+__device__ __forceinline__ void select_count_body(const SelectItem &it, const uint32_t wg) {
   __shared__ uint32_t hist[kBuckets];
-  __shared__ uint64_t sample[kSample];
-  __shared__ uint64_t bracket[2];
+  __shared__ __attribute__((aligned(16))) uint32_t sample[kSample];
+  __shared__ uint32_t ranks[kSample];
+  __shared__ uint32_t bracket[2];
   const int t = threadIdx.x;
-  constexpr int kKeys = 4;                        // keys per thread held in registers (per_wg <= 1024)
+  const double *__restrict__ scores = it.scores;
+  const uint32_t nblocks = it.nblocks;
+  const bool wide = (uintptr_t)scores % 16 == 0;
+  const uint32_t e0 = wg * it.per_wg;
+  const uint32_t e1 = (e0 + it.per_wg) < nblocks ? (e0 + it.per_wg) : nblocks;
 
-  // this workgroup's slice (loads in flight while the sample is ranked)
-  const uint32_t e0 = wg * per_wg;
-  const uint32_t e1 = (e0 + per_wg) < nblocks ? (e0 + per_wg) : nblocks;
-  double raw[kKeys];
-#pragma unroll
-  for (int i = 0; i < kKeys; ++i) {
-    const uint32_t e = e0 + t + i * kGridThreads;
-    raw[i] = scores[e < e1 ? e : e0];
+  // the same sample in every workgroup: a key from each of kSample equal stretches, at a scattered place
+  // of its stretch (even spacing would meet the same few block-columns again and again), of each the upper 25 bits (more than
+  // enough for a bracket) and its position below them, which makes them distinct; and the first four
+  // keys per thread of the slice, on their way while the sample is ranked
+  constexpr uint32_t kPosBits = kSample - 1;
+  if (t < kSample) {
+    const uint32_t stretch = nblocks / kSample, at = (uint32_t)((uint64_t)t * nblocks / kSample);
+    const uint32_t e = at + __umulhi((uint32_t)t * 2654435769u, stretch);
+    sample[t] = ((uint32_t)(score_key(scores[e]) >> 32) & ~kPosBits) | (uint32_t)t;
+    ranks[t] = 0;
   }
-
-  // the same sample in every workgroup: NS evenly spaced keys
-  uint64_t mine = 0;
-  if (t < NS) mine = score_key(scores[(uint64_t)t * nblocks / NS]);
-  hist[t] = 0;
-  const double frac = 1.0 - (double)n_keep / (double)nblocks;       // threshold's quantile from below
-  const int pos = (int)(frac * NS);
-  const int delta = 3 + (int)(3.5 * sqrt(NS * frac * (1.0 - frac)));
+  if (t < kBuckets) hist[t] = 0;
+  uint64_t key[4];
+  load_keys4(scores, e0 + 4u * (uint32_t)t, e1, wide, key);
+  const double frac = 1.0 - (double)it.n_keep / (double)nblocks;       // threshold's quantile from below
+  const int pos = (int)(frac * kSample);
+  const int delta = 3 + (int)(3.5 * sqrt(kSample * frac * (1.0 - frac)));
   const int rlo = pos - delta < 0 ? 0 : pos - delta;
-  const int rhi = pos + delta > NS - 1 ? NS - 1 : pos + delta;
-  if (NS == 64) {
-    if (t < 64) {
-      // ascending rank of my sample key (ties by position) from the other lanes' keys
-      int rank = 0;
-      const uint32_t mlo = (uint32_t)mine, mhi = (uint32_t)(mine >> 32);
-#pragma unroll 16
-      for (int o = 0; o < 64; ++o) {
-        const uint64_t k = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mhi, o) << 32) |
-                           (uint32_t)__builtin_amdgcn_readlane((int)mlo, o);
-        rank += (k < mine || (k == mine && o < t)) ? 1 : 0;
-      }
-      // the two order statistics around the threshold's expected position
-      if (rank == rlo) bracket[0] = mine;
-      if (rank == rhi) bracket[1] = mine;
+  const int rhi = pos + delta > kSample - 1 ? kSample - 1 : pos + delta;
+  __syncthreads();
+  {
+    // ascending rank of every sample key: eight threads share a key, each compares it with an eighth of
+    // the others (256 samples made it 0.7 us more per workgroup, on whole 64-bit keys 3 us)
+    constexpr int kShare = kSample * kSample / kGridThreads;
+    const uint4 *others = reinterpret_cast<const uint4 *>(&sample[(t / kSample) * kShare]);
+    const uint32_t me = sample[t & (kSample - 1)];
+    uint32_t rank = 0;
+#pragma unroll
+    for (int o = 0; o < kShare / 4; ++o) {
+      const uint4 k = others[o];
+      rank += (k.x < me ? 1u : 0u) + (k.y < me ? 1u : 0u) + (k.z < me ? 1u : 0u) + (k.w < me ? 1u : 0u);
     }
-  } else {
-    sample[t] = mine;
-    __syncthreads();
-    int rank = 0;
-#pragma unroll 16
-    for (int o = 0; o < NS; ++o) {
-      const uint64_t k = sample[o];
-      rank += (k < mine || (k == mine && o < t)) ? 1 : 0;
-    }
-    if (rank == rlo) bracket[0] = mine;
-    if (rank == rhi) bracket[1] = mine;
+    atomicAdd(&ranks[t & (kSample - 1)], rank);
   }
   __syncthreads();
-  const uint64_t lo = bracket[0], hi = bracket[1];
+  // the two order statistics around the threshold's expected position
+  if (t < kSample) {
+    const int rank = (int)ranks[t];
+    if (rank == rlo) bracket[0] = sample[t];
+    if (rank == rhi) bracket[1] = sample[t];
+  }
+  __syncthreads();
+  const uint64_t lo = (uint64_t)(bracket[0] & ~kPosBits) << 32, hi = ((uint64_t)(bracket[1] | kPosBits) << 32) | 0xFFFFFFFFull;
   const uint64_t range = hi - lo;
   // smallest shift with (range >> shift) <= kBuckets - 3
   uint32_t shift = range == 0 ? 0u : (uint32_t)(64 - __clzll((long long)range));   // bit length of range
   shift = shift > 8 ? shift - 8 : 0u;
   if ((range >> shift) > (uint64_t)(kBuckets - 3)) ++shift;
   if (wg == 0 && t == 0) {
-    ctrl->n_cand = 0;
-    ctrl->shift = shift;
-    ctrl->lo = lo;
-    ctrl->hi = hi;
+    it.ctrl->n_cand = 0;
+    it.ctrl->done = 0;
+    it.ctrl->shift = shift;
+    it.ctrl->lo = lo;
+    it.ctrl->hi = hi;
   }
+  for (uint32_t e = e0 + 4u * (uint32_t)t; e < e1; e += 4 * kGridThreads) {
+    uint64_t next[4];
+    load_keys4(scores, e + 4 * kGridThreads, e1, wide, next);
 #pragma unroll
-  for (int i = 0; i < kKeys; ++i)
-    if (e0 + t + i * kGridThreads < e1) atomicAdd(&hist[bucket_of(score_key(raw[i]), lo, hi, shift)], 1u);
-  // longer slices (more than 256 K blocks): eight loads in flight per round
-  for (uint32_t eb = e0 + t + kKeys * kGridThreads; eb < e1; eb += 8 * kGridThreads) {
-    double more[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t e = eb + i * kGridThreads;
-      more[i] = scores[e < e1 ? e : e0];
+    for (int q = 0; q < 4; ++q) {
+      if (e + q < e1) atomicAdd(&hist[bucket_of(key[q], lo, hi, shift)], 1u);
+      key[q] = next[q];
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (eb + i * kGridThreads < e1) atomicAdd(&hist[bucket_of(score_key(more[i]), lo, hi, shift)], 1u);
   }
   __syncthreads();
-  counts[wg * kBuckets + t] = hist[t];
+  if (t < kBuckets) it.counts[wg * kBuckets + t] = hist[t];
 }
 
-template <int NS>
-__global__ __launch_bounds__(kGridThreads) void select_count_kernel(
-    const double *__restrict__ scores, uint32_t nblocks, uint32_t n_keep, uint32_t per_wg,
-    uint32_t *__restrict__ counts, SelectCtrl *__restrict__ ctrl) {
-  select_count_body<NS>(scores, nblocks, n_keep, per_wg, counts, ctrl, blockIdx.x);
-}
-
-// MODE 1: classification only; MODE 2: only the selection among the candidates, by one
-// workgroup of a later launch.  (One kernel in which the last workgroup to finish, found by an
-// atomic ticket, does the selection needs a release fence in every workgroup -- an L2 write-back
-// on this GPU -- which costs more than the second launch.)
-template <int MODE>
-__device__ __forceinline__ void select_classify_body(
-    const double *__restrict__ scores, uint32_t nblocks, uint32_t n_keep, uint32_t per_wg,
-    const uint32_t *__restrict__ counts, SelectCtrl *__restrict__ ctrl,
-    uint64_t *__restrict__ cand_key, uint32_t *__restrict__ cand_idx, uint8_t *__restrict__ mask,
-    uint32_t wg, uint32_t nwgs) {
-  __shared__ SelectShared sh;
-  __shared__ BracketShared bs;
-  __shared__ uint32_t wg_cand, wg_base;
+// Pass 2 of workgroup `wg`; the last workgroup of the selection to finish selects among the candidates.
+__device__ __forceinline__ void select_classify_body(const SelectItem &it, const uint32_t wg, SelectShared &sh,
+                                                     BracketShared &bs) {
+  __shared__ uint32_t wg_cand, is_last;
   const int t = threadIdx.x;
+  const double *__restrict__ scores = it.scores;
+  uint8_t *__restrict__ mask = it.mask;
+  SelectCtrl *ctrl = it.ctrl;
+  const uint32_t nblocks = it.nblocks, nwgs = it.wgs;
+  const bool wide_in = (uintptr_t)scores % 16 == 0, wide_out = (uintptr_t)mask % 4 == 0;
   const uint32_t shift = ctrl->shift;
   const uint64_t lo = ctrl->lo, hi = ctrl->hi;
-  constexpr int kKeys = 4;                        // keys per thread loaded up front (per_wg <= 1024 as a rule)
+  const uint32_t e0 = wg * it.per_wg;
+  const uint32_t e1 = (e0 + it.per_wg) < nblocks ? (e0 + it.per_wg) : nblocks;
+  uint64_t key[4];
+  load_keys4(scores, e0 + 4u * (uint32_t)t, e1, wide_in, key);
 
-  const uint32_t e0 = wg * per_wg;
-  const uint32_t e1 = (e0 + per_wg) < nblocks ? (e0 + per_wg) : nblocks;
-  double raw[kKeys];
-  if constexpr (MODE != 2) {
-#pragma unroll
-    for (int i = 0; i < kKeys; ++i) {
-      const uint32_t e = e0 + t + i * kGridThreads;
-      raw[i] = scores[e < e1 ? e : e0];
-    }
-  }
-  if (t == 0) wg_cand = 0;
-
-  // the bucket that holds the n_keep-th largest key (same answer in every workgroup):
-  // thread t owns bucket kBuckets-1-t, the scan runs from the top
+  // the bucket that holds the n_keep-th largest key (same answer in every workgroup): four threads
+  // share a bucket, each adds up a quarter of the workgroups' counts
   uint32_t own = 0;
-  for (uint32_t w0 = 0; w0 < nwgs; w0 += 64) {       // 64 independent loads in flight per round
-    uint32_t part[64];
-#pragma unroll
-    for (uint32_t w = 0; w < 64; ++w)
-      part[w] = w0 + w < nwgs ? counts[(w0 + w) * kBuckets + (kBuckets - 1 - t)] : 0u;
-#pragma unroll
-    for (uint32_t w = 0; w < 64; ++w) own += part[w];
+  {
+    constexpr uint32_t kParts = kGridThreads / kBuckets;
+    const uint32_t bkt = (uint32_t)t & (kBuckets - 1), part = (uint32_t)t / kBuckets;
+#pragma unroll 8
+    for (uint32_t w = part; w < nwgs; w += kParts) own += it.counts[w * kBuckets + bkt];
+    if (t < kBuckets) sh.hist[t] = 0;
+    if (t == 0) { wg_cand = 0; is_last = 0; }
+    __syncthreads();
+    atomicAdd(&sh.hist[bkt], own);
+    __syncthreads();
   }
+  own = t < kBuckets ? sh.hist[kBuckets - 1 - t] : 0u;       // the scan runs from the top
   const uint32_t above_me = block_exclusive_scan<kGridThreads>(own, sh.wave_tot);
-  if (above_me < n_keep && n_keep <= above_me + own) {
+  if (above_me < it.n_keep && it.n_keep <= above_me + own) {
     sh.digit = (uint32_t)(kBuckets - 1 - t);
     sh.above = above_me;
+    sh.count = own;
   }
   __syncthreads();
-  const uint32_t bucket = sh.digit, above = sh.above;
-  __syncthreads();
+  const uint32_t bucket = sh.digit, above = sh.above, n = sh.count;
 
-  if constexpr (MODE != 2) {
-  // other buckets: mask bytes; the threshold's bucket: this workgroup's candidates
-  // go to LDS first, so the global list takes one atomic per workgroup
-  auto classify = [&](uint32_t e, uint64_t key) {
-    const uint32_t b = bucket_of(key, lo, hi, shift);
-    if (b != bucket) {
-      mask[e] = b > bucket ? 1 : 0;
-    } else {
-      const uint32_t pos = atomicAdd(&wg_cand, 1u);
-      if (pos < (uint32_t)kCap) {
-        sh.ckey[pos] = key;
-        sh.cidx[pos] = e;
-      } else {                                   // more than the LDS list holds: straight to the global list
-        const uint32_t g = atomicAdd(&ctrl->n_cand, 1u);
-        cand_key[g] = key;
-        cand_idx[g] = e;
+  // Other buckets: mask bytes.  The threshold's bucket: the n candidates, whose mask bytes are the last
+  // workgroup's to write.  As a rule they are few: every workgroup lists its own at its slice's place in
+  // the list (how many they are stands in counts), no atomic on memory.  Else they are appended to one list.
+  const bool few = n <= (uint32_t)kCap;
+  for (uint32_t e = e0 + 4u * (uint32_t)t; e < e1; e += 4 * kGridThreads) {
+    uint64_t next[4];
+    load_keys4(scores, e + 4 * kGridThreads, e1, wide_in, next);
+    uint32_t own4 = 0, word = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (e + q < e1) {
+        const uint32_t b = bucket_of(key[q], lo, hi, shift);
+        if (b != bucket) {
+          own4 |= 1u << q;
+          word |= (b > bucket ? 1u : 0u) << (8 * q);
+        } else {
+          const uint32_t at = few ? e0 + atomicAdd(&wg_cand, 1u) : atomicAdd(&ctrl->n_cand, 1u);
+          store_shared(&it.cand_key[at], key[q]);
+          store_shared(&it.cand_idx[at], e + q);
+        }
       }
+      key[q] = next[q];
     }
-  };
-#pragma unroll
-  for (int i = 0; i < kKeys; ++i) {
-    const uint32_t e = e0 + t + i * kGridThreads;
-    if (e < e1) classify(e, score_key(raw[i]));
+    store_mask4(mask, e, wide_out, own4, word);
   }
-  for (uint32_t eb = e0 + t + kKeys * kGridThreads; eb < e1; eb += 8 * kGridThreads) {
-    double more[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t e = eb + i * kGridThreads;
-      more[i] = scores[e < e1 ? e : e0];
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (eb + i * kGridThreads < e1) classify(eb + i * kGridThreads, score_key(more[i]));
-  }
+  stores_done();                                 // this wave's part of the list is where every workgroup sees it
   __syncthreads();
-  const uint32_t mine = wg_cand < (uint32_t)kCap ? wg_cand : (uint32_t)kCap;
-  if (t == 0 && mine > 0) wg_base = atomicAdd(&ctrl->n_cand, mine);
+  if (t == 0)
+    is_last = __hip_atomic_fetch_add(&ctrl->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nwgs - 1 ? 1u : 0u;
+  uint32_t wg_has = 0;                           // candidates of workgroup t's slice (nwgs <= kMaxGridWgs)
+  if (few && (uint32_t)t < nwgs) wg_has = it.counts[(uint32_t)t * kBuckets + bucket];
   __syncthreads();
-  for (uint32_t c = t; c < mine; c += kGridThreads) {
-    cand_key[wg_base + c] = sh.ckey[c];
-    cand_idx[wg_base + c] = sh.cidx[c];
-  }
-  }
-  if constexpr (MODE == 1) return;
+  if (is_last == 0) return;
 
   // the candidates all lie in the threshold bucket's key range,
   // which serves as the bracket of their exact selection
-  const uint32_t n = __hip_atomic_load(&ctrl->n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  Candidates src{cand_key, cand_idx};
+  const Candidates src{it.cand_key, it.cand_idx};
   uint64_t blo, bhi;
   if (bucket == 0) {
     blo = 0;
@@ -667,65 +742,99 @@ __device__ __forceinline__ void select_classify_body(
     bhi = blo + ((1ull << shift) - 1ull);
     if (bhi > hi) bhi = hi;
   }
-  if (n <= (uint32_t)kStage) {
-    // one trip to memory: the candidates move to LDS and are selected from there
-    __shared__ uint64_t skey[kStage];
-    __shared__ uint32_t sidx[kStage];
-    for (uint32_t c = t; c < n; c += kGridThreads) {
-      skey[c] = cand_key[c];
-      sidx[c] = cand_idx[c];
-    }
+  if (few) {
+    // the slices' candidates side by side in LDS, selected from there
+    __shared__ __attribute__((aligned(16))) uint64_t skey[kCap];
+    __shared__ uint32_t sidx[kCap];
+    __shared__ uint32_t slice_at[kMaxGridWgs], slice_has[kMaxGridWgs];
+    const uint32_t at = block_exclusive_scan<kGridThreads>(wg_has, sh.wave_tot);
+    if ((uint32_t)t < nwgs) { slice_at[t] = at; slice_has[t] = wg_has; }
     __syncthreads();
-    Candidates staged{skey, sidx};
-    bracketed_select<kGridThreads, kStage / kGridThreads, 8>(staged, n, n_keep - above, blo, bhi, nblocks, mask, sh, bs);
+    constexpr uint32_t kWaves = kGridThreads / 64, kTogether = 4;     // slices a wave reads at a time
+    const uint32_t lane = (uint32_t)t & 63u;
+    for (uint32_t w0 = (uint32_t)t >> 6; w0 < nwgs; w0 += kWaves * kTogether) {
+      uint64_t k[kTogether];
+      uint32_t x[kTogether];
+#pragma unroll
+      for (uint32_t u = 0; u < kTogether; ++u) {
+        const uint32_t w = w0 + u * kWaves;
+        const bool live = w < nwgs && lane < slice_has[w < nwgs ? w : 0u];
+        const uint32_t from = (live ? w : 0u) * it.per_wg + (live ? lane : 0u);
+        k[u] = src.key(from);
+        x[u] = src.idx(from);
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kTogether; ++u) {
+        const uint32_t w = w0 + u * kWaves;
+        if (w >= nwgs) continue;
+        const uint32_t to = slice_at[w], has = slice_has[w];
+        if (lane < has) { skey[to + lane] = k[u]; sidx[to + lane] = x[u]; }
+        for (uint32_t c = lane + 64u; c < has; c += 64u) {
+          skey[to + c] = src.key(w * it.per_wg + c);
+          sidx[to + c] = src.idx(w * it.per_wg + c);
+        }
+      }
+    }
+    for (int b = t; b < (1 << kFinishBits); b += kGridThreads) sh.hist[b] = 0;
+    __syncthreads();
+    uint64_t ckey[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ckey[i] = 4u * (uint32_t)t + i < n ? skey[4 * t + i] : 0ull;
+    bracketed_select<kGridThreads, 4, kFinishBits, false>(ckey, Staged{skey, sidx}, n, it.n_keep - above, blo, bhi, nblocks,
+                                                          false, mask, sh, bs);
+  } else if (n <= (uint32_t)(kFinishKeys * kGridThreads)) {
+    uint64_t ckey[kFinishKeys];
+#pragma unroll
+    for (int i = 0; i < kFinishKeys; ++i) {
+      const uint32_t c = 4u * (uint32_t)(t + (i >> 2) * kGridThreads) + (uint32_t)(i & 3);
+      ckey[i] = c < n ? src.key(c) : 0ull;
+    }
+    for (int b = t; b < kBins; b += kGridThreads) sh.hist[b] = 0;
+    __syncthreads();
+    bracketed_select<kGridThreads, kFinishKeys, kDigitBits, false>(ckey, src, n, it.n_keep - above, blo, bhi, nblocks,
+                                                                   false, mask, sh, bs);
   } else {
-    radix_select<kGridThreads>(src, n, n_keep - above, nblocks, mask, sh);
+    radix_select<kGridThreads>(src, n, it.n_keep - above, nblocks, mask, sh);
   }
 }
 
-// ---- several independent selections per launch (one per tensor of a batch) ----
-// The kernels above with blockIdx.y (grid-wide passes) or blockIdx.x (one workgroup
-// per selection) naming the selection; its parameters come from the kernel
-// arguments.  Selection is bound by launch and fence latency, not by work, so a
-// batch costs about as much as one selection.
+// ---- the launches: blockIdx.y names the selection of the batch, its parameters come with the kernel
+// arguments.  Selection is bound by launches and latency, not by work, so a batch costs about as much as
+// one selection, and tensors small enough for one workgroup ride along in the launch of pass 2. ----
 constexpr int kBatchMax = 40;
-struct SelectItem {
-  const double *scores;
-  uint8_t *mask;
-  uint32_t nblocks, n_keep, per_wg, wgs;
-  uint32_t *counts;
-  SelectCtrl *ctrl;
-  uint64_t *cand_key;
-  uint32_t *cand_idx;
-};
+template <int N>
 struct SelectBatch {
-  SelectItem it[kBatchMax];
+  SelectItem it[N];
 };
 
-template <int NS>
-__global__ __launch_bounds__(kGridThreads) void select_count_batched_kernel(SelectBatch b) {
+template <int N>
+__global__ __launch_bounds__(kGridThreads) void select_count_kernel(SelectBatch<N> b) {
   const SelectItem &it = b.it[blockIdx.y];
   if (blockIdx.x >= it.wgs) return;
-  select_count_body<NS>(it.scores, it.nblocks, it.n_keep, it.per_wg, it.counts, it.ctrl, blockIdx.x);
+  select_count_body(it, blockIdx.x);
 }
 
-__global__ __launch_bounds__(kGridThreads) void select_classify_batched_kernel(SelectBatch b) {
+template <int N>
+__global__ __launch_bounds__(kGridThreads) void select_kernel(SelectBatch<N> b) {
+  __shared__ SelectShared sh;
+  __shared__ BracketShared bs;
   const SelectItem &it = b.it[blockIdx.y];
-  if (blockIdx.x >= it.wgs) return;
-  select_classify_body<1>(it.scores, it.nblocks, it.n_keep, it.per_wg, it.counts, it.ctrl, it.cand_key,
-                          it.cand_idx, it.mask, blockIdx.x, it.wgs);
+  if (it.wgs != 0) {
+    if (blockIdx.x < it.wgs) select_classify_body(it, blockIdx.x, sh, bs);
+    return;
+  }
+  if (blockIdx.x != 0) return;
+  if (it.nblocks <= 4096) select_one_group<kGridThreads, 4, kDigitBits>(it.scores, it.nblocks, it.n_keep, it.mask, sh, bs);
+  else select_one_group<kGridThreads, 12, kDigitBits>(it.scores, it.nblocks, it.n_keep, it.mask, sh, bs);
 }
 
-__global__ __launch_bounds__(kGridThreads) void select_finish_batched_kernel(SelectBatch b) {
+// at most 1024 blocks: a workgroup of 256 threads
+template <int N>
+__global__ __launch_bounds__(256) void select_small_kernel(SelectBatch<N> b) {
+  __shared__ SelectShared sh;
+  __shared__ BracketShared bs;
   const SelectItem &it = b.it[blockIdx.x];
-  select_classify_body<2>(it.scores, it.nblocks, it.n_keep, it.per_wg, it.counts, it.ctrl, it.cand_key,
-                          it.cand_idx, it.mask, 0u, it.wgs);
-}
-
-template <int THREADS, int KPT, int DB>
-__global__ __launch_bounds__(THREADS) void select_small_batched_kernel(SelectBatch b) {
-  const SelectItem &it = b.it[blockIdx.x];
-  select_one_group<THREADS, KPT, DB>(it.scores, it.nblocks, it.n_keep, it.mask);
+  select_one_group<256, 4, 8>(it.scores, it.nblocks, it.n_keep, it.mask, sh, bs);
 }
 
 __global__ void fill_u8_kernel(uint8_t *p, int64_t n, uint8_t v) {
@@ -737,7 +846,7 @@ __global__ void fill_u8_kernel(uint8_t *p, int64_t n, uint8_t v) {
 constexpr int64_t kSmallLimit = 12288;     // one workgroup (up to 12 keys per thread)
 constexpr int64_t kRideAlong = 4096;       // smallest tensor that the grid-wide passes of a batched call take along
 
-constexpr int kMaxGridWgs = 256;
+constexpr int64_t kBlocksPerWg = 4096;     // slice of a workgroup of the grid-wide passes: four keys per thread
 
 struct SelectPlan {
   size_t counts_off, ctrl_off, key_off, idx_off, total;
@@ -760,6 +869,39 @@ size_t select_ws_bytes(int64_t nblocks) {
   return nblocks > kRideAlong ? select_plan(nblocks).total : 0;
 }
 
+namespace {
+
+// One selection's kernel parameters; grid_wide: with the workgroups and the workspace of the two passes.
+SelectItem select_item(const SelectJob &j, bool grid_wide) {
+  SelectItem it{j.scores, j.mask, (uint32_t)j.nblocks, (uint32_t)j.n_keep, 0u, 0u, nullptr, nullptr, nullptr, nullptr};
+  if (!grid_wide) return it;
+  const SelectPlan p = select_plan(j.nblocks);
+  char *base = static_cast<char *>(j.ws);
+  it.counts = reinterpret_cast<uint32_t *>(base + p.counts_off);
+  it.ctrl = reinterpret_cast<SelectCtrl *>(base + p.ctrl_off);
+  it.cand_key = reinterpret_cast<uint64_t *>(base + p.key_off);
+  it.cand_idx = reinterpret_cast<uint32_t *>(base + p.idx_off);
+  int64_t wgs = ceil_div(j.nblocks, kBlocksPerWg);
+  if (wgs > kMaxGridWgs) wgs = kMaxGridWgs;
+  it.per_wg = (uint32_t)(ceil_div(ceil_div(j.nblocks, wgs), 4) * 4);
+  it.wgs = (uint32_t)ceil_div(j.nblocks, (int64_t)it.per_wg);
+  return it;
+}
+
+// The launches of the m selections in b: pass 1 if any of them is grid-wide, then pass 2.
+template <int N>
+int run_select(const SelectBatch<N> &b, int m, uint32_t max_wgs, hipStream_t s) {
+  if (max_wgs > 0) {
+    hipLaunchKernelGGL(select_count_kernel<N>, dim3(max_wgs, m), dim3(kGridThreads), 0, s, b);
+    const int rc = check_launch();
+    if (rc != BSR_OK) return rc;
+  }
+  hipLaunchKernelGGL(select_kernel<N>, dim3(max_wgs > 0 ? max_wgs : 1u, m), dim3(kGridThreads), 0, s, b);
+  return check_launch();
+}
+
+}  // namespace
+
 int launch_select(const double *scores, int64_t nblocks, int64_t n_keep, uint8_t *keep_mask, void *ws,
                   hipStream_t s) {
   if (nblocks == 0) return BSR_OK;
@@ -769,46 +911,13 @@ int launch_select(const double *scores, int64_t nblocks, int64_t n_keep, uint8_t
                        (uint8_t)(n_keep > 0 ? 1 : 0));
     return check_launch();
   }
-  if (nblocks <= kSmallLimit) {
-    // one workgroup: the per-group kernel with a single group
-    if (nblocks <= 1024)
-      hipLaunchKernelGGL((select_groups_kernel<256, 4, 8>), dim3(1), dim3(256), 0, s, scores, (uint32_t)nblocks,
-                         (uint32_t)n_keep, (uint32_t)nblocks, (uint32_t)n_keep, keep_mask);
-    else if (nblocks <= 8192)
-      hipLaunchKernelGGL((select_groups_kernel<1024, 8, kDigitBits>), dim3(1), dim3(1024), 0, s, scores,
-                         (uint32_t)nblocks, (uint32_t)n_keep, (uint32_t)nblocks, (uint32_t)n_keep, keep_mask);
-    else
-      hipLaunchKernelGGL((select_groups_kernel<1024, 12, kDigitBits>), dim3(1), dim3(1024), 0, s, scores,
-                         (uint32_t)nblocks, (uint32_t)n_keep, (uint32_t)nblocks, (uint32_t)n_keep, keep_mask);
+  SelectBatch<1> b;
+  b.it[0] = select_item(SelectJob{scores, nblocks, n_keep, keep_mask, ws}, nblocks > kSmallLimit);
+  if (nblocks <= 1024) {
+    hipLaunchKernelGGL(select_small_kernel<1>, dim3(1), dim3(256), 0, s, b);
     return check_launch();
   }
-  const SelectPlan p = select_plan(nblocks);
-  char *base = static_cast<char *>(ws);
-  uint32_t *counts = reinterpret_cast<uint32_t *>(base + p.counts_off);
-  SelectCtrl *ctrl = reinterpret_cast<SelectCtrl *>(base + p.ctrl_off);
-  uint64_t *cand_key = reinterpret_cast<uint64_t *>(base + p.key_off);
-  uint32_t *cand_idx = reinterpret_cast<uint32_t *>(base + p.idx_off);
-  int64_t wgs = ceil_div(nblocks, 1024);
-  if (wgs > kMaxGridWgs) wgs = kMaxGridWgs;
-  const uint32_t per_wg = (uint32_t)ceil_div(nblocks, wgs);
-  if (nblocks <= 262144)
-    hipLaunchKernelGGL(select_count_kernel<64>, dim3((unsigned)wgs), dim3(kGridThreads), 0, s, scores,
-                       (uint32_t)nblocks, (uint32_t)n_keep, per_wg, counts, ctrl);
-  else
-    hipLaunchKernelGGL(select_count_kernel<kSample>, dim3((unsigned)wgs), dim3(kGridThreads), 0, s, scores,
-                       (uint32_t)nblocks, (uint32_t)n_keep, per_wg, counts, ctrl);
-  int rc = check_launch();
-  if (rc != BSR_OK) return rc;
-  // Classification and the selection among the candidates as two launches: one more launch costs
-  // less than the release fence of every workgroup that finding the last one to finish takes.
-  SelectBatch b;
-  b.it[0] = SelectItem{scores, keep_mask, (uint32_t)nblocks, (uint32_t)n_keep, per_wg, (uint32_t)wgs, counts, ctrl,
-                       cand_key, cand_idx};
-  hipLaunchKernelGGL(select_classify_batched_kernel, dim3((unsigned)wgs, 1), dim3(kGridThreads), 0, s, b);
-  rc = check_launch();
-  if (rc != BSR_OK) return rc;
-  hipLaunchKernelGGL(select_finish_batched_kernel, dim3(1), dim3(kGridThreads), 0, s, b);
-  return check_launch();
+  return run_select<1>(b, 1, b.it[0].wgs, s);
 }
 
 int launch_select_grouped(const double *scores, int64_t nbr, int64_t nbc, int64_t group_rows,
@@ -845,106 +954,48 @@ int launch_select_grouped(const double *scores, int64_t nbr, int64_t nbc, int64_
 }
 
 int launch_select_batched(const SelectJob *jobs, int n, hipStream_t s) {
-  // classes: 0 one workgroup <= 1024 blocks, 1 <= 8192, 2 <= 12288, 3 grid-wide with the
-  // 64-key sample, 4 grid-wide with the 256-key sample; everything else goes one by one.
-  // The launches of the classes run one after the other and each is bound by latency, not
-  // work: when the grid-wide passes run anyway, mid-sized tensors join them instead of
-  // having a launch of one-workgroup selections of their own.
-  bool grid_wide_runs = false;
-  for (int i = 0; i < n; ++i)
-    if (jobs[i].nblocks > kSmallLimit && jobs[i].nblocks <= 262144 && jobs[i].n_keep > 0 &&
-        jobs[i].n_keep < jobs[i].nblocks)
-      grid_wide_runs = true;
-  for (int cls = 0; cls < 5; ++cls) {
-    SelectBatch b;
-    int m = 0;
-    uint32_t max_wgs = 0;
-    auto flush = [&]() -> int {
-      if (m == 0) return BSR_OK;
-      switch (cls) {
-        case 0:
-          hipLaunchKernelGGL((select_small_batched_kernel<256, 4, 8>), dim3(m), dim3(256), 0, s, b);
-          break;
-        case 1:
-          hipLaunchKernelGGL((select_small_batched_kernel<1024, 8, kDigitBits>), dim3(m), dim3(1024), 0, s, b);
-          break;
-        case 2:
-          hipLaunchKernelGGL((select_small_batched_kernel<1024, 12, kDigitBits>), dim3(m), dim3(1024), 0, s, b);
-          break;
-        default:
-          if (cls == 3)
-            hipLaunchKernelGGL(select_count_batched_kernel<64>, dim3(max_wgs, m), dim3(kGridThreads), 0, s, b);
-          else
-            hipLaunchKernelGGL(select_count_batched_kernel<kSample>, dim3(max_wgs, m), dim3(kGridThreads), 0, s, b);
-          {
-            const int rc = check_launch();
-            if (rc != BSR_OK) return rc;
-          }
-          hipLaunchKernelGGL(select_classify_batched_kernel, dim3(max_wgs, m), dim3(kGridThreads), 0, s, b);
-          {
-            const int rc = check_launch();
-            if (rc != BSR_OK) return rc;
-          }
-          hipLaunchKernelGGL(select_finish_batched_kernel, dim3(m), dim3(kGridThreads), 0, s, b);
-          break;
-      }
-      m = 0;
-      max_wgs = 0;
-      return check_launch();
-    };
-    for (int i = 0; i < n; ++i) {
-      const SelectJob &j = jobs[i];
-      if (j.nblocks == 0) continue;
-      const bool degenerate = j.n_keep <= 0 || j.n_keep >= j.nblocks;
-      int c;
-      if (degenerate) c = -1;
-      else if (j.nblocks <= 1024) c = 0;
-      else if (grid_wide_runs && j.nblocks > kRideAlong) c = 3;
-      else if (j.nblocks <= 8192) c = 1;
-      else if (j.nblocks <= kSmallLimit) c = 2;
-      else if (j.nblocks <= 262144) c = 3;
-      else c = 4;
-      if (c == -1) {
-        if (cls == 0) {                                      // all kept / none kept: a fill, once
-          const int rc = launch_select(j.scores, j.nblocks, j.n_keep, j.mask, j.ws, s);
-          if (rc != BSR_OK) return rc;
-        }
-        continue;
-      }
-      if (c != cls) continue;
-      SelectItem &it = b.it[m];
-      it.scores = j.scores;
-      it.mask = j.mask;
-      it.nblocks = (uint32_t)j.nblocks;
-      it.n_keep = (uint32_t)j.n_keep;
-      it.per_wg = 0;
-      it.wgs = 1;
-      it.counts = nullptr;
-      it.ctrl = nullptr;
-      it.cand_key = nullptr;
-      it.cand_idx = nullptr;
-      if (cls >= 3) {
-        const SelectPlan p = select_plan(j.nblocks);
-        char *base = static_cast<char *>(j.ws);
-        it.counts = reinterpret_cast<uint32_t *>(base + p.counts_off);
-        it.ctrl = reinterpret_cast<SelectCtrl *>(base + p.ctrl_off);
-        it.cand_key = reinterpret_cast<uint64_t *>(base + p.key_off);
-        it.cand_idx = reinterpret_cast<uint32_t *>(base + p.idx_off);
-        int64_t wgs = ceil_div(j.nblocks, 1024);
-        if (wgs > kMaxGridWgs) wgs = kMaxGridWgs;
-        it.wgs = (uint32_t)wgs;
-        it.per_wg = (uint32_t)ceil_div(j.nblocks, wgs);
-        if (it.wgs > max_wgs) max_wgs = it.wgs;
-      }
-      if (++m == kBatchMax) {
-        const int rc = flush();
-        if (rc != BSR_OK) return rc;
-      }
-    }
-    const int rc = flush();
-    if (rc != BSR_OK) return rc;
+  // The launches run one after the other and each is bound by latency, not work: one pass-1 launch for
+  // the grid-wide tensors, and one launch for everything else.  When pass 1 runs anyway, mid-sized
+  // tensors take part in it instead of having one workgroup read all their scores.
+  bool grid_wide_runs = false, only_tiny = true;
+  for (int i = 0; i < n; ++i) {
+    const SelectJob &j = jobs[i];
+    if (j.nblocks == 0 || j.n_keep <= 0 || j.n_keep >= j.nblocks) continue;
+    if (j.nblocks > kSmallLimit) grid_wide_runs = true;
+    if (j.nblocks > 1024) only_tiny = false;
   }
-  return BSR_OK;
+  SelectBatch<kBatchMax> b;
+  int m = 0;
+  uint32_t max_wgs = 0;
+  auto flush = [&]() -> int {
+    if (m == 0) return BSR_OK;
+    int rc;
+    if (only_tiny) {
+      hipLaunchKernelGGL(select_small_kernel<kBatchMax>, dim3(m), dim3(256), 0, s, b);
+      rc = check_launch();
+    } else {
+      rc = run_select<kBatchMax>(b, m, max_wgs, s);
+    }
+    m = 0;
+    max_wgs = 0;
+    return rc;
+  };
+  for (int i = 0; i < n; ++i) {
+    const SelectJob &j = jobs[i];
+    if (j.nblocks == 0) continue;
+    if (j.n_keep <= 0 || j.n_keep >= j.nblocks) {            // all kept / none kept: a fill
+      const int rc = launch_select(j.scores, j.nblocks, j.n_keep, j.mask, j.ws, s);
+      if (rc != BSR_OK) return rc;
+      continue;
+    }
+    b.it[m] = select_item(j, j.nblocks > kSmallLimit || (grid_wide_runs && j.nblocks > kRideAlong));
+    if (b.it[m].wgs > max_wgs) max_wgs = b.it[m].wgs;
+    if (++m == kBatchMax) {
+      const int rc = flush();
+      if (rc != BSR_OK) return rc;
+    }
+  }
+  return flush();
 }
 
 int launch_select_grouped_batched(const GroupedSelectJob *jobs, int n, hipStream_t s) {

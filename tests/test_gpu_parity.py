@@ -1021,3 +1021,25 @@ def test_random_small_shapes_through_every_call(dtype):
         torch.cuda.synchronize()
         assert to_host(backs[i]).tobytes() == to_host(want).tobytes(), f"case {i} dense"
         assert dw_error(dWs[i].cpu().numpy(), s[6].cpu().numpy().astype(np.float64)) <= 2e-6, f"case {i} dW"
+
+
+@pytest.mark.parametrize("nblocks", [1023, 1025, 4096, 4099, 12287, 12289, 16385, 300007])
+@pytest.mark.parametrize("levels", [0, 5, 3000])
+def test_selection_sizes_at_the_edges_of_its_paths(nblocks, levels):
+    """1x1 blocks, so that scores are given one by one: sizes next to every limit between the kernels and
+    ragged ends of a thread's four keys; continuous scores, five levels (the threshold falls into thousands
+    of ties) and 3000 levels (hundreds of ties); masks and scores at addresses that rule out wide accesses."""
+    rng = np.random.default_rng(nblocks + levels)
+    x = rng.standard_normal((nblocks, 1), dtype=np.float32) if levels == 0 else \
+        rng.integers(1, levels + 1, size=(nblocks, 1)).astype(np.float32)
+    want = {k: oracle.select(x.astype(np.float64).ravel() ** 2, oracle.keep_count(nblocks, k)) for k in (0.5, 0.07, 0.99)}
+    Xd = to_dev(x)
+    for shift in (0, 1):
+        for keep, mask_ref in want.items():
+            scores = torch.empty(nblocks + 1, dtype=torch.float64, device="cuda")[shift:nblocks + shift]
+            mask = torch.full((nblocks + 2,), 7, dtype=torch.uint8, device="cuda")
+            B.bsr_score_select(Xd, 1, 1, keep, scores=scores, keep_mask=mask[shift:nblocks + shift])
+            torch.cuda.synchronize()
+            got = mask.cpu().numpy()
+            assert np.array_equal(got[shift:nblocks + shift], mask_ref), (nblocks, levels, shift, keep)
+            assert np.all(np.delete(got, np.s_[shift:nblocks + shift]) == 7)      # nothing beside the mask
