@@ -1,11 +1,13 @@
-"""ctypes binding of libbsr_actprune.so -- argument marshalling only.
+"""Binding of libbsr_actprune.so -- argument marshalling only.
 
 Every function here has the name of the C entry point it calls (see
 ``include/bsr_actprune.h``) and does nothing but turn torch tensors into device
 pointers, sizes and the current HIP stream, allocate missing output buffers
-with torch, and raise on a non-zero status.  No step of the pruning path is
-computed in Python or by torch operators; if the HIP library cannot be loaded
-the import fails loudly -- there is no fallback.
+with torch, and raise on a non-zero status.  The single-tensor calls do that in
+native code (``csrc/torch_calls.cpp``: they are short, and marshalling in Python
+took as long as their kernels), the others through ctypes.  No step of the
+pruning path is computed in Python or by torch operators; if a library cannot be
+loaded the call fails loudly -- there is no fallback.
 """
 from __future__ import annotations
 
@@ -25,6 +27,7 @@ BSR_ERR_WORKSPACE, BSR_ERR_ALIGN, BSR_ERR_HIP, BSR_ERR_LIMIT = -5, -6, -7, -8
 
 _PKG = Path(__file__).resolve().parent
 LIB_PATH = _PKG / "libbsr_actprune.so"
+CALLS_PATH = _PKG / "_torch_calls.so"
 
 EXPORTS = (
     "bsr_version", "bsr_error_string", "bsr_last_hip_error", "bsr_keep_count",
@@ -112,6 +115,22 @@ def lib() -> C.CDLL:
     return l
 
 
+_native = None
+
+
+def _load_native():
+    """The extension module with the single-tensor calls (built on first use only if it is not there)."""
+    global _native
+    if _native is None:
+        lib()
+        if not CALLS_PATH.exists():
+            from . import build as _build
+            _build.build_calls()
+        from . import _torch_calls
+        _native = _torch_calls
+    return _native
+
+
 # ---------------------------------------------------------------------------
 # marshalling helpers
 # ---------------------------------------------------------------------------
@@ -132,7 +151,7 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return (_native or _load_native()).current_stream() or None
     h = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
     return h or None
 
@@ -157,6 +176,15 @@ def _workspace(nbytes: int, device, ws: Optional[torch.Tensor]) -> Optional[torc
 def _check(code: int, where: str) -> None:
     if code != BSR_OK:
         raise BsrError(code, where)
+
+
+def _failed(code: int, x: torch.Tensor, where: str, values: Optional[torch.Tensor] = None):
+    """Raises what a native call reported; x is the tensor whose dtype the call goes by."""
+    if code == BSR_ERR_DTYPE:
+        dtype_code(x.dtype)
+        if values is not None and values.dtype != x.dtype:
+            raise BsrError(BSR_ERR_DTYPE, "values and dY differ in dtype")
+    raise BsrError(code, where)
 
 
 # ---------------------------------------------------------------------------
@@ -196,20 +224,8 @@ def bsr_score_select(X: torch.Tensor, br: int, bc: int, keep: float, *,
                      keep_mask: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None,
                      stream=None):
     """-> keep_mask (uint8 [nblocks]) or (keep_mask, scores) when scores are requested."""
-    M, K, ldx = _dense2d(X, "X")
-    nblocks = (-(-M // br)) * (-(-K // bc)) if br > 0 and bc > 0 else 0
-    if scores is None and want_scores:
-        scores = torch.empty(nblocks, dtype=torch.float64, device=X.device)
-    if keep_mask is None:
-        keep_mask = torch.empty(nblocks, dtype=torch.uint8, device=X.device)
-    code = dtype_code(X.dtype)
-    if ws is None:
-        ws = _workspace(bsr_workspace_bytes(BSR_OP_SCORE_SELECT, M, K, 0, br, bc, code), X.device, None)
-    rc = lib().bsr_score_select(_ptr(X), code, M, K, ldx, br, bc, float(keep), _ptr(scores),
-                                _ptr(keep_mask), _ptr(ws), ws.numel() if ws is not None else 0,
-                                _stream(stream))
-    _check(rc, "bsr_score_select")
-    return (keep_mask, scores) if scores is not None else keep_mask
+    r = (_native or _load_native()).score_select(X, br, bc, None, keep, scores, want_scores, keep_mask, ws, stream)
+    return r if type(r) is not int else _failed(r, X, "bsr_score_select")
 
 
 def bsr_score_select_static(X: torch.Tensor, br: int, bc: int, keep: float, keep_mask: torch.Tensor, *,
@@ -242,20 +258,9 @@ def bsr_score_select_grouped(X: torch.Tensor, br: int, bc: int, group_rows: int,
                              keep_mask: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None,
                              stream=None):
     """-> keep_mask (uint8 [nblocks]) or (keep_mask, scores); ranking groups of group_rows block-rows."""
-    M, K, ldx = _dense2d(X, "X")
-    nblocks = (-(-M // br)) * (-(-K // bc)) if br > 0 and bc > 0 else 0
-    if scores is None and want_scores:
-        scores = torch.empty(nblocks, dtype=torch.float64, device=X.device)
-    if keep_mask is None:
-        keep_mask = torch.empty(nblocks, dtype=torch.uint8, device=X.device)
-    code = dtype_code(X.dtype)
-    if ws is None:
-        ws = _workspace(bsr_workspace_bytes(BSR_OP_SCORE_SELECT, M, K, 0, br, bc, code), X.device, None)
-    rc = lib().bsr_score_select_grouped(_ptr(X), code, M, K, ldx, br, bc, int(group_rows), float(keep),
-                                        _ptr(scores), _ptr(keep_mask), _ptr(ws),
-                                        ws.numel() if ws is not None else 0, _stream(stream))
-    _check(rc, "bsr_score_select_grouped")
-    return (keep_mask, scores) if scores is not None else keep_mask
+    r = (_native or _load_native()).score_select(X, br, bc, int(group_rows), keep, scores, want_scores, keep_mask, ws,
+                                                 stream)
+    return r if type(r) is not int else _failed(r, X, "bsr_score_select_grouped")
 
 
 def bsr_compress(X: torch.Tensor, br: int, bc: int, keep_mask: torch.Tensor, n_keep: int, *,
@@ -263,35 +268,15 @@ def bsr_compress(X: torch.Tensor, br: int, bc: int, keep_mask: torch.Tensor, n_k
                  values: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None,
                  stream=None):
     """-> (row_ptr int32 [nbr+1], col_idx int32 [n_keep], values [n_keep, br, bc])."""
-    M, K, ldx = _dense2d(X, "X")
-    nbr = -(-M // br) if br > 0 else 0
-    dev = X.device
-    if row_ptr is None:
-        row_ptr = torch.empty(nbr + 1, dtype=torch.int32, device=dev)
-    if col_idx is None:
-        col_idx = torch.empty(max(n_keep, 0), dtype=torch.int32, device=dev)
-    if values is None:
-        values = torch.empty((max(n_keep, 0), br, bc), dtype=X.dtype, device=dev)
-    code = dtype_code(X.dtype)
-    if ws is None:
-        ws = _workspace(bsr_workspace_bytes(BSR_OP_COMPRESS, M, K, 0, br, bc, code), dev, None)
-    rc = lib().bsr_compress(_ptr(X), code, M, K, ldx, br, bc, _ptr(keep_mask), int(n_keep),
-                            _ptr(row_ptr), _ptr(col_idx), _ptr(values), _ptr(ws),
-                            ws.numel() if ws is not None else 0, _stream(stream))
-    _check(rc, "bsr_compress")
-    return row_ptr, col_idx, values
+    r = (_native or _load_native()).compress(X, br, bc, keep_mask, n_keep, row_ptr, col_idx, values, ws, stream)
+    return r if type(r) is not int else _failed(r, X, "bsr_compress")
 
 
 def bsr_decompress(row_ptr: torch.Tensor, col_idx: torch.Tensor, values: torch.Tensor, M: int,
                    K: int, br: int, bc: int, *, out: Optional[torch.Tensor] = None, stream=None):
     """-> X_out [M x K]: kept blocks bit for bit, +0.0 elsewhere."""
-    if out is None:
-        out = torch.empty((M, K), dtype=values.dtype, device=values.device)
-    _, _, ldx = _dense2d(out, "out")
-    rc = lib().bsr_decompress(_ptr(row_ptr), _ptr(col_idx), _ptr(values), dtype_code(values.dtype),
-                              M, K, ldx, br, bc, _ptr(out), _stream(stream))
-    _check(rc, "bsr_decompress")
-    return out
+    r = (_native or _load_native()).decompress(row_ptr, col_idx, values, M, K, br, bc, out, stream)
+    return r if type(r) is not int else _failed(r, values, "bsr_decompress")
 
 
 def bsr_t_dense_matmul(row_ptr: torch.Tensor, col_idx: torch.Tensor, values: torch.Tensor, M: int,
@@ -299,24 +284,8 @@ def bsr_t_dense_matmul(row_ptr: torch.Tensor, col_idx: torch.Tensor, values: tor
                        dW: Optional[torch.Tensor] = None, accumulate: bool = False,
                        ws: Optional[torch.Tensor] = None, stream=None):
     """-> dW [K x N] float32 = Xhat^T dY (added to dW when accumulate)."""
-    Md, N, lddy = _dense2d(dY, "dY")
-    if Md != M:
-        raise ValueError("dY must have M rows")
-    if dW is None:
-        if accumulate:
-            raise ValueError("accumulate needs an existing dW")
-        dW = torch.empty((K, N), dtype=torch.float32, device=dY.device)
-    _, _, lddw = _dense2d(dW, "dW")
-    code = dtype_code(dY.dtype)
-    if values.dtype != dY.dtype:
-        raise BsrError(BSR_ERR_DTYPE, "values and dY differ in dtype")
-    if ws is None:
-        ws = _workspace(bsr_workspace_bytes(BSR_OP_T_DENSE_MATMUL, M, K, N, br, bc, code), dY.device, None)
-    rc = lib().bsr_t_dense_matmul(_ptr(row_ptr), _ptr(col_idx), _ptr(values), code, M, K, br, bc,
-                                  _ptr(dY), N, lddy, _ptr(dW), lddw, 1 if accumulate else 0,
-                                  _ptr(ws), ws.numel() if ws is not None else 0, _stream(stream))
-    _check(rc, "bsr_t_dense_matmul")
-    return dW
+    r = (_native or _load_native()).t_dense_matmul(row_ptr, col_idx, values, M, K, br, bc, dY, dW, accumulate, ws, stream)
+    return r if type(r) is not int else _failed(r, dY, "bsr_t_dense_matmul", values)
 
 
 def bsr_affine_scale_grad(row_ptr: torch.Tensor, col_idx: torch.Tensor, values: torch.Tensor, M: int,
@@ -324,23 +293,9 @@ def bsr_affine_scale_grad(row_ptr: torch.Tensor, col_idx: torch.Tensor, values: 
                           dalpha: Optional[torch.Tensor] = None, accumulate: bool = False,
                           ws: Optional[torch.Tensor] = None, stream=None):
     """-> dalpha [K] float32: scale gradient of the affine layer from its pruned input (dY is [M x K])."""
-    Md, Kd, lddy = _dense2d(dY, "dY")
-    if Md != M or Kd != K:
-        raise ValueError("dY must be [M x K]")
-    if dalpha is None:
-        if accumulate:
-            raise ValueError("accumulate needs an existing dalpha")
-        dalpha = torch.empty(K, dtype=torch.float32, device=dY.device)
-    code = dtype_code(dY.dtype)
-    if values.dtype != dY.dtype:
-        raise BsrError(BSR_ERR_DTYPE, "values and dY differ in dtype")
-    if ws is None:
-        ws = _workspace(bsr_workspace_bytes(BSR_OP_AFFINE_SCALE_GRAD, M, K, 0, br, bc, code), dY.device, None)
-    rc = lib().bsr_affine_scale_grad(_ptr(row_ptr), _ptr(col_idx), _ptr(values), code, M, K, br, bc,
-                                     _ptr(dY), lddy, _ptr(dalpha), 1 if accumulate else 0,
-                                     _ptr(ws), ws.numel() if ws is not None else 0, _stream(stream))
-    _check(rc, "bsr_affine_scale_grad")
-    return dalpha
+    r = (_native or _load_native()).affine_scale_grad(row_ptr, col_idx, values, M, K, br, bc, dY, dalpha, accumulate, ws,
+                                                      stream)
+    return r if type(r) is not int else _failed(r, dY, "bsr_affine_scale_grad", values)
 
 
 class _SelectItem(C.Structure):

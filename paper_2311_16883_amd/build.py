@@ -1,8 +1,10 @@
-"""Build libbsr_actprune.so (HIP, gfx950) in-tree with hipcc.
+"""Build libbsr_actprune.so (HIP, gfx950) and the extension module over it, in-tree.
 
 ``python -m paper_2311_16883_amd.build`` compiles every ``csrc/*.hip`` file for
-gfx950 and links them into ``paper_2311_16883_amd/libbsr_actprune.so``.  hipcc
-cross-compiles without a GPU.
+gfx950 and links them into ``paper_2311_16883_amd/libbsr_actprune.so`` (hipcc
+cross-compiles without a GPU), then compiles ``csrc/torch_calls.cpp`` into
+``paper_2311_16883_amd/_torch_calls.so``, which calls that library with torch
+tensors as arguments.
 """
 from __future__ import annotations
 
@@ -10,6 +12,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -18,8 +21,10 @@ ROOT = PKG.parent
 CSRC = PKG / "csrc"
 OBJ = PKG / "_build"
 LIB = PKG / "libbsr_actprune.so"
+CALLS = PKG / "_torch_calls.so"
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+ROCM_INCLUDE = Path(HIPCC).resolve().parent.parent / "include"
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -67,7 +72,28 @@ def build_library(verbose: bool = False, jobs: int = 8) -> Path:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     os.replace(tmp, LIB)
+    build_calls(verbose)
     return LIB
+
+
+def build_calls(verbose: bool = False) -> Path:
+    """The extension module: host code only, needs the library to link against."""
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    tmp = CALLS.with_suffix(f".{os.getpid()}.tmp")
+    rocm = ROCM_INCLUDE if ROCM_INCLUDE.exists() else Path("/opt/rocm/include")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{ROOT / 'include'}",
+           *(f"-isystem{p}" for p in [*include_paths(), sysconfig.get_paths()["include"], str(rocm)]),
+           str(CSRC / "torch_calls.cpp"), "-o", str(tmp), f"-L{PKG}", "-lbsr_actprune", "-Wl,-rpath,$ORIGIN",
+           *(f"-L{p}" for p in library_paths()), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on torch_calls.cpp:\n{r.stderr}")
+    os.replace(tmp, CALLS)
+    return CALLS
 
 
 if __name__ == "__main__":

@@ -295,3 +295,20 @@ def test_static_entry_point_refuses_oversized_problems_on_the_host():
     assert lib.bsr_score_select_static(fake, 7, 64, 64, 64, 16, 16, 0.5, None, fake, None) == B.BSR_ERR_DTYPE
     assert lib.bsr_score_select_static(fake, B.BSR_F32, 64, 64, 64, 0, 16, 0.5, None, fake, None) == B.BSR_ERR_SHAPE
     assert lib.bsr_error_string(B.BSR_ERR_LIMIT) == b"BSR_ERR_LIMIT"
+
+
+@pytest.mark.parametrize("call", [
+    lambda x: B.bsr_score_select(x, 2, 2, 0.5),
+    lambda x: B.bsr_score_select_grouped(x, 2, 2, 1, 0.5),
+    lambda x: B.bsr_compress(x, 2, 2, x, 2),
+    lambda x: B.bsr_decompress(x, x, x, 4, 4, 2, 2, out=x),
+    lambda x: B.bsr_t_dense_matmul(x, x, x, 4, 4, 2, 2, x),
+    lambda x: B.bsr_affine_scale_grad(x, x, x, 4, 4, 2, 2, x),
+])
+def test_native_calls_refuse_what_is_no_device_matrix(call):
+    """The marshalling in native code raises on the host, before anything is allocated or launched."""
+    import torch
+    with pytest.raises(ValueError, match="2-D device tensor"):
+        call(torch.zeros(4, 4))
+    with pytest.raises(TypeError, match="must be a tensor"):
+        call([[0.0]])
