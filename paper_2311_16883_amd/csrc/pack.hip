@@ -113,6 +113,17 @@ template <> __device__ __forceinline__ uint32_t zero_bytes<4>() { return 0; }
 template <> __device__ __forceinline__ uint2 zero_bytes<8>() { return make_uint2(0, 0); }
 template <> __device__ __forceinline__ uint4 zero_bytes<16>() { return make_uint4(0, 0, 0, 0); }
 
+// 16 bytes from any 2-byte boundary (global loads need no more on this GPU).
+struct __attribute__((packed, aligned(2))) LooseVec {
+  uint4 v;
+};
+// VB of the kernels that move 16-byte vectors whose dense side starts at any element (rows of an odd
+// width, an unaligned view); a vector that crosses the matrix edge goes element by element.
+constexpr int kLoose = 1;
+template <> struct BytesOf<kLoose> { typedef uint4 type; };
+template <> __device__ __forceinline__ uint4 zero_bytes<kLoose>() { return make_uint4(0, 0, 0, 0); }
+template <int VB> constexpr int vector_bytes() { return VB == kLoose ? 16 : VB; }
+
 // Gather: one workgroup per block-row (grid-stride), threads over
 // (kept block, row, vector).  rowb / ldb / kb are in bytes.
 template <int VB>
@@ -185,7 +196,7 @@ struct CompressArgs {
   int64_t M, kb, ldb, bcb, nbr, nbc, n_keep;
   int br;
   uint32_t wg_begin;       // first workgroup of this tensor in a launch of several
-  int have_row_ptr;        // row_ptr was written by row_ptr_batched_kernel: nothing to count here
+  int have_row_ptr;        // row_ptr was written by row_ptr_kernel: nothing to count here
 };
 
 // i = block-row (the workgroup's number among those of its tensor)
@@ -233,16 +244,32 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const int64
   if (nk == 0) return;
 
   // ---- copy ----
-  const int vpb = (int)(bcb / VB);
+  constexpr int kBytes = vector_bytes<VB>();
+  const int vpb = (int)(bcb / kBytes);
   const int S = br * vpb;                                  // vectors per block
   const uint8_t *xrow = X + i * br * ldb;
-  uint8_t *vrow = values + (int64_t)prefix * S * VB;
+  uint8_t *vrow = values + (int64_t)prefix * S * kBytes;
   const int64_t rows_left = M - i * br;
   auto copy = [&](int q, int r, int v, int e) {
-    const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * VB;
+    const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * kBytes;
+    const uint8_t *src = xrow + (int64_t)r * ldb + cb;
     V val = zero_bytes<VB>();
-    if (r < rows_left && cb < kb) val = *reinterpret_cast<const V *>(xrow + (int64_t)r * ldb + cb);
-    store_stream(reinterpret_cast<V *>(vrow + ((int64_t)q * S + e) * VB), val);
+    if constexpr (VB == kLoose) {
+      if (r < rows_left) {
+        if (cb + kBytes <= kb) {
+          val = reinterpret_cast<const LooseVec *>(src)->v;
+        } else {
+          uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+          for (int k = 0; k < kBytes / 2; ++k)
+            if (cb + 2 * k < kb) w[k >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(src)[k] << (16 * (k & 1));
+          val = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+      }
+    } else {
+      if (r < rows_left && cb < kb) val = *reinterpret_cast<const V *>(src);
+    }
+    store_stream(reinterpret_cast<V *>(vrow + ((int64_t)q * S + e) * kBytes), val);
   };
   if (S <= 256) {
     const int G = 256 / S, g = t / S, e = t - g * S;      // G blocks per pass
@@ -420,79 +447,93 @@ __global__ __launch_bounds__(256) void span_count_kernel(const uint8_t *__restri
   if (lane == 0) wg_kept[w] = cnt;
 }
 
-// row_ptr of several tensors in one launch, one workgroup of 1024 threads per tensor: the mask is
-// read front to back, 16 blocks per thread and pass, with a running count of the kept blocks in
-// front of every block (lane exchanges inside a wave, the waves' totals through LDS); the thread
-// that holds the first block of a block-row writes that row's entry.  With row_ptr at hand the
-// conversion kernels need not count the mask in front of their rows (every workgroup on its own,
-// out of L2: more bytes than the tensor itself for narrow blocks).
+// row_ptr of one or several tensors (blockIdx.y) in one launch: a workgroup owns a slice of
+// kRowPtrSlice blocks of the mask, 16 per thread.  It counts the kept blocks in front of its slice --
+// a workgroup of 1024 threads takes in 16 KB of mask per round of loads, eight rounds on their way at a
+// time -- then scans its own, and the thread that holds the first block of a block-row writes that row's
+// entry.  With row_ptr at hand the conversion kernels need not count the mask in front of their rows
+// (every workgroup on its own, out of L2: more bytes than the tensor itself for narrow blocks).
+// (36 tensors of up to 49152 blocks: 5 us, 11 us with one workgroup per tensor.)
 constexpr int kRowPtrThreads = 1024;
+constexpr int kRowPtrPer = 16;                             // blocks per thread
+constexpr int kRowPtrSlice = kRowPtrPer * kRowPtrThreads;
 constexpr int kRowPtrBatchMax = 40;
-constexpr int64_t kRowPtrMaxBlocks = int64_t(1) << 22;     // one workgroup reads the whole mask
+constexpr int64_t kRowPtrMaxBlocks = int64_t(1) << 22;
 struct RowPtrItem {
   const uint8_t *mask;
   int32_t *row_ptr;
   int64_t nbr, nbc;
 };
+template <int N>
 struct RowPtrBatch {
-  RowPtrItem it[kRowPtrBatchMax];
+  RowPtrItem it[N];
 };
-__global__ __launch_bounds__(kRowPtrThreads) void row_ptr_batched_kernel(RowPtrBatch b) {
-  const RowPtrItem &it = b.it[blockIdx.x];
+template <int N>
+__global__ __launch_bounds__(kRowPtrThreads) void row_ptr_kernel(RowPtrBatch<N> b) {
+  const RowPtrItem &it = b.it[blockIdx.y];
   const uint8_t *__restrict__ mask = it.mask;
   int32_t *__restrict__ row_ptr = it.row_ptr;
   const uint32_t nbc = (uint32_t)it.nbc;
   const uint32_t nblocks = (uint32_t)(it.nbr * it.nbc);
-  constexpr int kPer = 16;                                  // blocks per thread and pass
-  __shared__ uint32_t wave_tot[2][kRowPtrThreads / 64];
+  const uint32_t e0 = blockIdx.x * (uint32_t)kRowPtrSlice;
+  if (e0 >= nblocks) return;
+  __shared__ uint32_t front[kRowPtrThreads / 64], wave_tot[kRowPtrThreads / 64];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t base = 0;                                        // kept blocks in front of this pass
-  const bool aligned = reinterpret_cast<uintptr_t>(mask) % 16 == 0;
-  int phase = 0;
-  for (uint32_t e0 = 0; e0 < nblocks; e0 += kPer * kRowPtrThreads, phase ^= 1) {
-    const uint32_t first = e0 + (uint32_t)t * kPer;
-    uint8_t f[kPer];
-    if (aligned && first + kPer <= nblocks) {
-      const uint4 v = *reinterpret_cast<const uint4 *>(mask + first);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  const uint32_t first = e0 + (uint32_t)t * kRowPtrPer;
+  uint32_t w[4] = {0, 0, 0, 0};                             // this thread's 16 mask bytes
+  if (first + kRowPtrPer <= nblocks) {
+    const uint4 v = reinterpret_cast<const LooseVec *>(mask + first)->v;
+    w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+  } else {
 #pragma unroll
-      for (int k = 0; k < kPer; ++k) f[k] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
-    } else {
+    for (int k = 0; k < kRowPtrPer; ++k)
+      if (first + k < nblocks) w[k >> 2] |= (uint32_t)mask[first + k] << (8 * (k & 3));
+  }
+  uint32_t before = 0;
+  const uint8_t *mine = mask + (uint32_t)t * kRowPtrPer;
+#pragma unroll 8
+  for (uint32_t r = 0; r < blockIdx.x; ++r) {
+    const uint4 x = reinterpret_cast<const LooseVec *>(mine + r * (uint32_t)kRowPtrSlice)->v;
+    before += nonzero_bytes(x.x) + nonzero_bytes(x.y) + nonzero_bytes(x.z) + nonzero_bytes(x.w);
+  }
 #pragma unroll
-      for (int k = 0; k < kPer; ++k) f[k] = first + k < nblocks ? mask[first + k] : (uint8_t)0;
-    }
-    uint32_t mine = 0;
+  for (int d = 32; d >= 1; d >>= 1) before += __shfl_xor(before, d, 64);
+  const uint32_t own = nonzero_bytes(w[0]) + nonzero_bytes(w[1]) + nonzero_bytes(w[2]) + nonzero_bytes(w[3]);
+  uint32_t incl = own;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) mine += f[k] != 0 ? 1u : 0u;
-    uint32_t incl = mine;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t up = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += up;
+  }
+  if (lane == 63) wave_tot[wave] = incl;
+  if (lane == 0) front[wave] = before;
+  __syncthreads();
+  uint32_t run = incl - own, all = 0;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t up = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += up;
-    }
-    if (lane == 63) wave_tot[phase][wave] = incl;
-    __syncthreads();
-    uint32_t before = base, all = 0;
+  for (int v = 0; v < kRowPtrThreads / 64; ++v) {
+    run += front[v];
+    all += front[v] + wave_tot[v];
+    if (v < wave) run += wave_tot[v];
+  }
+  if (first < nblocks) {
+    uint32_t r = first / nbc, c = first - r * nbc;          // block-row and column of the thread's first block
 #pragma unroll
-    for (int w = 0; w < kRowPtrThreads / 64; ++w) {
-      if (w < wave) before += wave_tot[phase][w];
-      all += wave_tot[phase][w];
-    }
-    uint32_t run = before + incl - mine;
-    if (first < nblocks) {
-      uint32_t r = first / nbc, c = first - r * nbc;        // block-row and column of the thread's first block
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        if (first + k < nblocks) {
-          if (c == 0) row_ptr[r] = (int32_t)run;
-          run += f[k] != 0 ? 1u : 0u;
-          if (++c == nbc) { c = 0; ++r; }
-        }
+    for (int k = 0; k < kRowPtrPer; ++k) {
+      if (first + k < nblocks) {
+        if (c == 0) row_ptr[r] = (int32_t)run;
+        run += (w[k >> 2] >> (8 * (k & 3))) & 0xFFu ? 1u : 0u;
+        if (++c == nbc) { c = 0; ++r; }
       }
     }
-    base += all;
   }
-  if (t == 0) row_ptr[it.nbr] = (int32_t)base;
+  if (t == 0 && nblocks - e0 <= (uint32_t)kRowPtrSlice) row_ptr[it.nbr] = (int32_t)all;
+}
+
+// The launch for the first m tensors of b, the longest of `most` blocks.
+template <int N>
+int run_row_ptr(const RowPtrBatch<N> &b, int m, int64_t most, hipStream_t s) {
+  hipLaunchKernelGGL(row_ptr_kernel<N>, dim3((unsigned)ceil_div(most, (int64_t)kRowPtrSlice), m), dim3(kRowPtrThreads), 0, s, b);
+  return check_launch();
 }
 
 struct CompressSpanArgs {
@@ -504,7 +545,7 @@ struct CompressSpanArgs {
   SpanGeom g;
   uint32_t span_words;
   uint32_t wg_begin;        // first workgroup of this tensor in a launch of several
-  int have_row_ptr;         // row_ptr was written by row_ptr_batched_kernel: nothing to count here
+  int have_row_ptr;         // row_ptr was written by row_ptr_kernel: nothing to count here
 };
 
 // wg = the workgroup's number among those of its tensor
@@ -799,6 +840,7 @@ enum { kPackSpan = 0, kPackDirect = 1, kPackOther = 2 };
 struct CompressPlan {
   int path, vb;
   bool count_first;          // span path: a first launch counts every workgroup's kept blocks
+  bool rows_first;           // direct path: a first launch writes row_ptr
   unsigned wgs;
   size_t lds;
   CompressArgs direct;
@@ -825,8 +867,7 @@ CompressPlan plan_compress(const CompressJob &j, int dtype) {
                               static_cast<uint32_t *>(j.values), j.M, nbr, j.n_keep, g, (uint32_t)span_words, 0u, 0};
     return p;
   }
-  // one fused launch when a block-row's columns fit its LDS list and re-reading the
-  // mask prefix in every workgroup stays cheap (nbr * nblocks / 2 bytes out of L2)
+  // one workgroup per block-row when its columns fit the LDS list
   const bool fused = nbr > 0 && nbc > 0 && nbc <= kFusedCols && nbr <= 65535 &&
                      nbr * nbr * nbc <= (int64_t(1) << 31);
   if (!fused) {
@@ -835,6 +876,13 @@ CompressPlan plan_compress(const CompressJob &j, int dtype) {
   }
   p.path = kPackDirect;
   p.vb = pick_bytes(e, j.bc, j.K, j.ldx, j.X, j.values);
+  // Rows of X that start anywhere, blocks that are whole 16-byte vectors: 16 bytes from where they are
+  // ([9947 x 411] bf16, 32x32 blocks: 22 us element by element, 7 us so).
+  if (p.vb < 16 && (int64_t)j.bc * e % 16 == 0 && (uintptr_t)j.values % 16 == 0) p.vb = kLoose;
+  // Every workgroup counts the mask in front of its row, nbr * nblocks / 2 bytes out of L2 in all, unless a
+  // launch writes row_ptr first (about 5 us): from 32 MB on that is the faster way (mask of 3136 x 96
+  // blocks, 472 MB: 48 us -> 5 + 29 us; 784 x 48 blocks, 15 MB: no gain).
+  p.rows_first = nbr * nbr * nbc / 2 > (int64_t(32) << 20);
   p.wgs = (unsigned)nbr;
   p.direct = CompressArgs{j.keep_mask, static_cast<const uint8_t *>(j.X), j.row_ptr, j.col_idx,
                           static_cast<uint8_t *>(j.values), j.M, j.K * e, j.ldx * e, (int64_t)j.bc * e, nbr, nbc,
@@ -883,7 +931,7 @@ int launch_compress(const uint8_t *keep_mask, const void *X, int dtype, int64_t 
                     int br, int bc, int64_t n_keep, int32_t *row_ptr, int32_t *col_idx, void *values,
                     void *ws, hipStream_t s) {
   const CompressJob job{keep_mask, X, M, K, ldx, br, bc, n_keep, row_ptr, col_idx, values, ws};
-  const CompressPlan p = plan_compress(job, dtype);
+  CompressPlan p = plan_compress(job, dtype);
   if (p.path == kPackSpan) {
     if (p.count_first) {
       const SpanGeom &g = p.span.g;
@@ -908,9 +956,17 @@ int launch_compress(const uint8_t *keep_mask, const void *X, int dtype, int64_t 
     if (rc != BSR_OK) return rc;
     return launch_pack(X, dtype, M, K, ldx, br, bc, row_ptr, col_idx, n_keep, values, s);
   }
+  if (p.rows_first) {
+    RowPtrBatch<1> b;
+    b.it[0] = RowPtrItem{keep_mask, row_ptr, p.direct.nbr, p.direct.nbc};
+    const int rc = run_row_ptr<1>(b, 1, p.direct.nbr * p.direct.nbc, s);
+    if (rc != BSR_OK) return rc;
+    p.direct.have_row_ptr = 1;
+  }
 #define BSR_COMPRESS(VB) hipLaunchKernelGGL((compress_kernel<VB>), dim3(p.wgs), dim3(256), 0, s, p.direct)
   switch (p.vb) {
     case 16: BSR_COMPRESS(16); break;
+    case kLoose: BSR_COMPRESS(kLoose); break;
     case 8: BSR_COMPRESS(8); break;
     case 4: BSR_COMPRESS(4); break;
     default: BSR_COMPRESS(2); break;
@@ -952,26 +1008,29 @@ int launch_decompress(const int32_t *row_ptr, const int32_t *col_idx, const void
 // pass, separate index build) goes through the single-tensor path.  The results are those of the
 // single-tensor calls (bit copies either way).
 int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream_t s) {
-  static const int kVbs[4] = {16, 8, 4, 2};
+  static const int kVbs[5] = {16, 8, 4, 2, kLoose};
   std::vector<CompressPlan> plans((size_t)n);
   for (int i = 0; i < n; ++i) plans[(size_t)i] = plan_compress(jobs[i], dtype);
   // with several tensors in the call one more launch costs little next to what it saves: row_ptr of
-  // every tensor first, one workgroup per tensor
-  if (n >= 2) {
-    RowPtrBatch rb;
+  // every tensor first
+  {
+    RowPtrBatch<kRowPtrBatchMax> rb;
     int m = 0;
+    int64_t most = 0;
     auto flush_rows = [&]() -> int {
       if (m == 0) return BSR_OK;
-      hipLaunchKernelGGL(row_ptr_batched_kernel, dim3(m), dim3(kRowPtrThreads), 0, s, rb);
+      const int rc = run_row_ptr<kRowPtrBatchMax>(rb, m, most, s);
       m = 0;
-      return check_launch();
+      most = 0;
+      return rc;
     };
     for (int i = 0; i < n; ++i) {
       CompressPlan &p = plans[(size_t)i];
       const CompressJob &j = jobs[i];
       const int64_t nbr = ceil_div(j.M, j.br), nbc = ceil_div(j.K, j.bc);
-      if (p.path == kPackOther || p.wgs == 0 || nbr * nbc > kRowPtrMaxBlocks) continue;
+      if (p.path == kPackOther || p.wgs == 0 || nbr * nbc > kRowPtrMaxBlocks || (n < 2 && !p.rows_first)) continue;
       rb.it[m] = RowPtrItem{j.keep_mask, j.row_ptr, nbr, nbc};
+      if (nbr * nbc > most) most = nbr * nbc;
       if (p.path == kPackSpan) {
         p.span.have_row_ptr = 1;
         p.span.wg_kept = nullptr;
@@ -988,7 +1047,7 @@ int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream
     if (rc != BSR_OK) return rc;
   }
   for (int path = kPackSpan; path <= kPackDirect; ++path) {
-    for (int vi = 0; vi < 4; ++vi) {
+    for (int vi = 0; vi < 5; ++vi) {
       const int vb = kVbs[vi];
       CompressBatch db;
       CompressSpanBatch sb;
@@ -1006,6 +1065,7 @@ int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream
         } else {
           switch (vb) {
             case 16: hipLaunchKernelGGL((compress_batched_kernel<16>), dim3(total), dim3(256), 0, s, db, m); break;
+            case kLoose: hipLaunchKernelGGL((compress_batched_kernel<kLoose>), dim3(total), dim3(256), 0, s, db, m); break;
             case 8: hipLaunchKernelGGL((compress_batched_kernel<8>), dim3(total), dim3(256), 0, s, db, m); break;
             case 4: hipLaunchKernelGGL((compress_batched_kernel<4>), dim3(total), dim3(256), 0, s, db, m); break;
             default: hipLaunchKernelGGL((compress_batched_kernel<2>), dim3(total), dim3(256), 0, s, db, m); break;

@@ -1043,3 +1043,29 @@ def test_selection_sizes_at_the_edges_of_its_paths(nblocks, levels):
             got = mask.cpu().numpy()
             assert np.array_equal(got[shift:nblocks + shift], mask_ref), (nblocks, levels, shift, keep)
             assert np.all(np.delete(got, np.s_[shift:nblocks + shift]) == 7)      # nothing beside the mask
+
+
+@pytest.mark.parametrize("M,K,br,bc,dtype,pad,shift", [
+    (70, 41, 32, 32, "bf16", 0, 0),          # odd row length: 16-byte vectors from 2-byte boundaries, cut at the edge
+    (333, 1001, 16, 16, "f32", 0, 0),        # the same from 4-byte boundaries
+    (130, 96, 32, 32, "bf16", 5, 1),         # rows of whole vectors in a view that starts and continues unaligned
+    (97, 33, 8, 8, "bf16", 2, 3),            # one valid column in the last block
+    (64, 64, 16, 16, "f32", 1, 1),
+    (51200, 128, 16, 16, "bf16", 0, 0),      # a mask so long that row_ptr is written by a launch of its own
+])
+def test_conversion_of_unaligned_rows_and_long_masks(M, K, br, bc, dtype, pad, shift):
+    X = rand_pair(M, K, 1, dtype, seed=M + K)[0]
+    wide = torch.full((M, K + pad), 3.0, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    view = wide.flatten()[shift:].as_strided((M if pad == 0 else M - 1, K), (K + pad, 1)) if shift else wide[:, :K]
+    view.copy_(to_dev(X)[:view.shape[0]])
+    X = X[:view.shape[0]]
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, br, bc, 0.4)
+    mask = B.bsr_score_select(view, br, bc, 0.4)
+    row_ptr, col_idx, values = B.bsr_compress(view, br, bc, mask, len(o_ci))
+    batch = B.CompressBatch([(view, br, bc, mask, len(o_ci)), (view, br, bc, mask, len(o_ci))])
+    outs = B.bsr_compress_batched(batch) + [(row_ptr, col_idx, values)]
+    torch.cuda.synchronize()
+    assert np.array_equal(mask.cpu().numpy(), o_mask)
+    for rp, ci, val in outs:
+        assert np.array_equal(rp.cpu().numpy(), o_rp) and np.array_equal(ci.cpu().numpy(), o_ci)
+        assert to_host(val).tobytes() == o_val.tobytes()
