@@ -45,6 +45,11 @@ typedef __attribute__((ext_vector_type(8))) short v8s;
 typedef __attribute__((ext_vector_type(8))) __bf16 v8bf;
 typedef __attribute__((ext_vector_type(16))) float v16f;
 
+// 16 bytes from any 2-byte boundary
+struct __attribute__((packed, aligned(2))) LooseVec {
+  u32x4 v;
+};
+
 constexpr int kMaxRowsPerSplit = 512;   // block-rows of one split: its block table must fit in LDS
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose
@@ -103,30 +108,36 @@ __device__ __forceinline__ int lane_fragment_offset(int col0) {
 
 constexpr int KT = 128, NT = 128;   // dW tile of one workgroup: 2 x WN waves, 64 x (128 / WN) each
 
+// Columns of the activation tile that a block-column takes: its own, or for 14-wide blocks a slot of 16,
+// so that a row of a block is whole 16-byte vectors there (two for bfloat16 where pieces of 4 bytes took
+// seven; the texture path spends as long on a narrow load as on a wide one).  The last vector of a
+// row reaches two columns beyond the block: what follows in memory, or zeros behind the last block, lands
+// in columns of the tile that belong to no row of dW.
+constexpr int slot_columns(int bc) { return bc == 14 ? 16 : bc; }
+constexpr int tile_block_columns(int bc) { return KT / slot_columns(bc); }
+
 // E = bytes per element of the inputs (2: bfloat16, 4: binary32).
-template <int E, int BR, int BC, int MS, int VB, int WN>
+template <int E, int BR, int BC, int MS, int WN>
 struct Geo {
   static constexpr int THREADS = 128 * WN;                // threads per role: 2 x WN waves
   static constexpr int NTW = NT / (32 * WN);               // 32-column pieces of dW per wave along N
   static constexpr int R = MS / BR;                       // block-rows per stage
   static constexpr int ROWS = R * BR;                     // rows of a stage that carry data
-  static constexpr bool KALIGNED = (KT % BC == 0);
-  static constexpr int JT = KALIGNED ? KT / BC : KT / BC + 2;   // block-columns that can cross a tile
+  static constexpr int CS = slot_columns(BC);
+  static constexpr int JT = tile_block_columns(BC);       // block-columns of a tile
   // every 16 x 32 piece of the activation tile lies inside one block: pruned
   // blocks are skipped outright and their LDS content is never read
-  static constexpr bool SKIP_ONLY = (BC % 32 == 0) && (BR % 16 == 0) && KALIGNED;
-  // elements per activation vector: at most 16 bytes, inside one block row
-  static constexpr int VA = (E == 2 && BC % 8 == 0) ? 8 : ((BC % 4 == 0) ? 4 : ((BC % 2 == 0) ? 2 : 1));
-  static constexpr int VPB = BR * BC / VA;                // vectors per block
+  static constexpr bool SKIP_ONLY = (BC % 32 == 0) && (BR % 16 == 0);
+  static constexpr int VA = 16 / E;                       // elements per activation vector: 16 bytes
+  static constexpr int VPR = CS / VA;                     // vectors per block row
+  static constexpr int VPB = BR * VPR;                    // vectors per block
+  static constexpr int VB = 16 / E;                       // elements per dY vector
   static constexpr int NA = (R * JT * VPB + THREADS - 1) / THREADS;
   static constexpr int NB = (ROWS * (NT / VB) + THREADS - 1) / THREADS;
   static constexpr int LDA = kLd, LDB = kLd;             // LDS rows (elements), swizzled not padded
   static constexpr int MSUB = MS / 16;
-  // a wave-wide activation load (64 vectors) never straddles two blocks: the keep
-  // decision and the block address are wave-uniform and live in scalar registers
-  static constexpr bool UNIFORM_A = (VPB % 64 == 0);
   static constexpr int STAGE_WORDS = (MS * LDA + MS * LDB) * E / 4;   // 32-bit words of one stage (A tile, B tile)
-  static_assert(MS % 16 == 0 && R >= 1 && MSUB <= 8, "stage shape");
+  static_assert(MS % 16 == 0 && R >= 1 && MSUB <= 8 && CS % VA == 0 && KT % CS == 0, "stage shape");
   static_assert(JT <= 32, "tile index is a 32-bit mask");
 };
 
@@ -134,6 +145,7 @@ struct Geo {
 // WN = multiplier waves along N (2: 64 x 64 per wave, 4: 64 x 32 per wave); the
 // workgroup has 2 x WN multiplier waves and as many loader waves.
 // T = uint16_t (bfloat16 bits) or float.
+// ODD: rows of dY may start on odd elements (bfloat16): see load_b.
 // What one tensor's launch needs (kernel arguments; an array of these for a batch).
 struct DwParams {
   const int32_t *row_ptr, *col_idx;
@@ -141,12 +153,11 @@ struct DwParams {
   float *out;
   int64_t M, K, N, lddy, ldo, split_stride, nbr, nbc, stages_per_split;
   int accumulate, tiles_k, tiles_n, splits;
-  uint32_t values_bytes;
   uint32_t wg_begin;       // first work item of this tensor in a batched launch's list
 };
 
 // wg = number of the workgroup among those of this tensor.
-template <typename T, int BR, int BC, int MS, int VB, int D, int WN>
+template <typename T, int BR, int BC, int MS, bool ODD, int D, int WN>
 __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t wg, const int xcd_map) {
   const int32_t *__restrict__ row_ptr = prm.row_ptr;
   const int32_t *__restrict__ col_idx = prm.col_idx;
@@ -156,9 +167,10 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const int64_t M = prm.M, K = prm.K, N = prm.N, lddy = prm.lddy, ldo = prm.ldo, split_stride = prm.split_stride;
   const int64_t nbr = prm.nbr, nbc = prm.nbc, stages_per_split = prm.stages_per_split;
   const int accumulate = prm.accumulate, tiles_k = prm.tiles_k, tiles_n = prm.tiles_n, splits = prm.splits;
-  const uint32_t values_bytes = prm.values_bytes;
   constexpr int E = (int)sizeof(T);
-  typedef Geo<E, BR, BC, MS, VB, WN> G;
+  static_assert(!ODD || E == 2, "binary32 rows start on whole words");
+  typedef Geo<E, BR, BC, MS, WN> G;
+  constexpr int VB = G::VB;
   constexpr int kRole = G::THREADS;              // threads per role
   constexpr int kThreads = 2 * kRole;            // workgroup
   typedef typename Chunk<G::VA * E>::type AVec;
@@ -213,7 +225,7 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const bool loader = wave_wg >= 2 * WN;
   const int wave = loader ? wave_wg - 2 * WN : wave_wg;      // wave inside its role
   const int tg = loader ? t - kRole : t;                       // thread inside its role
-  const int64_t k0 = (int64_t)tile_x * KT, n0 = (int64_t)tile_y * NT;
+  const int64_t n0 = (int64_t)tile_y * NT;
   const int64_t total_stages = ceil_div(nbr, G::R);
   const int64_t s_begin = (int64_t)split * stages_per_split;
   int64_t s_end = s_begin + stages_per_split;
@@ -221,8 +233,8 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const int nstages = s_end > s_begin ? (int)(s_end - s_begin) : 0;
   const int64_t i_begin = s_begin * G::R;
   const int nrows = nstages * G::R;                       // block-rows of this split (may run past nbr)
-  const int64_t jfirst = k0 / BC;
-  int64_t jlast = (k0 + KT - 1) / BC;
+  const int64_t jfirst = (int64_t)tile_x * G::JT;
+  int64_t jlast = jfirst + G::JT - 1;
   if (jlast > nbc - 1) jlast = nbc - 1;
   const int jt = (int)(jlast - jfirst + 1);
 
@@ -272,7 +284,7 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
     uint32_t colmask[2][2] = {{0u, 0u}, {0u, 0u}};
 #pragma unroll
     for (int jl = 0; jl < G::JT; ++jl) {
-      const int c0 = (int)((jfirst + jl) * BC - k0), c1 = c0 + BC - 1;
+      const int c0 = jl * G::CS, c1 = c0 + BC - 1;
 #pragma unroll
       for (int x = 0; x < 4; ++x)
         if (jl < jt && c0 <= x * 32 + 31 && c1 >= x * 32) colmask[x >> 1][x & 1] |= 1u << jl;
@@ -313,10 +325,10 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
       const int v = tg + it * kRole;
       const int slot = v / G::VPB, off = v % G::VPB;
       const int rbk = slot / G::JT, jl = slot % G::JT;
-      const int r = (off * G::VA) / BC, c = (off * G::VA) % BC;
-      const int col = (int)((jfirst + jl) * BC - k0) + c;
-      const bool used = slot < G::R * G::JT && jl < jt && col >= 0 && col + G::VA <= KT;
-      a_src[it] = (uint32_t)(off * G::VA * E);
+      const int r = off / G::VPR, c = (off % G::VPR) * G::VA;
+      const int col = jl * G::CS + c;
+      const bool used = slot < G::R * G::JT && jl < jt;
+      a_src[it] = (uint32_t)((r * BC + c) * E);
       a_tab[it] = used ? (uint32_t)(rbk * G::JT + jl) : (uint32_t)(nrows * G::JT);
       a_inc[it] = used ? (uint32_t)(G::R * G::JT) : 0u;
       a_val[it] = sTab[a_tab[it]];
@@ -332,7 +344,7 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
       const int v = tg + it * kRole;
       const int r = v / (NT / VB), c = (v % (NT / VB)) * VB;
       const bool used = r < G::ROWS && n0 + c < N;
-      b_cur[it] = used ? (uint32_t)(((int64_t)r * lddy + c) * E) : kOutOfRange;
+      b_cur[it] = used ? (uint32_t)(((int64_t)r * lddy + c) * E) : (ODD ? 0xFFFFFF00u : kOutOfRange);
       b_inc[it] = used ? (uint32_t)((int64_t)G::ROWS * lddy * E) : 0u;
       b_dst[it] = used ? swizzled<E>(r, c) : -1;
     }
@@ -349,13 +361,18 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
       for (int it = 0; it < G::NB; ++it)
         b_lds[buf][it] = b_dst[it] >= 0 ? buf * kStageElems + MS * G::LDA + b_dst[it] : kDump + lane * (16 / E);
     }
-    const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(values, values_bytes);
+    // (all stored blocks and not a byte more: 14-wide rows are read in vectors that reach over their end)
+    // (read as one scalar: a resource in vector registers would put a loop around every load)
+    const int64_t last = (int64_t)__builtin_amdgcn_readfirstlane(row_ptr[nbr]);
+    const int64_t stored = last < nbr * nbc ? last : nbr * nbc;
+    const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(values, (uint32_t)stored * (uint32_t)(BR * BC * E));
     int64_t split_rows = (i_begin + nrows) * BR;
     if (split_rows > M) split_rows = M;
     split_rows -= i_begin * BR;                                                // dY rows of this split
     const int64_t dy_split = split_rows > 0 ? ((split_rows - 1) * lddy + (N - n0)) * E : 0;
-    const __amdgpu_buffer_rsrc_t rsrc_b =
-        make_rsrc(reinterpret_cast<const char *>(dY) + (i_begin * BR * lddy + n0) * E, (uint32_t)dy_split);
+    const char *const dy_base = reinterpret_cast<const char *>(dY) + (i_begin * BR * lddy + n0) * E;
+    const __amdgpu_buffer_rsrc_t rsrc_b = make_rsrc(dy_base, (uint32_t)dy_split);
+    const uint32_t dy_end = (uint32_t)dy_split;
 
     AVec ra[D][G::NA];
     BVec rb[D][G::NB];
@@ -369,15 +386,41 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
       a_tab[it] += a_inc[it];
       a_val[it] = sTab[a_tab[it]];
     };
+    // dY in vectors of 16 bytes whatever the row pitch.  A vector that crosses column N brings the first
+    // columns of the next row into tile columns that belong to no column of dW; rows beyond the split read
+    // as zero.  Buffer loads need addresses that are multiples of 4 and check the range word by word.  Rows
+    // of an odd number of bfloat16 elements (ODD) are read by global loads, which need no alignment but
+    // check nothing: the address is held back so that the vector ends at the split's last element, and
+    // store_b moves the elements to their places or drops them.
     auto load_b = [&](int d, int it) {
-      rb[d][it] = buffer_load<VB * E>(rsrc_b, b_cur[it]);
+      if constexpr (ODD) {
+        const uint32_t end = b_cur[it] + 16u < dy_end ? b_cur[it] + 16u : dy_end;
+        rb[d][it] = reinterpret_cast<const LooseVec *>(dy_base - 16 + end)->v;
+      } else {
+        rb[d][it] = buffer_load<VB * E>(rsrc_b, b_cur[it]);
+      }
       b_cur[it] += b_inc[it];
     };
     // Ring slot d -> LDS stage buffer `buf`; unused vectors go to the dump slot,
     // so no store needs a predicate.
     T *const s0 = reinterpret_cast<T *>(sStage);
     auto store_a = [&](int d, int it, int buf) { *reinterpret_cast<AVec *>(&s0[a_lds[buf][it]]) = ra[d][it]; };
-    auto store_b = [&](int d, int it, int buf) { *reinterpret_cast<BVec *>(&s0[b_lds[buf][it]]) = rb[d][it]; };
+    // (the vector in ring slot d was requested D loads ago)
+    auto store_b = [&](int d, int it, int buf) {
+      BVec v = rb[d][it];
+      if constexpr (ODD) {
+        const uint32_t end = b_cur[it] - b_inc[it] * (uint32_t)D + 16u;
+        if (end > dy_end) {                                // held back by end - dy_end bytes
+          const uint32_t over = end - dy_end;
+          uint64_t lo = ((uint64_t)v[1] << 32) | v[0], hi = ((uint64_t)v[3] << 32) | v[2];
+          const uint32_t sh = 8u * (uint32_t)(over < 16 ? over : 16);
+          if (sh >= 64) { lo = sh >= 128 ? 0 : hi >> (sh - 64); hi = 0; }
+          else { lo = (lo >> sh) | (hi << (64 - sh)); hi >>= sh; }
+          v[0] = (uint32_t)lo; v[1] = (uint32_t)(lo >> 32); v[2] = (uint32_t)hi; v[3] = (uint32_t)(hi >> 32);
+        }
+      }
+      *reinterpret_cast<BVec *>(&s0[b_lds[buf][it]]) = v;
+    };
 
     // stages 0 .. D-1 into the ring, stage 0 on into LDS buffer 0, stage D after it
 #pragma unroll
@@ -553,9 +596,12 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
       for (int w = 0; w < G::NTW; ++w)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int64_t k = k0 + (2 * wk + u) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          // (the part that is the same in all lanes first: it stays in scalar registers)
+          int64_t k = jfirst * BC + (2 * wk + u) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          const int tc = (2 * wk + u) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);   // column of the activation tile
+          if constexpr (G::CS != BC) k = (jfirst + tc / G::CS) * BC + tc % G::CS;
           const int64_t n = n0 + (G::NTW * wn + w) * 32 + (lane & 31);
-          if (k < K && n < N) {
+          if ((G::CS == BC || tc % G::CS < BC) && k < K && n < N) {
             float *dst = o + k * ldo + n;
             if (kAcc) *dst += acc[u][w][r];
             else *dst = acc[u][w][r];
@@ -566,9 +612,14 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   else write_tile(std::false_type{});
 }
 
-template <typename T, int BR, int BC, int MS, int VB, int D, int WN>
-__global__ __launch_bounds__(256 * WN) void dw_mfma_kernel(DwParams prm, int xcd_map) {
-  dw_mfma_body<T, BR, BC, MS, VB, D, WN>(prm, blockIdx.x, xcd_map);
+// Waves per SIMD to leave registers for: two workgroups of 1024 threads share a compute unit with bfloat16
+// inputs (64 registers; with 76 only one fits: 120 us instead of 83 for [50176 x 1536] in 16x16 blocks).
+template <typename T, int WN>
+constexpr int min_waves() { return sizeof(T) == 2 && WN == 4 ? 8 : 1; }
+
+template <typename T, int BR, int BC, int MS, bool ODD, int D, int WN>
+__global__ __launch_bounds__(256 * WN, (min_waves<T, WN>())) void dw_mfma_kernel(DwParams prm, int xcd_map) {
+  dw_mfma_body<T, BR, BC, MS, ODD, D, WN>(prm, blockIdx.x, xcd_map);
 }
 
 // Several tensors per launch.  The work items (split, tile) of all products form one list,
@@ -587,14 +638,14 @@ struct DwBatch {
   uint32_t xcd_begin[9];
 };
 
-template <typename T, int BR, int BC, int MS, int VB, int D, int WN>
+template <typename T, int BR, int BC, int MS, bool ODD, int D, int WN>
 __global__ __launch_bounds__(256 * WN) void dw_mfma_batched_kernel(DwBatch b, int n) {
   const uint32_t x = blockIdx.x & 7u, slot = blockIdx.x >> 3;
   if (slot >= b.xcd_begin[x + 1] - b.xcd_begin[x]) return;
   const uint32_t g = b.xcd_begin[x] + slot;
   int i = 0;
   while (i + 1 < n && g >= b.it[i + 1].wg_begin) ++i;
-  dw_mfma_body<T, BR, BC, MS, VB, D, WN>(b.it[i], g - b.it[i].wg_begin, 0);
+  dw_mfma_body<T, BR, BC, MS, ODD, D, WN>(b.it[i], g - b.it[i].wg_begin, 0);
 }
 
 struct Plan {
@@ -609,13 +660,15 @@ struct Plan {
 // reduction).  The constants are measured orders of magnitude on MI355X, in microseconds
 // (a stage of a workgroup that shares its compute unit takes 0.7 us); only the choice of s
 // depends on them.
+inline int64_t dw_tiles_k(int64_t K, int bc) { return ceil_div(ceil_div(K, (int64_t)bc), (int64_t)tile_block_columns(bc)); }
+
 template <int E, int BR, int MS>
 Plan make_plan(int64_t M, int64_t K, int64_t N) {
   constexpr int R = MS / BR;
   constexpr int kSlots = E == 2 ? 512 : 256;
   const int64_t nbr = ceil_div(M, BR);
   const int64_t stages = ceil_div(nbr, R);
-  const int64_t tiles = ceil_div(K, 128) * ceil_div(N, 128);
+  const int64_t tiles = dw_tiles_k(K, BR) * ceil_div(N, 128);
   Plan p;
   p.splits = 1;
   p.stages_per_split = stages > 0 ? stages : 1;
@@ -643,13 +696,9 @@ Plan make_plan(int64_t M, int64_t K, int64_t N) {
   return p;
 }
 
-// elements per dY vector: 16 bytes at most
+// Rows of dY that may start on an odd bfloat16 element: the kernel instance with global loads.
 template <int E>
-int dy_vector(const void *dY, int64_t N, int64_t lddy) {
-  int vb = 16 / E;
-  while (vb > 1 && (N % vb != 0 || lddy % vb != 0 || (uintptr_t)dY % (E * vb) != 0)) vb >>= 1;
-  return vb;
-}
+bool dy_odd(const void *dY, int64_t lddy) { return E == 2 && (lddy % 2 != 0 || (uintptr_t)dY % 4 != 0); }
 
 // The plan of a product that shares its launch with `companions` - 1 others.  A product on
 // its own needs enough splits to occupy every compute unit; in a batch the other products
@@ -667,7 +716,7 @@ Plan make_plan_batched(int64_t M, int64_t K, int64_t N, int companions) {
   constexpr int64_t kSlots = 512, kFixed = 16;                 // fixed part of an item, in stages
   constexpr double kBytesPerStage = 2.0e6;                     // partial-tile bytes that cost the time of one stage (measured)
   const int64_t stages = ceil_div(ceil_div(M, BR), R);
-  const int64_t tiles = ceil_div(K, 128) * ceil_div(N, 128);
+  const int64_t tiles = dw_tiles_k(K, BR) * ceil_div(N, 128);
   const int64_t s_min = ceil_div(stages * R, (int64_t)kMaxRowsPerSplit);
   if (s_min >= alone.splits) return alone;
   const double split_cost = (double)companions * (double)K * (double)N * 8.0 / kBytesPerStage;
@@ -701,9 +750,7 @@ int fill_params(const DwJob &j, DwParams *prm, uint32_t *wgs, int companions = 1
   prm->split_stride = p.splits > 1 ? j.K * j.N : 0;
   prm->nbr = nbr; prm->nbc = nbc; prm->stages_per_split = p.stages_per_split;
   prm->accumulate = p.splits > 1 ? 0 : j.accumulate;
-  prm->tiles_k = (int)ceil_div(j.K, 128); prm->tiles_n = (int)ceil_div(j.N, 128); prm->splits = p.splits;
-  // 32-bit buffer offsets: both operands must stay below 4 GiB (checked by dw_mfma_supported)
-  prm->values_bytes = (uint32_t)(nbr * nbc * BR * BC * E);
+  prm->tiles_k = (int)dw_tiles_k(j.K, BC); prm->tiles_n = (int)ceil_div(j.N, 128); prm->splits = p.splits;
   prm->wg_begin = 0;
   const int64_t n_items = (int64_t)p.splits * prm->tiles_k * prm->tiles_n;
   *wgs = (uint32_t)(8 * ceil_div(n_items, 8));        // XCD-aware work item order: whole groups of 8
@@ -722,25 +769,20 @@ int run(const int32_t *row_ptr, const int32_t *col_idx, const void *values, int6
   if (rc != BSR_OK) return rc;
   const dim3 grid(wgs);
   const int xcd_map = 1;      // XCD-aware work item order (0 = plain order, kept for measurements)
-  int vb = dy_vector<E>(dY, N, lddy);
-#define BSR_DW_LAUNCH(VB)                                                                         \
-  hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, VB, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map)
-  if constexpr (E == 2) {
-    if (vb == 8) { BSR_DW_LAUNCH(8); vb = 0; }
+  if (dy_odd<E>(dY, lddy)) {
+    if constexpr (E == 2)
+      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, true, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
+  } else {
+    hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, false, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
   }
-  if (vb == 0) {}
-  else if (vb == 4) BSR_DW_LAUNCH(4);
-  else if (vb == 2) BSR_DW_LAUNCH(2);
-  else BSR_DW_LAUNCH(1);
-#undef BSR_DW_LAUNCH
   rc = check_launch();
   if (rc != BSR_OK || prm.splits == 1) return rc;
   return launch_splitk_reduce(prm.out, prm.splits, K, N, dW, lddw, accumulate, s);
 }
 
-// The jobs of one kernel instance (block shape and dY vector width `want_vb`), kDwBatchMax per launch.
+// The jobs of one kernel instance (block shape, dY rows on odd elements or not), kDwBatchMax per launch.
 template <typename T, int BR, int BC, int MS, int D, int WN>
-int run_batched(const DwJob *jobs, int n, int want_vb, hipStream_t s) {
+int run_batched(const DwJob *jobs, int n, bool odd, hipStream_t s) {
   constexpr int E = (int)sizeof(T);
   DwBatch b;
   ReduceJob red[kDwBatchMax];
@@ -773,13 +815,10 @@ int run_batched(const DwJob *jobs, int n, int want_vb, hipStream_t s) {
     for (int q = 0; q < 8; ++q)
       if (b.xcd_begin[q + 1] - b.xcd_begin[q] > longest) longest = b.xcd_begin[q + 1] - b.xcd_begin[q];
     const dim3 grid(8 * longest), block(256 * WN);
-    switch (want_vb) {
-      case 8:
-        if constexpr (E == 2) hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, 8, D, WN>), grid, block, 0, s, b, m);
-        break;
-      case 4: hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, 4, D, WN>), grid, block, 0, s, b, m); break;
-      case 2: hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, 2, D, WN>), grid, block, 0, s, b, m); break;
-      default: hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, 1, D, WN>), grid, block, 0, s, b, m); break;
+    if (odd) {
+      if constexpr (E == 2) hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, true, D, WN>), grid, block, 0, s, b, m);
+    } else {
+      hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, false, D, WN>), grid, block, 0, s, b, m);
     }
     int rc = check_launch();
     if (rc == BSR_OK && nred > 0) rc = launch_splitk_reduce_batched(red, nred, s);
@@ -790,11 +829,11 @@ int run_batched(const DwJob *jobs, int n, int want_vb, hipStream_t s) {
   };
   int mine = 0;                                              // products of this kernel instance
   for (int i = 0; i < n; ++i)
-    if (jobs[i].br == BR && jobs[i].bc == BC && dy_vector<E>(jobs[i].dY, jobs[i].N, jobs[i].lddy) == want_vb) ++mine;
+    if (jobs[i].br == BR && jobs[i].bc == BC && dy_odd<E>(jobs[i].dY, jobs[i].lddy) == odd) ++mine;
   int left = mine;
   for (int i = 0; i < n; ++i) {
     const DwJob &j = jobs[i];
-    if (j.br != BR || j.bc != BC || dy_vector<E>(j.dY, j.N, j.lddy) != want_vb) continue;
+    if (j.br != BR || j.bc != BC || dy_odd<E>(j.dY, j.lddy) != odd) continue;
     uint32_t wgs;
     // products that share this launch: the rest of the list, up to the launch's capacity
     const int companions = m + (left < kDwBatchMax - m ? left : kDwBatchMax - m);
@@ -835,6 +874,8 @@ bool dw_mfma_supported(int dtype, int br, int bc, const void *values, int64_t M,
   const int64_t e = elem_bytes(dtype);
   if (ceil_div(M, br) * br * ceil_div(K, bc) * bc * e >= (int64_t(1) << 31)) return false;
   if ((M + 8 * 64) * lddy * e >= (int64_t(1) << 32) - 64 || N > lddy) return false;
+  // (fewer than one 16-byte vector of dY in all: rows on odd elements have nothing to read it from)
+  if (dtype == BSR_BF16 && M > 0 && (M - 1) * lddy + N < 8) return false;
   return true;
 }
 
@@ -871,21 +912,19 @@ int launch_dw_mfma(int dtype, const int32_t *row_ptr, const int32_t *col_idx, co
 }
 
 int launch_dw_mfma_batched(int dtype, const DwJob *jobs, int n, hipStream_t s) {
-  static const int kVbs[4] = {8, 4, 2, 1};
-  for (int vi = 0; vi < 4; ++vi) {
-    const int vb = kVbs[vi];
+  for (const bool odd : {false, true}) {
     int rc;
     if (dtype == BSR_F32) {
-      if (vb == 8) continue;
-      if ((rc = run_batched<float, 32, 32, 64, 2, 4>(jobs, n, vb, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<float, 64, 64, 64, 2, 4>(jobs, n, vb, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<float, 16, 16, 32, 2, 4>(jobs, n, vb, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<float, 14, 14, 32, 2, 4>(jobs, n, vb, s)) != BSR_OK) return rc;
+      if (odd) continue;
+      if ((rc = run_batched<float, 32, 32, 64, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<float, 64, 64, 64, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<float, 16, 16, 32, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<float, 14, 14, 32, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
     } else {
-      if ((rc = run_batched<uint16_t, 32, 32, 64, 2, 2>(jobs, n, vb, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 64, 64, 64, 2, 2>(jobs, n, vb, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 16, 16, 32, 2, 2>(jobs, n, vb, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 14, 14, 32, 2, 2>(jobs, n, vb, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<uint16_t, 32, 32, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<uint16_t, 64, 64, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<uint16_t, 16, 16, 32, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<uint16_t, 14, 14, 32, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
     }
   }
   return BSR_OK;

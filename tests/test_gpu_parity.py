@@ -1069,3 +1069,35 @@ def test_conversion_of_unaligned_rows_and_long_masks(M, K, br, bc, dtype, pad, s
     for rp, ci, val in outs:
         assert np.array_equal(rp.cpu().numpy(), o_rp) and np.array_equal(ci.cpu().numpy(), o_ci)
         assert to_host(val).tobytes() == o_val.tobytes()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("b", [14, 16, 32, 64])
+@pytest.mark.parametrize("M,K,N,pad,shift", [
+    (129, 130, 129, 0, 0),       # dY rows on odd elements, one column in the last tile
+    (517, 197, 131, 2, 1),       # odd pitch and an odd start in memory
+    (200, 113, 7, 0, 0),         # a row of dY shorter than one vector
+    (63, 57, 130, 1, 0),         # even pitch wider than the row: vectors cross into the padding
+    (1, 14, 9, 0, 0),            # one row
+    (300, 225, 128, 0, 0),       # whole tiles
+])
+def test_dw_rows_of_dy_at_any_alignment(M, K, N, pad, shift, b, dtype):
+    """dY is read in 16-byte vectors whatever its pitch and start: what a vector holds beyond a row's end, the
+    matrix' end or a 14-wide block must reach no entry of dW.  Its surroundings are NaN here.  Tolerance: binary32
+    accumulation of at most 517 products, as in the other parity tests."""
+    X, dY = rand_pair(M, K, N, dtype, seed=M + N + b)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, b, b, 0.6)
+    ref = oracle.dw(oracle.mask_dense(X, b, b, o_mask), dY)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    flat = torch.full((shift + M * (N + pad) + 64,), float("nan"), device="cuda", dtype=dt)
+    dYd = flat[shift:].as_strided((M, N), (N + pad, 1))
+    dYd.copy_(to_dev(dY))
+    vals = torch.full((o_val.size + 64,), float("nan"), device="cuda", dtype=dt)
+    val = vals[:o_val.size].view(o_val.shape)
+    val.copy_(to_dev(o_val))
+    rp, ci = torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda()
+    batch = B.MatmulBatch([(rp, ci, val, M, K, b, b, dYd)] * 2)
+    got = [B.bsr_t_dense_matmul(rp, ci, val, M, K, b, b, dYd), *B.bsr_t_dense_matmul_batched(batch)]
+    torch.cuda.synchronize()
+    for dW in got:
+        assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
