@@ -165,8 +165,10 @@ __device__ __forceinline__ void narrow_body(const NarrowParams &prm, const uint3
     // group the first five (c even) or the last four, and four of the eight 1 KB pieces of its dY group:
     // 9 or 8 copies per stage, always.
     const int c = wave - kMathWaves, g = c >> 1, rh = c & 1;
-    const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(prm.values, prm.values_bytes);
     const uint32_t block_bytes = (uint32_t)(b * b * 2), row_bytes = (uint32_t)(b * 2);
+    // the stored blocks and not a byte more: the second half of a slot reaches over the end of the last one
+    const uint32_t stored = (uint32_t)__builtin_amdgcn_readfirstlane(prm.row_ptr[prm.nbr]) * block_bytes;
+    const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(prm.values, stored < prm.values_bytes ? stored : prm.values_bytes);
     constexpr uint32_t kDead = kBeyond + 4096u;
     // Activation tile: LDS fills in lane order, 16 bytes per lane.  The 16 bytes at byte o of the group
     // are row o / 576 of the tile and, inside the row, half h of the 32-byte slot of block-column j:
