@@ -202,19 +202,16 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const int tile_x = n_fastest ? tile / tiles_n : tile % tiles_k;
   const int tile_y = n_fastest ? tile % tiles_n : tile / tiles_k;
 
-  // LDS: two stage buffers (A tile then B tile each) that also stage the column
-  // indices of the split before the main loop, a 1 KB dump slot (16 bytes per
-  // lane) for stores of unused vectors, the block table and the activity bits.
+  // LDS: two stage buffers (A tile then B tile each), a 1 KB dump slot (16 bytes per lane) for stores of
+  // unused vectors, the block table and the activity bits.
   constexpr int kTail = (D + 2) * G::R;           // block-rows the loaders may run past the split
   __shared__ __attribute__((aligned(16))) uint32_t sStage[2 * G::STAGE_WORDS + 256];
   // sTab[rr * JT + jl]: byte offset in `values` of the block in block-row rr of the
   // split and block-column jl of the tile, kDead if pruned / outside
   __shared__ uint32_t sTab[(kMaxRowsPerSplit + kTail) * G::JT];
-  // first the raw column masks per block-row, then per stage the activity bits of
-  // its 16-row steps (two per step, for the waves with wk = 0 in the low half-word)
+  __shared__ uint32_t sMask[kMaxRowsPerSplit];      // kept block-columns of the tile per block-row
+  // per stage the activity bits of its 16-row steps (two per step, for the waves with wk = 0 in the low half-word)
   __shared__ uint32_t sPam[kMaxRowsPerSplit + 64];
-  int32_t *const sPtr = reinterpret_cast<int32_t *>(sTab);   // row_ptr of the split while the table is built
-  static_assert((kMaxRowsPerSplit + kTail) * G::JT > kMaxRowsPerSplit, "row_ptr fits in the table's memory");
   static_assert(kMaxRowsPerSplit <= kThreads, "one block-row per thread in the prologue");
 
   // the wave index lives in a scalar register: everything derived from it (the
@@ -239,45 +236,42 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const int jt = (int)(jlast - jfirst + 1);
 
   // ---- block table: which blocks of the tile's block-columns each block-row keeps ----
-  for (int rr = t; rr <= nrows; rr += kThreads) {
-    const int64_t i = i_begin + rr;
-    sPtr[rr] = row_ptr[i < nbr ? i : nbr];
-  }
-  __syncthreads();
-  const int32_t pos0 = sPtr[0];
-  const int ncols = sPtr[nrows] - pos0;                    // column indices of the whole split
-  const bool cols_in_lds = ncols <= 2 * G::STAGE_WORDS;
-  if (cols_in_lds)
-    for (int e = t; e < ncols; e += kThreads) sStage[e] = (uint32_t)col_idx[pos0 + e];
-  __syncthreads();
-  uint32_t my_mask = 0;                                     // block-row t: kept block-columns of the tile
-  int32_t my_base = 0;                                      // position of the first of them in col_idx / values
-  if (t < nrows) {
-    const int32_t p0 = sPtr[t], p1 = sPtr[t + 1];
-    bool first = true;
-    for (int32_t p = p0; p < p1; ++p) {
-      const int64_t j = cols_in_lds ? (int64_t)sStage[p - pos0] : (int64_t)col_idx[p];
-      if (j >= jfirst && j <= jlast) {
-        if (first) { my_base = p; first = false; }
-        my_mask |= 1u << (int)(j - jfirst);
+  // A few lanes share a block-row and take its entries in turn (they may stand in any order): two
+  // dependent trips to memory, row_ptr and col_idx, no staging.
+  {
+    int per_row = 1;                                        // lanes per block-row: a power of two
+    while (per_row < 64 && 2 * per_row * nrows <= kThreads) per_row *= 2;
+    const int rr = t / per_row, sub = t & (per_row - 1);
+    const int32_t *const rp = row_ptr + i_begin;            // (nbr < 2^31)
+    const bool live = rr < nrows && rr < (int)(nbr - i_begin);
+    const int32_t p0 = live ? rp[rr] : 0, p1 = live ? rp[rr + 1] : 0;
+    const int j0 = (int)jfirst;
+    for (int e = t; e < (nrows + kTail) * G::JT; e += kThreads) sTab[e] = kDead;
+    if (t < kMaxRowsPerSplit) sMask[t] = 0u;
+    for (int e = t; e < kMaxRowsPerSplit + 64; e += kThreads) sPam[e] = 0u;
+    // rows / columns of the stage buffers that no stage ever writes must read as zero
+    if (!G::SKIP_ONLY || G::ROWS < MS) {
+      uint4 *const z = reinterpret_cast<uint4 *>(sStage);
+      for (int e = t; e < 2 * G::STAGE_WORDS / 4; e += kThreads) z[e] = make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    constexpr int kTogether = 4;                            // entries a lane requests at a time
+    for (int32_t pb = p0 + sub; pb < p1; pb += kTogether * per_row) {
+      int32_t j[kTogether];
+#pragma unroll
+      for (int u = 0; u < kTogether; ++u) j[u] = pb + u * per_row < p1 ? col_idx[pb + u * per_row] : -1;
+#pragma unroll
+      for (int u = 0; u < kTogether; ++u) {
+        const int jl = j[u] - j0;
+        if (jl >= 0 && jl < jt) {
+          sTab[rr * G::JT + jl] = (uint32_t)(pb + u * per_row) * (uint32_t)(BR * BC * E);
+          atomicOr(&sMask[rr], 1u << jl);
+        }
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
-  if (t < nrows) {
-#pragma unroll
-    for (int jl = 0; jl < G::JT; ++jl)
-      sTab[t * G::JT + jl] = ((my_mask >> jl) & 1u)
-                                 ? (uint32_t)(my_base + __popc(my_mask & ((1u << jl) - 1u))) * (uint32_t)(BR * BC * E)
-                                 : kDead;
-  }
-  for (int e = t; e < kTail * G::JT; e += kThreads) sTab[nrows * G::JT + e] = kDead;
-  for (int e = t; e < kMaxRowsPerSplit + 64; e += kThreads) sPam[e] = e == t ? my_mask : 0u;
-  // rows / columns of the stage buffers that no stage ever writes must read as zero
-  if (!G::SKIP_ONLY || G::ROWS < MS)
-    for (int e = t; e < 2 * G::STAGE_WORDS; e += kThreads) sStage[e] = 0u;
-  __syncthreads();
-  {
+  if (!loader && tg < nstages) {
     // Block-columns of the tile that overlap the two 32-column pieces of the
     // activation tile owned by the waves with wk = 0 / 1: a 16-row step of a piece
     // carries data iff a block-row it overlaps keeps one of these columns.
@@ -289,11 +283,11 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
       for (int x = 0; x < 4; ++x)
         if (jl < jt && c0 <= x * 32 + 31 && c1 >= x * 32) colmask[x >> 1][x & 1] |= 1u << jl;
     }
-    uint32_t pam = 0;
-    if (t < nstages) {
+    for (int q = tg; q < nstages; q += kRole) {
+      uint32_t pam = 0;
 #pragma unroll
       for (int rbk = 0; rbk < G::R; ++rbk) {
-        const uint32_t m = sPam[t * G::R + rbk];
+        const uint32_t m = sMask[q * G::R + rbk];
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
           if (m & colmask[x >> 1][x & 1]) {
@@ -303,13 +297,15 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
           }
         }
       }
+      sPam[q] = pam;
     }
-    __syncthreads();
-    if (t < kMaxRowsPerSplit) sPam[t] = pam;
-    __syncthreads();
   }
 
   if (loader) {
+    if (nstages == 0) {
+      __syncthreads();
+      return;
+    }
     // ================= loader waves =================
     // Activation vector `it` of a stage belongs to block (block-row a_row of the
     // stage, block-column a_jl of the tile); its global offset is the block's table
@@ -458,7 +454,10 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   }
 
   // ================= multiplier waves =================
-  const int wk = wave / WN, wn = wave % WN;
+  // With eight multiplier waves, waves s and s + 4 run on SIMD s: they take different halves of the tile's
+  // rows (whose kept blocks differ), and different strips so that the strips of a narrow dW (N <= 64) are
+  // spread over all four SIMDs.
+  const int wk = WN == 4 ? (wave & 1) ^ (wave >> 2) : wave / WN, wn = WN == 4 ? wave >> 1 : wave % WN;
   v16f acc[2][G::NTW];
 #pragma unroll
   for (int u = 0; u < 2; ++u)
@@ -575,12 +574,13 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
     else multiply_f32(q, buf);
   };
 
-  __syncthreads();                           // stage 0 is in LDS buffer 0
+  const bool in_matrix = n0 + G::NTW * wn * 32 < N;   // (strips beyond the last column of dW have nothing to do)
+  __syncthreads();                           // stage 0 is in LDS buffer 0, the activity bits are complete
   for (int q0 = 0; q0 < nstages; q0 += 2) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       if (q0 + u >= nstages) break;
-      multiply(q0 + u, u);
+      if (in_matrix) multiply(q0 + u, u);
       __syncthreads();
     }
   }
@@ -673,8 +673,10 @@ Plan make_plan(int64_t M, int64_t K, int64_t N) {
   p.splits = 1;
   p.stages_per_split = stages > 0 ? stages : 1;
   if (stages <= 0 || tiles <= 0) return p;
-  // (binary32 stages are bound by the matrix core: 16 times the passes per multiply-add)
-  const double us_stage = (E == 4 ? 1.3 : 0.70) * MS / 64.0, us_round = 8.0;
+  // (binary32 stages are bound by the matrix core: 16 times the passes per multiply-add, spread over half
+  // the waves when dW has at most two strips of columns.  A split contraction costs a second launch; for a
+  // few stages it is not worth it.)
+  const double us_stage = (E == 4 ? (N > 64 ? 3.0 : 2.0) : 0.70) * MS / 64.0, us_round = 8.0, us_reduce = 4.5;
   const double us_split = 2.0 * (double)K * (double)N * 4.0 / 3.0e6;
   // (at least one split per 256 block-rows, although the table would hold 512: for 16-row blocks at
   // 50176 rows 14 splits of 112 stages take 106 us where 7 of 224 take 156 us)
@@ -687,7 +689,7 @@ Plan make_plan(int64_t M, int64_t K, int64_t N) {
     const int64_t sps = ceil_div(stages, s);
     const int64_t s_eff = ceil_div(stages, sps);
     const int64_t rounds = ceil_div(tiles * s_eff, (int64_t)kSlots);
-    const double cost = (double)rounds * ((double)sps * us_stage + us_round) + (s_eff > 1 ? (double)s_eff * us_split : 0.0);
+    const double cost = (double)rounds * ((double)sps * us_stage + us_round) + (s_eff > 1 ? us_reduce + (double)s_eff * us_split : 0.0);
     if (best_s == 0 || cost < best) { best = cost; best_s = s_eff; }
   }
   const int64_t sps = ceil_div(stages, best_s);

@@ -1101,3 +1101,22 @@ def test_dw_rows_of_dy_at_any_alignment(M, K, N, pad, shift, b, dtype):
     torch.cuda.synchronize()
     for dW in got:
         assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,K,N,b", [(500, 200, 70, 14), (700, 330, 64, 16), (1100, 256, 40, 32), (900, 640, 130, 64)])
+def test_dw_entries_of_a_block_row_in_any_order(M, K, N, b, dtype):
+    """col_idx (and values with it) shuffled inside every block-row; odd numbers of block-rows, fewer and more block-rows
+    than a workgroup has lanes for, and a dW of at most two strips of columns (N <= 64)."""
+    rng = np.random.default_rng(M + b)
+    X, dY = rand_pair(M, K, N, dtype, seed=M + N)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, b, b, 0.5)
+    ref = oracle.dw(oracle.mask_dense(X, b, b, o_mask), dY)
+    order = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(o_rp[:-1], o_rp[1:])]).astype(np.int64)
+    rp, ci = torch.from_numpy(o_rp).cuda(), torch.from_numpy(np.ascontiguousarray(o_ci[order])).cuda()
+    val, dYd = to_dev(np.ascontiguousarray(o_val[order])), to_dev(dY)
+    got = [B.bsr_t_dense_matmul(rp, ci, val, M, K, b, b, dYd),
+           *B.bsr_t_dense_matmul_batched(B.MatmulBatch([(rp, ci, val, M, K, b, b, dYd)] * 2))]
+    torch.cuda.synchronize()
+    for dW in got:
+        assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
