@@ -197,11 +197,24 @@ struct CompressArgs {
   int br;
   uint32_t wg_begin;       // first workgroup of this tensor in a launch of several
   int have_row_ptr;        // row_ptr was written by row_ptr_kernel: nothing to count here
+  uint32_t parts;          // workgroups that share a block-row: each lists it, each copies every parts-th kept block
 };
 
-// i = block-row (the workgroup's number among those of its tensor)
+// How many workgroups share a block-row in a launch over `wgs` block-rows: block-rows differ in kept
+// blocks, and a few hundred of them leave compute units idle behind the ones that got one more.  ([12544 x
+// 384] binary32, 392 block-rows: 11.1 us alone, 8.9 shared by four; [50176 x 3072] in 64x64 blocks, 784
+// block-rows: 72 us alone, 69 shared by two.  More than four only repeat the listing.)
+inline uint32_t row_parts(int64_t wgs, int64_t most) {
+  int64_t p = wgs > 0 ? 2048 / wgs : 1;
+  if (p > most) p = most;
+  return (uint32_t)(p < 1 ? 1 : p > 4 ? 4 : p);
+}
+
+// i = block-row, part = which of the workgroups that share it
 template <int VB>
-__device__ __forceinline__ void compress_body(const CompressArgs &a, const int64_t i) {
+__device__ __forceinline__ void compress_body(const CompressArgs &a, const uint32_t wg) {
+  const int64_t i = wg / a.parts;
+  const int part = (int)(wg - (uint32_t)i * a.parts), parts = (int)a.parts;
   typedef typename BytesOf<VB>::type V;
   const uint8_t *__restrict__ mask = a.mask;
   const uint8_t *__restrict__ X = a.X;
@@ -214,14 +227,15 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const int64
   __shared__ uint32_t total;
   __shared__ int32_t kept_j[kFusedCols];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint8_t *mrow = mask + i * nbc;
+  const uint8_t first = t < nbc ? mrow[t] : (uint8_t)0;    // on its way while the mask in front is counted
   const uint32_t prefix = a.have_row_ptr ? (uint32_t)row_ptr[i] : count_kept_prefix(mask, i * nbc, wave_tot, &total);
 
   // ---- this row's kept block-columns, in order ----
   uint32_t row_kept = 0;
-  const uint8_t *mrow = mask + i * nbc;
   for (int64_t c0 = 0; c0 < nbc; c0 += 256) {
     const int64_t j = c0 + t;
-    const bool flag = j < nbc && mrow[j] != 0;
+    const bool flag = j < nbc && (c0 == 0 ? first : mrow[j]) != 0;
     const unsigned long long ball = __ballot(flag);
     if (lane == 0) wave_tot[wave] = (uint32_t)__popcll(ball);
     __syncthreads();
@@ -230,12 +244,12 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const int64
     const uint32_t pos = before + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull));
     if (flag) {
       kept_j[pos] = (int32_t)j;
-      if ((int64_t)prefix + pos < n_keep) col_idx[prefix + pos] = (int32_t)j;
+      if (part == 0 && (int64_t)prefix + pos < n_keep) col_idx[prefix + pos] = (int32_t)j;
     }
     row_kept += wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
     __syncthreads();
   }
-  if (t == 0 && !a.have_row_ptr) {
+  if (t == 0 && part == 0 && !a.have_row_ptr) {
     row_ptr[i] = (int32_t)prefix;
     if (i == nbr - 1) row_ptr[nbr] = (int32_t)(prefix + row_kept);
   }
@@ -276,13 +290,13 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const int64
     if (g < G) {
       const int r = e / vpb, v = e - r * vpb;
 #pragma unroll 4
-      for (int q = g; q < (int)nk; q += G) copy(q, r, v, e);
+      for (int q = g * parts + part; q < (int)nk; q += G * parts) copy(q, r, v, e);
     }
   } else {
     for (int e = t; e < S; e += 256) {
       const int r = e / vpb, v = e - r * vpb;
 #pragma unroll 4
-      for (int q = 0; q < (int)nk; ++q) copy(q, r, v, e);
+      for (int q = part; q < (int)nk; q += parts) copy(q, r, v, e);
     }
   }
 }
@@ -847,7 +861,8 @@ struct CompressPlan {
   CompressSpanArgs span;
 };
 
-CompressPlan plan_compress(const CompressJob &j, int dtype) {
+// row_wgs: block-rows of the whole call (what shares the launch)
+CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
   CompressPlan p{};
   const int64_t nbr = ceil_div(j.M, j.br), nbc = ceil_div(j.K, j.bc);
   const int e = elem_bytes(dtype);
@@ -879,14 +894,15 @@ CompressPlan plan_compress(const CompressJob &j, int dtype) {
   // Rows of X that start anywhere, blocks that are whole 16-byte vectors: 16 bytes from where they are
   // ([9947 x 411] bf16, 32x32 blocks: 22 us element by element, 7 us so).
   if (p.vb < 16 && (int64_t)j.bc * e % 16 == 0 && (uintptr_t)j.values % 16 == 0) p.vb = kLoose;
-  // Every workgroup counts the mask in front of its row, nbr * nblocks / 2 bytes out of L2 in all, unless a
+  // Every workgroup counts the mask in front of its row, wgs * nblocks / 2 bytes out of L2 in all, unless a
   // launch writes row_ptr first (about 5 us): from 32 MB on that is the faster way (mask of 3136 x 96
   // blocks, 472 MB: 48 us -> 5 + 29 us; 784 x 48 blocks, 15 MB: no gain).
-  p.rows_first = nbr * nbr * nbc / 2 > (int64_t(32) << 20);
-  p.wgs = (unsigned)nbr;
+  const uint32_t parts = row_parts(row_wgs, nbc);
+  p.wgs = (unsigned)nbr * parts;
+  p.rows_first = (int64_t)p.wgs * nbr * nbc / 2 > (int64_t(32) << 20);
   p.direct = CompressArgs{j.keep_mask, static_cast<const uint8_t *>(j.X), j.row_ptr, j.col_idx,
                           static_cast<uint8_t *>(j.values), j.M, j.K * e, j.ldx * e, (int64_t)j.bc * e, nbr, nbc,
-                          j.n_keep, j.br, 0u, 0};
+                          j.n_keep, j.br, 0u, 0, parts};
   return p;
 }
 
@@ -931,7 +947,7 @@ int launch_compress(const uint8_t *keep_mask, const void *X, int dtype, int64_t 
                     int br, int bc, int64_t n_keep, int32_t *row_ptr, int32_t *col_idx, void *values,
                     void *ws, hipStream_t s) {
   const CompressJob job{keep_mask, X, M, K, ldx, br, bc, n_keep, row_ptr, col_idx, values, ws};
-  CompressPlan p = plan_compress(job, dtype);
+  CompressPlan p = plan_compress(job, dtype, br > 0 ? ceil_div(M, br) : 0);
   if (p.path == kPackSpan) {
     if (p.count_first) {
       const SpanGeom &g = p.span.g;
@@ -1010,7 +1026,9 @@ int launch_decompress(const int32_t *row_ptr, const int32_t *col_idx, const void
 int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream_t s) {
   static const int kVbs[5] = {16, 8, 4, 2, kLoose};
   std::vector<CompressPlan> plans((size_t)n);
-  for (int i = 0; i < n; ++i) plans[(size_t)i] = plan_compress(jobs[i], dtype);
+  int64_t row_wgs = 0;
+  for (int i = 0; i < n; ++i) row_wgs += ceil_div(jobs[i].M, jobs[i].br);
+  for (int i = 0; i < n; ++i) plans[(size_t)i] = plan_compress(jobs[i], dtype, row_wgs);
   // with several tensors in the call one more launch costs little next to what it saves: row_ptr of
   // every tensor first
   {
