@@ -215,60 +215,39 @@ struct WideBody {
     // ---- tables: which block-columns of the tile every block-row of a chunk keeps, and where ----
     auto build_tables = [&](const int cbegin, const int crows) {
         // (built by the copy waves alone: the multiplying waves carry their accumulators through
-        // here and have no registers to spare; they wait at the three barriers)
+        // here and have no registers to spare; they wait at the two barriers.)  A few lanes share a
+        // block-row and take its entries in turn, whatever their order: two dependent trips to memory.
         constexpr int kTableThreads = 64 * kCopyWaves;
         const int t = c * 64 + lane;
-        int32_t *const sPtr = reinterpret_cast<int32_t *>(sRing);                 // crows + 1 row pointers
-        uint32_t *const sCols = reinterpret_cast<uint32_t *>(sRing + 16384);      // the chunk's column indices
-        constexpr int kColsCap = (kRing * kStageBytes - 16384) / 4;
-        for (int rr = t; rr <= crows; rr += kTableThreads) sPtr[rr] = row_ptr[cbegin + rr];
+        int per_row = 1;                                    // lanes per block-row: a power of two
+        while (per_row < 64 && 2 * per_row * crows <= kTableThreads) per_row *= 2;
+        const int sub = t & (per_row - 1);
+        int rr = t / per_row;
+        const int32_t *const rp = row_ptr + cbegin;
+        int32_t p0 = rr < crows ? rp[rr] : 0, p1 = rr < crows ? rp[rr + 1] : 0;
+        for (int e = t; e < (crows + kRowPad) * JT; e += kTableThreads) sOff[e] = kBeyond;
+        for (int e = t; e < crows + kRowPad; e += kTableThreads) sKept[e] = 0u;
         __syncthreads();
-        const int32_t pos0 = sPtr[0];
-        const int32_t ncols = sPtr[crows] - pos0;
-        const bool cols_in_lds = ncols >= 0 && ncols <= kColsCap;
-        if (cols_in_lds)
-          for (int e = t; e < ncols; e += kTableThreads) sCols[e] = (uint32_t)col_idx[pos0 + e];
-        __syncthreads();
-        for (int rr = t; rr < crows + kRowPad; rr += kTableThreads) {
-          uint32_t off[JT];
+        while (rr < crows) {
+          if (p1 - p0 > prm.nbc) p1 = p0 + prm.nbc;         // a valid row never holds more
+          constexpr int kTogether = 4;                      // entries a lane requests at a time
+          for (int32_t pb = p0 + sub; pb < p1; pb += kTogether * per_row) {
+            int j[kTogether];
 #pragma unroll
-          for (int jl = 0; jl < JT; ++jl) off[jl] = kBeyond;
-          uint32_t mask = 0;
-          if (rr < crows) {
-            const int32_t p0 = sPtr[rr];
-            int32_t p1 = sPtr[rr + 1];
-            if (p1 - p0 > prm.nbc) p1 = p0 + prm.nbc;       // a valid row never holds more
-            // eight entries at a time, so that their reads are on their way together
-            for (int32_t p = p0; p < p1; p += 8) {
-              int j[8];
+            for (int u = 0; u < kTogether; ++u) j[u] = pb + u * per_row < p1 ? col_idx[pb + u * per_row] : -1;
 #pragma unroll
-              for (int u = 0; u < 8; ++u) {
-                const int32_t q = p + u < p1 ? p + u : p1 - 1;
-                j[u] = cols_in_lds ? (int)sCols[q - pos0] : (int)col_idx[q];
-              }
-#pragma unroll
-              for (int u = 0; u < 8; ++u) {
-                const uint32_t jl_kept = (uint32_t)(j[u] - jfirst);
-                if (p + u < p1 && jl_kept < (uint32_t)jt) {
-                  mask |= 1u << jl_kept;
-#pragma unroll
-                  for (int jl = 0; jl < JT; ++jl)
-                    if ((uint32_t)jl == jl_kept) off[jl] = (uint32_t)(p + u) * kBlockBytes;
-                }
+            for (int u = 0; u < kTogether; ++u) {
+              const uint32_t jl = (uint32_t)(j[u] - jfirst);
+              if (j[u] >= 0 && jl < (uint32_t)jt) {
+                sOff[rr * JT + (int)jl] = (uint32_t)(pb + u * per_row) * kBlockBytes;
+                atomicOr(&sKept[rr], SPB == 2 ? 3u << (2 * jl) : 1u << jl);      // bits of the kept pieces
               }
             }
           }
-#pragma unroll
-          for (int jl = 0; jl < JT; ++jl) sOff[rr * JT + jl] = off[jl];
-          uint32_t pm = mask;                               // kept pieces from kept block-columns
-          if (SPB == 2) {
-            pm = 0;
-#pragma unroll
-            for (int jl = 0; jl < JT; ++jl) pm |= ((mask >> jl) & 1u) * (3u << (2 * jl));
-          }
-          sKept[rr] = pm;
+          rr += kTableThreads / per_row;
+          if (rr < crows) { p0 = rp[rr]; p1 = rp[rr + 1]; }
         }
-        __syncthreads();          // the tables are complete and the ring's memory is free again
+        __syncthreads();          // the tables are complete
     };
     // The block-rows of the split go in chunks whose tables fit LDS.  The two kinds of waves run
     // the same chunks and meet at the same barriers, each in code of its own.
@@ -276,7 +255,6 @@ struct WideBody {
     if (copy_wave) {
       for (int r0 = 0; r0 < nrows; r0 += kWideMaxRows) {
         const int crows = chunk_rows(r0), cbegin = i_begin + r0, nstages = crows * SPB;
-        build_tables(cbegin, crows);
         // ================= copy waves =================
         // dY goes in whole 128-byte lines: a copy takes 8 rows x 64 columns (two strips side by
         // side); the 16-byte chunks of rows 2, 3, 6, 7 of a group are stored with bit 2 of their
@@ -286,14 +264,21 @@ struct WideBody {
           const int64_t row = (int64_t)cbegin * BS + 16 * (c >> 1) + (lane >> 3);
           vb = (uint32_t)((row * prm.lddy + n0 + 64 * (c & 1)) * 2 + (((lane & 7) ^ (4 * ((lane >> 4) & 1))) * 16));
         }
+        // dY of the first stages does not depend on the tables and goes out before they are built
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) {
+          copy_pair_to_lds(rsrc_b, m0_slot[d] + b_lds_delta, vb, vb + b_hi_delta);
+          vb += b_step;
+        }
+        build_tables(cbegin, crows);
         // table columns of the three pieces
         const uint32_t *offp[3] = {sOff + c / SPB, sOff + (c + 4) / SPB, sOff + (c + 8) / SPB};
-        // Issues the copies of one stage and returns how many instructions that were: a pair for each
-        // kept piece of the wave's three (a pruned piece is not copied at all: the texture path spends
-        // as long on a copy from beyond the buffer as on a real one) and a pair for dY.
-        auto issue = [&](uint32_t m0, uint32_t o0, uint32_t o1, uint32_t o2, bool lower_half) -> uint32_t {
+        // Issues the copies of a stage's activation pieces and returns how many instructions that were: a
+        // pair for each kept piece of the wave's three (a pruned piece is not copied at all: the texture
+        // path spends as long on a copy from beyond the buffer as on a real one).
+        auto issue_pieces = [&](uint32_t m0, uint32_t o0, uint32_t o1, uint32_t o2, bool lower_half) -> uint32_t {
           const uint32_t vh = va + ((SPB == 2 && lower_half) ? 32u * kRowBytes : 0u);
-          uint32_t n = 2;
+          uint32_t n = 0;
           if ((uint32_t)__builtin_amdgcn_readfirstlane((int)o0) != kBeyond) {
             const uint32_t l0 = o0 + vh;
             copy_pair_to_lds(rsrc_a, m0, l0, l0 + a_hi_delta);
@@ -309,11 +294,16 @@ struct WideBody {
             copy_pair_to_lds(rsrc_a, m0 + 8u * kSlabBytes, l2, l2 + a_hi_delta);
             n += 2;
           }
-          copy_pair_to_lds(rsrc_b, m0 + b_lds_delta, vb, vb + b_hi_delta);
-          vb += b_step;
           return n;
         };
-        // Waits until at most `allowed` of this wave's copies are on their way (allowed = 4, 6, .. 16: the
+        // ... and of the whole stage: a pair for dY behind them.
+        auto issue = [&](uint32_t m0, uint32_t o0, uint32_t o1, uint32_t o2, bool lower_half) -> uint32_t {
+          const uint32_t n = issue_pieces(m0, o0, o1, o2, lower_half);
+          copy_pair_to_lds(rsrc_b, m0 + b_lds_delta, vb, vb + b_hi_delta);
+          vb += b_step;
+          return n + 2;
+        };
+        // Waits until at most `allowed` of this wave's copies are on their way (allowed = 0, 2, .. 16: the
         // copies of the two stages behind the one that must have landed).
         auto wait_copies = [&](uint32_t allowed) {
           if (allowed >= 12u) {
@@ -325,13 +315,17 @@ struct WideBody {
             else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
           } else {
             if (allowed >= 6u) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else if (allowed >= 4u) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else if (allowed >= 2u) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           }
         };
-        uint32_t cnt[kAhead];                               // copies issued for the stages q .. q + 2
+        // copies issued for the stages q .. q + 2: of the first ones the pieces only, since all their dY
+        // copies were issued in front of those
+        uint32_t cnt[kAhead];
 #pragma unroll
         for (int d = 0; d < kAhead; ++d)
-          cnt[d] = issue(m0_slot[d], vector_value(offp[0][(d / SPB) * JT]), vector_value(offp[1][(d / SPB) * JT]),
+          cnt[d] = issue_pieces(m0_slot[d], vector_value(offp[0][(d / SPB) * JT]), vector_value(offp[1][(d / SPB) * JT]),
                          vector_value(offp[2][(d / SPB) * JT]), (d & 1) != 0);
         uint32_t c1 = cnt[1], c2 = cnt[2];                  // of the stages q + 1 and q + 2
         // table entries are read one stage ahead of their use
@@ -367,8 +361,7 @@ struct WideBody {
     }
     for (int r0 = 0; r0 < nrows; r0 += kWideMaxRows) {
       const int crows = chunk_rows(r0), nstages = crows * SPB;
-      __syncthreads();          // (the three barriers of the table build)
-      __syncthreads();
+      __syncthreads();          // (the two barriers of the table build)
       __syncthreads();
         // ================= multiplying waves =================
         // requests the activation fragments of pieces [first, first + NP) of the wave in ring slot `slot`
