@@ -50,7 +50,10 @@ struct __attribute__((packed, aligned(2))) LooseVec {
   u32x4 v;
 };
 
-constexpr int kMaxRowsPerSplit = 512;   // block-rows of one split: its block table must fit in LDS
+// Block-rows of one split, at most: its block table must fit in LDS.  (Stages of 64 rows for 14x14 and 16x16
+// blocks: half the barriers of stages of 32, cross-patch 19.7 -> 17.6 us, and with tables of 256 block-rows two
+// workgroups still share a compute unit.)
+constexpr int max_rows_per_split(int br, int ms) { return br <= 16 && ms >= 64 ? 256 : 512; }
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose
 // index is a compile-time constant in every trip, whatever its length (register
@@ -136,6 +139,8 @@ struct Geo {
   static constexpr int NB = (ROWS * (NT / VB) + THREADS - 1) / THREADS;
   static constexpr int LDA = kLd, LDB = kLd;             // LDS rows (elements), swizzled not padded
   static constexpr int MSUB = MS / 16;
+  // block-rows of one split: its table must fit in LDS beside the stages (two workgroups per compute unit)
+  static constexpr int MAXR = max_rows_per_split(BR, MS);
   static constexpr int STAGE_WORDS = (MS * LDA + MS * LDB) * E / 4;   // 32-bit words of one stage (A tile, B tile)
   static_assert(MS % 16 == 0 && R >= 1 && MSUB <= 8 && CS % VA == 0 && KT % CS == 0, "stage shape");
   static_assert(JT <= 32, "tile index is a 32-bit mask");
@@ -208,11 +213,11 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   __shared__ __attribute__((aligned(16))) uint32_t sStage[2 * G::STAGE_WORDS + 256];
   // sTab[rr * JT + jl]: byte offset in `values` of the block in block-row rr of the
   // split and block-column jl of the tile, kDead if pruned / outside
-  __shared__ uint32_t sTab[(kMaxRowsPerSplit + kTail) * G::JT];
-  __shared__ uint32_t sMask[kMaxRowsPerSplit];      // kept block-columns of the tile per block-row
+  __shared__ uint32_t sTab[(G::MAXR + kTail) * G::JT];
+  __shared__ uint32_t sMask[G::MAXR];      // kept block-columns of the tile per block-row
   // per stage the activity bits of its 16-row steps (two per step, for the waves with wk = 0 in the low half-word)
-  __shared__ uint32_t sPam[kMaxRowsPerSplit + 64];
-  static_assert(kMaxRowsPerSplit <= kThreads, "one block-row per thread in the prologue");
+  __shared__ uint32_t sPam[G::MAXR + 64];
+  static_assert(G::MAXR <= kThreads, "one block-row per thread in the prologue");
 
   // the wave index lives in a scalar register: everything derived from it (the
   // role, the activity bits, the skip branches) is then wave-uniform for the
@@ -247,8 +252,8 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
     const int32_t p0 = live ? rp[rr] : 0, p1 = live ? rp[rr + 1] : 0;
     const int j0 = (int)jfirst;
     for (int e = t; e < (nrows + kTail) * G::JT; e += kThreads) sTab[e] = kDead;
-    if (t < kMaxRowsPerSplit) sMask[t] = 0u;
-    for (int e = t; e < kMaxRowsPerSplit + 64; e += kThreads) sPam[e] = 0u;
+    if (t < G::MAXR) sMask[t] = 0u;
+    for (int e = t; e < G::MAXR + 64; e += kThreads) sPam[e] = 0u;
     // rows / columns of the stage buffers that no stage ever writes must read as zero
     if (!G::SKIP_ONLY || G::ROWS < MS) {
       uint4 *const z = reinterpret_cast<uint4 *>(sStage);
@@ -680,7 +685,7 @@ Plan make_plan(int64_t M, int64_t K, int64_t N) {
   const double us_split = 2.0 * (double)K * (double)N * 4.0 / 3.0e6;
   // (at least one split per 256 block-rows, although the table would hold 512: for 16-row blocks at
   // 50176 rows 14 splits of 112 stages take 106 us where 7 of 224 take 156 us)
-  const int64_t s_min = ceil_div(stages * R, (int64_t)256);
+  const int64_t s_min = ceil_div(stages, (int64_t)(256 / R));
   int64_t s_max = stages < 64 ? stages : 64;
   if (s_max < s_min) s_max = s_min;
   double best = 0;
@@ -719,7 +724,7 @@ Plan make_plan_batched(int64_t M, int64_t K, int64_t N, int companions) {
   constexpr double kBytesPerStage = 2.0e6;                     // partial-tile bytes that cost the time of one stage (measured)
   const int64_t stages = ceil_div(ceil_div(M, BR), R);
   const int64_t tiles = dw_tiles_k(K, BR) * ceil_div(N, 128);
-  const int64_t s_min = ceil_div(stages * R, (int64_t)kMaxRowsPerSplit);
+  const int64_t s_min = ceil_div(stages, (int64_t)(max_rows_per_split(BR, MS) / R));
   if (s_min >= alone.splits) return alone;
   const double split_cost = (double)companions * (double)K * (double)N * 8.0 / kBytesPerStage;
   double best = 0;
@@ -887,8 +892,8 @@ size_t dw_mfma_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int 
   switch (br) {
     case 32: return f32 ? ws_for<4, 32, 64>(M, K, N) : ws_for<2, 32, 64>(M, K, N);
     case 64: return f32 ? ws_for<4, 64, 64>(M, K, N) : ws_for<2, 64, 64>(M, K, N);
-    case 16: return f32 ? ws_for<4, 16, 32>(M, K, N) : ws_for<2, 16, 32>(M, K, N);
-    case 14: return f32 ? ws_for<4, 14, 32>(M, K, N) : ws_for<2, 14, 32>(M, K, N);
+    case 16: return f32 ? ws_for<4, 16, 32>(M, K, N) : ws_for<2, 16, 64>(M, K, N);
+    case 14: return f32 ? ws_for<4, 14, 32>(M, K, N) : ws_for<2, 14, 64>(M, K, N);
     default: return 0;
   }
 }
@@ -907,8 +912,8 @@ int launch_dw_mfma(int dtype, const int32_t *row_ptr, const int32_t *col_idx, co
   }
   if (br == 32 && bc == 32) return run<uint16_t, 32, 32, 64, 2, 4>(BSR_ARGS);
   if (br == 64 && bc == 64) return run<uint16_t, 64, 64, 64, 2, 4>(BSR_ARGS);
-  if (br == 16 && bc == 16) return run<uint16_t, 16, 16, 32, 2, 4>(BSR_ARGS);
-  if (br == 14 && bc == 14) return run<uint16_t, 14, 14, 32, 2, 4>(BSR_ARGS);
+  if (br == 16 && bc == 16) return run<uint16_t, 16, 16, 64, 2, 4>(BSR_ARGS);
+  if (br == 14 && bc == 14) return run<uint16_t, 14, 14, 64, 2, 4>(BSR_ARGS);
 #undef BSR_ARGS
   return BSR_ERR_SHAPE;
 }
@@ -925,8 +930,8 @@ int launch_dw_mfma_batched(int dtype, const DwJob *jobs, int n, hipStream_t s) {
     } else {
       if ((rc = run_batched<uint16_t, 32, 32, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
       if ((rc = run_batched<uint16_t, 64, 64, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 16, 16, 32, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 14, 14, 32, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<uint16_t, 16, 16, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
+      if ((rc = run_batched<uint16_t, 14, 14, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
     }
   }
   return BSR_OK;
