@@ -229,7 +229,6 @@ __device__ __forceinline__ void score_span_body(const uint8_t *__restrict__ X, i
   for (int k = 0; k < kVecs; ++k)
     if (t + 256 * k < nvec) sv[t + 256 * k] = reg[k];
   __syncthreads();
-  const T *sp = reinterpret_cast<const T *>(lds);
   const int kk = (int)K;
   // a row segment is summed in pieces of 32 elements (`pieces` per segment)
   for (int pc = t; pc < rows * g.nbc * pieces; pc += 256) {
@@ -238,11 +237,24 @@ __device__ __forceinline__ void score_span_body(const uint8_t *__restrict__ X, i
     const int c0 = (int)j * bc + (int)sub * 32;
     int c1 = c0 + 32 < (int)(j + 1) * bc ? c0 + 32 : (int)(j + 1) * bc;
     if (c1 > kk) c1 = kk;
-    const T *p = sp + (int)row * kk;
     double acc = 0.0;
-    for (int c = c0; c < c1; ++c) {
-      const double x = (double)elem_to_float<T>(p[c]);
-      acc = fma(x, x, acc);
+    if constexpr (sizeof(T) == 2) {
+      // (rows and segments are whole words here: two elements per LDS read)
+      const uint32_t *p = lds + (int)row * (kk >> 1) + (c0 >> 1);
+      const int n = (c1 - c0) >> 1;
+#pragma unroll 4
+      for (int c = 0; c < n; ++c) {
+        const uint32_t v = p[c];
+        const double lo = (double)__uint_as_float(v << 16), hi = (double)__uint_as_float(v & 0xFFFF0000u);
+        acc = fma(lo, lo, acc);
+        acc = fma(hi, hi, acc);
+      }
+    } else {
+      const T *p = reinterpret_cast<const T *>(lds) + (int)row * kk;
+      for (int c = c0; c < c1; ++c) {
+        const double x = (double)elem_to_float<T>(p[c]);
+        acc = fma(x, x, acc);
+      }
     }
     part[pc] = acc;
   }
