@@ -895,11 +895,11 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
   // ([9947 x 411] bf16, 32x32 blocks: 22 us element by element, 7 us so).
   if (p.vb < 16 && (int64_t)j.bc * e % 16 == 0 && (uintptr_t)j.values % 16 == 0) p.vb = kLoose;
   // Every workgroup counts the mask in front of its row, wgs * nblocks / 2 bytes out of L2 in all, unless a
-  // launch writes row_ptr first (about 5 us): from 32 MB on that is the faster way (mask of 3136 x 96
-  // blocks, 472 MB: 48 us -> 5 + 29 us; 784 x 48 blocks, 15 MB: no gain).
+  // launch writes row_ptr first (6 to 8 us): from 256 MB on that is the faster way (mask of 3136 x 96
+  // blocks, 472 MB: 48 us -> 8 + 30 us; 3136 x 48, 236 MB: 70 us either way; 1568 x 48, 59 MB: 35 -> 39 us).
   const uint32_t parts = row_parts(row_wgs, nbc);
   p.wgs = (unsigned)nbr * parts;
-  p.rows_first = (int64_t)p.wgs * nbr * nbc / 2 > (int64_t(32) << 20);
+  p.rows_first = (int64_t)p.wgs * nbr * nbc / 2 > (int64_t(256) << 20);
   p.direct = CompressArgs{j.keep_mask, static_cast<const uint8_t *>(j.X), j.row_ptr, j.col_idx,
                           static_cast<uint8_t *>(j.values), j.M, j.K * e, j.ldx * e, (int64_t)j.bc * e, nbr, nbc,
                           j.n_keep, j.br, 0u, 0, parts};

@@ -1051,7 +1051,7 @@ def test_selection_sizes_at_the_edges_of_its_paths(nblocks, levels):
     (130, 96, 32, 32, "bf16", 5, 1),         # rows of whole vectors in a view that starts and continues unaligned
     (97, 33, 8, 8, "bf16", 2, 3),            # one valid column in the last block
     (64, 64, 16, 16, "f32", 1, 1),
-    (51200, 128, 16, 16, "bf16", 0, 0),      # a mask so long that row_ptr is written by a launch of its own
+    (137216, 128, 16, 16, "bf16", 0, 0),     # a mask so long that row_ptr is written by a launch of its own
 ])
 def test_conversion_of_unaligned_rows_and_long_masks(M, K, br, bc, dtype, pad, shift):
     X = rand_pair(M, K, 1, dtype, seed=M + K)[0]
