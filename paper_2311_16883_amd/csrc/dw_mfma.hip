@@ -150,7 +150,7 @@ struct Geo {
 // WN = multiplier waves along N (2: 64 x 64 per wave, 4: 64 x 32 per wave); the
 // workgroup has 2 x WN multiplier waves and as many loader waves.
 // T = uint16_t (bfloat16 bits) or float.
-// ODD: rows of dY may start on odd elements (bfloat16): see load_b.
+// ODD: rows of dY may start or end on odd elements (bfloat16): see load_b.
 // What one tensor's launch needs (kernel arguments; an array of these for a batch).
 struct DwParams {
   const int32_t *row_ptr, *col_idx;
@@ -389,8 +389,9 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
     };
     // dY in vectors of 16 bytes whatever the row pitch.  A vector that crosses column N brings the first
     // columns of the next row into tile columns that belong to no column of dW; rows beyond the split read
-    // as zero.  Buffer loads need addresses that are multiples of 4 and check the range word by word.  Rows
-    // of an odd number of bfloat16 elements (ODD) are read by global loads, which need no alignment but
+    // as zero.  Buffer loads need addresses that are multiples of 4 and check the range word by word: only
+    // a split that ends on a whole word is safe with them.  Rows that start or end on odd bfloat16 elements (ODD: odd
+    // N, odd pitch or an odd start) are read by global loads, which need no alignment but
     // check nothing: the address is held back so that the vector ends at the split's last element, and
     // store_b moves the elements to their places or drops them.
     auto load_b = [&](int d, int it) {
@@ -703,9 +704,13 @@ Plan make_plan(int64_t M, int64_t K, int64_t N) {
   return p;
 }
 
-// Rows of dY that may start on an odd bfloat16 element: the kernel instance with global loads.
+// Rows of dY that may start or end on an odd bfloat16 element: the kernel instance with global loads.  (A row
+// of odd length ends in the middle of a 32-bit word whatever its pitch; a buffer load takes a word that the
+// range covers only in part as out of range, and the last row of a split would lose its last element.)
 template <int E>
-bool dy_odd(const void *dY, int64_t lddy) { return E == 2 && (lddy % 2 != 0 || (uintptr_t)dY % 4 != 0); }
+bool dy_odd(const void *dY, int64_t N, int64_t lddy) {
+  return E == 2 && (N % 2 != 0 || lddy % 2 != 0 || (uintptr_t)dY % 4 != 0);
+}
 
 // The plan of a product that shares its launch with `companions` - 1 others.  A product on
 // its own needs enough splits to occupy every compute unit; in a batch the other products
@@ -776,7 +781,7 @@ int run(const int32_t *row_ptr, const int32_t *col_idx, const void *values, int6
   if (rc != BSR_OK) return rc;
   const dim3 grid(wgs);
   const int xcd_map = 1;      // XCD-aware work item order (0 = plain order, kept for measurements)
-  if (dy_odd<E>(dY, lddy)) {
+  if (dy_odd<E>(dY, N, lddy)) {
     if constexpr (E == 2)
       hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, true, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
   } else {
@@ -787,7 +792,7 @@ int run(const int32_t *row_ptr, const int32_t *col_idx, const void *values, int6
   return launch_splitk_reduce(prm.out, prm.splits, K, N, dW, lddw, accumulate, s);
 }
 
-// The jobs of one kernel instance (block shape, dY rows on odd elements or not), kDwBatchMax per launch.
+// The jobs of one kernel instance (block shape, dY rows from or to odd elements or not), kDwBatchMax per launch.
 template <typename T, int BR, int BC, int MS, int D, int WN>
 int run_batched(const DwJob *jobs, int n, bool odd, hipStream_t s) {
   constexpr int E = (int)sizeof(T);
@@ -836,11 +841,11 @@ int run_batched(const DwJob *jobs, int n, bool odd, hipStream_t s) {
   };
   int mine = 0;                                              // products of this kernel instance
   for (int i = 0; i < n; ++i)
-    if (jobs[i].br == BR && jobs[i].bc == BC && dy_odd<E>(jobs[i].dY, jobs[i].lddy) == odd) ++mine;
+    if (jobs[i].br == BR && jobs[i].bc == BC && dy_odd<E>(jobs[i].dY, jobs[i].N, jobs[i].lddy) == odd) ++mine;
   int left = mine;
   for (int i = 0; i < n; ++i) {
     const DwJob &j = jobs[i];
-    if (j.br != BR || j.bc != BC || dy_odd<E>(j.dY, j.lddy) != odd) continue;
+    if (j.br != BR || j.bc != BC || dy_odd<E>(j.dY, j.N, j.lddy) != odd) continue;
     uint32_t wgs;
     // products that share this launch: the rest of the list, up to the launch's capacity
     const int companions = m + (left < kDwBatchMax - m ? left : kDwBatchMax - m);

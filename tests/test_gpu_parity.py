@@ -1077,14 +1077,19 @@ def test_conversion_of_unaligned_rows_and_long_masks(M, K, br, bc, dtype, pad, s
     (129, 130, 129, 0, 0),       # dY rows on odd elements, one column in the last tile
     (517, 197, 131, 2, 1),       # odd pitch and an odd start in memory
     (200, 113, 7, 0, 0),         # a row of dY shorter than one vector
-    (63, 57, 130, 1, 0),         # even pitch wider than the row: vectors cross into the padding
+    (63, 57, 130, 1, 0),         # odd pitch wider than the row: vectors cross into the padding
     (1, 14, 9, 0, 0),            # one row
     (300, 225, 128, 0, 0),       # whole tiles
+    (90, 60, 130, 2, 0),         # even pitch wider than the row
+    (90, 60, 131, 1, 0),         # odd row in an even pitch: its last element shares a word with the padding
+    (700, 130, 131, 1, 0),       # ... over several splits
+    (700, 130, 77, 1, 0),        # ... and in the first column tile
+    (40, 33, 5, 3, 0),           # ... shorter than one vector
 ])
 def test_dw_rows_of_dy_at_any_alignment(M, K, N, pad, shift, b, dtype):
     """dY is read in 16-byte vectors whatever its pitch and start: what a vector holds beyond a row's end, the
     matrix' end or a 14-wide block must reach no entry of dW.  Its surroundings are NaN here.  Tolerance: binary32
-    accumulation of at most 517 products, as in the other parity tests."""
+    accumulation of at most 700 products, as in the other parity tests."""
     X, dY = rand_pair(M, K, N, dtype, seed=M + N + b)
     _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, b, b, 0.6)
     ref = oracle.dw(oracle.mask_dense(X, b, b, o_mask), dY)
@@ -1101,6 +1106,23 @@ def test_dw_rows_of_dy_at_any_alignment(M, K, N, pad, shift, b, dtype):
     torch.cuda.synchronize()
     for dW in got:
         assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
+
+
+@pytest.mark.parametrize("N,pad", [(131, 1), (77, 1), (130, 2)])
+@pytest.mark.parametrize("br,bc", [(1, 32), (8, 16)])
+def test_dw_of_re_tiled_blocks_with_padded_rows_of_dy(br, bc, N, pad):
+    """Block shapes without a kernel instance reach the same loads of dY through the re-tiling (M * K above the limit of
+    the general kernel); the padding of dY's rows is NaN."""
+    M, K = 700, 130
+    X, dY = rand_pair(M, K, N, "bf16", seed=M + N + br)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, br, bc, 0.6)
+    ref = oracle.dw(oracle.mask_dense(X, br, bc, o_mask), dY)
+    dYd = torch.full((M, N + pad), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :N]
+    dYd.copy_(to_dev(dY))
+    rp, ci, val = torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda(), to_dev(o_val)
+    dW = B.bsr_t_dense_matmul(rp, ci, val, M, K, br, bc, dYd)
+    torch.cuda.synchronize()
+    assert dw_error(dW.cpu().numpy(), ref) <= DW_TOL_DERIVED
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
