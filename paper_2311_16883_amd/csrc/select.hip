@@ -24,10 +24,11 @@
 //   pass 1  every workgroup draws the same small sample, takes from it two order
 //           statistics lo <= hi that bracket the rank of the threshold, and
 //           counts its slice of the keys into 256 buckets: bucket 0 below lo, the
-//           last bucket above hi, equal-width buckets in between (any monotone
-//           bucketing keeps the selection exact; a good bracket only makes the
-//           threshold bucket small).  Each workgroup stores its own counts: no
-//           atomics, nothing to clear.
+//           last bucket above hi, equal-width buckets in between -- those on
+//           either side of a gap, where the sample shows that nothing lies in most
+//           of [lo, hi] (any monotone bucketing keeps the selection exact; a good
+//           one only makes the threshold bucket small).  Each workgroup stores its
+//           own counts: no atomics, nothing to clear.
 //   pass 2  every workgroup adds up the counts, finds the bucket that holds the
 //           n_keep-th largest key, keeps the buckets above it, prunes the ones
 //           below and appends the keys inside it to a candidate list (one atomic
@@ -41,6 +42,8 @@
 // What bounds it is latency: a launch, a trip to memory, a handful of barriers.
 // So lane exchanges inside a wave are DPP moves (no LDS round trips), a key is
 // read once per pass with 16-byte loads, and mask bytes leave four at a time.
+#include <cmath>
+
 #include "common.h"
 
 namespace bsr {
@@ -549,15 +552,34 @@ __global__ __launch_bounds__(THREADS) void select_groups_batched_kernel(GroupBat
 
 // Control block shared by the two grid-wide passes (lives in the workspace;
 // written by workgroup 0 of pass 1).
+// The bucketing of the keys: 0 below lo, kBuckets - 1 above hi, between them buckets 2^shift wide.  mid != 0: the
+// keys in [lo, mid) go to buckets 1 .. kGapBucket, the last of which takes all of the gap in front of mid, those in
+// [mid, hi] to the buckets behind them, 2^shift_mid wide.
+struct Buckets {
+  uint64_t lo, hi, mid;
+  uint32_t shift, shift_mid;
+};
+constexpr uint32_t kGapBucket = kBuckets / 2;
 struct SelectCtrl {
-  uint32_t n_cand, shift, done, pad;
-  uint64_t lo, hi;
+  uint32_t n_cand, done;
+  Buckets buckets;
 };
 
-__device__ __forceinline__ uint32_t bucket_of(uint64_t key, uint64_t lo, uint64_t hi, uint32_t shift) {
-  if (key < lo) return 0u;
-  if (key > hi) return (uint32_t)kBuckets - 1u;
-  return 1u + (uint32_t)((key - lo) >> shift);
+__device__ __forceinline__ uint32_t bucket_of(uint64_t key, const Buckets &b) {
+  if (key < b.lo) return 0u;
+  if (key > b.hi) return (uint32_t)kBuckets - 1u;
+  if (__builtin_expect(b.mid != 0, 0)) {                                  // (the same in all lanes)
+    if (key >= b.mid) return kGapBucket + 1u + (uint32_t)((key - b.mid) >> b.shift_mid);
+    const uint64_t at = (key - b.lo) >> b.shift;
+    return at < (uint64_t)(kGapBucket - 1u) ? 1u + (uint32_t)at : kGapBucket;
+  }
+  return 1u + (uint32_t)((key - b.lo) >> b.shift);
+}
+// Smallest shift with (range >> shift) <= last, last < 2^bits and as few of them as possible.
+__device__ __forceinline__ uint32_t bucket_shift(uint64_t range, uint32_t bits, uint32_t last) {
+  uint32_t shift = range == 0 ? 0u : (uint32_t)(64 - __clzll((long long)range));   // bit length of range
+  shift = shift > bits ? shift - bits : 0u;
+  return (range >> shift) > (uint64_t)last ? shift + 1u : shift;
 }
 
 // What one selection needs in the kernel arguments.  wgs == 0: the one-workgroup selection.
@@ -565,6 +587,7 @@ struct SelectItem {
   const double *scores;
   uint8_t *mask;
   uint32_t nblocks, n_keep, per_wg, wgs;
+  uint32_t rank_lo, rank_hi;    // order statistics of the sample that bracket the threshold (pass 1)
   uint32_t *counts;
   SelectCtrl *ctrl;
   uint64_t *cand_key;
@@ -575,8 +598,7 @@ struct SelectItem {
 __device__ __forceinline__ void select_count_body(const SelectItem &it, const uint32_t wg) {
   __shared__ uint32_t hist[kBuckets];
   __shared__ __attribute__((aligned(16))) uint32_t sample[kSample];
-  __shared__ uint32_t ranks[kSample];
-  __shared__ uint32_t bracket[2];
+  __shared__ uint32_t ranks[kSample], sorted[kSample];
   const int t = threadIdx.x;
   const double *__restrict__ scores = it.scores;
   const uint32_t nblocks = it.nblocks;
@@ -598,11 +620,6 @@ __device__ __forceinline__ void select_count_body(const SelectItem &it, const ui
   if (t < kBuckets) hist[t] = 0;
   uint64_t key[4];
   load_keys4(scores, e0 + 4u * (uint32_t)t, e1, wide, key);
-  const double frac = 1.0 - (double)it.n_keep / (double)nblocks;       // threshold's quantile from below
-  const int pos = (int)(frac * kSample);
-  const int delta = 3 + (int)(3.5 * sqrt(kSample * frac * (1.0 - frac)));
-  const int rlo = pos - delta < 0 ? 0 : pos - delta;
-  const int rhi = pos + delta > kSample - 1 ? kSample - 1 : pos + delta;
   __syncthreads();
   {
     // ascending rank of every sample key: eight threads share a key, each compares it with an eighth of
@@ -619,32 +636,48 @@ __device__ __forceinline__ void select_count_body(const SelectItem &it, const ui
     atomicAdd(&ranks[t & (kSample - 1)], rank);
   }
   __syncthreads();
-  // the two order statistics around the threshold's expected position
-  if (t < kSample) {
-    const int rank = (int)ranks[t];
-    if (rank == rlo) bracket[0] = sample[t];
-    if (rank == rhi) bracket[1] = sample[t];
-  }
+  if (t < kSample) sorted[ranks[t]] = sample[t];
   __syncthreads();
-  const uint64_t lo = (uint64_t)(bracket[0] & ~kPosBits) << 32, hi = ((uint64_t)(bracket[1] | kPosBits) << 32) | 0xFFFFFFFFull;
-  const uint64_t range = hi - lo;
-  // smallest shift with (range >> shift) <= kBuckets - 3
-  uint32_t shift = range == 0 ? 0u : (uint32_t)(64 - __clzll((long long)range));   // bit length of range
-  shift = shift > 8 ? shift - 8 : 0u;
-  if ((range >> shift) > (uint64_t)(kBuckets - 3)) ++shift;
+  // lo and hi: the two order statistics around the threshold's expected position (rank_lo, rank_hi).  Where the keys lie in two heaps --
+  // all-zero blocks beside others, hot channels -- and the bracket spans both, equal-width buckets would all stand
+  // in the gap between them and each heap share one (301056 blocks, a third of them zero: 8 + 200 us for the selection
+  // among the candidates instead of 20 in all).  So where a gap of the sample takes more than half of the bracket, the
+  // buckets are dealt out on its two sides; they are no wider then than without the gap.
+  Buckets bk;
+  {
+    const uint32_t lane = (uint32_t)t & 63u;
+    const uint32_t v0 = sorted[lane], v1 = sorted[lane + 64];
+    static_assert(kSample == 128, "two keys of the sample per lane");
+    auto nth = [&](uint32_t r) { return lane_value(r < 64u ? v0 : v1, (int)(r & 63u)); };
+    const uint32_t low = nth(it.rank_lo), high = nth(it.rank_hi);
+    bk.lo = (uint64_t)(low & ~kPosBits) << 32;
+    bk.hi = ((uint64_t)(high | kPosBits) << 32) | 0xFFFFFFFFull;
+    bk.mid = 0;
+    bk.shift_mid = 0;
+    // (such a gap holds the middle of the bracket)
+    const uint32_t middle = low + (high - low) / 2;
+    const uint32_t upto = (uint32_t)(__popcll(__ballot(v0 <= middle)) + __popcll(__ballot(v1 <= middle)));
+    const uint32_t below = nth(upto - 1u), above = nth(upto < (uint32_t)kSample ? upto : upto - 1u);
+    const uint32_t gap = above / kSample - below / kSample;
+    if (__builtin_expect((gap >= 2) & (2 * gap > high / kSample - low / kSample), 0)) {
+      bk.mid = (uint64_t)(above & ~kPosBits) << 32;
+      bk.shift = bucket_shift((((uint64_t)(below | kPosBits) << 32) | 0xFFFFFFFFull) - bk.lo, 7, kGapBucket - 2);
+      bk.shift_mid = bucket_shift(bk.hi - bk.mid, 7, kBuckets - kGapBucket - 3);
+    } else {
+      bk.shift = bucket_shift(bk.hi - bk.lo, 8, kBuckets - 3);
+    }
+  }
   if (wg == 0 && t == 0) {
     it.ctrl->n_cand = 0;
     it.ctrl->done = 0;
-    it.ctrl->shift = shift;
-    it.ctrl->lo = lo;
-    it.ctrl->hi = hi;
+    it.ctrl->buckets = bk;
   }
   for (uint32_t e = e0 + 4u * (uint32_t)t; e < e1; e += 4 * kGridThreads) {
     uint64_t next[4];
     load_keys4(scores, e + 4 * kGridThreads, e1, wide, next);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (e + q < e1) atomicAdd(&hist[bucket_of(key[q], lo, hi, shift)], 1u);
+      if (e + q < e1) atomicAdd(&hist[bucket_of(key[q], bk)], 1u);
       key[q] = next[q];
     }
   }
@@ -662,8 +695,7 @@ __device__ __forceinline__ void select_classify_body(const SelectItem &it, const
   SelectCtrl *ctrl = it.ctrl;
   const uint32_t nblocks = it.nblocks, nwgs = it.wgs;
   const bool wide_in = (uintptr_t)scores % 16 == 0, wide_out = (uintptr_t)mask % 4 == 0;
-  const uint32_t shift = ctrl->shift;
-  const uint64_t lo = ctrl->lo, hi = ctrl->hi;
+  const Buckets bk = ctrl->buckets;
   const uint32_t e0 = wg * it.per_wg;
   const uint32_t e1 = (e0 + it.per_wg) < nblocks ? (e0 + it.per_wg) : nblocks;
   uint64_t key[4];
@@ -704,7 +736,7 @@ __device__ __forceinline__ void select_classify_body(const SelectItem &it, const
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (e + q < e1) {
-        const uint32_t b = bucket_of(key[q], lo, hi, shift);
+        const uint32_t b = bucket_of(key[q], bk);
         if (b != bucket) {
           own4 |= 1u << q;
           word |= (b > bucket ? 1u : 0u) << (8 * q);
@@ -733,14 +765,17 @@ __device__ __forceinline__ void select_classify_body(const SelectItem &it, const
   uint64_t blo, bhi;
   if (bucket == 0) {
     blo = 0;
-    bhi = lo - 1;                  // (bucket 0 is empty if lo == 0: never the threshold's)
+    bhi = bk.lo - 1;               // (bucket 0 is empty if lo == 0: never the threshold's)
   } else if (bucket == (uint32_t)kBuckets - 1) {
-    blo = hi + 1;
+    blo = bk.hi + 1;
     bhi = ~0ull;
   } else {
-    blo = lo + ((uint64_t)(bucket - 1) << shift);
-    bhi = blo + ((1ull << shift) - 1ull);
-    if (bhi > hi) bhi = hi;
+    const bool behind = bk.mid != 0 && bucket > kGapBucket;
+    const uint32_t width = behind ? bk.shift_mid : bk.shift;
+    const uint64_t last = bk.mid != 0 && !behind ? bk.mid - 1 : bk.hi;
+    blo = behind ? bk.mid + ((uint64_t)(bucket - kGapBucket - 1u) << width) : bk.lo + ((uint64_t)(bucket - 1u) << width);
+    bhi = blo + ((1ull << width) - 1ull);
+    if (bhi > last || (bk.mid != 0 && bucket == kGapBucket)) bhi = last;
   }
   if (few) {
     // the slices' candidates side by side in LDS, selected from there
@@ -873,8 +908,14 @@ namespace {
 
 // One selection's kernel parameters; grid_wide: with the workgroups and the workspace of the two passes.
 SelectItem select_item(const SelectJob &j, bool grid_wide) {
-  SelectItem it{j.scores, j.mask, (uint32_t)j.nblocks, (uint32_t)j.n_keep, 0u, 0u, nullptr, nullptr, nullptr, nullptr};
+  SelectItem it{j.scores, j.mask, (uint32_t)j.nblocks, (uint32_t)j.n_keep, 0u, 0u, 0u, 0u, nullptr, nullptr, nullptr, nullptr};
   if (!grid_wide) return it;
+  // the threshold's expected position in the sorted sample, and seven standard deviations around it
+  const double frac = 1.0 - (double)it.n_keep / (double)it.nblocks;    // threshold's quantile from below
+  const int pos = (int)(frac * kSample);
+  const int delta = 3 + (int)(3.5 * std::sqrt(kSample * frac * (1.0 - frac)));
+  it.rank_lo = (uint32_t)(pos - delta < 0 ? 0 : pos - delta);
+  it.rank_hi = (uint32_t)(pos + delta > kSample - 1 ? kSample - 1 : pos + delta);
   const SelectPlan p = select_plan(j.nblocks);
   char *base = static_cast<char *>(j.ws);
   it.counts = reinterpret_cast<uint32_t *>(base + p.counts_off);

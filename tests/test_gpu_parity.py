@@ -1045,6 +1045,53 @@ def test_selection_sizes_at_the_edges_of_its_paths(nblocks, levels):
             assert np.all(np.delete(got, np.s_[shift:nblocks + shift]) == 7)      # nothing beside the mask
 
 
+def two_heaps(nblocks, low, share, strays, seed):
+    """Scores for 1x1 blocks: `share` of them around `low` (0: exactly zero), the others around 1, `strays` between."""
+    rng = np.random.default_rng(seed)
+    x = np.abs(rng.standard_normal(nblocks, dtype=np.float32) * 0.2 + 1) + np.float32(0.01)
+    x[rng.random(nblocks) < share] *= np.float32(low)
+    x[rng.choice(nblocks, strays, replace=False)] = np.geomspace(1e-9, 1e-2, strays).astype(np.float32)
+    return x.reshape(-1, 1)
+
+
+@pytest.mark.parametrize("nblocks", [12289, 50001, 301056])
+@pytest.mark.parametrize("low", [0.0, 1e-12])
+@pytest.mark.parametrize("share,strays,keeps", [
+    (0.36, 0, (0.5, 0.6)),               # the bracket spans both heaps, the threshold lies in the upper one
+    (0.52, 0, (0.5, 0.4)),               # ... in the lower one
+    (0.5, 300, (0.5, 0.499, 0.501)),     # ... between them, among the few keys of the gap
+])
+def test_selection_of_scores_in_two_heaps(nblocks, low, share, strays, keeps):
+    """The grid-wide selection deals its buckets out on both sides of the gap; whole mask against the oracle."""
+    x = two_heaps(nblocks, low, share, strays, seed=nblocks + strays)
+    scores = x.astype(np.float64).ravel() ** 2
+    for keep in keeps:
+        mask = B.bsr_score_select(to_dev(x), 1, 1, keep)
+        torch.cuda.synchronize()
+        assert np.array_equal(mask.cpu().numpy(), oracle.select(scores, oracle.keep_count(nblocks, keep))), (share, keep)
+
+
+def test_selection_beside_a_heap_takes_about_as_long_as_without():
+    """A third of the blocks all-zero (padding): the threshold's bucket must not swallow the other two thirds.  The call
+    took ten times as long when it did; bound: three times, on the fastest of 20 calls each."""
+    times = []
+    for share in (0.0, 0.36):
+        x = to_dev(two_heaps(301056, 0.0, share, 0, seed=7))
+        ws = torch.empty(B.bsr_workspace_bytes(B.BSR_OP_SCORE_SELECT, 301056, 1, 0, 1, 1, torch.float32),
+                         dtype=torch.uint8, device="cuda")
+        best = float("inf")
+        for _ in range(20):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            for _ in range(4):
+                B.bsr_score_select(x, 1, 1, 0.5, ws=ws)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+    assert times[1] <= 3 * times[0], times
+
+
 @pytest.mark.parametrize("M,K,br,bc,dtype,pad,shift", [
     (70, 41, 32, 32, "bf16", 0, 0),          # odd row length: 16-byte vectors from 2-byte boundaries, cut at the edge
     (333, 1001, 16, 16, "f32", 0, 0),        # the same from 4-byte boundaries
