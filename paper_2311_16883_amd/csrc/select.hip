@@ -31,8 +31,8 @@
 //           own counts: no atomics, nothing to clear.
 //   pass 2  every workgroup adds up the counts, finds the bucket that holds the
 //           n_keep-th largest key, keeps the buckets above it, prunes the ones
-//           below and appends the keys inside it to a candidate list (one atomic
-//           per workgroup).  The workgroup that finishes last selects among the
+//           below and lists the keys inside it, at places that follow from the
+//           counts (no atomics on memory).  The workgroup that finishes last selects among the
 //           candidates exactly, with the bucket's key range as a bracket: 32-bit
 //           codes linear in the key, one radix pass as a rule, then a ranking of
 //           the handful that share the threshold's code through lane reads.  The
@@ -561,8 +561,8 @@ struct Buckets {
 };
 constexpr uint32_t kGapBucket = kBuckets / 2;
 struct SelectCtrl {
-  uint32_t n_cand, done;
   Buckets buckets;
+  uint32_t done;            // workgroups of pass 2 that have listed their candidates
 };
 
 __device__ __forceinline__ uint32_t bucket_of(uint64_t key, const Buckets &b) {
@@ -638,11 +638,11 @@ __device__ __forceinline__ void select_count_body(const SelectItem &it, const ui
   __syncthreads();
   if (t < kSample) sorted[ranks[t]] = sample[t];
   __syncthreads();
-  // lo and hi: the two order statistics around the threshold's expected position (rank_lo, rank_hi).  Where the keys lie in two heaps --
-  // all-zero blocks beside others, hot channels -- and the bracket spans both, equal-width buckets would all stand
-  // in the gap between them and each heap share one (301056 blocks, a third of them zero: 8 + 200 us for the selection
-  // among the candidates instead of 20 in all).  So where a gap of the sample takes more than half of the bracket, the
-  // buckets are dealt out on its two sides; they are no wider then than without the gap.
+  // lo and hi: the two order statistics around the threshold's expected position (rank_lo, rank_hi).  Where the
+  // keys lie in two heaps -- all-zero blocks beside others, hot channels -- and the bracket spans both, equal-width
+  // buckets would all stand in the gap between them and each heap share one (score + select of 301056 blocks, a
+  // third of them zero: 220 us, 42 with both sides' buckets).  So where a gap of the sample takes more than half of
+  // the bracket, the buckets are dealt out on its two sides; they are no wider then than without the gap.
   Buckets bk;
   {
     const uint32_t lane = (uint32_t)t & 63u;
@@ -668,7 +668,6 @@ __device__ __forceinline__ void select_count_body(const SelectItem &it, const ui
     }
   }
   if (wg == 0 && t == 0) {
-    it.ctrl->n_cand = 0;
     it.ctrl->done = 0;
     it.ctrl->buckets = bk;
   }
@@ -727,8 +726,16 @@ __device__ __forceinline__ void select_classify_body(const SelectItem &it, const
 
   // Other buckets: mask bytes.  The threshold's bucket: the n candidates, whose mask bytes are the last
   // workgroup's to write.  As a rule they are few: every workgroup lists its own at its slice's place in
-  // the list (how many they are stands in counts), no atomic on memory.  Else they are appended to one list.
+  // the list (how many they are stands in counts).  Else the list has no holes: a workgroup's part begins
+  // where those in front of it have theirs.  No atomic on memory either way.
   const bool few = n <= (uint32_t)kCap;
+  uint32_t list_at = e0;
+  if (!few) {
+    const uint32_t in_front = wave_sum((uint32_t)t < wg ? it.counts[(uint32_t)t * kBuckets + bucket] : 0u);
+    if ((t & 63) == 0) sh.wave_tot[t >> 6] = in_front;
+    __syncthreads();
+    list_at = wave_sum((t & 63) < kGridThreads / 64 ? sh.wave_tot[t & 63] : 0u);
+  }
   for (uint32_t e = e0 + 4u * (uint32_t)t; e < e1; e += 4 * kGridThreads) {
     uint64_t next[4];
     load_keys4(scores, e + 4 * kGridThreads, e1, wide_in, next);
@@ -741,7 +748,7 @@ __device__ __forceinline__ void select_classify_body(const SelectItem &it, const
           own4 |= 1u << q;
           word |= (b > bucket ? 1u : 0u) << (8 * q);
         } else {
-          const uint32_t at = few ? e0 + atomicAdd(&wg_cand, 1u) : atomicAdd(&ctrl->n_cand, 1u);
+          const uint32_t at = list_at + atomicAdd(&wg_cand, 1u);
           store_shared(&it.cand_key[at], key[q]);
           store_shared(&it.cand_idx[at], e + q);
         }
