@@ -200,14 +200,25 @@ struct CompressArgs {
   uint32_t parts;          // workgroups that share a block-row: each lists it, each copies every parts-th kept block
 };
 
-// How many workgroups share a block-row in a launch over `wgs` block-rows: block-rows differ in kept
-// blocks, and a few hundred of them leave compute units idle behind the ones that got one more.  ([12544 x
-// 384] binary32, 392 block-rows: 11.1 us alone, 8.9 shared by four; [50176 x 3072] in 64x64 blocks, 784
-// block-rows: 72 us alone, 69 shared by two.  More than four only repeat the listing.)
-inline uint32_t row_parts(int64_t wgs, int64_t most) {
+// How many workgroups share a block-row in a launch over `wgs` block-rows; nbc = block-columns, `copied` = bytes of
+// kept blocks per block-row.  Up to 256 block-rows leave compute units idle: up to four share one (1568 x 3072
+// binary32, 49 block-rows: 13.0 us alone, 6.5 shared by four).  Beyond that, sharing evens out block-rows that differ in
+// kept blocks, but every sharer lists the block-row and counts the mask in front of it again: up to three share, each
+// copies 8 KB at least, and the more block-rows there are the larger the blocks must be.  Score, select and convert
+// one after the other, bf16, alone and shared: [12544 x 1536] in 32x32 blocks, 392 block-rows, 40.7 and 35.5 us;
+// [25088 x 1536] in 64x64 blocks 54.5 and 43.3; [25088 x 384] in 32x32 blocks, 784 block-rows of 12 KB, 21.3 and 22.6;
+// [6272 x 1536] in 16x16 blocks 30.8 and 31.8.  The conversion repeated on the same X: 10.6 and 11.7; 19.0 and 15.4; 5.9
+// and 7.1; 6.7 and 9.5; [25088 x 1536] in 32x32 blocks 18.9 and 21.7, with the rest 54.5 and 53.4.
+inline uint32_t row_parts(int64_t wgs, int64_t nbc, int64_t copied) {
   int64_t p = wgs > 0 ? 2048 / wgs : 1;
-  if (p > most) p = most;
-  return (uint32_t)(p < 1 ? 1 : p > 4 ? 4 : p);
+  if (p > 4) p = 4;
+  if (p > nbc) p = nbc;
+  if (wgs > 256) {
+    if (p > 3) p = 3;
+    if (p > copied / 8192) p = copied / 8192;
+    if (p > 4 * copied / (3 * nbc * wgs)) p = 4 * copied / (3 * nbc * wgs);
+  }
+  return (uint32_t)(p < 1 ? 1 : p);
 }
 
 // i = block-row, part = which of the workgroups that share it
@@ -897,7 +908,7 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
   // Every workgroup counts the mask in front of its row, wgs * nblocks / 2 bytes out of L2 in all, unless a
   // launch writes row_ptr first (6 to 8 us): from 256 MB on that is the faster way (mask of 3136 x 96
   // blocks, 472 MB: 48 us -> 8 + 30 us; 3136 x 48, 236 MB: 70 us either way; 1568 x 48, 59 MB: 35 -> 39 us).
-  const uint32_t parts = row_parts(row_wgs, nbc);
+  const uint32_t parts = row_parts(row_wgs, nbc, j.n_keep * j.br * j.bc * e / nbr);
   p.wgs = (unsigned)nbr * parts;
   p.rows_first = (int64_t)p.wgs * nbr * nbc / 2 > (int64_t(256) << 20);
   p.direct = CompressArgs{j.keep_mask, static_cast<const uint8_t *>(j.X), j.row_ptr, j.col_idx,

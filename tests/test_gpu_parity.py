@@ -1118,6 +1118,18 @@ def test_conversion_of_unaligned_rows_and_long_masks(M, K, br, bc, dtype, pad, s
         assert to_host(val).tobytes() == o_val.tobytes()
 
 
+@pytest.mark.parametrize("M,K,dtype", [
+    (2048, 300, "bf16"),          # 64 block-rows: four workgroups share each
+    (9593, 1536, "bf16"),         # 300: three
+    (22400, 768, "f32"),          # 700: two
+    (9600, 384, "bf16"),          # 300 of few bytes: none
+])
+def test_conversion_with_shared_block_rows(M, K, dtype):
+    """How many workgroups share a block-row depends on their number and on what there is to copy."""
+    X = rand_pair(M, K, 1, dtype, seed=M + K)[0]
+    check_forward(X, 32, 32, 0.5, label="shared block-rows")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("b", [14, 16, 32, 64])
 @pytest.mark.parametrize("M,K,N,pad,shift", [
