@@ -22,7 +22,7 @@ struct ScoreGeom {
   int gb;    // row groups per block-row
   int rb;    // block-rows handled per pass
   int nchunks;
-  int direct;  // 1: score_direct_body, one lane per vector column of a block-row; nchunks = its workgroups
+  int direct;  // score_direct_body (1; 2: its form for few tall blocks), gb lanes per vector column of a block; nchunks = its workgroups
 };
 
 // bx, by, gy: the workgroup's place in its tensor's (chunks x passes) grid.  Threads beyond
@@ -100,14 +100,20 @@ __device__ __forceinline__ void score_body(
 // The sum does not depend on it: the rows r, r + 8, ... of a vector column are added top to
 // bottom, then the eight such sums pairwise (r and r + 4, r and r + 2, r and r + 1), then the vector
 // columns; a step of that is an addition inside a lane or a lane exchange, depending on RS.
+// TALL: few blocks of 128 rows and more, where eight lanes per vector column leave the chip idle and a lane with a
+// chain of additions as long as its rows.  rs = 8 .. 64 lanes share a column, a number that follows from the matrix and the
+// block alone (score_geometry), and each keeps two sums, of the even and of the odd elements.  ([4096 x 384] binary32
+// in 256x16 blocks, score and select: 16.0 us through the LDS body, 7.5 so.)
 // wg = index of the workgroup among the ceil(nbr * nbc * (bc / V) * RS / 256) of its tensor.
 template <typename T, int V, int RS>
 __device__ __forceinline__ void score_direct_body(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
-    int64_t nbc, double *__restrict__ scores, uint32_t wg) {
-  constexpr int kOwn = kRowClasses / RS;                   // row classes a lane owns
+    int64_t nbc, int rs, double *__restrict__ scores, uint32_t wg) {
+  constexpr bool TALL = RS == 0;
+  const int lanes = TALL ? rs : RS;
+  constexpr int kOwn = TALL ? 2 : kRowClasses / (TALL ? 1 : RS);   // sums a lane keeps: its row classes
   const uint32_t vpb = (uint32_t)(bc / V);                 // lanes across a block row: a power of two
-  const uint32_t lpb = vpb * (uint32_t)RS;                 // lanes per block: a power of two, at most 64
+  const uint32_t lpb = vpb * (uint32_t)lanes;              // lanes per block: a power of two, at most 64
   const uint32_t per_row = (uint32_t)nbc * lpb;            // lanes per block-row
   const uint32_t gid = wg * (uint32_t)kScoreThreads + threadIdx.x;
   const uint32_t i = gid / per_row, c = gid - i * per_row;
@@ -123,18 +129,19 @@ __device__ __forceinline__ void score_direct_body(
   // (eight, not more: with sixteen the registers they need leave room for three waves per SIMD only,
   // and a workgroup has nothing in flight while it adds up)
   constexpr int kInFlight = 8;
-  for (int r0 = (int)part; r0 < rows; r0 += kInFlight * RS) {
+  for (int r0 = (int)part; r0 < rows; r0 += kInFlight * lanes) {
     Vec<T, V> v[kInFlight];
 #pragma unroll
     for (int b = 0; b < kInFlight; ++b)
-      if (r0 + b * RS < rows) v[b] = load_stream(reinterpret_cast<const Vec<T, V> *>(p + (int64_t)(r0 + b * RS) * ldx));
+      if (r0 + b * lanes < rows) v[b] = load_stream(reinterpret_cast<const Vec<T, V> *>(p + (int64_t)(r0 + b * lanes) * ldx));
 #pragma unroll
     for (int b = 0; b < kInFlight; ++b) {
-      if (r0 + b * RS < rows) {
+      if (r0 + b * lanes < rows) {
 #pragma unroll
         for (int q = 0; q < V; ++q) {
           const double x = (double)elem_to_float<T>(v[b].e[q]);
-          acc[b % kOwn] = fma(x, x, acc[b % kOwn]);
+          const int k = TALL ? q % 2 : b % kOwn;
+          acc[k] = fma(x, x, acc[k]);
         }
       }
     }
@@ -144,8 +151,7 @@ __device__ __forceinline__ void score_direct_body(
 #pragma unroll
     for (int k = 0; k < half; ++k) acc[k] += acc[k + half];
   double sum = acc[0];
-#pragma unroll
-  for (int o = RS / 2; o >= 1; o /= 2) sum += __shfl_xor(sum, o * (int)vpb);
+  for (int o = lanes / 2; o >= 1; o /= 2) sum += __shfl_xor(sum, o * (int)vpb);
   for (uint32_t o = 1; o < vpb; o <<= 1) sum += __shfl_xor(sum, (int)o);
   if (live && within == 0) scores[(int64_t)i * nbc + j] = sum;
 }
@@ -153,12 +159,16 @@ __device__ __forceinline__ void score_direct_body(
 template <typename T, int V>
 __device__ __forceinline__ void score_direct(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
-    int64_t nbc, int rs, double *__restrict__ scores, uint32_t wg) {
-  switch (rs) {
-    case 1: score_direct_body<T, V, 1>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
-    case 2: score_direct_body<T, V, 2>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
-    case 4: score_direct_body<T, V, 4>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
-    default: score_direct_body<T, V, 8>(X, M, K, ldx, br, bc, nbr, nbc, scores, wg); break;
+    int64_t nbc, const ScoreGeom &g, double *__restrict__ scores, uint32_t wg) {
+  if (g.direct == 2) {
+    score_direct_body<T, V, 0>(X, M, K, ldx, br, bc, nbr, nbc, g.gb, scores, wg);
+    return;
+  }
+  switch (g.gb) {
+    case 1: score_direct_body<T, V, 1>(X, M, K, ldx, br, bc, nbr, nbc, 1, scores, wg); break;
+    case 2: score_direct_body<T, V, 2>(X, M, K, ldx, br, bc, nbr, nbc, 2, scores, wg); break;
+    case 4: score_direct_body<T, V, 4>(X, M, K, ldx, br, bc, nbr, nbc, 4, scores, wg); break;
+    default: score_direct_body<T, V, 8>(X, M, K, ldx, br, bc, nbr, nbc, 8, scores, wg); break;
   }
 }
 
@@ -166,7 +176,7 @@ template <typename T, int V>
 __global__ __launch_bounds__(kScoreThreads) void score_kernel(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
     int64_t nbc, ScoreGeom g, double *__restrict__ scores) {
-  if (g.direct) score_direct<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g.gb, scores, blockIdx.x);
+  if (g.direct) score_direct<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g, scores, blockIdx.x);
   else score_body<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g, scores, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
@@ -192,7 +202,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_batched_kernel(ScoreBatch
   const ScoreItem &it = b.it[i];
   const uint32_t local = blockIdx.x - it.wg_begin;
   if (it.g.direct) {
-    score_direct<T, V>(static_cast<const T *>(it.X), it.M, it.K, it.ldx, it.br, it.bc, it.nbr, it.nbc, it.g.gb, it.scores,
+    score_direct<T, V>(static_cast<const T *>(it.X), it.M, it.K, it.ldx, it.br, it.bc, it.nbr, it.nbc, it.g, it.scores,
                             local);
     return;
   }
@@ -394,9 +404,12 @@ ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensor
     if (want < 65536) want = 65536;
     int rs = 1;
     while (nbr * nbc * vpb * rs < want && vpb * rs * 2 <= 64 && rs * 2 * 4 <= br && rs < kRowClasses) rs *= 2;
+    // (tall blocks: the same rs in a launch of one tensor and of many, since it decides the order of the additions)
+    const bool tall = br >= 128 && rs == kRowClasses && nbr * nbc * vpb * rs < 65536;
+    while (tall && nbr * nbc * vpb * rs < 65536 && vpb * rs * 2 <= 64 && rs * 2 * 4 <= br) rs *= 2;
     const int64_t lanes = nbr * nbc * vpb * rs;
     if (lanes >= 16384 && lanes < (int64_t(1) << 31)) {
-      g.direct = 1;
+      g.direct = tall ? 2 : 1;
       g.jc = g.vpbt = g.vct = g.rb = 1;
       g.gb = rs;
       g.nchunks = (int)ceil_div(lanes, (int64_t)kScoreThreads);

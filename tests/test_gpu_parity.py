@@ -1045,6 +1045,26 @@ def test_selection_sizes_at_the_edges_of_its_paths(nblocks, levels):
             assert np.all(np.delete(got, np.s_[shift:nblocks + shift]) == 7)      # nothing beside the mask
 
 
+@pytest.mark.parametrize("M,K,br,bc,dtype", [
+    (4096, 384, 256, 16, "f32"), (4096, 384, 256, 16, "bf16"),      # 16 and 32 lanes per vector column
+    (2048, 256, 256, 8, "bf16"),                                    # 64
+    (4090, 380, 196, 8, "f32"),                                     # cut blocks on both edges
+    (12544, 384, 512, 32, "f32"),                                   # 8: as many as fit a wave
+    (12544, 1536, 512, 32, "bf16"), (20000, 1536, 128, 8, "bf16"),  # either side of the limit between the two forms
+])
+def test_scores_of_tall_blocks(M, K, br, bc, dtype):
+    """Against the oracle, and the same bits in a call of many tensors (where a column is shared by fewer lanes)."""
+    X = rand_pair(M, K, 1, dtype, seed=M + br)[0]
+    check_forward(X, br, bc, 0.5, label="tall blocks")
+    Xd = to_dev(X)
+    n = -(-M // br) * -(-K // bc)
+    alone = B.bsr_score_select(Xd, br, bc, 0.5, want_scores=True)[1]
+    scores = [torch.empty(n, dtype=torch.float64, device="cuda") for _ in range(6)]
+    B.bsr_score_select_batched(B.SelectBatch([Xd] * 6, [(br, bc)] * 6, [0.5] * 6, scores=scores))
+    torch.cuda.synchronize()
+    assert all(torch.equal(s, alone) for s in scores)
+
+
 def two_heaps(nblocks, low, share, strays, seed):
     """Scores for 1x1 blocks: `share` of them around `low` (0: exactly zero), the others around 1, `strays` between."""
     rng = np.random.default_rng(seed)
