@@ -119,19 +119,25 @@ constexpr int KT = 128, NT = 128;   // dW tile of one workgroup: 2 x WN waves, 6
 constexpr int slot_columns(int bc) { return bc == 14 ? 16 : bc; }
 constexpr int tile_block_columns(int bc) { return KT / slot_columns(bc); }
 
+// Forms of the kernel.  kOdd (bfloat16): rows of dY may start or end on odd elements, see load_b.  kPacked (binary32, 14x14
+// blocks): no slots, a tile is 128 columns of the matrix, read in vectors of two elements; its first and last
+// block-column may lie in the tile in part.
+enum Form { kPlain, kOdd, kPacked };
+
 // E = bytes per element of the inputs (2: bfloat16, 4: binary32).
-template <int E, int BR, int BC, int MS, int WN>
+template <int E, int BR, int BC, int MS, int WN, Form FORM>
 struct Geo {
+  static constexpr bool PACKED = FORM == kPacked;
   static constexpr int THREADS = 128 * WN;                // threads per role: 2 x WN waves
   static constexpr int NTW = NT / (32 * WN);               // 32-column pieces of dW per wave along N
   static constexpr int R = MS / BR;                       // block-rows per stage
   static constexpr int ROWS = R * BR;                     // rows of a stage that carry data
-  static constexpr int CS = slot_columns(BC);
-  static constexpr int JT = tile_block_columns(BC);       // block-columns of a tile
+  static constexpr int CS = PACKED ? BC : slot_columns(BC);
+  static constexpr int JT = PACKED ? KT / BC + 2 : tile_block_columns(BC);   // block-columns of a tile
   // every 16 x 32 piece of the activation tile lies inside one block: pruned
   // blocks are skipped outright and their LDS content is never read
   static constexpr bool SKIP_ONLY = (BC % 32 == 0) && (BR % 16 == 0);
-  static constexpr int VA = 16 / E;                       // elements per activation vector: 16 bytes
+  static constexpr int VA = PACKED ? 2 : 16 / E;          // elements per activation vector: 16 bytes
   static constexpr int VPR = CS / VA;                     // vectors per block row
   static constexpr int VPB = BR * VPR;                    // vectors per block
   static constexpr int VB = 16 / E;                       // elements per dY vector
@@ -142,7 +148,7 @@ struct Geo {
   // block-rows of one split: its table must fit in LDS beside the stages (two workgroups per compute unit)
   static constexpr int MAXR = max_rows_per_split(BR, MS);
   static constexpr int STAGE_WORDS = (MS * LDA + MS * LDB) * E / 4;   // 32-bit words of one stage (A tile, B tile)
-  static_assert(MS % 16 == 0 && R >= 1 && MSUB <= 8 && CS % VA == 0 && KT % CS == 0, "stage shape");
+  static_assert(MS % 16 == 0 && R >= 1 && MSUB <= 8 && CS % VA == 0 && (PACKED || KT % CS == 0), "stage shape");
   static_assert(JT <= 32, "tile index is a 32-bit mask");
 };
 
@@ -150,7 +156,6 @@ struct Geo {
 // WN = multiplier waves along N (2: 64 x 64 per wave, 4: 64 x 32 per wave); the
 // workgroup has 2 x WN multiplier waves and as many loader waves.
 // T = uint16_t (bfloat16 bits) or float.
-// ODD: rows of dY may start or end on odd elements (bfloat16): see load_b.
 // What one tensor's launch needs (kernel arguments; an array of these for a batch).
 struct DwParams {
   const int32_t *row_ptr, *col_idx;
@@ -162,7 +167,7 @@ struct DwParams {
 };
 
 // wg = number of the workgroup among those of this tensor.
-template <typename T, int BR, int BC, int MS, bool ODD, int D, int WN>
+template <typename T, int BR, int BC, int MS, Form FORM, int D, int WN>
 __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t wg, const int xcd_map) {
   const int32_t *__restrict__ row_ptr = prm.row_ptr;
   const int32_t *__restrict__ col_idx = prm.col_idx;
@@ -173,8 +178,9 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const int64_t nbr = prm.nbr, nbc = prm.nbc, stages_per_split = prm.stages_per_split;
   const int accumulate = prm.accumulate, tiles_k = prm.tiles_k, tiles_n = prm.tiles_n, splits = prm.splits;
   constexpr int E = (int)sizeof(T);
-  static_assert(!ODD || E == 2, "binary32 rows start on whole words");
-  typedef Geo<E, BR, BC, MS, WN> G;
+  constexpr bool ODD = FORM == kOdd, PACKED = FORM == kPacked;
+  static_assert(ODD ? E == 2 : !PACKED || (E == 4 && BC == 14), "binary32 rows of dY start on whole words");
+  typedef Geo<E, BR, BC, MS, WN, FORM> G;
   constexpr int VB = G::VB;
   constexpr int kRole = G::THREADS;              // threads per role
   constexpr int kThreads = 2 * kRole;            // workgroup
@@ -235,10 +241,12 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const int nstages = s_end > s_begin ? (int)(s_end - s_begin) : 0;
   const int64_t i_begin = s_begin * G::R;
   const int nrows = nstages * G::R;                       // block-rows of this split (may run past nbr)
-  const int64_t jfirst = (int64_t)tile_x * G::JT;
-  int64_t jlast = jfirst + G::JT - 1;
+  const int64_t k0 = (int64_t)tile_x * KT;                 // (first column of the tile where blocks are packed)
+  const int64_t jfirst = PACKED ? k0 / BC : (int64_t)tile_x * G::JT;
+  int64_t jlast = PACKED ? (k0 + KT - 1) / BC : jfirst + G::JT - 1;
   if (jlast > nbc - 1) jlast = nbc - 1;
   const int jt = (int)(jlast - jfirst + 1);
+  auto tile_column = [&](int jl) { return PACKED ? (int)((jfirst + jl) * BC - k0) : jl * G::CS; };   // of block-column jl
 
   // ---- block table: which blocks of the tile's block-columns each block-row keeps ----
   // A few lanes share a block-row and take its entries in turn (they may stand in any order): two
@@ -283,7 +291,7 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
     uint32_t colmask[2][2] = {{0u, 0u}, {0u, 0u}};
 #pragma unroll
     for (int jl = 0; jl < G::JT; ++jl) {
-      const int c0 = jl * G::CS, c1 = c0 + BC - 1;
+      const int c0 = tile_column(jl), c1 = c0 + BC - 1;
 #pragma unroll
       for (int x = 0; x < 4; ++x)
         if (jl < jt && c0 <= x * 32 + 31 && c1 >= x * 32) colmask[x >> 1][x & 1] |= 1u << jl;
@@ -327,8 +335,8 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
       const int slot = v / G::VPB, off = v % G::VPB;
       const int rbk = slot / G::JT, jl = slot % G::JT;
       const int r = off / G::VPR, c = (off % G::VPR) * G::VA;
-      const int col = jl * G::CS + c;
-      const bool used = slot < G::R * G::JT && jl < jt;
+      const int col = tile_column(jl) + c;
+      const bool used = slot < G::R * G::JT && jl < jt && (!PACKED || (col >= 0 && col + G::VA <= KT));
       a_src[it] = (uint32_t)((r * BC + c) * E);
       a_tab[it] = used ? (uint32_t)(rbk * G::JT + jl) : (uint32_t)(nrows * G::JT);
       a_inc[it] = used ? (uint32_t)(G::R * G::JT) : 0u;
@@ -603,7 +611,7 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           // (the part that is the same in all lanes first: it stays in scalar registers)
-          int64_t k = jfirst * BC + (2 * wk + u) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          int64_t k = (PACKED ? k0 : jfirst * BC) + (2 * wk + u) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           const int tc = (2 * wk + u) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);   // column of the activation tile
           if constexpr (G::CS != BC) k = (jfirst + tc / G::CS) * BC + tc % G::CS;
           const int64_t n = n0 + (G::NTW * wn + w) * 32 + (lane & 31);
@@ -623,9 +631,9 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
 template <typename T, int WN>
 constexpr int min_waves() { return sizeof(T) == 2 && WN == 4 ? 8 : 1; }
 
-template <typename T, int BR, int BC, int MS, bool ODD, int D, int WN>
+template <typename T, int BR, int BC, int MS, Form FORM, int D, int WN>
 __global__ __launch_bounds__(256 * WN, (min_waves<T, WN>())) void dw_mfma_kernel(DwParams prm, int xcd_map) {
-  dw_mfma_body<T, BR, BC, MS, ODD, D, WN>(prm, blockIdx.x, xcd_map);
+  dw_mfma_body<T, BR, BC, MS, FORM, D, WN>(prm, blockIdx.x, xcd_map);
 }
 
 // Several tensors per launch.  The work items (split, tile) of all products form one list,
@@ -644,20 +652,26 @@ struct DwBatch {
   uint32_t xcd_begin[9];
 };
 
-template <typename T, int BR, int BC, int MS, bool ODD, int D, int WN>
+template <typename T, int BR, int BC, int MS, Form FORM, int D, int WN>
 __global__ __launch_bounds__(256 * WN) void dw_mfma_batched_kernel(DwBatch b, int n) {
   const uint32_t x = blockIdx.x & 7u, slot = blockIdx.x >> 3;
   if (slot >= b.xcd_begin[x + 1] - b.xcd_begin[x]) return;
   const uint32_t g = b.xcd_begin[x] + slot;
   int i = 0;
   while (i + 1 < n && g >= b.it[i + 1].wg_begin) ++i;
-  dw_mfma_body<T, BR, BC, MS, ODD, D, WN>(b.it[i], g - b.it[i].wg_begin, 0);
+  dw_mfma_body<T, BR, BC, MS, FORM, D, WN>(b.it[i], g - b.it[i].wg_begin, 0);
 }
 
 struct Plan {
+  double cost;             // as make_plan estimates it, in microseconds
   int splits;
   int64_t stages_per_split;
 };
+
+// Tiles of dW along K.
+inline int64_t dw_tiles_k(int64_t K, int bc, bool packed) {
+  return packed ? ceil_div(K, (int64_t)KT) : ceil_div(ceil_div(K, (int64_t)bc), (int64_t)tile_block_columns(bc));
+}
 
 // Number of splits of the contraction.  The tiles x splits work items are processed in rounds
 // of one workgroup per compute unit (binary32: 128 KB of LDS each) or two (2-byte elements); a
@@ -666,23 +680,22 @@ struct Plan {
 // reduction).  The constants are measured orders of magnitude on MI355X, in microseconds
 // (a stage of a workgroup that shares its compute unit takes 0.7 us); only the choice of s
 // depends on them.
-inline int64_t dw_tiles_k(int64_t K, int bc) { return ceil_div(ceil_div(K, (int64_t)bc), (int64_t)tile_block_columns(bc)); }
-
 template <int E, int BR, int MS>
-Plan make_plan(int64_t M, int64_t K, int64_t N) {
+Plan make_plan(int64_t M, int64_t K, int64_t N, bool packed) {
   constexpr int R = MS / BR;
   constexpr int kSlots = E == 2 ? 512 : 256;
   const int64_t nbr = ceil_div(M, BR);
   const int64_t stages = ceil_div(nbr, R);
-  const int64_t tiles = dw_tiles_k(K, BR) * ceil_div(N, 128);
+  const int64_t tiles = dw_tiles_k(K, BR, packed) * ceil_div(N, 128);
   Plan p;
+  p.cost = 0;
   p.splits = 1;
   p.stages_per_split = stages > 0 ? stages : 1;
   if (stages <= 0 || tiles <= 0) return p;
   // (binary32 stages are bound by the matrix core: 16 times the passes per multiply-add, spread over half
   // the waves when dW has at most two strips of columns.  A split contraction costs a second launch; for a
   // few stages it is not worth it.)
-  const double us_stage = (E == 4 ? (N > 64 ? 3.0 : 2.0) : 0.70) * MS / 64.0, us_round = 8.0, us_reduce = 4.5;
+  const double us_stage = (E == 4 ? (N > 64 ? 3.0 : 2.0) : 0.70) * (packed ? 1.13 : 1.0) * MS / 64.0, us_round = 8.0, us_reduce = 4.5;
   const double us_split = 2.0 * (double)K * (double)N * 4.0 / 3.0e6;
   // (at least one split per 256 block-rows, although the table would hold 512: for 16-row blocks at
   // 50176 rows 14 splits of 112 stages take 106 us where 7 of 224 take 156 us)
@@ -701,6 +714,7 @@ Plan make_plan(int64_t M, int64_t K, int64_t N) {
   const int64_t sps = ceil_div(stages, best_s);
   p.splits = (int)ceil_div(stages, sps);
   p.stages_per_split = sps;
+  p.cost = best;
   return p;
 }
 
@@ -721,14 +735,14 @@ bool dy_odd(const void *dY, int64_t N, int64_t lddy) {
 // traffic costs, as if the companions were products of the same shape.  Never more splits
 // than on its own: the workspace is sized for that.
 template <int E, int BR, int MS>
-Plan make_plan_batched(int64_t M, int64_t K, int64_t N, int companions) {
-  const Plan alone = make_plan<E, BR, MS>(M, K, N);
+Plan make_plan_batched(int64_t M, int64_t K, int64_t N, int companions, bool packed) {
+  const Plan alone = make_plan<E, BR, MS>(M, K, N, packed);
   if (companions <= 1 || alone.splits <= 1) return alone;
   constexpr int R = MS / BR;
   constexpr int64_t kSlots = 512, kFixed = 16;                 // fixed part of an item, in stages
   constexpr double kBytesPerStage = 2.0e6;                     // partial-tile bytes that cost the time of one stage (measured)
   const int64_t stages = ceil_div(ceil_div(M, BR), R);
-  const int64_t tiles = dw_tiles_k(K, BR) * ceil_div(N, 128);
+  const int64_t tiles = dw_tiles_k(K, BR, packed) * ceil_div(N, 128);
   const int64_t s_min = ceil_div(stages, (int64_t)(max_rows_per_split(BR, MS) / R));
   if (s_min >= alone.splits) return alone;
   const double split_cost = (double)companions * (double)K * (double)N * 8.0 / kBytesPerStage;
@@ -748,10 +762,32 @@ Plan make_plan_batched(int64_t M, int64_t K, int64_t N, int companions) {
   return p;
 }
 
+// The form of the kernel for a product on its own or among `companions` of its block shape in a call.  With slots a
+// tile of 14x14 blocks holds 112 columns of dW, packed it holds 128: a stage takes 13 % longer (binary32: 11 loads of 8
+// bytes in place of 8 of 16), but dW may need fewer tiles.  Both forms are planned, and the one that needs less time is
+// taken: by the plan's own estimate for one product, by the rounds of one workgroup per compute unit for several.
+// ([12544 x 384 x 384], 4 tiles of slots or 3 packed: 54 and 50 us, six of them 252 and 229; [12544 x 336 x 384], 3 of
+// either: 45 and 49, six 200 and 226; [12544 x 1536 x 384], 14 or 12: six 821 and 925.  bfloat16 gains from slots at
+// every size.)
+template <int E, int BR, int MS>
+Form form_of(const DwJob &j, int companions) {
+  if (dy_odd<E>(j.dY, j.N, j.lddy)) return kOdd;
+  if constexpr (E == 4 && BR == 14) {
+    auto cost = [&](bool packed) {
+      const Plan p = make_plan_batched<E, BR, MS>(j.M, j.K, j.N, companions, packed);
+      if (companions <= 1) return p.cost;
+      const int64_t items = (int64_t)companions * dw_tiles_k(j.K, BR, packed) * ceil_div(j.N, 128) * p.splits;
+      return (double)(ceil_div(items, (int64_t)256) * (p.stages_per_split + 16)) * (packed ? 1.13 : 1.0);
+    };
+    if (cost(true) < cost(false)) return kPacked;
+  }
+  return kPlain;
+}
+
 // Kernel parameters of one product; *wgs = workgroups of its launch, *splits as planned.
 template <int E, int BR, int BC, int MS>
-int fill_params(const DwJob &j, DwParams *prm, uint32_t *wgs, int companions = 1) {
-  const Plan p = make_plan_batched<E, BR, MS>(j.M, j.K, j.N, companions);
+int fill_params(const DwJob &j, Form form, DwParams *prm, uint32_t *wgs, int companions = 1) {
+  const Plan p = make_plan_batched<E, BR, MS>(j.M, j.K, j.N, companions, form == kPacked);
   const size_t need = p.splits > 1 ? (size_t)p.splits * j.K * j.N * sizeof(float) : 0;
   if (need > 0 && (j.ws == nullptr || j.ws_bytes < need)) return BSR_ERR_WORKSPACE;
   const int64_t nbr = ceil_div(j.M, BR), nbc = ceil_div(j.K, BC);
@@ -762,7 +798,7 @@ int fill_params(const DwJob &j, DwParams *prm, uint32_t *wgs, int companions = 1
   prm->split_stride = p.splits > 1 ? j.K * j.N : 0;
   prm->nbr = nbr; prm->nbc = nbc; prm->stages_per_split = p.stages_per_split;
   prm->accumulate = p.splits > 1 ? 0 : j.accumulate;
-  prm->tiles_k = (int)dw_tiles_k(j.K, BC); prm->tiles_n = (int)ceil_div(j.N, 128); prm->splits = p.splits;
+  prm->tiles_k = (int)dw_tiles_k(j.K, BC, form == kPacked); prm->tiles_n = (int)ceil_div(j.N, 128); prm->splits = p.splits;
   prm->wg_begin = 0;
   const int64_t n_items = (int64_t)p.splits * prm->tiles_k * prm->tiles_n;
   *wgs = (uint32_t)(8 * ceil_div(n_items, 8));        // XCD-aware work item order: whole groups of 8
@@ -777,24 +813,28 @@ int run(const int32_t *row_ptr, const int32_t *col_idx, const void *values, int6
   const DwJob job{row_ptr, col_idx, values, M, K, BR, BC, dY, N, lddy, dW, lddw, accumulate, ws, ws_bytes};
   DwParams prm;
   uint32_t wgs;
-  int rc = fill_params<E, BR, BC, MS>(job, &prm, &wgs);
+  const Form form = form_of<E, BR, MS>(job, 1);
+  int rc = fill_params<E, BR, BC, MS>(job, form, &prm, &wgs);
   if (rc != BSR_OK) return rc;
   const dim3 grid(wgs);
   const int xcd_map = 1;      // XCD-aware work item order (0 = plain order, kept for measurements)
-  if (dy_odd<E>(dY, N, lddy)) {
+  if (form == kOdd) {
     if constexpr (E == 2)
-      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, true, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
+      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kOdd, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
+  } else if (form == kPacked) {
+    if constexpr (E == 4 && BC == 14)
+      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kPacked, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
   } else {
-    hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, false, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
+    hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kPlain, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
   }
   rc = check_launch();
   if (rc != BSR_OK || prm.splits == 1) return rc;
   return launch_splitk_reduce(prm.out, prm.splits, K, N, dW, lddw, accumulate, s);
 }
 
-// The jobs of one kernel instance (block shape, dY rows from or to odd elements or not), kDwBatchMax per launch.
+// The jobs of one kernel instance (block shape and form), kDwBatchMax per launch.
 template <typename T, int BR, int BC, int MS, int D, int WN>
-int run_batched(const DwJob *jobs, int n, bool odd, hipStream_t s) {
+int run_batched(const DwJob *jobs, int n, Form form, hipStream_t s) {
   constexpr int E = (int)sizeof(T);
   DwBatch b;
   ReduceJob red[kDwBatchMax];
@@ -827,10 +867,13 @@ int run_batched(const DwJob *jobs, int n, bool odd, hipStream_t s) {
     for (int q = 0; q < 8; ++q)
       if (b.xcd_begin[q + 1] - b.xcd_begin[q] > longest) longest = b.xcd_begin[q + 1] - b.xcd_begin[q];
     const dim3 grid(8 * longest), block(256 * WN);
-    if (odd) {
-      if constexpr (E == 2) hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, true, D, WN>), grid, block, 0, s, b, m);
+    if (form == kOdd) {
+      if constexpr (E == 2) hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, kOdd, D, WN>), grid, block, 0, s, b, m);
+    } else if (form == kPacked) {
+      if constexpr (E == 4 && BC == 14)
+        hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, kPacked, D, WN>), grid, block, 0, s, b, m);
     } else {
-      hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, false, D, WN>), grid, block, 0, s, b, m);
+      hipLaunchKernelGGL((dw_mfma_batched_kernel<T, BR, BC, MS, kPlain, D, WN>), grid, block, 0, s, b, m);
     }
     int rc = check_launch();
     if (rc == BSR_OK && nred > 0) rc = launch_splitk_reduce_batched(red, nred, s);
@@ -839,18 +882,21 @@ int run_batched(const DwJob *jobs, int n, bool odd, hipStream_t s) {
     total = 0;
     return rc;
   };
-  int mine = 0;                                              // products of this kernel instance
+  int same_shape = 0, mine = 0;                              // products of this block shape, of this kernel instance
   for (int i = 0; i < n; ++i)
-    if (jobs[i].br == BR && jobs[i].bc == BC && dy_odd<E>(jobs[i].dY, jobs[i].N, jobs[i].lddy) == odd) ++mine;
+    if (jobs[i].br == BR && jobs[i].bc == BC) ++same_shape;
+  if (same_shape > kDwBatchMax) same_shape = kDwBatchMax;
+  for (int i = 0; i < n; ++i)
+    if (jobs[i].br == BR && jobs[i].bc == BC && form_of<E, BR, MS>(jobs[i], same_shape) == form) ++mine;
   int left = mine;
   for (int i = 0; i < n; ++i) {
     const DwJob &j = jobs[i];
-    if (j.br != BR || j.bc != BC || dy_odd<E>(j.dY, j.N, j.lddy) != odd) continue;
+    if (j.br != BR || j.bc != BC || form_of<E, BR, MS>(j, same_shape) != form) continue;
     uint32_t wgs;
     // products that share this launch: the rest of the list, up to the launch's capacity
     const int companions = m + (left < kDwBatchMax - m ? left : kDwBatchMax - m);
     --left;
-    int rc = fill_params<E, BR, BC, MS>(j, &b.it[m], &wgs, companions);
+    int rc = fill_params<E, BR, BC, MS>(j, form, &b.it[m], &wgs, companions);
     if (rc != BSR_OK) return rc;
     b.it[m].wg_begin = total;                                // first item of this product in the launch's list
     total += (uint32_t)(b.it[m].splits * b.it[m].tiles_k * b.it[m].tiles_n);
@@ -867,8 +913,12 @@ int run_batched(const DwJob *jobs, int n, bool odd, hipStream_t s) {
 
 template <int E, int BR, int MS>
 size_t ws_for(int64_t M, int64_t K, int64_t N) {
-  const Plan p = make_plan<E, BR, MS>(M, K, N);
-  return p.splits > 1 ? (size_t)p.splits * K * N * sizeof(float) : 0;
+  int splits = make_plan<E, BR, MS>(M, K, N, false).splits;
+  if constexpr (E == 4 && BR == 14) {                        // (of the form that splits more: form_of)
+    const int packed = make_plan<E, BR, MS>(M, K, N, true).splits;
+    if (packed > splits) splits = packed;
+  }
+  return splits > 1 ? (size_t)splits * K * N * sizeof(float) : 0;
 }
 
 }  // namespace
@@ -924,20 +974,20 @@ int launch_dw_mfma(int dtype, const int32_t *row_ptr, const int32_t *col_idx, co
 }
 
 int launch_dw_mfma_batched(int dtype, const DwJob *jobs, int n, hipStream_t s) {
-  for (const bool odd : {false, true}) {
-    int rc;
-    if (dtype == BSR_F32) {
-      if (odd) continue;
-      if ((rc = run_batched<float, 32, 32, 64, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<float, 64, 64, 64, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<float, 16, 16, 32, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<float, 14, 14, 32, 2, 4>(jobs, n, odd, s)) != BSR_OK) return rc;
-    } else {
-      if ((rc = run_batched<uint16_t, 32, 32, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 64, 64, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 16, 16, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
-      if ((rc = run_batched<uint16_t, 14, 14, 64, 2, 2>(jobs, n, odd, s)) != BSR_OK) return rc;
-    }
+  int rc;
+  if (dtype == BSR_F32) {
+    if ((rc = run_batched<float, 32, 32, 64, 2, 4>(jobs, n, kPlain, s)) != BSR_OK) return rc;
+    if ((rc = run_batched<float, 64, 64, 64, 2, 4>(jobs, n, kPlain, s)) != BSR_OK) return rc;
+    if ((rc = run_batched<float, 16, 16, 32, 2, 4>(jobs, n, kPlain, s)) != BSR_OK) return rc;
+    for (const Form form : {kPlain, kPacked})
+      if ((rc = run_batched<float, 14, 14, 32, 2, 4>(jobs, n, form, s)) != BSR_OK) return rc;
+    return BSR_OK;
+  }
+  for (const Form form : {kPlain, kOdd}) {
+    if ((rc = run_batched<uint16_t, 32, 32, 64, 2, 2>(jobs, n, form, s)) != BSR_OK) return rc;
+    if ((rc = run_batched<uint16_t, 64, 64, 64, 2, 2>(jobs, n, form, s)) != BSR_OK) return rc;
+    if ((rc = run_batched<uint16_t, 16, 16, 64, 2, 2>(jobs, n, form, s)) != BSR_OK) return rc;
+    if ((rc = run_batched<uint16_t, 14, 14, 64, 2, 2>(jobs, n, form, s)) != BSR_OK) return rc;
   }
   return BSR_OK;
 }

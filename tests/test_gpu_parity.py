@@ -1187,6 +1187,36 @@ def test_dw_rows_of_dy_at_any_alignment(M, K, N, pad, shift, b, dtype):
         assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
 
 
+@pytest.mark.parametrize("M,K,N", [
+    (6000, 128, 700),            # one tile of 128 columns instead of two of eight slots
+    (3001, 512, 800),            # four instead of five; tiles begin inside a block-column, an odd number of block-rows
+    (3000, 1010, 400),           # eight instead of ten, the last one ragged
+    (15, 256, 5),                # two block-rows, slots
+])
+def test_dw_of_14x14_binary32_blocks_without_slots(M, K, N):
+    """Sizes whose plan has no slots, alone and in a call of three: blocks that lie in two tiles, the entries of a
+    block-row in order and shuffled; NaN around values and dY."""
+    rng = np.random.default_rng(M)
+    X, dY = rand_pair(M, K, N, "f32", seed=M + K)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, 14, 14, 0.6)
+    ref = oracle.dw(oracle.mask_dense(X, 14, 14, o_mask), dY)
+    dYd = torch.full((M + 2, N + 3), float("nan"), device="cuda")[1:M + 1, 1:N + 1]
+    dYd.copy_(to_dev(dY))
+    vals = torch.full((o_val.size + 64,), float("nan"), device="cuda")
+    rp = torch.from_numpy(o_rp).cuda()
+    order = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(o_rp[:-1], o_rp[1:])]).astype(np.int64)
+    got = []
+    for pick in (np.arange(len(o_ci)), order):
+        val = vals[:o_val.size].view(o_val.shape)
+        val.copy_(to_dev(np.ascontiguousarray(o_val[pick])))
+        ci = torch.from_numpy(np.ascontiguousarray(o_ci[pick])).cuda()
+        got += [B.bsr_t_dense_matmul(rp, ci, val, M, K, 14, 14, dYd),
+                *B.bsr_t_dense_matmul_batched(B.MatmulBatch([(rp, ci, val, M, K, 14, 14, dYd)] * 3))]
+    torch.cuda.synchronize()
+    for dW in got:
+        assert dw_error(dW.cpu().numpy(), ref) <= DW_TOL["f32"]
+
+
 @pytest.mark.parametrize("N,pad", [(131, 1), (77, 1), (130, 2)])
 @pytest.mark.parametrize("br,bc", [(1, 32), (8, 16)])
 def test_dw_of_re_tiled_blocks_with_padded_rows_of_dy(br, bc, N, pad):
