@@ -201,8 +201,9 @@ struct CompressArgs {
 };
 
 // How many workgroups share a block-row in a launch over `wgs` block-rows; nbc = block-columns, `copied` = bytes of
-// kept blocks per block-row.  Up to 256 block-rows leave compute units idle: up to four share one (1568 x 3072
-// binary32, 49 block-rows: 13.0 us alone, 6.5 shared by four).  Beyond that, sharing evens out block-rows that differ in
+// kept blocks per block-row.  Up to 256 block-rows leave compute units idle: up to four share one if each copies 3 KB
+// (1568 x 3072 binary32 in 32x32 blocks, 49 block-rows: 13.0 us alone, 6.5 shared by four; 1568 x 384 bf16 in 8x8 blocks,
+// 3 KB per block-row: 4.9 and 5.3).  Beyond that, sharing evens out block-rows that differ in
 // kept blocks, but every sharer lists the block-row and counts the mask in front of it again: up to three share, each
 // copies 8 KB at least, and the more block-rows there are the larger the blocks must be.  Score, select and convert
 // one after the other, bf16, alone and shared: [12544 x 1536] in 32x32 blocks, 392 block-rows, 40.7 and 35.5 us;
@@ -213,6 +214,7 @@ inline uint32_t row_parts(int64_t wgs, int64_t nbc, int64_t copied) {
   int64_t p = wgs > 0 ? 2048 / wgs : 1;
   if (p > 4) p = 4;
   if (p > nbc) p = nbc;
+  if (p > copied / 3072) p = copied / 3072;
   if (wgs > 256) {
     if (p > 3) p = 3;
     if (p > copied / 8192) p = copied / 8192;
@@ -906,11 +908,15 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
   // ([9947 x 411] bf16, 32x32 blocks: 22 us element by element, 7 us so).
   if (p.vb < 16 && (int64_t)j.bc * e % 16 == 0 && (uintptr_t)j.values % 16 == 0) p.vb = kLoose;
   // Every workgroup counts the mask in front of its row, wgs * nblocks / 2 bytes out of L2 in all, unless a
-  // launch writes row_ptr first (6 to 8 us): from 256 MB on that is the faster way (mask of 3136 x 96
-  // blocks, 472 MB: 48 us -> 8 + 30 us; 3136 x 48, 236 MB: 70 us either way; 1568 x 48, 59 MB: 35 -> 39 us).
-  const uint32_t parts = row_parts(row_wgs, nbc, j.n_keep * j.br * j.bc * e / nbr);
+  // launch writes row_ptr first (6 to 8 us).  That is the faster way from 256 MB on (mask of 3136 x 96 blocks, 472 MB:
+  // 48 us -> 8 + 30 us; 3136 x 48, 236 MB: 70 us either way; 1568 x 48, 59 MB: 35 -> 39 us), if the count is not hidden
+  // behind the copies: 472 MB for 1568 x 384 blocks of 8x8 take 38 -> 32 us where 39 MB are copied (bf16), 46 -> 48 us
+  // where it is 77 MB (binary32).
+  const int64_t copied = j.n_keep * j.br * j.bc * e;
+  const uint32_t parts = row_parts(row_wgs, nbc, copied / nbr);
   p.wgs = (unsigned)nbr * parts;
-  p.rows_first = (int64_t)p.wgs * nbr * nbc / 2 > (int64_t(256) << 20);
+  const int64_t counted = (int64_t)p.wgs * nbr * nbc / 2;
+  p.rows_first = counted > (int64_t(256) << 20) && counted > 8 * copied;
   p.direct = CompressArgs{j.keep_mask, static_cast<const uint8_t *>(j.X), j.row_ptr, j.col_idx,
                           static_cast<uint8_t *>(j.values), j.M, j.K * e, j.ldx * e, (int64_t)j.bc * e, nbr, nbc,
                           j.n_keep, j.br, 0u, 0, parts};
