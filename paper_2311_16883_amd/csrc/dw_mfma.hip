@@ -49,6 +49,7 @@ typedef __attribute__((ext_vector_type(16))) float v16f;
 struct __attribute__((packed, aligned(2))) LooseVec {
   u32x4 v;
 };
+static_assert(alignof(LooseVec) == 2, "no more than the addresses keep");
 
 // Block-rows of one split, at most: its block table must fit in LDS.  (Stages of 64 rows for 14x14 and 16x16
 // blocks: half the barriers of stages of 32, cross-patch 19.7 -> 17.6 us, and with tables of 256 block-rows two

@@ -113,10 +113,16 @@ template <> __device__ __forceinline__ uint32_t zero_bytes<4>() { return 0; }
 template <> __device__ __forceinline__ uint2 zero_bytes<8>() { return make_uint2(0, 0); }
 template <> __device__ __forceinline__ uint4 zero_bytes<16>() { return make_uint4(0, 0, 0, 0); }
 
-// 16 bytes from any 2-byte boundary (global loads need no more on this GPU).
+// 16 bytes from any 2-byte boundary, 16 mask bytes from any address (global loads need no more on this GPU).  Made of
+// a plain vector type: HIP's uint4 is a class, which a packed struct leaves at its own alignment of 16.
+typedef __attribute__((ext_vector_type(4))) uint32_t PlainVec;
 struct __attribute__((packed, aligned(2))) LooseVec {
-  uint4 v;
+  PlainVec v;
 };
+struct __attribute__((packed, aligned(1))) LooseBytes {
+  PlainVec v;
+};
+static_assert(alignof(LooseVec) == 2 && alignof(LooseBytes) == 1, "no more than the addresses keep");
 // VB of the kernels that move 16-byte vectors whose dense side starts at any element (rows of an odd
 // width, an unaligned view); a vector that crosses the matrix edge goes element by element.
 constexpr int kLoose = 1;
@@ -284,7 +290,8 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint3
     if constexpr (VB == kLoose) {
       if (r < rows_left) {
         if (cb + kBytes <= kb) {
-          val = reinterpret_cast<const LooseVec *>(src)->v;
+          const PlainVec p = reinterpret_cast<const LooseVec *>(src)->v;
+          val = make_uint4(p.x, p.y, p.z, p.w);
         } else {
           uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -509,7 +516,7 @@ __global__ __launch_bounds__(kRowPtrThreads) void row_ptr_kernel(RowPtrBatch<N> 
   const uint32_t first = e0 + (uint32_t)t * kRowPtrPer;
   uint32_t w[4] = {0, 0, 0, 0};                             // this thread's 16 mask bytes
   if (first + kRowPtrPer <= nblocks) {
-    const uint4 v = reinterpret_cast<const LooseVec *>(mask + first)->v;
+    const PlainVec v = reinterpret_cast<const LooseBytes *>(mask + first)->v;
     w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
   } else {
 #pragma unroll
@@ -520,7 +527,7 @@ __global__ __launch_bounds__(kRowPtrThreads) void row_ptr_kernel(RowPtrBatch<N> 
   const uint8_t *mine = mask + (uint32_t)t * kRowPtrPer;
 #pragma unroll 8
   for (uint32_t r = 0; r < blockIdx.x; ++r) {
-    const uint4 x = reinterpret_cast<const LooseVec *>(mine + r * (uint32_t)kRowPtrSlice)->v;
+    const PlainVec x = reinterpret_cast<const LooseBytes *>(mine + r * (uint32_t)kRowPtrSlice)->v;
     before += nonzero_bytes(x.x) + nonzero_bytes(x.y) + nonzero_bytes(x.z) + nonzero_bytes(x.w);
   }
 #pragma unroll

@@ -1138,6 +1138,24 @@ def test_conversion_of_unaligned_rows_and_long_masks(M, K, br, bc, dtype, pad, s
         assert to_host(val).tobytes() == o_val.tobytes()
 
 
+@pytest.mark.parametrize("M,K,b", [(137216, 128, 16), (3000, 200, 32), (500, 70, 14)])
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_conversion_with_a_mask_at_any_address(M, K, b, shift):
+    """A mask is bytes: nothing may rest on its address, neither in the launch that writes row_ptr (many tensors; a long
+    mask) nor in the conversions that count the mask themselves."""
+    X = rand_pair(M, K, 1, "bf16", seed=M)[0]
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, b, b, 0.4)
+    mask = torch.ones(o_mask.size + shift + 16, dtype=torch.uint8, device="cuda")[shift:shift + o_mask.size]
+    mask.copy_(torch.from_numpy(o_mask))
+    Xd = to_dev(X)
+    outs = [B.bsr_compress(Xd, b, b, mask, len(o_ci))]
+    outs += B.bsr_compress_batched(B.CompressBatch([(Xd, b, b, mask, len(o_ci))] * 2))
+    torch.cuda.synchronize()
+    for rp, ci, val in outs:
+        assert np.array_equal(rp.cpu().numpy(), o_rp) and np.array_equal(ci.cpu().numpy(), o_ci)
+        assert to_host(val).tobytes() == o_val.tobytes()
+
+
 @pytest.mark.parametrize("M,K,dtype", [
     (2048, 300, "bf16"),          # 64 block-rows: four workgroups share each
     (9593, 1536, "bf16"),         # 300: three
