@@ -50,7 +50,7 @@ int extent(PyObject *o) {
   return v > INT_MAX ? INT_MAX : v < 0 ? -1 : (int)v;
 }
 
-// int(o), as the Python forms of the calls apply it to counts
+// int(o)
 int64_t converted_integer(PyObject *o) {
   if (PyLong_Check(o)) return integer(o);
   PyObject *n = PyNumber_Long(o);
@@ -61,9 +61,13 @@ int64_t converted_integer(PyObject *o) {
   return v;
 }
 
+// float(o)
 double real(PyObject *o) {
-  const double v = PyFloat_AsDouble(o);
-  if (v == -1.0 && PyErr_Occurred()) throw PythonError();
+  if (PyFloat_Check(o)) return PyFloat_AS_DOUBLE(o);
+  PyObject *f = PyNumber_Float(o);
+  if (f == nullptr) throw PythonError();
+  const double v = PyFloat_AS_DOUBLE(f);
+  Py_DECREF(f);
   return v;
 }
 
@@ -224,7 +228,9 @@ PyObject *compress(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::Tensor &X = tensor(a[0], "X");
     const Dense x = dense2d(X, "X");
     const int br = extent(a[1]), bc = extent(a[2]);
-    const int64_t n_keep = converted_integer(a[4]), places = n_keep > 0 ? n_keep : 0;
+    // (a count that sizes an output has to be a whole number; one that does not is converted as by int())
+    const int64_t n_keep = a[6] == Py_None || a[7] == Py_None ? integer(a[4]) : converted_integer(a[4]);
+    const int64_t places = n_keep > 0 ? n_keep : 0;
     const Output row_ptr = output(a[5], "row_ptr", {blocks(x.rows, br) + 1}, at::kInt, X);
     const Output col_idx = output(a[6], "col_idx", {places}, at::kInt, X);
     const Output values = output(a[7], "values", {places, br, bc}, X.scalar_type(), X);

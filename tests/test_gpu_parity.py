@@ -1138,6 +1138,26 @@ def test_conversion_of_unaligned_rows_and_long_masks(M, K, br, bc, dtype, pad, s
         assert to_host(val).tobytes() == o_val.tobytes()
 
 
+def test_numbers_that_the_calls_accept_and_refuse():
+    """keep is whatever float() takes.  A count that sizes an output is a whole number of any integer type; where all
+    outputs are given it is what int() makes of it."""
+    X = torch.randn(64, 64, device="cuda")
+    mask = B.bsr_score_select(X, 16, 16, 0.5)
+    for keep in ("0.5", np.float32(0.5), torch.tensor(0.5)):
+        assert torch.equal(B.bsr_score_select(X, 16, 16, keep), mask)
+    with pytest.raises(ValueError):
+        B.bsr_score_select(X, 16, 16, "half")
+    rp, ci, val = B.bsr_compress(X, 16, 16, mask, 8)
+    for n in (np.int64(8), torch.tensor(8)):
+        assert torch.equal(B.bsr_compress(X, 16, 16, mask, n)[1], ci)
+    for given in ({}, {"col_idx": ci}, {"values": val}):
+        with pytest.raises(TypeError):
+            B.bsr_compress(X, 16, 16, mask, 8.5, **given)
+    out = B.bsr_compress(X, 16, 16, mask, 8.5, row_ptr=rp, col_idx=ci.clone(), values=val.clone())
+    torch.cuda.synchronize()
+    assert torch.equal(out[1], ci) and torch.equal(out[2], val)
+
+
 @pytest.mark.parametrize("M,K,b", [(137216, 128, 16), (3000, 200, 32), (500, 70, 14)])
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_conversion_with_a_mask_at_any_address(M, K, b, shift):
