@@ -161,13 +161,15 @@ int64_t blocks(int64_t n, int64_t b) { return b > 0 ? (n + b - 1) / b : 0; }
 
 PyObject *code_result(int rc) { return PyLong_FromLong(rc); }
 
-// Runs f, which calls the C library, without the GIL.
+// Runs f, which calls the C library, without the GIL; it is held again however f ends.
+struct GilReleased {
+  PyThreadState *const save = PyEval_SaveThread();
+  ~GilReleased() { PyEval_RestoreThread(save); }
+};
 template <typename F>
 int released(F f) {
-  PyThreadState *save = PyEval_SaveThread();
-  const int rc = f();
-  PyEval_RestoreThread(save);
-  return rc;
+  const GilReleased guard;
+  return f();
 }
 
 bool arity(Py_ssize_t n, Py_ssize_t want) {
