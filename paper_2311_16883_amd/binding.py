@@ -12,6 +12,7 @@ loaded the call fails loudly -- there is no fallback.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 from pathlib import Path
 from typing import Sequence, Optional, Tuple
 
@@ -27,7 +28,6 @@ BSR_ERR_WORKSPACE, BSR_ERR_ALIGN, BSR_ERR_HIP, BSR_ERR_LIMIT = -5, -6, -7, -8
 
 _PKG = Path(__file__).resolve().parent
 LIB_PATH = _PKG / "libbsr_actprune.so"
-CALLS_PATH = _PKG / "_torch_calls.so"
 
 EXPORTS = (
     "bsr_version", "bsr_error_string", "bsr_last_hip_error", "bsr_keep_count",
@@ -123,11 +123,14 @@ def _load_native():
     global _native
     if _native is None:
         lib()
-        if not CALLS_PATH.exists():
-            from . import build as _build
+        from . import build as _build
+        path = _build.calls_path()
+        if not path.exists():
             _build.build_calls()
-        from . import _torch_calls
-        _native = _torch_calls
+        spec = importlib.util.spec_from_file_location(f"{__package__}._torch_calls", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _native = module
     return _native
 
 

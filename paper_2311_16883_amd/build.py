@@ -3,12 +3,13 @@
 ``python -m paper_2311_16883_amd.build`` compiles every ``csrc/*.hip`` file for
 gfx950 and links them into ``paper_2311_16883_amd/libbsr_actprune.so`` (hipcc
 cross-compiles without a GPU), then compiles ``csrc/torch_calls.cpp`` into
-``paper_2311_16883_amd/_torch_calls.so``, which calls that library with torch
-tensors as arguments.
+``paper_2311_16883_amd/_torch_calls_<torch version>.<ABI tag>.so`` (see
+``calls_path``), which calls that library with torch tensors as arguments.
 """
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -21,7 +22,6 @@ ROOT = PKG.parent
 CSRC = PKG / "csrc"
 OBJ = PKG / "_build"
 LIB = PKG / "libbsr_actprune.so"
-CALLS = PKG / "_torch_calls.so"
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 ROCM_INCLUDE = Path(HIPCC).resolve().parent.parent / "include"
@@ -35,6 +35,12 @@ FLAGS = [
 ]
 
 
+
+def calls_path() -> Path:
+    """The extension module.  It fits one interpreter ABI and one build of torch, and its name says which: a module
+    left by another of either is not found and a new one is built, where loading it could crash."""
+    import torch
+    return PKG / f"_torch_calls_{re.sub('[^0-9A-Za-z]+', '_', torch.__version__)}{sysconfig.get_config_var('EXT_SUFFIX')}"
 
 
 def sources():
@@ -80,20 +86,21 @@ def build_calls(verbose: bool = False) -> Path:
     """The extension module: host code only, needs the library to link against."""
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
-    tmp = CALLS.with_suffix(f".{os.getpid()}.tmp")
+    path = calls_path()
+    tmp = path.with_suffix(f".{os.getpid()}.tmp")
     rocm = ROCM_INCLUDE if ROCM_INCLUDE.exists() else Path("/opt/rocm/include")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+    cmd = [HIPCC, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{ROOT / 'include'}",
            *(f"-isystem{p}" for p in [*include_paths(), sysconfig.get_paths()["include"], str(rocm)]),
-           str(CSRC / "torch_calls.cpp"), "-o", str(tmp), f"-L{PKG}", "-lbsr_actprune", "-Wl,-rpath,$ORIGIN",
+           str(CSRC / "torch_calls.cpp"), "-x", "none", "-o", str(tmp), f"-L{PKG}", "-lbsr_actprune", "-Wl,-rpath,$ORIGIN",
            *(f"-L{p}" for p in library_paths()), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"g++ failed on torch_calls.cpp:\n{r.stderr}")
-    os.replace(tmp, CALLS)
-    return CALLS
+        raise RuntimeError(f"hipcc failed on torch_calls.cpp:\n{r.stderr}")
+    os.replace(tmp, path)
+    return path
 
 
 if __name__ == "__main__":

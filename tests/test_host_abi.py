@@ -312,3 +312,14 @@ def test_native_calls_refuse_what_is_no_device_matrix(call):
         call(torch.zeros(4, 4))
     with pytest.raises(TypeError, match="must be a tensor"):
         call([[0.0]])
+
+
+def test_native_module_is_the_one_of_this_interpreter_and_torch(monkeypatch):
+    """Its file carries both in its name, so that one left by another build is not taken for it."""
+    import sysconfig
+    import torch
+    from paper_2311_16883_amd import build
+    path = Path(B._load_native().__file__)
+    assert path == build.calls_path() and path.name.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(torch, "__version__", "0.1+other")
+    assert build.calls_path() != path
