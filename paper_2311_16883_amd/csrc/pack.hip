@@ -209,27 +209,27 @@ struct CompressArgs {
 // How many workgroups share a block-row in a launch over `wgs` block-rows; nbc = block-columns, `copied` = bytes of
 // kept blocks per block-row.  Up to 256 block-rows leave compute units idle: up to four share one if each copies 3 KB
 // (1568 x 3072 binary32 in 32x32 blocks, 49 block-rows: 13.0 us alone, 6.5 shared by four; 1568 x 384 bf16 in 8x8 blocks,
-// 3 KB per block-row: 4.9 and 5.3).  Beyond that, sharing evens out block-rows that differ in
-// kept blocks, but every sharer lists the block-row and counts the mask in front of it again: up to three share, each
-// copies 8 KB at least, and the more block-rows there are the larger the blocks must be.  Score, select and convert
-// one after the other, bf16, alone and shared: [12544 x 1536] in 32x32 blocks, 392 block-rows, 40.7 and 35.5 us;
-// [25088 x 1536] in 64x64 blocks 54.5 and 43.3; [25088 x 384] in 32x32 blocks, 784 block-rows of 12 KB, 21.3 and 22.6;
-// [6272 x 1536] in 16x16 blocks 30.8 and 31.8.  The conversion repeated on the same X: 10.6 and 11.7; 19.0 and 15.4; 5.9
-// and 7.1; 6.7 and 9.5; [25088 x 1536] in 32x32 blocks 18.9 and 21.7, with the rest 54.5 and 53.4.
+// 3 KB per block-row: 4.9 and 5.3).  Beyond that, sharing evens out block-rows that differ in kept blocks, but every
+// sharer lists the block-row and counts the mask in front of it again: up to three share, and each has to copy the
+// more the more block-rows and the more mask there is.  Score, select and convert one after the other, bf16, alone and
+// shared: [12544 x 1536] in 32x32 blocks, 392 block-rows, 40.7 and 35.5 us; [25088 x 1536] in 64x64 blocks 54.5 and 43.3;
+// [9947 x 411] in 32x32 blocks, 311 block-rows of 13 KB, 19.4 and 18.9; [25088 x 384], 784 block-rows of 12 KB, 21.3 and
+// 22.6; [6272 x 1536] in 16x16 blocks 30.8 and 31.8.  The conversion repeated on the same X: 10.6 and 11.7; 19.0 and 15.4;
+// 5.1 and 5.1; 5.9 and 7.1; 6.7 and 9.5; [25088 x 1536] in 32x32 blocks 18.9 and 21.7, with the rest 54.5 and 53.4.
 inline uint32_t row_parts(int64_t wgs, int64_t nbc, int64_t copied) {
   int64_t p = wgs > 0 ? 2048 / wgs : 1;
   if (p > 4) p = 4;
   if (p > nbc) p = nbc;
   if (p > copied / 3072) p = copied / 3072;
   if (wgs > 256) {
+    const int64_t each = wgs * (nbc > 20 ? 3 * nbc : 60) / 4;   // bytes
     if (p > 3) p = 3;
-    if (p > copied / 8192) p = copied / 8192;
-    if (p > 4 * copied / (3 * nbc * wgs)) p = 4 * copied / (3 * nbc * wgs);
+    if (p > copied / each) p = copied / each;
   }
   return (uint32_t)(p < 1 ? 1 : p);
 }
 
-// i = block-row, part = which of the workgroups that share it
+// wg = the workgroup's number among those of its tensor: its block-row i and which of the sharers it is
 template <int VB>
 __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint32_t wg) {
   const int64_t i = wg / a.parts;

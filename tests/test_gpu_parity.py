@@ -1180,7 +1180,8 @@ def test_conversion_with_a_mask_at_any_address(M, K, b, shift):
     (2048, 300, "bf16"),          # 64 block-rows: four workgroups share each
     (9593, 1536, "bf16"),         # 300: three
     (22400, 768, "f32"),          # 700: two
-    (9600, 384, "bf16"),          # 300 of few bytes: none
+    (9600, 384, "bf16"),          # 300 of 12 KB: two
+    (22400, 384, "bf16"),         # 700 of 12 KB: none
 ])
 def test_conversion_with_shared_block_rows(M, K, dtype):
     """How many workgroups share a block-row depends on their number and on what there is to copy."""
