@@ -698,8 +698,10 @@ Plan make_plan(int64_t M, int64_t K, int64_t N, bool packed) {
   // few stages it is not worth it.)
   const double us_stage = (E == 4 ? (N > 64 ? 3.0 : 2.0) : 0.70) * (packed ? 1.13 : 1.0) * MS / 64.0, us_round = 8.0, us_reduce = 4.5;
   const double us_split = 2.0 * (double)K * (double)N * 4.0 / 3.0e6;
-  // (at least one split per 256 block-rows, although the table would hold 512: for 16-row blocks at
-  // 50176 rows 14 splits of 112 stages take 106 us where 7 of 224 take 156 us)
+  // (at least one split per 256 block-rows.  That is what the table of bfloat16 14x14 and 16x16 blocks holds; the others
+  // hold 512, but 16-row blocks in stages of 32 rows took 156 us at 50176 rows in 7 splits of 448 block-rows and 106
+  // in 14 of 224)
+  static_assert(max_rows_per_split(BR, MS) >= 256, "a split of the plan fits the table");
   const int64_t s_min = ceil_div(stages, (int64_t)(256 / R));
   int64_t s_max = stages < 64 ? stages : 64;
   if (s_max < s_min) s_max = s_min;
@@ -791,6 +793,8 @@ int fill_params(const DwJob &j, Form form, DwParams *prm, uint32_t *wgs, int com
   const Plan p = make_plan_batched<E, BR, MS>(j.M, j.K, j.N, companions, form == kPacked);
   const size_t need = p.splits > 1 ? (size_t)p.splits * j.K * j.N * sizeof(float) : 0;
   if (need > 0 && (j.ws == nullptr || j.ws_bytes < need)) return BSR_ERR_WORKSPACE;
+  // (the kernel's tables in LDS are sized for no more)
+  if (p.stages_per_split * (MS / BR) > max_rows_per_split(BR, MS)) return BSR_ERR_SHAPE;
   const int64_t nbr = ceil_div(j.M, BR), nbc = ceil_div(j.K, BC);
   prm->row_ptr = j.row_ptr; prm->col_idx = j.col_idx; prm->values = j.values; prm->dY = j.dY;
   prm->out = p.splits > 1 ? static_cast<float *>(j.ws) : j.dW;
