@@ -167,9 +167,10 @@ struct DwParams {
   uint32_t wg_begin;       // first work item of this tensor in a batched launch's list
 };
 
-// wg = number of the workgroup among those of this tensor.
+// wg = number of the workgroup among those of this tensor; by_xcd: every XCD takes a range of consecutive work items
+// (a batched launch has cut its list that way already).
 template <typename T, int BR, int BC, int MS, Form FORM, int D, int WN>
-__device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t wg, const int xcd_map) {
+__device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t wg, const bool by_xcd) {
   const int32_t *__restrict__ row_ptr = prm.row_ptr;
   const int32_t *__restrict__ col_idx = prm.col_idx;
   const T *__restrict__ values = static_cast<const T *>(prm.values);
@@ -198,7 +199,7 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
   const int tiles = tiles_k * tiles_n;
   const int items = tiles * splits;
   int item;
-  if (xcd_map) {
+  if (by_xcd) {
     const int per_xcd = (items + 7) / 8;
     item = (wg & 7) * per_xcd + (wg >> 3);
     if ((int)(wg >> 3) >= per_xcd) return;
@@ -633,8 +634,8 @@ template <typename T, int WN>
 constexpr int min_waves() { return sizeof(T) == 2 && WN == 4 ? 8 : 1; }
 
 template <typename T, int BR, int BC, int MS, Form FORM, int D, int WN>
-__global__ __launch_bounds__(256 * WN, (min_waves<T, WN>())) void dw_mfma_kernel(DwParams prm, int xcd_map) {
-  dw_mfma_body<T, BR, BC, MS, FORM, D, WN>(prm, blockIdx.x, xcd_map);
+__global__ __launch_bounds__(256 * WN, (min_waves<T, WN>())) void dw_mfma_kernel(DwParams prm) {
+  dw_mfma_body<T, BR, BC, MS, FORM, D, WN>(prm, blockIdx.x, true);
 }
 
 // Several tensors per launch.  The work items (split, tile) of all products form one list,
@@ -660,7 +661,7 @@ __global__ __launch_bounds__(256 * WN) void dw_mfma_batched_kernel(DwBatch b, in
   const uint32_t g = b.xcd_begin[x] + slot;
   int i = 0;
   while (i + 1 < n && g >= b.it[i + 1].wg_begin) ++i;
-  dw_mfma_body<T, BR, BC, MS, FORM, D, WN>(b.it[i], g - b.it[i].wg_begin, 0);
+  dw_mfma_body<T, BR, BC, MS, FORM, D, WN>(b.it[i], g - b.it[i].wg_begin, false);
 }
 
 struct Plan {
@@ -822,15 +823,14 @@ int run(const int32_t *row_ptr, const int32_t *col_idx, const void *values, int6
   int rc = fill_params<E, BR, BC, MS>(job, form, &prm, &wgs);
   if (rc != BSR_OK) return rc;
   const dim3 grid(wgs);
-  const int xcd_map = 1;      // XCD-aware work item order (0 = plain order, kept for measurements)
   if (form == kOdd) {
     if constexpr (E == 2)
-      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kOdd, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
+      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kOdd, D, WN>), grid, dim3(256 * WN), 0, s, prm);
   } else if (form == kPacked) {
     if constexpr (E == 4 && BC == 14)
-      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kPacked, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
+      hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kPacked, D, WN>), grid, dim3(256 * WN), 0, s, prm);
   } else {
-    hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kPlain, D, WN>), grid, dim3(256 * WN), 0, s, prm, xcd_map);
+    hipLaunchKernelGGL((dw_mfma_kernel<T, BR, BC, MS, kPlain, D, WN>), grid, dim3(256 * WN), 0, s, prm);
   }
   rc = check_launch();
   if (rc != BSR_OK || prm.splits == 1) return rc;
