@@ -629,7 +629,8 @@ __device__ __forceinline__ void dw_mfma_body(const DwParams &prm, const uint32_t
 }
 
 // Waves per SIMD to leave registers for: two workgroups of 1024 threads share a compute unit with bfloat16
-// inputs (64 registers; with 76 only one fits: 120 us instead of 83 for [50176 x 1536] in 16x16 blocks).
+// inputs (64 registers; with 76 only one fits: 120 us instead of 83 for [50176 x 1536 x 384] in 16x16 blocks, keep
+// 0.25, in stages of 32 rows; 72 in stages of 64).
 template <typename T, int WN>
 constexpr int min_waves() { return sizeof(T) == 2 && WN == 4 ? 8 : 1; }
 
@@ -737,7 +738,8 @@ bool dy_odd(const void *dY, int64_t N, int64_t lddy) {
 // duration is roughly (rounds of 512 items) x (stages of an item + a fixed part); the number
 // of splits is the one that makes this smallest, the partial tiles counted at what their
 // traffic costs, as if the companions were products of the same shape.  Never more splits
-// than on its own: the workspace is sized for that.
+// than on its own: the workspace is sized for that.  (binary32 workgroups have a compute unit each, 256 in a round;
+// planned for 512 all the same.)
 template <int E, int BR, int MS>
 Plan make_plan_batched(int64_t M, int64_t K, int64_t N, int companions, bool packed) {
   const Plan alone = make_plan<E, BR, MS>(M, K, N, packed);

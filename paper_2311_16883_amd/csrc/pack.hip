@@ -902,7 +902,7 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
                               static_cast<uint32_t *>(j.values), j.M, nbr, j.n_keep, g, (uint32_t)span_words, 0u, 0};
     return p;
   }
-  // one workgroup per block-row when its columns fit the LDS list
+  // one workgroup per block-row, or a few, when its columns fit the LDS list
   const bool fused = nbr > 0 && nbc > 0 && nbc <= kFusedCols && nbr <= 65535 &&
                      nbr * nbr * nbc <= (int64_t(1) << 31);
   if (!fused) {

@@ -480,7 +480,7 @@ __device__ __forceinline__ void bracketed_select(const uint64_t (&key)[KPT], con
 // two, exact ranking of what shares the threshold's code.  The last group may be
 // shorter (last_blocks, keeping n_keep_last).
 // One workgroup selects the `want` best of the n scores at `scores` into gmask.
-// (12288 scores take 8.0 us, 12.9 before keys were kept in registers and lane exchanges became DPP moves.)
+// (12288 scores take 7.5 us, 13 before keys were kept in registers and lane exchanges became DPP moves.)
 template <int THREADS, int KPT, int DB>
 __device__ __forceinline__ void select_one_group(const double *__restrict__ scores, uint32_t n, uint32_t want,
                                                  uint8_t *__restrict__ gmask, SelectShared &sh, BracketShared &bs) {
