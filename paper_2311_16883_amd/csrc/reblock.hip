@@ -10,138 +10,115 @@
 // matrix-core formulation does.  What the BSR form still saves is the memory the
 // activation occupies between forward and backward pass (paper Sec. III).
 //
-// reblock_kernel: a workgroup owns 32 matrix rows x a chunk of columns.  It zeroes
-// an LDS tile, copies every stored block that intersects the tile into it (the
-// entries of consecutive block-rows are consecutive in col_idx / values, so they
-// are one index range), and writes the tile out as 32x32 blocks with their
-// row_ptr / col_idx (all blocks present, columns ascending).
-#include <climits>
-
+// reblock_kernel: a workgroup owns 32 matrix rows x a chunk of columns.  A table in LDS says which stored block
+// holds each block position of that part of the matrix (the entries of a block-row may stand in any order); then every
+// thread puts together 16-byte vectors of the re-tiled operand, from loads of as many elements as block widths and
+// `values` allow, and stores them where they belong.  Bound by memory: the kept values are read once, the re-tiled
+// operand is written once, and nothing passes through LDS.  ([25088 x 384] bfloat16 in 1x32 blocks, keep 0.5: 11.0 us,
+// where staging the tile in LDS word by word took 14.8; [20322 x 2944] in 1x64 blocks, keep 0.25: 32 us, 134 where each
+// of six column chunks walked all entries element by element.)
 #include "common.h"
 
 namespace bsr {
 
 namespace {
 
-constexpr int kRbEntries = 2048;          // entries listed in LDS per round
-constexpr int kRbTileBytes = 32768;       // LDS tile: 32 rows x chunk
+constexpr int kRbTable = 4096;            // block positions in the table of a workgroup
+constexpr int kRbInFlight = 4;            // vectors a thread puts together at a time
+constexpr int kRbOnce = 4096;             // blocks longer than this: at most one boundary in 32 rows or in a chunk
 
-// WORDS: blocks of at most 32 rows whose rows are whole 32-bit words.  The stored blocks
-// of the tile's block-rows are one contiguous run of words in `values`; it is read
-// linearly, eight loads in flight per thread, and every word finds its place in the
-// tile from (entry, row, word) = decode(position).  Otherwise `group` lanes walk the
-// part of each block that lies inside the tile, element by element.
-template <typename T, bool WORDS>
+// w / d for rows and columns counted from the start of a block: w < d + 512.
+__device__ __forceinline__ uint32_t place_div(uint32_t w, uint32_t d, uint32_t magic) {
+  return d > (uint32_t)kRbOnce ? (w >= d ? 1u : 0u) : span_div(w, d, magic);
+}
+
+// V = elements per load of `values`: a divisor of bc.
+template <typename T, int V>
 __global__ __launch_bounds__(256) void reblock_kernel(
-    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx, const T *__restrict__ values,
-    int64_t K, int br, int bc, int64_t nbr, int64_t nbr2, int64_t nbc2, int kc, int group, int ebatch,
-    uint32_t magic_blk, uint32_t magic_seg, int32_t *__restrict__ rp2, int32_t *__restrict__ ci2,
-    T *__restrict__ values2) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  T *tile = reinterpret_cast<T *>(smem);                                        // [32][kc]
-  int32_t *erow = reinterpret_cast<int32_t *>(smem + (size_t)32 * kc * sizeof(T));   // tile row of an entry's first row
-  int32_t *ecol = erow + kRbEntries;                                            // tile column of its first column
-  __shared__ int32_t rp[34];
+    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx, const T *__restrict__ values, int br,
+    int bc, int64_t nbr, int64_t nbc, int64_t nbr2, int64_t nbc2, int kc, int tcols, uint32_t magic_br, uint32_t magic_bc,
+    int32_t *__restrict__ rp2, int32_t *__restrict__ ci2, T *__restrict__ values2) {
+  __shared__ int32_t slot[kRbTable];        // [block-row][block-column of the chunk]: stored block, -1 if pruned
   const int t = threadIdx.x;
+  constexpr int kVec = 16 / (int)sizeof(T);                                     // elements of a vector
+  constexpr int kPieces = kVec / V;
+  typedef Vec<T, V> Piece;
   const int64_t k0 = (int64_t)blockIdx.x * kc;
-  const int gl = t & (group - 1), grp = t / group, ngrp = 256 / group;
-  constexpr int kVec = 16 / (int)sizeof(T);                                     // elements per 16-byte vector
+  const int64_t j0 = k0 / bc;
+  const int c0 = (int)(k0 - j0 * bc);                                           // of the chunk's first column inside its block
+  const int ncols = (int)(nbc - j0 < tcols ? nbc - j0 : tcols);
+  const int64_t J0 = k0 / 32;
+  const int jb = (int)(nbc2 - J0 < kc / 32 ? nbc2 - J0 : kc / 32);              // 32x32 blocks of the chunk
+  const int nvec = jb * 32 * (32 / kVec);
   for (int64_t I = blockIdx.y; I < nbr2; I += gridDim.y) {
     const int64_t m0 = I * 32;
     const int64_t i_first = m0 / br;
+    const int r0 = (int)(m0 - i_first * br);                                    // of the first row inside its block-row
     int64_t i_last = (m0 + 31) / br;
     if (i_last > nbr - 1) i_last = nbr - 1;
     const int ni = (int)(i_last - i_first + 1);                                 // source block-rows: 1 .. 32
-    if (t <= ni) rp[t] = row_ptr[i_first + t];
-    uint4 *t4 = reinterpret_cast<uint4 *>(tile);
-    for (int v = t; v < 32 * kc / kVec; v += 256) t4[v] = make_uint4(0, 0, 0, 0);
+    // the entries of a block-row are dealt to a few lanes (256 / 32 at least)
+    int per_row = 8;
+    while (2 * per_row * ni <= 256) per_row *= 2;
+    const int rr = t / per_row, sub = t & (per_row - 1);
+    const int32_t p0 = rr < ni ? row_ptr[i_first + rr] : 0, p1 = rr < ni ? row_ptr[i_first + rr + 1] : 0;
+    for (int e = t; e < ni * tcols; e += 256) slot[e] = -1;
     __syncthreads();
-    const int64_t P0 = rp[0], P1 = rp[ni];
-    for (int64_t pb = P0; pb < P1; pb += ebatch) {
-      const int nb = (int)((P1 - pb) < ebatch ? (P1 - pb) : ebatch);
-      for (int q = t; q < nb; q += 256) {
-        const int64_t p = pb + q;
-        int lo = 0, hi = ni - 1;                                                // last source block-row with rp <= p
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (p >= rp[mid]) lo = mid; else hi = mid - 1;
-        }
-        const int64_t j = col_idx[p];
-        const int64_t c0 = j * bc - k0;
-        erow[q] = (int32_t)((i_first + lo) * br - m0);                          // -br < . < 32
-        ecol[q] = (j < 0 || c0 >= kc || c0 + bc <= 0) ? INT_MIN : (int32_t)c0;
-      }
-      __syncthreads();
-      if (WORDS) {
-        constexpr int kPerWord = 4 / (int)sizeof(T);
-        const uint32_t seg_words = (uint32_t)bc / kPerWord, blk_words = (uint32_t)br * seg_words;
-        const int kcw = kc / kPerWord;
-        const uint32_t total = (uint32_t)nb * blk_words;                       // < 2^16 (ebatch)
-        const uint32_t *vw = reinterpret_cast<const uint32_t *>(values) + pb * blk_words;
-        uint32_t *tw = reinterpret_cast<uint32_t *>(tile);
-        for (uint32_t w0 = 0; w0 < total; w0 += 8 * 256) {
-          uint32_t reg[8];
+    constexpr int kTogether = 4;                                                // entries a lane requests at a time
+    for (int32_t pb = p0 + sub; pb < p1; pb += kTogether * per_row) {
+      int64_t j[kTogether];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const uint32_t w = w0 + t + 256 * k;
-            reg[k] = w < total ? vw[w] : 0u;
-          }
+      for (int u = 0; u < kTogether; ++u) j[u] = pb + u * per_row < p1 ? (int64_t)col_idx[pb + u * per_row] - j0 : -1;
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const uint32_t w = w0 + t + 256 * k;
-            if (w < total) {
-              const uint32_t q = span_div(w, blk_words, magic_blk), rem = w - q * blk_words;
-              const uint32_t r = span_div(rem, seg_words, magic_seg), c = rem - r * seg_words;
-              const int32_t ec = ecol[q];
-              const int row = erow[q] + (int)r;
-              const int col = ec / kPerWord + (int)c;                           // ec is a multiple of the word size
-              if (ec != INT_MIN && row >= 0 && row < 32 && col >= 0 && col < kcw) tw[row * kcw + col] = reg[k];
-            }
-          }
-        }
-      } else
-      // `group` lanes per entry: they walk the part of the block that lies inside the tile
-      for (int q = grp; q < nb; q += ngrp) {
-        const int32_t er = erow[q], ec = ecol[q];
-        if (ec == INT_MIN) continue;
-        const int rs0 = er < 0 ? -er : 0;
-        const int rs1 = br < 32 - er ? br : 32 - er;
-        const int cs0 = ec < 0 ? -ec : 0;
-        const int cs1 = bc < kc - ec ? bc : kc - ec;
-        const int nr = rs1 - rs0, ncol = cs1 - cs0;
-        if (nr <= 0 || ncol <= 0) continue;
-        const T *src = values + ((pb + q) * br + rs0) * (int64_t)bc + cs0;
-        T *dst = tile + (er + rs0) * kc + ec + cs0;
-        int r = gl / ncol, c = gl - r * ncol;
-        while (r < nr) {
-          dst[r * kc + c] = src[(int64_t)r * bc + c];
-          c += group;
-          while (c >= ncol) { c -= ncol; ++r; }
-        }
-      }
-      __syncthreads();
+      for (int u = 0; u < kTogether; ++u)
+        if (j[u] >= 0 && j[u] < ncols) slot[rr * tcols + (int)j[u]] = pb + u * per_row;
     }
-    // ---- the tile as 32x32 blocks ----
-    const int jb = kc / 32;                                                     // blocks in the chunk
-    const int64_t J0 = k0 / 32;
-    constexpr int kVpb = 32 / kVec;                                             // vectors per block row
-    for (int v = t; v < 32 * jb * kVpb; v += 256) {
-      const int vv = v % kVpb, r = (v / kVpb) % 32, jl = v / (kVpb * 32);
-      if (J0 + jl < nbc2) {
-        const uint4 val = *reinterpret_cast<const uint4 *>(tile + r * kc + jl * 32 + vv * kVec);
-        *reinterpret_cast<uint4 *>(values2 + (((I * nbc2 + J0 + jl) * 32 + r) * 32 + vv * kVec)) = val;
+    __syncthreads();
+    // ---- the 32x32 blocks of the chunk, vector after vector ----
+    T *const out = values2 + (I * nbc2 + J0) * 1024;
+    for (int v0 = t; v0 < nvec; v0 += 256 * kRbInFlight) {
+      Piece x[kRbInFlight][kPieces];
+#pragma unroll
+      for (int k = 0; k < kRbInFlight; ++k) {
+        const uint32_t v = (uint32_t)(v0 + 256 * k);
+        const uint32_t r = (v / (32 / kVec)) % 32, c = (v / 32) / (32 / kVec) * 32 + v % (32 / kVec) * kVec;
+        const uint32_t br_row = (uint32_t)r0 + r, brr = place_div(br_row, (uint32_t)br, magic_br);
+        const uint32_t in_row = br_row - brr * (uint32_t)br;
+        const bool live = (int)v < nvec && (int)brr < ni;
+#pragma unroll
+        for (int q = 0; q < kPieces; ++q) {
+          const uint32_t col = (uint32_t)c0 + c + (uint32_t)(q * V), jl = place_div(col, (uint32_t)bc, magic_bc);
+          const int32_t p = live && (int)jl < ncols ? slot[brr * (uint32_t)tcols + jl] : -1;
+          if (p >= 0) {
+            x[k][q] = *reinterpret_cast<const Piece *>(values + ((int64_t)p * br + in_row) * bc + (col - jl * (uint32_t)bc));
+          } else {
+#pragma unroll
+            for (int i = 0; i < V; ++i) x[k][q].e[i] = (T)0;
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kRbInFlight; ++k) {
+        const int v = v0 + 256 * k;
+        if (v < nvec) {
+          Vec<T, kVec> y;
+#pragma unroll
+          for (int q = 0; q < kPieces; ++q)
+#pragma unroll
+            for (int i = 0; i < V; ++i) y.e[q * V + i] = x[k][q].e[i];
+          *reinterpret_cast<Vec<T, kVec> *>(out + (int64_t)v * kVec) = y;
+        }
       }
     }
     if (blockIdx.x == 0) {
-      for (int64_t J = t; J < nbc2; J += 256) ci2[I * nbc2 + J] = (int32_t)J;
+      for (int64_t J = t; J < nbc2; J += 256) ci2[I * nbc2 + J] = (int32_t)(J);
       if (t == 0) {
         rp2[I] = (int32_t)(I * nbc2);
         if (I == nbr2 - 1) rp2[nbr2] = (int32_t)(nbr2 * nbc2);
       }
     }
-    __syncthreads();
+    __syncthreads();                        // the table is free for the next rows
   }
-  (void)K;
 }
 
 struct ReblockPlan {
@@ -183,35 +160,37 @@ int launch_dw_reblocked(int dtype, const int32_t *row_ptr, const int32_t *col_id
   int32_t *ci2 = reinterpret_cast<int32_t *>(w + p.ci_off);
   const int e = elem_bytes(dtype);
   const int64_t k2 = p.nbc2 * 32;
-  const int kc_max = kRbTileBytes / (32 * e);
-  const int kc = (int)(k2 < kc_max ? k2 : kc_max);
-  // lanes per stored block: about its area inside a tile, a power of two
-  const int64_t area = (int64_t)(br < 32 ? br : 32) * (bc < kc ? bc : kc);
-  int group = 1;
-  while (group < 64 && group < area) group <<= 1;
-  const int64_t nbr = ceil_div(M, br);
+  const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
+  // Columns of a chunk: as many as give a thread eight vectors (fewer workgroups scan a row's entries then), or fewer
+  // where the table of very small blocks would not fit.  Chunks start on multiples of 32 columns, tiles on multiples of
+  // 32 rows: blocks that do not divide 32 may reach over both ends.
+  auto spanned = [](int64_t n, int64_t b) { return 32 % b == 0 ? n / b : (n + b - 2) / b + 1; };
+  const int64_t table_rows = spanned(32, br);
+  auto table_cols = [&](int64_t c) { return spanned(c, bc); };
+  int64_t kc = 16384 / e / 16;
+  while (kc > 32 && table_rows * table_cols(kc) > kRbTable) kc -= 32;
+  if (kc > k2) kc = k2;
+  const int tcols = (int)table_cols(kc);
   const dim3 grid((unsigned)ceil_div(k2, kc), (unsigned)(p.nbr2 < 65535 ? p.nbr2 : 65535));
-  const size_t lds = (size_t)32 * kc * e + 2 * (size_t)kRbEntries * 4;
-  // word mode: rows of whole words, at most 32 rows, few column chunks (every chunk reads the whole run)
-  const int64_t blk_words = (int64_t)br * bc * e / 4;
-  const bool words = ((int64_t)bc * e) % 4 == 0 && br <= 32 && blk_words <= 4096 && grid.x <= 4 &&
-                     (uintptr_t)values % 4 == 0;
-  int ebatch = kRbEntries;
-  uint32_t magic_blk = 0, magic_seg = 0;
-  if (words) {
-    if (ebatch > 65536 / blk_words) ebatch = (int)(65536 / blk_words);
-    auto magic = [](uint32_t d) { return (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); };
-    magic_blk = magic((uint32_t)blk_words);
-    magic_seg = magic((uint32_t)(bc * e / 4));
-  }
-#define BSR_REBLOCK(T, W)                                                                                   \
-  hipLaunchKernelGGL((reblock_kernel<T, W>), grid, dim3(256), lds, s, row_ptr, col_idx,                     \
-                     static_cast<const T *>(values), K, br, bc, nbr, p.nbr2, p.nbc2, kc, group, ebatch,     \
-                     magic_blk, magic_seg, rp2, ci2, reinterpret_cast<T *>(w + p.values_off))
+  auto magic = [](uint32_t d) { return (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); };
+#define BSR_REBLOCK(T, V)                                                                                   \
+  hipLaunchKernelGGL((reblock_kernel<T, V>), grid, dim3(256), 0, s, row_ptr, col_idx,                       \
+                     static_cast<const T *>(values), br, bc, nbr, nbc, p.nbr2, p.nbc2, (int)kc, tcols,      \
+                     magic((uint32_t)br), magic((uint32_t)bc), rp2, ci2, reinterpret_cast<T *>(w + p.values_off))
+  const int v = pick_vector(16 / e, e, bc, bc, bc, values);
   if (dtype == BSR_F32) {
-    if (words) BSR_REBLOCK(float, true); else BSR_REBLOCK(float, false);
+    switch (v) {
+      case 4: BSR_REBLOCK(float, 4); break;
+      case 2: BSR_REBLOCK(float, 2); break;
+      default: BSR_REBLOCK(float, 1); break;
+    }
   } else {
-    if (words) BSR_REBLOCK(uint16_t, true); else BSR_REBLOCK(uint16_t, false);
+    switch (v) {
+      case 8: BSR_REBLOCK(uint16_t, 8); break;
+      case 4: BSR_REBLOCK(uint16_t, 4); break;
+      case 2: BSR_REBLOCK(uint16_t, 2); break;
+      default: BSR_REBLOCK(uint16_t, 1); break;
+    }
   }
 #undef BSR_REBLOCK
   const int rc = check_launch();

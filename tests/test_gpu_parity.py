@@ -1290,3 +1290,32 @@ def test_dw_entries_of_a_block_row_in_any_order(M, K, N, b, dtype):
     torch.cuda.synchronize()
     for dW in got:
         assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
+
+
+@pytest.mark.parametrize("M,K,N,br,bc,dtype,shift", [
+    (130, 1100, 40, 1, 64, "bf16", 0),       # three column chunks, one wave of rows beyond a tile
+    (97, 1100, 24, 1, 64, "bf16", 2),        # ... values on a 4-byte boundary
+    (97, 1100, 24, 1, 64, "f32", 1),
+    (600, 130, 33, 1, 1, "f32", 0),          # the table of the chunk is full
+    (600, 130, 33, 1, 1, "bf16", 1),
+    (300, 300, 40, 48, 48, "bf16", 0),       # blocks across tiles and chunks
+    (300, 600, 40, 5, 7, "bf16", 3),
+    (210, 400, 16, 33, 96, "f32", 0),
+    (40, 5000, 16, 3, 4600, "bf16", 0),      # blocks wider than any chunk
+    (5000, 40, 16, 4600, 6, "f32", 0),       # ... taller than any tile
+])
+def test_dw_re_tiling_of_any_block_shape(M, K, N, br, bc, dtype, shift):
+    """Block shapes that are re-tiled first, at the edges of its column chunks and of its table; entries of a block-row
+    shuffled, values that start `shift` elements into their buffer.  Tolerance as in the other parity tests."""
+    rng = np.random.default_rng(M + bc)
+    X, dY = rand_pair(M, K, N, dtype, seed=M + K)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, br, bc, 0.55)
+    ref = oracle.dw(oracle.mask_dense(X, br, bc, o_mask), dY)
+    order = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(o_rp[:-1], o_rp[1:])]).astype(np.int64)
+    flat = torch.full((o_val.size + 64,), float("nan"), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    val = flat[shift:shift + o_val.size].view(o_val.shape)
+    val.copy_(to_dev(np.ascontiguousarray(o_val[order])))
+    rp, ci = torch.from_numpy(o_rp).cuda(), torch.from_numpy(np.ascontiguousarray(o_ci[order])).cuda()
+    dW = B.bsr_t_dense_matmul(rp, ci, val, M, K, br, bc, to_dev(dY))
+    torch.cuda.synchronize()
+    assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
