@@ -236,6 +236,27 @@ struct alignas(sizeof(T) * V) Vec {
   T e[V];
 };
 
+// V elements as they come from memory: a native vector of words, which the compiler moves as a whole.  (An array of
+// several 16-bit elements is taken apart where a load is under a condition: each load then waits for the one before.)
+template <int BYTES> struct RawWords;
+template <> struct RawWords<16> { typedef uint32_t __attribute__((ext_vector_type(4))) type; };
+template <> struct RawWords<8> { typedef uint32_t __attribute__((ext_vector_type(2))) type; };
+template <> struct RawWords<4> { typedef uint32_t type; };
+struct RawHalf { uint16_t v; };
+template <> struct RawWords<2> { typedef RawHalf type; };
+template <typename T, int V>
+using Raw = typename RawWords<(int)sizeof(T) * V>::type;
+
+// Element q of such a vector as a binary32 number.
+template <typename T, int V>
+__device__ __forceinline__ float raw_elem(const Raw<T, V> &v, int q) {
+  if constexpr (sizeof(T) == 4 && V == 1) return __uint_as_float(v);
+  else if constexpr (sizeof(T) == 4) return __uint_as_float(v[q]);
+  else if constexpr (V == 1) return bf16_bits_to_float(v.v);
+  else if constexpr (V == 2) return __uint_as_float(q ? v & 0xFFFF0000u : v << 16);
+  else return __uint_as_float(q % 2 ? v[q / 2] & 0xFFFF0000u : v[q / 2] << 16);
+}
+
 // Loads and stores of data that the kernel touches once (the streaming side of the HBM-bound
 // kernels): non-temporal accesses, which leave the caches to what is read again.  V is any
 // trivially copyable type of 2, 4, 8 or 16 bytes at its natural alignment.

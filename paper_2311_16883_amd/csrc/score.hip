@@ -57,18 +57,18 @@ __device__ __forceinline__ void score_body(
         // additions stays r ascending, whatever the batching
         constexpr int kInFlight = 8;
         for (int r0 = gr; r0 < rows; r0 += kInFlight * g.gb) {
-          Vec<T, V> v[kInFlight];
+          Raw<T, V> v[kInFlight];
 #pragma unroll
           for (int b = 0; b < kInFlight; ++b) {
             const int r = r0 + b * g.gb;
-            if (r < rows) v[b] = *reinterpret_cast<const Vec<T, V> *>(p + (int64_t)r * ldx);
+            if (r < rows) v[b] = *reinterpret_cast<const Raw<T, V> *>(p + (int64_t)r * ldx);
           }
 #pragma unroll
           for (int b = 0; b < kInFlight; ++b) {
             if (r0 + b * g.gb < rows) {
 #pragma unroll
               for (int q = 0; q < V; ++q) {
-                const double x = (double)elem_to_float<T>(v[b].e[q]);
+                const double x = (double)raw_elem<T, V>(v[b], q);
                 acc = fma(x, x, acc);
               }
             }
@@ -127,19 +127,21 @@ __device__ __forceinline__ void score_direct_body(
 #pragma unroll
   for (int k = 0; k < kOwn; ++k) acc[k] = 0.0;
   // (eight, not more: with sixteen the registers they need leave room for three waves per SIMD only,
-  // and a workgroup has nothing in flight while it adds up)
+  // and a workgroup has nothing in flight while it adds up.  As native vectors: loads of eight 16-bit elements under
+  // a condition came one at a time; score and select of 24 tensors [25088 x 384] took 92 us so, 81 now, of
+  // [6000 x 768] in 64x64 blocks 11.9 and 9.8)
   constexpr int kInFlight = 8;
   for (int r0 = (int)part; r0 < rows; r0 += kInFlight * lanes) {
-    Vec<T, V> v[kInFlight];
+    Raw<T, V> v[kInFlight];
 #pragma unroll
     for (int b = 0; b < kInFlight; ++b)
-      if (r0 + b * lanes < rows) v[b] = load_stream(reinterpret_cast<const Vec<T, V> *>(p + (int64_t)(r0 + b * lanes) * ldx));
+      if (r0 + b * lanes < rows) v[b] = load_stream(reinterpret_cast<const Raw<T, V> *>(p + (int64_t)(r0 + b * lanes) * ldx));
 #pragma unroll
     for (int b = 0; b < kInFlight; ++b) {
       if (r0 + b * lanes < rows) {
 #pragma unroll
         for (int q = 0; q < V; ++q) {
-          const double x = (double)elem_to_float<T>(v[b].e[q]);
+          const double x = (double)raw_elem<T, V>(v[b], q);
           const int k = TALL ? q % 2 : b % kOwn;
           acc[k] = fma(x, x, acc[k]);
         }
@@ -231,9 +233,9 @@ __device__ __forceinline__ void score_span_body(const uint8_t *__restrict__ X, i
   const int nvec = rows * g.row_words * 4 / (int)sizeof(V);
   const V *src = reinterpret_cast<const V *>(X + m0 * g.row_words * 4);
   V reg[kVecs];
+  // (no load is under a condition: behind the span's end the last vector again)
 #pragma unroll
-  for (int k = 0; k < kVecs; ++k)
-    if (t + 256 * k < nvec) reg[k] = src[t + 256 * k];
+  for (int k = 0; k < kVecs; ++k) reg[k] = src[t + 256 * k < nvec ? t + 256 * k : nvec - 1];
   V *sv = reinterpret_cast<V *>(lds);
 #pragma unroll
   for (int k = 0; k < kVecs; ++k)
@@ -326,18 +328,18 @@ __global__ __launch_bounds__(256) void score_rows_kernel(const uint8_t *__restri
   const int rows = (int)((M - m0) < (int64_t)nb * g.br ? (M - m0) : (int64_t)nb * g.br);
   const int rv = g.row_words / 4;                        // vectors per matrix row
   const int nvec = rows * rv;
-  const Vec<T, VE> *src = reinterpret_cast<const Vec<T, VE> *>(X + m0 * g.row_words * 4);
-  Vec<T, VE> reg[kVecs];
+  const Raw<T, VE> *src = reinterpret_cast<const Raw<T, VE> *>(X + m0 * g.row_words * 4);
+  Raw<T, VE> reg[kVecs];
+  // (no load is under a condition: behind the span's end the last vector again)
 #pragma unroll
-  for (int k = 0; k < kVecs; ++k)
-    if (t + 256 * k < nvec) reg[k] = src[t + 256 * k];
+  for (int k = 0; k < kVecs; ++k) reg[k] = src[t + 256 * k < nvec ? t + 256 * k : nvec - 1];
 #pragma unroll
   for (int k = 0; k < kVecs; ++k) {
     if (t + 256 * k < nvec) {
       double acc = 0.0;
 #pragma unroll
       for (int q = 0; q < VE; ++q) {
-        const double x = (double)elem_to_float<T>(reg[k].e[q]);
+        const double x = (double)raw_elem<T, VE>(reg[k], q);
         acc = fma(x, x, acc);
       }
       part[t + 256 * k] = acc;
@@ -373,10 +375,10 @@ int run_score_span(const void *X, int64_t M, int64_t K, int bc, const SpanGeom &
   const uint8_t *x = static_cast<const uint8_t *>(X);
   switch (g.vb) {
     case 16:
-      hipLaunchKernelGGL((score_span_kernel<T, uint4>), grid, dim3(256), lds, s, x, M, K, bc, nbr, g, span_words, pieces, magic_pieces, scores);
+      hipLaunchKernelGGL((score_span_kernel<T, RawWords<16>::type>), grid, dim3(256), lds, s, x, M, K, bc, nbr, g, span_words, pieces, magic_pieces, scores);
       break;
     case 8:
-      hipLaunchKernelGGL((score_span_kernel<T, uint2>), grid, dim3(256), lds, s, x, M, K, bc, nbr, g, span_words, pieces, magic_pieces, scores);
+      hipLaunchKernelGGL((score_span_kernel<T, RawWords<8>::type>), grid, dim3(256), lds, s, x, M, K, bc, nbr, g, span_words, pieces, magic_pieces, scores);
       break;
     default:
       hipLaunchKernelGGL((score_span_kernel<T, uint32_t>), grid, dim3(256), lds, s, x, M, K, bc, nbr, g, span_words, pieces, magic_pieces, scores);
@@ -489,8 +491,8 @@ template <typename T>
 int launch_span_batch(const SpanScoreBatch &b, int n, uint32_t wgs, size_t lds, int vb, hipStream_t s) {
   const dim3 grid(wgs), block(256);
   switch (vb) {
-    case 16: hipLaunchKernelGGL((score_span_batched_kernel<T, uint4>), grid, block, lds, s, b, n); break;
-    case 8: hipLaunchKernelGGL((score_span_batched_kernel<T, uint2>), grid, block, lds, s, b, n); break;
+    case 16: hipLaunchKernelGGL((score_span_batched_kernel<T, RawWords<16>::type>), grid, block, lds, s, b, n); break;
+    case 8: hipLaunchKernelGGL((score_span_batched_kernel<T, RawWords<8>::type>), grid, block, lds, s, b, n); break;
     default: hipLaunchKernelGGL((score_span_batched_kernel<T, uint32_t>), grid, block, lds, s, b, n); break;
   }
   return check_launch();
