@@ -22,7 +22,9 @@ constexpr int kAffSplits = 512;                  // splits of the sum over block
 constexpr int kAffRows = 8;                      // block-rows whose tables are built together
 constexpr int kAffCols = 64 * kAffVecs;          // block-columns a workgroup's vectors can fall into, at most
 
-template <typename T, int V>
+// BY_ROWS: the four waves share the rows of a block-row; otherwise (fewer than eight rows) they take every fourth block-row
+// (1x32 blocks, [25088 x 384] bfloat16: 24.0 us, 44.7 with one wave at work).
+template <typename T, int V, bool BY_ROWS>
 __global__ __launch_bounds__(256) void affine_dscale_kernel(
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx, const T *__restrict__ values,
     const T *__restrict__ dY, int64_t M, int64_t K, int64_t lddy, int br, int bc, int64_t nbr, int64_t nbc,
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(256) void affine_dscale_kernel(
       if (j >= j0 && j < j0 + ncols) slot[b * ncols + (int)(j - j0)] = (int32_t)p;
     }
     __syncthreads();
-    for (int b = 0; b < nb; ++b) {
+    for (int b = BY_ROWS ? 0 : rg; b < nb; b += BY_ROWS ? 1 : 4) {
       const int64_t i = ib + b;
       const int rows = (int)((M - i * br) < br ? (M - i * br) : br);
       const T *yrow = dY + i * br * lddy + w0 * V;
@@ -80,23 +82,40 @@ __global__ __launch_bounds__(256) void affine_dscale_kernel(
         if (p < 0) continue;
         const T *xs = values + (int64_t)p * block_elems + (int64_t)vu[u] * V;
         const T *ys = yrow + (int64_t)(lane + 64 * u) * V;
-        for (int r0 = rg; r0 < rows; r0 += 4 * kInFlight) {
-          Vec<T, V> xv[kInFlight], yv[kInFlight];
+        if constexpr (BY_ROWS) {
+          // Vectors of several 16-bit elements: kInFlight loads are always issued; past the last row they repeat it, and the
+          // sum leaves them out.  (Under a condition of its own each of them waits for the load before: [25088 x 384]
+          // bfloat16, 32x32 blocks, keep 0.5, both kernels: 17.0 us so, 12.3 now.  Loads of whole words do not wait, and
+          // repeats cost 1 .. 8 %.)
+          constexpr bool kRepeat = sizeof(T) == 2 && V >= 4;
+          for (int r0 = rg; r0 < rows; r0 += 4 * kInFlight) {
+            Vec<T, V> xv[kInFlight], yv[kInFlight];
 #pragma unroll
-          for (int k = 0; k < kInFlight; ++k) {
-            const int r = r0 + 4 * k;
-            if (r < rows) {
-              xv[k] = *reinterpret_cast<const Vec<T, V> *>(xs + (int64_t)r * bc);
-              yv[k] = *reinterpret_cast<const Vec<T, V> *>(ys + (int64_t)r * lddy);
+            for (int k = 0; k < kInFlight; ++k) {
+              const int r = !kRepeat || r0 + 4 * k < rows ? r0 + 4 * k : rows - 1;
+              if (kRepeat || r < rows) {
+                xv[k] = *reinterpret_cast<const Vec<T, V> *>(xs + (int64_t)r * bc);
+                yv[k] = *reinterpret_cast<const Vec<T, V> *>(ys + (int64_t)r * lddy);
+              }
+            }
+#pragma unroll
+            for (int k = 0; k < kInFlight; ++k) {
+              const bool in = r0 + 4 * k < rows;
+              if (kRepeat || in) {
+#pragma unroll
+                for (int q = 0; q < V; ++q) {
+                  const float sum = fmaf(elem_to_float<T>(xv[k].e[q]), elem_to_float<T>(yv[k].e[q]), acc[u][q]);
+                  acc[u][q] = kRepeat && !in ? acc[u][q] : sum;
+                }
+              }
             }
           }
+        } else {
+          for (int r = 0; r < rows; ++r) {
+            const Vec<T, V> xv = *reinterpret_cast<const Vec<T, V> *>(xs + (int64_t)r * bc);
+            const Vec<T, V> yv = *reinterpret_cast<const Vec<T, V> *>(ys + (int64_t)r * lddy);
 #pragma unroll
-          for (int k = 0; k < kInFlight; ++k) {
-            if (r0 + 4 * k < rows) {
-#pragma unroll
-              for (int q = 0; q < V; ++q)
-                acc[u][q] = fmaf(elem_to_float<T>(xv[k].e[q]), elem_to_float<T>(yv[k].e[q]), acc[u][q]);
-            }
+            for (int q = 0; q < V; ++q) acc[u][q] = fmaf(elem_to_float<T>(xv.e[q]), elem_to_float<T>(yv.e[q]), acc[u][q]);
           }
         }
       }
@@ -173,10 +192,12 @@ int launch_affine_dscale(const int32_t *row_ptr, const int32_t *col_idx, const v
   affine_split(nbr, p.gx, &p.splits, &p.rows_per_split);
   float *partial = static_cast<float *>(ws);
   const dim3 grid((unsigned)p.gx, (unsigned)p.splits);
-#define BSR_AFFINE(T, V)                                                                                     \
-  hipLaunchKernelGGL((affine_dscale_kernel<T, V>), grid, dim3(256), 0, s, row_ptr, col_idx,                  \
+#define BSR_AFFINE_(T, V, W)                                                                                 \
+  hipLaunchKernelGGL((affine_dscale_kernel<T, V, W>), grid, dim3(256), 0, s, row_ptr, col_idx,               \
                      static_cast<const T *>(values), static_cast<const T *>(dY), M, K, lddy, br, bc, nbr,    \
                      nbc, p.rows_per_split, partial)
+#define BSR_AFFINE(T, V) \
+  if (br >= 8) BSR_AFFINE_(T, V, true); else BSR_AFFINE_(T, V, false)
   if (dtype == BSR_F32) {
     switch (p.v) {
       case 4: BSR_AFFINE(float, 4); break;
@@ -192,6 +213,7 @@ int launch_affine_dscale(const int32_t *row_ptr, const int32_t *col_idx, const v
     }
   }
 #undef BSR_AFFINE
+#undef BSR_AFFINE_
   const int rc = check_launch();
   if (rc != BSR_OK) return rc;
   hipLaunchKernelGGL(affine_reduce_kernel, dim3((unsigned)ceil_div(K, 4)), dim3(256), 0, s, partial,

@@ -1319,3 +1319,21 @@ def test_dw_re_tiling_of_any_block_shape(M, K, N, br, bc, dtype, shift):
     dW = B.bsr_t_dense_matmul(rp, ci, val, M, K, br, bc, to_dev(dY))
     torch.cuda.synchronize()
     assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
+
+
+@pytest.mark.parametrize("br", [1, 2, 3, 7, 8, 9, 15, 17, 33])
+@pytest.mark.parametrize("M,K,bc,dtype", [(203, 144, 16, "bf16"), (203, 132, 12, "bf16"), (130, 96, 8, "f32")])
+def test_affine_scale_grad_rows_of_a_block(M, K, bc, dtype, br):
+    """Blocks of fewer and of more rows than the waves of a workgroup take together, last block-rows of every length; the
+    rows beyond the last one are NaN.  The bound is that of the parity test above."""
+    X, dY = rand_pair(M, K, K, dtype, seed=M + br)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, br, bc, 0.6)
+    xh = oracle.mask_dense(X, br, bc, o_mask)
+    ref = oracle.affine_dscale(xh, dY)
+    dYd = torch.full((M + 64, K), float("nan"), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)[:M]
+    dYd.copy_(to_dev(dY))
+    rp, ci = torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda()
+    got = B.bsr_affine_scale_grad(rp, ci, to_dev(o_val.reshape(-1, bc)).reshape(o_val.shape), M, K, br, bc, dYd)
+    torch.cuda.synchronize()
+    bound = 2.0 ** -23 * (np.log2(M) + 4) * np.sum(np.abs(synth.to_f64(xh) * synth.to_f64(dY)), axis=0)
+    assert np.all(np.abs(got.cpu().numpy() - ref) <= bound + 1e-30)
