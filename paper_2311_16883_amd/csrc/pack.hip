@@ -234,7 +234,6 @@ template <int VB>
 __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint32_t wg) {
   const int64_t i = wg / a.parts;
   const int part = (int)(wg - (uint32_t)i * a.parts), parts = (int)a.parts;
-  typedef typename BytesOf<VB>::type V;
   const uint8_t *__restrict__ mask = a.mask;
   const uint8_t *__restrict__ X = a.X;
   int32_t *__restrict__ row_ptr = a.row_ptr;
@@ -283,41 +282,57 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint3
   const uint8_t *xrow = X + i * br * ldb;
   uint8_t *vrow = values + (int64_t)prefix * S * kBytes;
   const int64_t rows_left = M - i * br;
-  auto copy = [&](int q, int r, int v, int e) {
-    const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * kBytes;
-    const uint8_t *src = xrow + (int64_t)r * ldb + cb;
-    V val = zero_bytes<VB>();
+  // Vector (r, v) of the blocks q0, q0 + step, ...
+  auto copy_blocks = [&](int q0, int step, int r, int v, int e) {
+    typedef typename RawWords<kBytes>::type W;
+    const bool row_in = r < rows_left;
+    const uint8_t *src = xrow + (row_in ? (int64_t)r * ldb : 0);
     if constexpr (VB == kLoose) {
-      if (r < rows_left) {
-        if (cb + kBytes <= kb) {
-          const PlainVec p = reinterpret_cast<const LooseVec *>(src)->v;
-          val = make_uint4(p.x, p.y, p.z, p.w);
-        } else {
-          uint32_t w[4] = {0, 0, 0, 0};
+      // (one after the other: the four together take 2 .. 5 % longer)
+#pragma unroll 4
+      for (int q = q0; q < (int)nk; q += step) {
+        const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * kBytes;
+        W val = {};
+        if (row_in) {
+          if (cb + kBytes <= kb) {
+            val = reinterpret_cast<const LooseVec *>(src + cb)->v;
+          } else {
 #pragma unroll
-          for (int k = 0; k < kBytes / 2; ++k)
-            if (cb + 2 * k < kb) w[k >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(src)[k] << (16 * (k & 1));
-          val = make_uint4(w[0], w[1], w[2], w[3]);
+            for (int k = 0; k < kBytes / 2; ++k)
+              if (cb + 2 * k < kb) val[k >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(src + cb)[k] << (16 * (k & 1));
+          }
         }
+        store_stream(reinterpret_cast<W *>(vrow + ((int64_t)q * S + e) * kBytes), val);
       }
     } else {
-      if (r < rows_left && cb < kb) val = *reinterpret_cast<const V *>(src);
+      // The loads of four blocks together, none of them under a condition (each would wait for the one before): past the last
+      // block that block again, beyond the matrix the first vector of the block-row.  ([25088 x 768] bfloat16, 16x16 blocks:
+      // 16.7 -> 14.6 us; [50176 x 1536], 32x32: 45.2 -> 41.2.)
+      constexpr int kInFlight = 4;
+      for (; q0 < (int)nk; q0 += kInFlight * step) {
+        W val[kInFlight];
+        bool in[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+          const int q = q0 + u * step < (int)nk ? q0 + u * step : (int)nk - 1;
+          const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * kBytes;
+          in[u] = row_in && cb < kb;
+          val[u] = *reinterpret_cast<const W *>(src + (in[u] ? cb : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+          W out = {};
+          if (in[u]) out = val[u];
+          if (q0 + u * step < (int)nk) store_stream(reinterpret_cast<W *>(vrow + ((int64_t)(q0 + u * step) * S + e) * kBytes), out);
+        }
+      }
     }
-    store_stream(reinterpret_cast<V *>(vrow + ((int64_t)q * S + e) * kBytes), val);
   };
   if (S <= 256) {
     const int G = 256 / S, g = t / S, e = t - g * S;      // G blocks per pass
-    if (g < G) {
-      const int r = e / vpb, v = e - r * vpb;
-#pragma unroll 4
-      for (int q = g * parts + part; q < (int)nk; q += G * parts) copy(q, r, v, e);
-    }
+    if (g < G) copy_blocks(g * parts + part, G * parts, e / vpb, e % vpb, e);
   } else {
-    for (int e = t; e < S; e += 256) {
-      const int r = e / vpb, v = e - r * vpb;
-#pragma unroll 4
-      for (int q = part; q < (int)nk; q += parts) copy(q, r, v, e);
-    }
+    for (int e = t; e < S; e += 256) copy_blocks(part, parts, e / vpb, e % vpb, e);
   }
 }
 
