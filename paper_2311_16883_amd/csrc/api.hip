@@ -51,7 +51,7 @@ size_t score_select_ws(int64_t nblocks) { return scores_bytes(nblocks) + select_
 
 // How well a product suits the wide-tile kernel: its tiles of 384 x 128 times the ways its
 // contraction can be split, i.e. the workgroups it can keep busy.  A call takes the wide
-// kernel when that reaches half the compute units.
+// kernel when that reaches half the compute units, and when the products are large enough (wide_work).
 int64_t wide_parallelism(int64_t M, int64_t K, int64_t N, int br) {
   const int64_t nbr = ceil_div(M, br);
   return ceil_div(K, 384) * ceil_div(N, 128) * (nbr < 16 ? nbr : 16);
@@ -65,9 +65,16 @@ bool use_narrow(int dtype, int br, int bc, const void *values, const void *dY, i
   return dw_narrow_supported(dtype, br, bc, values, dY, M, K, N, lddy) && ceil_div(M, br) >= 16;
 }
 
+// Work from which a call's products are worth the wide kernel, in units of that: its start, its write-out and its few large
+// workgroups cost more than the 128 x 128 tiles until there is enough to multiply.  ([6272 x 384 x 1536] in 32x32 blocks, keep
+// 0.5: 27.6 us wide, 22.3 in 128 x 128 tiles; [800 x 2048 x 2048] 21.6 and 16.0; [12544 x 768 x 768] 31.6 and 34.3;
+// [25088 x 1536 x 384] 39.6 and 43.1; two products [3136 x 384 x 1536] 29.2 and 24.8, [6272 x 384 x 1536] 31.4 and 32.9.)
+double wide_work(int64_t M, int64_t K, int64_t N) { return (double)M * (double)K * (double)N / 5.0e9; }
+
 bool use_wide_single(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K, int64_t N,
                      int64_t lddy) {
-  return dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy) && wide_parallelism(M, K, N, br) >= 128;
+  return dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy) && wide_parallelism(M, K, N, br) >= 128 &&
+         wide_work(M, K, N) >= 1.0;
 }
 
 }  // namespace
@@ -395,6 +402,7 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
   std::vector<DwJob> batch, single, wide, narrow;
   batch.reserve(n);
   int64_t wide_par = 0;
+  double work = 0.0;
   size_t off = 0;
   for (int i = 0; i < n; ++i) {
     const bsr_matmul_item &it = items[i];
@@ -418,6 +426,7 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
     } else if (dw_wide_supported(dtype, it.br, it.bc, it.values, it.dY, it.M, it.K, it.N, it.lddy)) {
       wide.push_back(job);
       wide_par += wide_parallelism(it.M, it.K, it.N, it.br);
+      work += wide_work(it.M, it.K, it.N);
     } else if (dw_mfma_supported(dtype, it.br, it.bc, it.values, it.M, it.K, it.N, it.lddy)) {
       batch.push_back(job);
     } else {
@@ -425,8 +434,8 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
     }
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // too few tiles to fill the GPU even with a deep split: the narrow-tile kernel suits those better
-  if (!wide.empty() && wide_par < 128) {
+  // too few tiles to fill the GPU even with a deep split, or too little to multiply: the narrow-tile kernel suits those better
+  if (!wide.empty() && (wide_par < 128 || work < 1.0)) {
     batch.insert(batch.end(), wide.begin(), wide.end());
     wide.clear();
   }

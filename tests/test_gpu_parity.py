@@ -1337,3 +1337,37 @@ def test_affine_scale_grad_rows_of_a_block(M, K, bc, dtype, br):
     torch.cuda.synchronize()
     bound = 2.0 ** -23 * (np.log2(M) + 4) * np.sum(np.abs(synth.to_f64(xh) * synth.to_f64(dY)), axis=0)
     assert np.all(np.abs(got.cpu().numpy() - ref) <= bound + 1e-30)
+
+
+def check_large_dw(M, K, N, bs, keep, copies):
+    """dW of one shape, `copies` products in a call (1: the single call): entries of a block-row shuffled, rows of dY with a
+    NaN tail.  The reference is the binary64 product of the masked matrix, which pins the oracle too."""
+    print(f"[case] large dW M={M} K={K} N={N} block={bs} keep={keep} x{copies}", flush=True)
+    rng = np.random.default_rng(M + bs)
+    X, dY = rand_pair(M, K, N, "bf16", seed=M + N + bs)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, bs, bs, keep)
+    xhat = torch.from_numpy(synth.to_f64(oracle.mask_dense(X, bs, bs, o_mask))).cuda()
+    ref = (xhat.T @ torch.from_numpy(synth.to_f64(dY)).cuda()).cpu().numpy()
+    order = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(o_rp[:-1], o_rp[1:])]).astype(np.int64)
+    rp, ci = torch.from_numpy(o_rp).cuda(), torch.from_numpy(np.ascontiguousarray(o_ci[order])).cuda()
+    val = to_dev(np.ascontiguousarray(o_val[order]))
+    dYd = torch.full((M, N + 8), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :N]
+    dYd.copy_(to_dev(dY))
+    if copies == 1:
+        got = [B.bsr_t_dense_matmul(rp, ci, val, M, K, bs, bs, dYd)]
+    else:
+        got = B.bsr_t_dense_matmul_batched(B.MatmulBatch([(rp, ci, val, M, K, bs, bs, dYd)] * copies))
+    torch.cuda.synchronize()
+    for dW in got:
+        assert dw_error(dW.cpu().numpy(), ref) <= DW_TOL_DERIVED
+
+
+@pytest.mark.parametrize("copies", [1, 2])
+@pytest.mark.parametrize("M,K,N,bs,keep", [
+    (5001, 1100, 1000, 32, 0.3),             # everything ragged, enough work for the wide tiles
+    (5001, 1100, 1000, 64, 0.3),
+    (3000, 1300, 1280, 32, 0.5),             # just below (alone) and above (two products) that amount
+    (3000, 1300, 1280, 64, 0.9),
+])
+def test_dw_on_both_sides_of_the_wide_tiles_amount_of_work(M, K, N, bs, keep, copies):
+    check_large_dw(M, K, N, bs, keep, copies)
