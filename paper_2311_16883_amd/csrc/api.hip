@@ -68,13 +68,17 @@ bool use_narrow(int dtype, int br, int bc, const void *values, const void *dY, i
 // Work from which a call's products are worth the wide kernel, in units of that: its start, its write-out and its few large
 // workgroups cost more than the 128 x 128 tiles until there is enough to multiply.  ([6272 x 384 x 1536] in 32x32 blocks, keep
 // 0.5: 27.6 us wide, 22.3 in 128 x 128 tiles; [800 x 2048 x 2048] 21.6 and 16.0; [12544 x 768 x 768] 31.6 and 34.3;
-// [25088 x 1536 x 384] 39.6 and 43.1; two products [3136 x 384 x 1536] 29.2 and 24.8, [6272 x 384 x 1536] 31.4 and 32.9.)
-double wide_work(int64_t M, int64_t K, int64_t N) { return (double)M * (double)K * (double)N / 5.0e9; }
+// [25088 x 1536 x 384] 39.6 and 43.1; two products [3136 x 384 x 1536] 29.2 and 24.8, [6272 x 384 x 1536] 31.4 and 32.9.  16x16 blocks, where the wide kernel
+// copies by halves of a piece: [25088 x 1536 x 384] 48.9 and 46.7, [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536],
+// keep 0.25, 68 and 87.)
+double wide_work(int64_t M, int64_t K, int64_t N, int br) {
+  return (double)M * (double)K * (double)N / (br == 16 ? 2.5e10 : 5.0e9);
+}
 
 bool use_wide_single(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K, int64_t N,
                      int64_t lddy) {
   return dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy) && wide_parallelism(M, K, N, br) >= 128 &&
-         wide_work(M, K, N) >= 1.0;
+         wide_work(M, K, N, br) >= 1.0;
 }
 
 }  // namespace
@@ -426,7 +430,7 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
     } else if (dw_wide_supported(dtype, it.br, it.bc, it.values, it.dY, it.M, it.K, it.N, it.lddy)) {
       wide.push_back(job);
       wide_par += wide_parallelism(it.M, it.K, it.N, it.br);
-      work += wide_work(it.M, it.K, it.N);
+      work += wide_work(it.M, it.K, it.N, it.br);
     } else if (dw_mfma_supported(dtype, it.br, it.bc, it.values, it.M, it.K, it.N, it.lddy)) {
       batch.push_back(job);
     } else {

@@ -1,5 +1,5 @@
 // Weight gradient from a BSR activation (paper Sec. III, Fig. 2: dW = Xhat^T * dY)
-// for bfloat16 inputs and 32x32 or 64x64 blocks, with workgroup tiles that span
+// for bfloat16 inputs and 16x16, 32x32 or 64x64 blocks, with workgroup tiles that span
 // 384 rows of dW, so that every row of dY is read once per 384 columns of the
 // activation (once in all for the 384-wide ResMLP inputs) and every kept block
 // once per 128 output columns.
@@ -38,6 +38,10 @@
 //    multiplying wave's decision is a bit test and a branch, and a fragment of the
 //    activation is read only for a kept block.  The table covers 480 block-rows;
 //    longer contractions run in chunks, the accumulators carried across.
+//  * 16x16 blocks: a piece is two block-columns wide and a stage two block-rows high.  Copied and multiplied are halves of
+//    a piece, 16 rows x 32 columns, that hold a kept block; one copy instruction fetches both blocks of a half, each lane with
+//    its own block's offset, and brings zeros for a pruned block beside a kept one (its offset lies beyond the buffer).
+//    ([50176 x 1536 x 384], keep 0.25: 75 us in 128 x 128 tiles, 67 so; 18 products [4116 x 768 x 3072], keep 0.25: 476, 285.)
 //  * The multiplying waves are software-pipelined across the barrier by half a
 //    stage: the fragments of a wave's last two pieces are multiplied after the
 //    next barrier, while the first reads of the next stage are on their way.
@@ -67,8 +71,10 @@ constexpr int kStrips = kTileN / 32;
 constexpr int kSlabBytes = 2048;       // 32 contraction rows x 32 columns of bfloat16
 constexpr int kStageBytes = (kPieces + kStrips) * kSlabBytes;   // 32 KB
 constexpr int kRing = 4;               // stages in LDS: 128 KB
-constexpr int kWideMaxRows = 480;      // block-rows of one split: 12 table words per block-row in LDS
-constexpr int kRowPad = 12;            // table rows behind the split's last that read as "nothing kept"
+// block-rows whose tables fit LDS (a word per block-row and block-column of the tile), and table rows behind the last one that
+// read as "nothing kept" (stages are walked in fours, three ahead)
+constexpr int wide_max_rows(int bs) { return bs == 16 ? 240 : 480; }
+constexpr int wide_row_pad(int bs) { return bs == 16 ? 16 : 12; }
 constexpr int kWK = 3, kWN = 4;        // multiplying waves along the rows / columns of dW
 constexpr int kMathWaves = kWK * kWN;  // 12: three per SIMD
 constexpr int kCopyWaves = 4;          // one per SIMD
@@ -101,6 +107,13 @@ __device__ __forceinline__ void copy_pair_to_lds(__amdgpu_buffer_rsrc_t rsrc, ui
                "buffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
                "buffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds"
                :: "s"(lds_addr), "v"(voff_lo), "v"(voff_hi), "s"(rsrc) : "memory", "m0");
+}
+
+// ... one copy: lane l's bytes land at lds_addr + 16 * l.
+__device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds_addr, uint32_t voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+               "buffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
 }
 
 // The compiler moves arithmetic on values it knows to be the same in all lanes to the scalar unit;
@@ -137,19 +150,22 @@ __device__ __forceinline__ v8bf read_fragment(const uint8_t *p) {
 template <int NP>
 struct PartFrags {
   v8bf a0[NP], a1[NP];
-  uint32_t mine;      // kept pieces (bit i = piece i of the part), wave-uniform
+  uint32_t mine;      // kept pieces (bit i = piece i of the part; 16x16 blocks: of the first step, bit 4 + i of the second), wave-uniform
 };
 struct StripFrags {
   v8bf b0, b1;        // the wave's dY strip, two contraction steps
 };
 
-// BS = block size (32 or 64).  item = (split, tile) of this product, tile = (tk, tn), tn fastest:
+// BS = block size (16, 32 or 64).  item = (split, tile) of this product, tile = (tk, tn), tn fastest:
 // workgroups that run side by side share the activation rows of their split.
 template <int BS>
 struct WideBody {
   static __device__ __forceinline__ void run(const WideParams &prm, const uint32_t item) {
-    constexpr int JT = kTileK / BS;                  // block-columns of a tile: 12 or 6
-    constexpr int SPB = BS / 32;                     // stages per block-row = pieces per block-column
+    constexpr bool SMALL = BS == 16;                 // a stage = two block-rows, a piece = two block-columns
+    constexpr int JT = kTileK / BS;                  // block-columns of a tile: 24, 12 or 6
+    constexpr int SPB = SMALL ? 1 : BS / 32;         // (larger blocks) stages per block-row = pieces per block-column
+    constexpr int RPS = SMALL ? 2 : 1;               // block-rows per stage, or one
+    constexpr int kWideMaxRows = wide_max_rows(BS), kRowPad = wide_row_pad(BS);
     constexpr uint32_t kBlockBytes = BS * BS * 2;
     constexpr uint32_t kRowBytes = BS * 2;           // bytes of one row of a block
 
@@ -157,7 +173,7 @@ struct WideBody {
     // per block-row of the split and block-column of the tile: byte offset of the kept block in
     // `values`, or kBeyond; per block-row: the bits of its kept pieces
     __shared__ uint32_t sOff[(kWideMaxRows + kRowPad) * JT];
-    __shared__ uint32_t sKept[kWideMaxRows + kRowPad];
+    __shared__ __attribute__((aligned(8))) uint32_t sKept[kWideMaxRows + kRowPad];
 
     const int32_t *__restrict__ row_ptr = prm.row_ptr;
     const int32_t *__restrict__ col_idx = prm.col_idx;
@@ -192,7 +208,9 @@ struct WideBody {
     const uint32_t b_step = (uint32_t)(32 * prm.lddy * 2);
     // per-lane part of the offsets inside a block (pieces c, c + 4, c + 8 lie in the same half of
     // their 64-wide blocks)
-    const uint32_t va = (uint32_t)(lane >> 2) * kRowBytes + (uint32_t)(lane & 3) * 16u + (SPB == 2 ? (uint32_t)(c & 1) * 64u : 0u);
+    // (16x16 blocks: a copy takes 16 rows of two blocks side by side, chunks 0-1 and 2-3 of its 64-byte rows)
+    const uint32_t va = SMALL ? (uint32_t)(lane >> 2) * kRowBytes + (uint32_t)(lane & 1) * 16u
+                              : (uint32_t)(lane >> 2) * kRowBytes + (uint32_t)(lane & 3) * 16u + (SPB == 2 ? (uint32_t)(c & 1) * 64u : 0u);
     uint32_t m0_slot[kRing];
 #pragma unroll
     for (int k = 0; k < kRing; ++k) m0_slot[k] = ring_lds + (uint32_t)(c * kSlabBytes + k * kStageBytes);
@@ -240,7 +258,7 @@ struct WideBody {
               const uint32_t jl = (uint32_t)(j[u] - jfirst);
               if (j[u] >= 0 && jl < (uint32_t)jt) {
                 sOff[rr * JT + (int)jl] = (uint32_t)(pb + u * per_row) * kBlockBytes;
-                atomicOr(&sKept[rr], SPB == 2 ? 3u << (2 * jl) : 1u << jl);      // bits of the kept pieces
+                atomicOr(&sKept[rr], SMALL ? 1u << (jl >> 1) : SPB == 2 ? 3u << (2 * jl) : 1u << jl);      // bits of the kept pieces
               }
             }
           }
@@ -254,7 +272,7 @@ struct WideBody {
     auto chunk_rows = [&](int r0) { return __builtin_amdgcn_readfirstlane(nrows - r0 < kWideMaxRows ? nrows - r0 : kWideMaxRows); };
     if (copy_wave) {
       for (int r0 = 0; r0 < nrows; r0 += kWideMaxRows) {
-        const int crows = chunk_rows(r0), cbegin = i_begin + r0, nstages = crows * SPB;
+        const int crows = chunk_rows(r0), cbegin = i_begin + r0, nstages = (crows + RPS - 1) / RPS * SPB;
         // ================= copy waves =================
         // dY goes in whole 128-byte lines: a copy takes 8 rows x 64 columns (two strips side by
         // side); the 16-byte chunks of rows 2, 3, 6, 7 of a group are stored with bit 2 of their
@@ -320,6 +338,59 @@ struct WideBody {
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           }
         };
+        if constexpr (SMALL) {
+          // 16x16 blocks: per piece and 16-row half of the stage one copy, which brings zeros in the place of a pruned block
+          // beside a kept one; none where both are pruned.
+          const uint32_t *off = sOff + 2 * c + ((lane >> 1) & 1);      // this lane's block of piece c, first half of stage q
+          struct Offsets { uint32_t o[3][2]; };
+          auto offsets = [&](int stage) {
+            Offsets x;
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+#pragma unroll
+              for (int h = 0; h < 2; ++h) x.o[u][h] = off[(2 * stage + h) * JT + 8 * u];
+            return x;
+          };
+          auto issue_small = [&](uint32_t m0, const Offsets &x) -> uint32_t {
+            uint32_t n = 0;
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+#pragma unroll
+              for (int h = 0; h < 2; ++h)
+                if (__builtin_amdgcn_ballot_w64(x.o[u][h] != kBeyond) != 0ull) {
+                  copy_to_lds(rsrc_a, m0 + (uint32_t)(u * 4 * kSlabBytes + h * 1024), x.o[u][h] + va);
+                  ++n;
+                }
+            return n;
+          };
+          uint32_t cnt[kAhead];
+#pragma unroll
+          for (int d = 0; d < kAhead; ++d) cnt[d] = issue_small(m0_slot[d], offsets(d));
+          uint32_t c1 = cnt[1], c2 = cnt[2];
+          Offsets next = offsets(kAhead);
+          auto stage = [&](auto slot_c) {
+            constexpr int slot = decltype(slot_c)::value;
+            constexpr int slot_new = (slot + kAhead) % kRing;
+            wait_copies(c1 + c2);
+            stage_barrier();
+            const uint32_t c3 = issue_small(m0_slot[slot_new], next) + 2u;
+            copy_pair_to_lds(rsrc_b, m0_slot[slot_new] + b_lds_delta, vb, vb + b_hi_delta);
+            vb += b_step;
+            c1 = c2;
+            c2 = c3;
+            next = offsets(slot + kAhead + 1);
+          };
+          for (int trip = 0; trip < (nstages + kRing - 1) / kRing; ++trip) {
+            stage(std::integral_constant<int, 0>{});
+            stage(std::integral_constant<int, 1>{});
+            stage(std::integral_constant<int, 2>{});
+            stage(std::integral_constant<int, 3>{});
+            off += 2 * kRing * JT;
+          }
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          __syncthreads();        // the ring and the tables are free for the next chunk
+          continue;
+        }
         // copies issued for the stages q .. q + 2: of the first ones the pieces only, since all their dY
         // copies were issued in front of those
         uint32_t cnt[kAhead];
@@ -360,7 +431,7 @@ struct WideBody {
       return;
     }
     for (int r0 = 0; r0 < nrows; r0 += kWideMaxRows) {
-      const int crows = chunk_rows(r0), nstages = crows * SPB;
+      const int crows = chunk_rows(r0), nstages = (crows + RPS - 1) / RPS * SPB;
       __syncthreads();          // (the two barriers of the table build)
       __syncthreads();
         // ================= multiplying waves =================
@@ -373,7 +444,10 @@ struct WideBody {
           const uint32_t m = scalar_value(mine);
 #pragma unroll
           for (int i = 0; i < NP; ++i) {
-            if (m & (1u << i)) {
+            if constexpr (SMALL) {
+              if (m & (1u << i)) f.a0[i] = read_fragment<64>(bufA + i * kSlabBytes);
+              if (m & (16u << i)) f.a1[i] = read_fragment<64>(bufA + i * kSlabBytes + 1024);
+            } else if (m & (1u << i)) {
               f.a0[i] = read_fragment<64>(bufA + i * kSlabBytes);
               f.a1[i] = read_fragment<64>(bufA + i * kSlabBytes + 1024);
             }
@@ -391,7 +465,10 @@ struct WideBody {
           const uint32_t m = scalar_value(f.mine);
 #pragma unroll
           for (int i = 0; i < NP; ++i) {
-            if (m & (1u << i)) {
+            if constexpr (SMALL) {
+              if (m & (1u << i)) acc[first + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a0[i], b.b0, acc[first + i], 0, 0, 0);
+              if (m & (16u << i)) acc[first + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a1[i], b.b1, acc[first + i], 0, 0, 0);
+            } else if (m & (1u << i)) {
               acc[first + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a0[i], b.b0, acc[first + i], 0, 0, 0);
               acc[first + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a1[i], b.b1, acc[first + i], 0, 0, 0);
             }
@@ -408,7 +485,7 @@ struct WideBody {
         StripFrags strip[2];                          // by stage parity
         head.mine = 0u;
         rest.mine = 0u;
-        uint32_t kept_next = kept[0];                 // read one stage ahead of its use
+        uint32_t kept_next = kept[0], kept_next1 = SMALL ? kept[1] : 0u;      // read one stage ahead of their use
         const uint32_t my_shift = (uint32_t)(kPW * wk);
         // One stage, software-pipelined across the barrier by part of a stage: after barrier q the
         // fragments of the first pieces of stage q are requested, then the last pieces of stage q - 1
@@ -416,14 +493,16 @@ struct WideBody {
         // stage q are requested and the first ones multiplied.
         auto stage = [&](auto slot_c) {
           constexpr int slot = decltype(slot_c)::value;                  // stage q = 4 * trip + slot
-          const uint32_t mine =
-              (uint32_t)__builtin_amdgcn_readfirstlane((int)((vector_value(kept_next) >> my_shift) & ((1u << kPW) - 1u)));
+          uint32_t bits = (vector_value(kept_next) >> my_shift) & ((1u << kPW) - 1u);
+          if constexpr (SMALL) bits |= ((vector_value(kept_next1) >> my_shift) & ((1u << kPW) - 1u)) << 4;
+          const uint32_t mine = (uint32_t)__builtin_amdgcn_readfirstlane((int)bits);
           stage_barrier();               // everybody's copies of stage q have landed, and everybody has the fragments of stage q - 1
-          kept_next = kept[(slot + 1) / SPB];
+          kept_next = kept[(slot + 1) * RPS / SPB];
+          if constexpr (SMALL) kept_next1 = kept[(slot + 1) * RPS + 1];
           StripFrags &bq = strip[slot & 1];
           const StripFrags &bprev = strip[(slot + 1) & 1];
           if (mine != 0u) load_strip(bq, slot);
-          load_part(head, slot, At0{}, mine & ((1u << kFirst) - 1u));
+          load_part(head, slot, At0{}, mine & (SMALL ? 0x11u * ((1u << kFirst) - 1u) : (1u << kFirst) - 1u));
           multiply(rest, bprev, AtRest{});
           load_part(rest, slot, AtRest{}, mine >> kFirst);
           multiply(head, bq, At0{});
@@ -434,7 +513,7 @@ struct WideBody {
           stage(std::integral_constant<int, 1>{});
           stage(std::integral_constant<int, 2>{});
           stage(std::integral_constant<int, 3>{});
-          kept += kRing / SPB;
+          kept += kRing * RPS / SPB;
         }
         multiply(rest, strip[1], AtRest{});              // the last pieces of the last stage
       __syncthreads();        // the ring and the tables are free for the next chunk
@@ -550,7 +629,8 @@ WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *r
 template <int BS>
 void wide_fill(const DwJob &j, int splits, WideParams *p) {
   const int64_t nbr = ceil_div(j.M, BS), nbc = ceil_div(j.K, BS);
-  const int64_t rps = nbr > 0 ? ceil_div(nbr, (int64_t)splits) : 1;
+  int64_t rps = nbr > 0 ? ceil_div(nbr, (int64_t)splits) : 1;
+  if (BS == 16 && rps > 1) rps += rps & 1;                 // (whole stages)
   const int eff = nbr > 0 ? (int)ceil_div(nbr, rps) : 1;
   p->row_ptr = j.row_ptr; p->col_idx = j.col_idx; p->values = j.values; p->dY = j.dY;
   p->out = eff > 1 ? static_cast<float *>(j.ws) : j.dW;
@@ -572,7 +652,7 @@ uint32_t wide_cut(const WideBatch &b, int lo, int hi, uint32_t *begin) {
   int64_t cost[kWideBatchMax], all = 0;
   uint32_t first = 0, total = 0;
   for (int i = lo; i < hi; ++i) {
-    cost[i] = (int64_t)b.it[i].rows_per_split * (BS / 32) + 30;
+    cost[i] = (int64_t)b.it[i].rows_per_split * BS / 32 + 30;
     const int64_t items = (int64_t)b.it[i].splits * b.it[i].tiles_k * b.it[i].tiles_n;
     all += cost[i] * items;
     if (i == lo) first = b.it[i].wg_begin;
@@ -607,7 +687,7 @@ int wide_launch(const DwJob *const *jobs, int m, hipStream_t s, std::vector<Redu
   for (int i = 0; i < m; ++i) {
     tiles[i] = wide_tiles(jobs[i]->K, jobs[i]->N);
     rows[i] = ceil_div(jobs[i]->M, (int64_t)BS);
-    stages[i] = rows[i] * (BS / 32);
+    stages[i] = ceil_div(rows[i] * BS, (int64_t)32);
     bytes_out[i] = 4.0 * (double)jobs[i]->K * (double)jobs[i]->N;
   }
   const WidePlan plan = wide_plan(tiles, stages, rows, bytes_out, m);
@@ -656,16 +736,16 @@ int wide_run_batched(const DwJob *jobs, int n, hipStream_t s, std::vector<Reduce
 
 }  // namespace
 
-// Shapes the wide kernel takes: bfloat16, 32x32 or 64x64 blocks, dY rows that are whole
+// Shapes the wide kernel takes: bfloat16, 16x16, 32x32 or 64x64 blocks, dY rows that are whole
 // 16-byte chunks, operands addressable with 32-bit byte offsets.
 bool dw_wide_supported(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K,
                        int64_t N, int64_t lddy) {
-  if (dtype != BSR_BF16 || br != bc || (br != 32 && br != 64)) return false;
+  if (dtype != BSR_BF16 || br != bc || (br != 16 && br != 32 && br != 64)) return false;
   if ((uintptr_t)values % 16 != 0 || (uintptr_t)dY % 16 != 0 || N % 8 != 0 || lddy % 8 != 0 || N > lddy) return false;
   if (M <= 0 || K <= 0 || N <= 0) return false;
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
   if (nbr * nbc * br * bc * 2 >= (int64_t(1) << 32) - 2 * 65536) return false;
-  if ((nbr * br + 64 + 4 * 32) * lddy * 2 + 2 * N + 1024 >= (int64_t(1) << 32) - 65536) return false;
+  if ((nbr * br + 64 + 4 * 32 + (br == 16 ? 16 : 0)) * lddy * 2 + 2 * N + 1024 >= (int64_t(1) << 32) - 65536) return false;
   if (nbr >= (int64_t(1) << 30) || nbc >= (int64_t(1) << 30)) return false;
   return true;
 }
@@ -679,11 +759,13 @@ size_t dw_wide_ws_bytes(int64_t M, int64_t K, int64_t N, int br) {
 
 int launch_dw_wide(const DwJob &j, hipStream_t s) {
   const DwJob *one = &j;
+  if (j.br == 16) return wide_launch<16>(&one, 1, s, nullptr);
   return j.br == 32 ? wide_launch<32>(&one, 1, s, nullptr) : wide_launch<64>(&one, 1, s, nullptr);
 }
 
 int launch_dw_wide_batched(const DwJob *jobs, int n, hipStream_t s, std::vector<ReduceJob> *later) {
-  const int rc = wide_run_batched<32>(jobs, n, s, later);
+  int rc = wide_run_batched<16>(jobs, n, s, later);
+  if (rc == BSR_OK) rc = wide_run_batched<32>(jobs, n, s, later);
   if (rc != BSR_OK) return rc;
   return wide_run_batched<64>(jobs, n, s, later);
 }

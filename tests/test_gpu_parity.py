@@ -1368,6 +1368,9 @@ def check_large_dw(M, K, N, bs, keep, copies):
     (5001, 1100, 1000, 64, 0.3),
     (3000, 1300, 1280, 32, 0.5),             # just below (alone) and above (two products) that amount
     (3000, 1300, 1280, 64, 0.9),
+    (20003, 410, 3080, 16, 0.3),             # 16x16 blocks, ragged; splits of more block-rows than one table holds
+    (9100, 1500, 1000, 16, 0.6),             # just below and above
+    (1003, 5000, 5008, 16, 0.1),             # splits of a few stages, odd numbers of block-rows
 ])
 def test_dw_on_both_sides_of_the_wide_tiles_amount_of_work(M, K, N, bs, keep, copies):
     check_large_dw(M, K, N, bs, keep, copies)
