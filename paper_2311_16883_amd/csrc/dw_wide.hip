@@ -82,7 +82,6 @@ constexpr int kWideThreads = 64 * (kMathWaves + kCopyWaves);
 constexpr int kPW = kPieces / kWK;     // pieces per multiplying wave: 4
 constexpr int kFirst = 2;              // of which the fragments of the first two are requested first
 constexpr int kAhead = kRing - 1;      // stages whose copies are on their way while one is multiplied
-constexpr int kWideMaxSplits = 16;     // splits of the contraction the planner may pick (the workspace is sized for them)
 constexpr uint32_t kBeyond = 0xFFFF0000u;          // a byte offset no buffer reaches (plus a per-lane part < 64 KB)
 
 struct WideParams {
@@ -584,6 +583,15 @@ __global__ __launch_bounds__(kWideThreads) void dw_wide_batched_kernel(WideBatch
 
 int64_t wide_tiles(int64_t K, int64_t N) { return ceil_div(K, kTileK) * ceil_div(N, kTileN); }
 
+// Splits of the contraction the planner may pick (the workspace is sized for them): sixteen, or up to 24 where a product of
+// few tiles would leave compute units without one ([50176 x 1536 x 384], 12 tiles, keep 0.25: 47.9 us in 16
+// splits, 44.9 in 21; in 16x16 blocks 68 and 61; [50176 x 1536 x 256], 8 tiles, keep 0.75: 62.7 and 54.2 in 24).
+int64_t wide_max_splits(int64_t M, int64_t K, int64_t N, int bs) {
+  const int64_t rows = ceil_div(M, bs), fill = 256 / wide_tiles(K, N);
+  const int64_t s = fill < 16 ? 16 : fill < 24 ? fill : 24;
+  return rows < s ? rows : s;
+}
+
 // The plan of one launch.  The products [0, whole) are not split: one workgroup runs all the
 // block-rows of a tile and writes dW itself.  The others are split `splits` ways along the
 // contraction, into partial tiles that a second kernel adds up.  With many tiles the first
@@ -597,11 +605,10 @@ struct WidePlan {
 // first copies, write-out); work is done in rounds of 256 workgroups; a partial tile is
 // written once and read once by the reduction.  Measured orders of magnitude on MI355X;
 // only the choice depends on them.
-WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *rows, const double *bytes_out, int m) {
+WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *most, const double *bytes_out, int m) {
   const double us_stage = 0.5, fixed_stages = 30.0, bytes_per_us = 3.0e6;
-  int64_t min_rows = rows[0];
-  for (int i = 1; i < m; ++i) min_rows = rows[i] < min_rows ? rows[i] : min_rows;
-  int64_t s_max = min_rows < kWideMaxSplits ? min_rows : kWideMaxSplits;
+  int64_t s_max = most[0];
+  for (int i = 1; i < m; ++i) s_max = most[i] < s_max ? most[i] : s_max;
   if (s_max < 1) s_max = 1;
   WidePlan best{0, 1};
   double best_cost = 0;
@@ -682,15 +689,15 @@ uint32_t wide_cut(const WideBatch &b, int lo, int hi, uint32_t *begin) {
 template <int BS>
 int wide_launch(const DwJob *const *jobs, int m, hipStream_t s, std::vector<ReduceJob> *later) {
   if (m <= 0) return BSR_OK;
-  int64_t tiles[kWideBatchMax], stages[kWideBatchMax], rows[kWideBatchMax];
+  int64_t tiles[kWideBatchMax], stages[kWideBatchMax], most[kWideBatchMax];
   double bytes_out[kWideBatchMax];
   for (int i = 0; i < m; ++i) {
     tiles[i] = wide_tiles(jobs[i]->K, jobs[i]->N);
-    rows[i] = ceil_div(jobs[i]->M, (int64_t)BS);
-    stages[i] = ceil_div(rows[i] * BS, (int64_t)32);
+    stages[i] = ceil_div(ceil_div(jobs[i]->M, (int64_t)BS) * BS, (int64_t)32);
+    most[i] = wide_max_splits(jobs[i]->M, jobs[i]->K, jobs[i]->N, BS);
     bytes_out[i] = 4.0 * (double)jobs[i]->K * (double)jobs[i]->N;
   }
-  const WidePlan plan = wide_plan(tiles, stages, rows, bytes_out, m);
+  const WidePlan plan = wide_plan(tiles, stages, most, bytes_out, m);
   WideBatch b;
   ReduceJob red[kWideBatchMax];
   int nred = 0;
@@ -752,8 +759,7 @@ bool dw_wide_supported(int dtype, int br, int bc, const void *values, const void
 
 // Workspace of the wide kernel: partial tiles of the largest number of splits it may pick.
 size_t dw_wide_ws_bytes(int64_t M, int64_t K, int64_t N, int br) {
-  const int64_t rows = ceil_div(M, br);
-  const int64_t s = rows < kWideMaxSplits ? rows : kWideMaxSplits;
+  const int64_t s = wide_max_splits(M, K, N, br);
   return s > 1 ? (size_t)s * (size_t)K * (size_t)N * sizeof(float) : 0;
 }
 
