@@ -142,6 +142,49 @@ __global__ __launch_bounds__(256) void splitk_reduce4_kernel(const float4 *__res
   }
 }
 
+// ... and for many splits of a small dW, where the kernels above are a few workgroups with a long chain of loads each: a
+// thread has eight partial matrices' loads on their way, and `groups` threads share an output vector, each with a part of
+// the splits; their sums meet in LDS.  Always the same order: splits ascending inside a part, then the parts.  V = float4 (as
+// above) or float.  (Partial matrices of [196 x 196], 64 splits: 7.5 -> 4.0 us; whole dW calls [26212 x 141 x 130] 27.1 -> 16.7,
+// [13620 x 96 x 32] 14.6 -> 11.4.  Of few splits the simpler kernels are faster: [3000 x 400 x 300], nine splits, 13.7 and 14.8.)
+constexpr int kReduceInFlight = 8;
+__device__ __forceinline__ float4 add(const float4 &a, const float4 &b) {
+  return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+__device__ __forceinline__ float add(float a, float b) { return a + b; }
+
+template <typename V>
+__global__ __launch_bounds__(256) void splitk_reduce_shared_kernel(const V *__restrict__ partial, int splits, uint32_t groups,
+                                                                   int64_t K, int64_t nv, float *__restrict__ dW,
+                                                                   int64_t lddw, int accumulate) {
+  __shared__ V sh[256];
+  const int64_t total = K * nv;
+  const uint32_t per = 256u / groups, t = threadIdx.x, o = t % per, g = t / per;
+  const int lo = (int)((uint32_t)splits * g / groups), hi = (int)((uint32_t)splits * (g + 1) / groups);
+  for (int64_t base = (int64_t)blockIdx.x * per; base < total; base += (int64_t)gridDim.x * per) {
+    const int64_t e = base + o;
+    const V *src = partial + (e < total ? e : total - 1);
+    V s{};
+    for (int sp = lo; sp < hi; sp += kReduceInFlight) {
+      V v[kReduceInFlight];
+#pragma unroll
+      for (int k = 0; k < kReduceInFlight; ++k) v[k] = src[(int64_t)(sp + k < hi ? sp + k : hi - 1) * total];
+#pragma unroll
+      for (int k = 0; k < kReduceInFlight; ++k)
+        if (sp + k < hi) s = add(s, v[k]);
+    }
+    sh[t] = s;
+    __syncthreads();
+    if (g == 0 && e < total) {
+      for (uint32_t q = 1; q < groups; ++q) s = add(s, sh[q * per + o]);
+      const int64_t k = e / nv;
+      V *dst = reinterpret_cast<V *>(dW + k * lddw) + (e - k * nv);
+      *dst = accumulate ? add(*dst, s) : s;
+    }
+    __syncthreads();
+  }
+}
+
 // The same sums for several tensors in one launch (item = tensor, found from the prefix of
 // workgroup counts); per element the order of the additions is that of the kernels above.
 struct ReduceBatch {
@@ -197,7 +240,22 @@ int launch_splitk_reduce(const float *partial, int splits, int64_t K, int64_t N,
                          int64_t lddw, int accumulate, hipStream_t s) {
   const int64_t total = K * N;
   if (total == 0) return BSR_OK;
-  if (N % 4 == 0 && lddw % 4 == 0 && (uintptr_t)dW % 16 == 0 && (uintptr_t)partial % 16 == 0) {
+  const bool vec = N % 4 == 0 && lddw % 4 == 0 && (uintptr_t)dW % 16 == 0 && (uintptr_t)partial % 16 == 0;
+  // (threads share an output while that leaves the chip room, and each has four splits or more)
+  const int64_t outs = vec ? total / 4 : total;
+  unsigned groups = 1;
+  while (groups < 16 && outs * groups < 512 * 256 && splits >= 8 * (int)groups) groups *= 2;
+  if (splits >= 16 && groups > 1) {
+    const int64_t wgs = ceil_div(outs * groups, (int64_t)256);
+    if (vec)
+      hipLaunchKernelGGL((splitk_reduce_shared_kernel<float4>), dim3((unsigned)wgs), dim3(256), 0, s,
+                         reinterpret_cast<const float4 *>(partial), splits, groups, K, N / 4, dW, lddw, accumulate);
+    else
+      hipLaunchKernelGGL((splitk_reduce_shared_kernel<float>), dim3((unsigned)wgs), dim3(256), 0, s, partial, splits, groups, K,
+                         N, dW, lddw, accumulate);
+    return check_launch();
+  }
+  if (vec) {
     const int64_t blocks = ceil_div(total / 4, 256);
     hipLaunchKernelGGL(splitk_reduce4_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)),
                        dim3(256), 0, s, reinterpret_cast<const float4 *>(partial), splits, K, N / 4,

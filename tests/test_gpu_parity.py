@@ -1374,3 +1374,21 @@ def check_large_dw(M, K, N, bs, keep, copies):
 ])
 def test_dw_on_both_sides_of_the_wide_tiles_amount_of_work(M, K, N, bs, keep, copies):
     check_large_dw(M, K, N, bs, keep, copies)
+
+
+@pytest.mark.parametrize("M,K,N,pad", [(6000, 40, 30, 0), (6000, 40, 31, 1), (9000, 100, 33, 0), (3000, 14, 4, 4), (12000, 130, 128, 4), (2100, 70, 1, 0)])
+def test_dw_of_many_splits_of_a_small_matrix(M, K, N, pad):
+    """Partial matrices that several threads share per entry: vectors and single entries, the last workgroup in part, dW with a
+    pitch of its own and accumulated into.  Tolerance: binary32 accumulation, as in the other parity tests; 1e-4 of the
+    largest entry or of the 0.25 it is added to."""
+    X, dY = rand_pair(M, K, N, "f32", seed=M + N)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, 14, 14, 0.6)
+    ref = oracle.dw(oracle.mask_dense(X, 14, 14, o_mask), dY)
+    rp, ci, val, dYd = torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda(), to_dev(o_val), to_dev(dY)
+    out = torch.full((K, N + pad), 0.25, dtype=torch.float32, device="cuda")
+    dW = B.bsr_t_dense_matmul(rp, ci, val, M, K, 14, 14, dYd)
+    B.bsr_t_dense_matmul(rp, ci, val, M, K, 14, 14, dYd, dW=out[:, :N], accumulate=True)
+    torch.cuda.synchronize()
+    assert dw_error(dW.cpu().numpy(), ref) <= DW_TOL["f32"]
+    assert dw_error(out[:, :N].cpu().numpy() - 0.25, ref) <= 1e-4 * max(1.0, 0.25 / np.max(np.abs(ref)))
+    assert bool((out[:, N:] == 0.25).all())
