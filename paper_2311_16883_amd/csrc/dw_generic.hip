@@ -153,15 +153,35 @@ __device__ __forceinline__ float4 add(const float4 &a, const float4 &b) {
 }
 __device__ __forceinline__ float add(float a, float b) { return a + b; }
 
+struct SharedReduceBatch {
+  ReduceJob it[kReduceBatchMax];
+  uint32_t wg_begin[kReduceBatchMax + 1];
+  uint8_t groups[kReduceBatchMax];
+};
+
+inline __host__ __device__ bool reduce_by_vectors(const ReduceJob &j) {
+  return j.N % 4 == 0 && j.lddw % 4 == 0 && (uintptr_t)j.dW % 16 == 0 && (uintptr_t)j.partial % 16 == 0;
+}
+
+inline int64_t reduce_outputs(const ReduceJob &j) { return reduce_by_vectors(j) ? j.K * j.N / 4 : j.K * j.N; }
+
+// Threads that share an output of a product, 1: the simpler kernels.  (While that leaves the chip room, `outs` = outputs of
+// all products of the launch, and each has four splits or more.)
+int reduce_groups(const ReduceJob &j, int64_t outs) {
+  if (j.splits < 16) return 1;
+  int groups = 1;
+  while (groups < 16 && outs * groups < 512 * 256 && j.splits >= 8 * groups) groups *= 2;
+  return groups;
+}
+
 template <typename V>
-__global__ __launch_bounds__(256) void splitk_reduce_shared_kernel(const V *__restrict__ partial, int splits, uint32_t groups,
-                                                                   int64_t K, int64_t nv, float *__restrict__ dW,
-                                                                   int64_t lddw, int accumulate) {
-  __shared__ V sh[256];
-  const int64_t total = K * nv;
+__device__ __forceinline__ void shared_reduce_body(const ReduceJob &it, const uint32_t groups, const uint32_t wg,
+                                                   const uint32_t wgs, V *sh) {
+  const int64_t nv = it.N / (int64_t)(sizeof(V) / 4), total = it.K * nv;
+  const V *partial = reinterpret_cast<const V *>(it.partial);
   const uint32_t per = 256u / groups, t = threadIdx.x, o = t % per, g = t / per;
-  const int lo = (int)((uint32_t)splits * g / groups), hi = (int)((uint32_t)splits * (g + 1) / groups);
-  for (int64_t base = (int64_t)blockIdx.x * per; base < total; base += (int64_t)gridDim.x * per) {
+  const int lo = (int)((uint32_t)it.splits * g / groups), hi = (int)((uint32_t)it.splits * (g + 1) / groups);
+  for (int64_t base = (int64_t)wg * per; base < total; base += (int64_t)wgs * per) {
     const int64_t e = base + o;
     const V *src = partial + (e < total ? e : total - 1);
     V s{};
@@ -178,11 +198,31 @@ __global__ __launch_bounds__(256) void splitk_reduce_shared_kernel(const V *__re
     if (g == 0 && e < total) {
       for (uint32_t q = 1; q < groups; ++q) s = add(s, sh[q * per + o]);
       const int64_t k = e / nv;
-      V *dst = reinterpret_cast<V *>(dW + k * lddw) + (e - k * nv);
-      *dst = accumulate ? add(*dst, s) : s;
+      V *dst = reinterpret_cast<V *>(it.dW + k * it.lddw) + (e - k * nv);
+      *dst = it.accumulate ? add(*dst, s) : s;
     }
     __syncthreads();
   }
+}
+
+template <typename V>
+__global__ __launch_bounds__(256) void splitk_reduce_shared_kernel(ReduceJob job, uint32_t groups) {
+  __shared__ V sh[256];
+  shared_reduce_body<V>(job, groups, blockIdx.x, gridDim.x, sh);
+}
+
+__global__ __launch_bounds__(256) void splitk_reduce_shared_batched_kernel(SharedReduceBatch b, int n) {
+  __shared__ float4 sh[256];
+  int i = 0;
+  while (i + 1 < n && blockIdx.x >= b.wg_begin[i + 1]) ++i;
+  const ReduceJob &it = b.it[i];
+  const uint32_t wg = blockIdx.x - b.wg_begin[i], wgs = b.wg_begin[i + 1] - b.wg_begin[i];
+  if (reduce_by_vectors(it)) shared_reduce_body<float4>(it, b.groups[i], wg, wgs, sh);
+  else shared_reduce_body<float>(it, b.groups[i], wg, wgs, reinterpret_cast<float *>(sh));
+}
+
+inline int64_t shared_reduce_wgs(const ReduceJob &j, int groups) {
+  return ceil_div(reduce_outputs(j) * groups, (int64_t)256);
 }
 
 // The same sums for several tensors in one launch (item = tensor, found from the prefix of
@@ -240,19 +280,13 @@ int launch_splitk_reduce(const float *partial, int splits, int64_t K, int64_t N,
                          int64_t lddw, int accumulate, hipStream_t s) {
   const int64_t total = K * N;
   if (total == 0) return BSR_OK;
-  const bool vec = N % 4 == 0 && lddw % 4 == 0 && (uintptr_t)dW % 16 == 0 && (uintptr_t)partial % 16 == 0;
-  // (threads share an output while that leaves the chip room, and each has four splits or more)
-  const int64_t outs = vec ? total / 4 : total;
-  unsigned groups = 1;
-  while (groups < 16 && outs * groups < 512 * 256 && splits >= 8 * (int)groups) groups *= 2;
-  if (splits >= 16 && groups > 1) {
-    const int64_t wgs = ceil_div(outs * groups, (int64_t)256);
-    if (vec)
-      hipLaunchKernelGGL((splitk_reduce_shared_kernel<float4>), dim3((unsigned)wgs), dim3(256), 0, s,
-                         reinterpret_cast<const float4 *>(partial), splits, groups, K, N / 4, dW, lddw, accumulate);
-    else
-      hipLaunchKernelGGL((splitk_reduce_shared_kernel<float>), dim3((unsigned)wgs), dim3(256), 0, s, partial, splits, groups, K,
-                         N, dW, lddw, accumulate);
+  const ReduceJob job{partial, dW, K, N, lddw, splits, accumulate};
+  const int groups = reduce_groups(job, reduce_outputs(job));
+  const bool vec = reduce_by_vectors(job);
+  if (groups > 1) {
+    const dim3 grid((unsigned)shared_reduce_wgs(job, groups));
+    if (vec) hipLaunchKernelGGL((splitk_reduce_shared_kernel<float4>), grid, dim3(256), 0, s, job, (uint32_t)groups);
+    else hipLaunchKernelGGL((splitk_reduce_shared_kernel<float>), grid, dim3(256), 0, s, job, (uint32_t)groups);
     return check_launch();
   }
   if (vec) {
@@ -272,15 +306,30 @@ int launch_splitk_reduce_batched(const ReduceJob *jobs, int n, hipStream_t s) {
   for (int i0 = 0; i0 < n; i0 += kReduceBatchMax) {
     const int m = n - i0 < kReduceBatchMax ? n - i0 : kReduceBatchMax;
     ReduceBatch b;
-    uint32_t wgs = 0;
+    SharedReduceBatch c;
+    uint32_t wgs = 0, shared_wgs = 0;
+    int nb = 0, nc = 0;
+    int64_t outs = 0;
+    for (int i = 0; i < m; ++i) outs += reduce_outputs(jobs[i0 + i]);
     for (int i = 0; i < m; ++i) {
-      b.it[i] = jobs[i0 + i];
-      b.wg_begin[i] = wgs;
-      const int64_t blocks = ceil_div(ceil_div(jobs[i0 + i].K * jobs[i0 + i].N, 4), 256);
+      const ReduceJob &j = jobs[i0 + i];
+      const int groups = reduce_groups(j, outs);
+      if (groups > 1) {
+        c.it[nc] = j;
+        c.groups[nc] = (uint8_t)groups;
+        c.wg_begin[nc++] = shared_wgs;
+        shared_wgs += (uint32_t)shared_reduce_wgs(j, groups);
+        continue;
+      }
+      b.it[nb] = j;
+      b.wg_begin[nb++] = wgs;
+      const int64_t blocks = ceil_div(ceil_div(j.K * j.N, 4), 256);
       wgs += (uint32_t)(blocks < 1 ? 1 : (blocks < 2048 ? blocks : 2048));
     }
-    b.wg_begin[m] = wgs;
-    hipLaunchKernelGGL(splitk_reduce_batched_kernel, dim3(wgs), dim3(256), 0, s, b, m);
+    b.wg_begin[nb] = wgs;
+    c.wg_begin[nc] = shared_wgs;
+    if (nb > 0) hipLaunchKernelGGL(splitk_reduce_batched_kernel, dim3(wgs), dim3(256), 0, s, b, nb);
+    if (nc > 0) hipLaunchKernelGGL(splitk_reduce_shared_batched_kernel, dim3(shared_wgs), dim3(256), 0, s, c, nc);
     const int rc = check_launch();
     if (rc != BSR_OK) return rc;
   }
