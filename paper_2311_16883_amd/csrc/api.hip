@@ -75,6 +75,18 @@ double wide_work(int64_t M, int64_t K, int64_t N, int br) {
   return (double)M * (double)K * (double)N / (br == 16 ? 2.5e10 : 5.0e9);
 }
 
+// Block shapes without a kernel of their own: whether re-tiling and the matrix cores (two or three launches, 11 .. 19 us at the
+// least) take less time than the general kernel, which walks the block-rows one after the other and multiplies on the
+// vector units, the slower the fewer rows a block has (tall blocks: by the size of the activation alone; [700 x 100 x 300] in 128x16
+// blocks 29 general and 14 re-tiled).  Measured over 60 shapes up to 3000 x 600 x 2000, in us: [2543 x 26 x 60]
+// in 1x32 blocks 63 general and 13 re-tiled, [563 x 19 x 1069] 28 and 15, [412 x 213 x 26] in 7x5 blocks 9 and 19, [209 x 328 x 190]
+// 14 and 21, [522 x 484 x 131] in 8x8 blocks 25 and 16, [158 x 26 x 932] 10 and 14.
+bool retiling_pays(int64_t M, int64_t K, int64_t N, int br) {
+  if (br > 16) return M * K > 65536;
+  const double general_us = 9.0 + 0.025 * (double)ceil_div(M, br) + 1e-6 * (double)M * (double)K * (double)N * (0.25 + 0.75 / br);
+  return general_us > 15.3;
+}
+
 bool use_wide_single(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K, int64_t N,
                      int64_t lddy) {
   return dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy) && wide_parallelism(M, K, N, br) >= 128 &&
@@ -270,7 +282,7 @@ int bsr_t_dense_matmul(const int32_t *row_ptr, const int32_t *col_idx, const voi
                           ws, ws_bytes, static_cast<hipStream_t>(stream));
   // other block shapes: re-tiled into 32x32 blocks for the matrix-core kernel, unless the
   // problem is so small that the single launch of the general kernel is the faster way
-  if (M * K > 65536 && dw_reblock_supported(dtype, br, bc, M, K, N, lddy) &&
+  if (retiling_pays(M, K, N, br) && dw_reblock_supported(dtype, br, bc, M, K, N, lddy) &&
       ws_bytes >= dw_reblock_ws_bytes(dtype, M, K, N))
     return launch_dw_reblocked(dtype, row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw,
                                accumulate, ws, ws_bytes, static_cast<hipStream_t>(stream));

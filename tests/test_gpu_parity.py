@@ -1293,15 +1293,15 @@ def test_dw_entries_of_a_block_row_in_any_order(M, K, N, b, dtype):
 
 
 @pytest.mark.parametrize("M,K,N,br,bc,dtype,shift", [
-    (130, 1100, 40, 1, 64, "bf16", 0),       # three column chunks, one wave of rows beyond a tile
-    (97, 1100, 24, 1, 64, "bf16", 2),        # ... values on a 4-byte boundary
-    (97, 1100, 24, 1, 64, "f32", 1),
+    (130, 1100, 100, 1, 64, "bf16", 0),       # three column chunks, one wave of rows beyond a tile
+    (97, 1100, 100, 1, 64, "bf16", 2),        # ... values on a 4-byte boundary
+    (97, 1100, 100, 1, 64, "f32", 1),
     (600, 130, 33, 1, 1, "f32", 0),          # the table of the chunk is full
     (600, 130, 33, 1, 1, "bf16", 1),
     (300, 300, 40, 48, 48, "bf16", 0),       # blocks across tiles and chunks
-    (300, 600, 40, 5, 7, "bf16", 3),
+    (300, 600, 200, 5, 7, "bf16", 3),
     (210, 400, 16, 33, 96, "f32", 0),
-    (40, 5000, 16, 3, 4600, "bf16", 0),      # blocks wider than any chunk
+    (40, 5000, 150, 3, 4600, "bf16", 0),      # blocks wider than any chunk
     (5000, 40, 16, 4600, 6, "f32", 0),       # ... taller than any tile
 ])
 def test_dw_re_tiling_of_any_block_shape(M, K, N, br, bc, dtype, shift):
@@ -1392,3 +1392,21 @@ def test_dw_of_many_splits_of_a_small_matrix(M, K, N, pad):
     assert dw_error(dW.cpu().numpy(), ref) <= DW_TOL["f32"]
     assert dw_error(out[:, :N].cpu().numpy() - 0.25, ref) <= 1e-4 * max(1.0, 0.25 / np.max(np.abs(ref)))
     assert bool((out[:, N:] == 0.25).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,K,N,br,bc", [
+    (254, 60, 16, 1, 32), (250, 50, 30, 1, 8),        # few and more block-rows than the general kernel should walk
+    (1760, 40, 9, 7, 5), (1770, 40, 9, 7, 5),
+    (300, 300, 30, 7, 5), (300, 300, 250, 7, 5),      # little and more to multiply
+    (64, 2000, 40, 16, 48), (64, 2000, 200, 16, 48),
+])
+def test_dw_of_small_products_general_and_re_tiled(M, K, N, br, bc, dtype):
+    """Both sides of the line between the general kernel and the re-tiling.  Tolerance as in the other parity tests."""
+    X, dY = rand_pair(M, K, N, dtype, seed=M + K + N)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, br, bc, 0.5)
+    ref = oracle.dw(oracle.mask_dense(X, br, bc, o_mask), dY)
+    rp, ci = torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda()
+    dW = B.bsr_t_dense_matmul(rp, ci, to_dev(o_val.reshape(-1, bc)).reshape(o_val.shape), M, K, br, bc, to_dev(dY))
+    torch.cuda.synchronize()
+    assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
