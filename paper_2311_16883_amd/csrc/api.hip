@@ -450,9 +450,11 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
     }
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // too few tiles to fill the GPU even with a deep split, or too little to multiply: the narrow-tile kernel suits those better
+  // too few tiles to fill the GPU even with a deep split, or too little to multiply: the 128 x 128 tiles suit those better,
+  // where they can address the operands (half the activation that the wide tiles take)
   if (!wide.empty() && (wide_par < 128 || work < 1.0)) {
-    batch.insert(batch.end(), wide.begin(), wide.end());
+    for (const DwJob &j : wide)
+      (dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy) ? batch : single).push_back(j);
     wide.clear();
   }
   // the partial tiles of both kinds of products are added up by one launch behind the two kernels

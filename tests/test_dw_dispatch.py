@@ -1,0 +1,68 @@
+"""Which kernels a dW call would launch, and with what workspace: the host code runs against a recorder of launches
+(tests/launch_recorder.c), at sizes that need no memory here.  CPU only."""
+import json
+import re
+import subprocess
+import sys
+from pathlib import Path
+
+import pytest
+
+from paper_2311_16883_amd import binding as B
+
+HERE = Path(__file__).resolve().parent
+LIB = HERE.parent / "paper_2311_16883_amd" / "libbsr_actprune.so"
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    so = tmp_path_factory.mktemp("recorder") / "liblaunch_recorder.so"
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(so), str(HERE / "launch_recorder.c")], check=True)
+    B.lib()                                  # built if it is not there yet
+
+    def record(calls, lib=LIB):
+        """Per call: return code, queried workspace, launched kernels as "name<leading template arguments>"."""
+        r = subprocess.run([sys.executable, str(HERE / "recorded_calls.py"), str(so), str(lib)], input=json.dumps(calls),
+                           capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr
+        got = json.loads(r.stdout)
+        for g in got:
+            g["kernels"] = [(kernel_name(n), w) for n, w in g["kernels"]]
+            g["names"] = [n for n, _ in g["kernels"]]
+        return got
+
+    return record
+
+
+def kernel_name(mangled):
+    """dw_wide<16>, dw_mfma<16>, dw_generic, reblock, dw_narrow, reduce, from the mangled names."""
+    for key, name in (("dw_wide_batched_kernel", "dw_wide"), ("dw_mfma_batched_kernel", "dw_mfma"), ("dw_mfma_kernel", "dw_mfma"),
+                      ("dw_narrow_batched_kernel", "dw_narrow")):
+        if key in mangled:
+            return "%s<%s>" % (name, re.search(r"Li(\d+)E", mangled).group(1))
+    for key, name in (("dw_generic_kernel", "dw_generic"), ("reblock_kernel", "reblock"), ("splitk_reduce", "reduce")):
+        if key in mangled:
+            return name
+    return mangled
+
+
+def one(M, K, N, b, **more):
+    return {"items": [dict(M=M, K=K, N=N, b=b, **more)]}
+
+
+def batch(*items):
+    return {"items": [dict(zip("MKNb", it)) if isinstance(it, tuple) else it for it in items], "batched": True}
+
+
+def products(got):
+    return [n for n in got["names"] if n != "reduce"]
+
+
+@pytest.mark.parametrize("M,K,N", [(4000, 300000, 8), (4096, 270000, 8), (2900000, 384, 384), (1 << 20, 1024, 8)])
+@pytest.mark.parametrize("copies", [1, 2])
+def test_batched_dw_beyond_2_gib_is_not_given_to_the_kernel_that_cannot_address_it(recorder, M, K, N, copies):
+    """16x16 blocks of 2 GiB and more, too little to multiply (or too few tiles) for the wide tiles: the 128x128 kernel takes
+    offsets from 2 GiB on for "pruned"; the general kernel multiplies them."""
+    got, = recorder([batch(*[(M, K, N, 16)] * copies)])
+    assert got["rc"] == 0
+    assert products(got) == ["dw_generic"] * copies
