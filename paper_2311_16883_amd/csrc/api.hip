@@ -147,14 +147,15 @@ size_t bsr_workspace_bytes(int op, int64_t M, int64_t K, int64_t N, int br, int 
       {
         size_t a = dw_generic_ws_bytes(M, K, N, br, bc);
         if (dw_mfma_supported(dtype, br, bc, nullptr, M, K, N, N)) {
-          size_t b = dw_mfma_ws_bytes(dtype, M, K, N, br, bc);
-          if (dw_wide_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
-            const size_t c = dw_wide_ws_bytes(M, K, N, br);
-            if (c > b) b = c;
-          }
+          const size_t b = dw_mfma_ws_bytes(dtype, M, K, N, br, bc);
           if (b > a) a = b;
         } else if (dw_reblock_supported(dtype, br, bc, M, K, N, N)) {
           const size_t b = dw_reblock_ws_bytes(dtype, M, K, N);
+          if (b > a) a = b;
+        }
+        // (the wide tiles take activations that the 128 x 128 tiles don't: from 2 GiB up to 4 GiB)
+        if (dw_wide_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
+          const size_t b = dw_wide_ws_bytes(M, K, N, br);
           if (b > a) a = b;
         }
         if (dw_narrow_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {

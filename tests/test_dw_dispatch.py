@@ -66,3 +66,28 @@ def test_batched_dw_beyond_2_gib_is_not_given_to_the_kernel_that_cannot_address_
     got, = recorder([batch(*[(M, K, N, 16)] * copies)])
     assert got["rc"] == 0
     assert products(got) == ["dw_generic"] * copies
+
+
+def operands_below(M, K, b, gib):
+    """Stored blocks, all kept, in bytes: below gib GiB?"""
+    return -(-M // b) * -(-K // b) * b * b * 2 < gib << 30
+
+
+@pytest.mark.parametrize("b", [16, 32, 64])
+def test_dw_calls_with_the_queried_workspace_are_taken(recorder, b):
+    """Activations around 2 GiB, where the 128x128 tiles end, and 4 GiB, where the wide tiles end, alone and in batches of two:
+    exactly the workspace that the query names is enough, whatever kernel the call takes."""
+    shapes = [(700000, 1536, 1536), (1500000, 768, 768), (1000000, 1536, 512), (400000, 3072, 768), (350000, 3072, 768),
+              (349000, 3072, 768), (699000, 1536, 1536), (698000, 3072, 768), (700000, 3072, 768), (2900000, 384, 384),
+              (4000, 300000, 8), (4000, 300000, 1024), (1 << 20, 1024, 8), (1 << 20, 1024, 136), (5000000, 400, 136)]
+    single = recorder([one(M, K, N, b) for M, K, N in shapes])
+    pairs = recorder([batch((M, K, N, b), (M, K, N, b)) for M, K, N in shapes])
+    mixed = recorder([batch((M, K, N, b), (6272, 384, 1536, b)) for M, K, N in shapes])
+    assert [g["rc"] for g in single + pairs + mixed] == [0] * 3 * len(shapes)
+    kernels = {n for g in single for n in g["names"]}
+    assert {f"dw_wide<{b}>", "dw_generic"} <= kernels
+    for (M, K, N), g in zip(shapes, single):
+        if not operands_below(M, K, b, 2):
+            assert "dw_mfma<%d>" % b not in g["names"]
+        if not operands_below(M, K, b, 4):
+            assert products(g) == ["dw_generic"]

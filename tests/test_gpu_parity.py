@@ -1410,3 +1410,31 @@ def test_dw_of_small_products_general_and_re_tiled(M, K, N, br, bc, dtype):
     dW = B.bsr_t_dense_matmul(rp, ci, to_dev(o_val.reshape(-1, bc)).reshape(o_val.shape), M, K, br, bc, to_dev(dY))
     torch.cuda.synchronize()
     assert dw_error(dW.cpu().numpy(), ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
+
+
+@pytest.mark.parametrize("b", [16, 32, 64])
+def test_dw_of_more_than_2_gib_of_blocks(b):
+    """More stored bytes than the 128x128 tiles can address: the wide tiles, alone and in a batch, with the workspace that the
+    queries name.  The reference is the binary64 product of the masked matrix."""
+    M, K, N, keep = 360100, 3064, 776, 0.98
+    print(f"[case] dW of {M}x{K}, N={N}, block={b}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(b)
+    X = torch.randn(M, K, generator=gen, device="cuda", dtype=torch.bfloat16)
+    dY = (torch.randn(M, N, generator=gen, device="cuda") * 1e-3).to(torch.bfloat16)
+    nbr, nbc = -(-M // b), -(-K // b)
+    mask = B.bsr_score_select(X, b, b, keep)
+    n_keep = B.bsr_keep_count(nbr * nbc, keep)
+    assert n_keep * b * b * 2 > 1 << 31
+    rp, ci, val = B.bsr_compress(X, b, b, mask, n_keep)
+    got = [B.bsr_t_dense_matmul(rp, ci, val, M, K, b, b, dY)]
+    got += B.bsr_t_dense_matmul_batched(B.MatmulBatch([(rp, ci, val, M, K, b, b, dY)] * 2))
+    ref = torch.zeros(K, N, device="cuda", dtype=torch.float64)
+    step = 320 * b
+    for m in range(0, M, step):
+        rows = min(step, M - m)
+        kept = mask.view(nbr, nbc)[m // b:m // b + 320].repeat_interleave(b, 0)[:rows].repeat_interleave(b, 1)[:, :K]
+        ref += (X[m:m + rows].double() * kept).t().contiguous() @ dY[m:m + rows].double()
+    torch.cuda.synchronize()
+    for dW in got:
+        assert dw_error(dW.cpu().numpy(), ref.cpu().numpy()) <= DW_TOL_DERIVED
