@@ -68,9 +68,12 @@ bool use_narrow(int dtype, int br, int bc, const void *values, const void *dY, i
 // Work from which a call's products are worth the wide kernel, in units of that: its start, its write-out and its few large
 // workgroups cost more than the 128 x 128 tiles until there is enough to multiply.  ([6272 x 384 x 1536] in 32x32 blocks, keep
 // 0.5: 27.6 us wide, 22.3 in 128 x 128 tiles; [800 x 2048 x 2048] 21.6 and 16.0; [12544 x 768 x 768] 31.6 and 34.3;
-// [25088 x 1536 x 384] 39.6 and 43.1; two products [3136 x 384 x 1536] 29.2 and 24.8, [6272 x 384 x 1536] 31.4 and 32.9.  16x16 blocks, where the wide kernel
-// copies by halves of a piece: [25088 x 1536 x 384] 48.9 and 46.7, [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536],
-// keep 0.25, 68 and 87.)
+// [25088 x 1536 x 384] 39.6 and 43.1; two products [3136 x 384 x 1536] 29.2 and 24.8, [6272 x 384 x 1536] 31.4 and 32.9.
+// 16x16 blocks, where the wide kernel copies by halves of a piece: [25088 x 1536 x 384] 48.9 and 46.7, [23896 x 880 x 2016]
+// 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87.)  Only where the 128 x 128 tiles can address the operands: the
+// general kernel, the other choice, takes 1.1 .. 9 times as long ([1000 x 1000 x 4000] with a far pitch of dY 277 and 31 us,
+// [4000 x 300000 x 8] 10.1 and 6.3 ms), or as long where there is next to nothing to multiply ([512 x 3072 x 8] 17 and 17,
+// [128 x 6144 x 8] 13 and 15).
 double wide_work(int64_t M, int64_t K, int64_t N, int br) {
   return (double)M * (double)K * (double)N / (br == 16 ? 2.5e10 : 5.0e9);
 }
@@ -90,7 +93,7 @@ bool retiling_pays(int64_t M, int64_t K, int64_t N, int br) {
 bool use_wide_single(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K, int64_t N,
                      int64_t lddy) {
   return dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy) && wide_parallelism(M, K, N, br) >= 128 &&
-         wide_work(M, K, N, br) >= 1.0;
+         (wide_work(M, K, N, br) >= 1.0 || !dw_mfma_supported(dtype, br, bc, values, M, K, N, lddy));
 }
 
 }  // namespace
@@ -454,9 +457,12 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
   // too few tiles to fill the GPU even with a deep split, or too little to multiply: the 128 x 128 tiles suit those better,
   // where they can address the operands (half the activation that the wide tiles take)
   if (!wide.empty() && (wide_par < 128 || work < 1.0)) {
-    for (const DwJob &j : wide)
-      (dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy) ? batch : single).push_back(j);
-    wide.clear();
+    std::vector<DwJob> stay;
+    for (const DwJob &j : wide) {
+      const bool mfma = dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy);
+      (mfma ? batch : wide_par < 128 ? single : stay).push_back(j);
+    }
+    wide.swap(stay);
   }
   // the partial tiles of both kinds of products are added up by one launch behind the two kernels
   std::vector<ReduceJob> reductions;

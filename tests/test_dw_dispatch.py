@@ -58,14 +58,16 @@ def products(got):
     return [n for n in got["names"] if n != "reduce"]
 
 
-@pytest.mark.parametrize("M,K,N", [(4000, 300000, 8), (4096, 270000, 8), (2900000, 384, 384), (1 << 20, 1024, 8)])
+@pytest.mark.parametrize("M,K,N,other", [(4000, 300000, 8, "dw_wide<16>"), (4096, 270000, 8, "dw_wide<16>"),
+                                         (2900000, 384, 384, "dw_generic"), (1 << 20, 1024, 8, "dw_generic")])
 @pytest.mark.parametrize("copies", [1, 2])
-def test_batched_dw_beyond_2_gib_is_not_given_to_the_kernel_that_cannot_address_it(recorder, M, K, N, copies):
+def test_batched_dw_beyond_2_gib_is_not_given_to_the_kernel_that_cannot_address_it(recorder, M, K, N, other, copies):
     """16x16 blocks of 2 GiB and more, too little to multiply (or too few tiles) for the wide tiles: the 128x128 kernel takes
-    offsets from 2 GiB on for "pruned"; the general kernel multiplies them."""
+    offsets from 2 GiB on for "pruned".  The wide tiles multiply them all the same if they are enough to fill the GPU, else
+    the general kernel."""
     got, = recorder([batch(*[(M, K, N, 16)] * copies)])
     assert got["rc"] == 0
-    assert products(got) == ["dw_generic"] * copies
+    assert products(got) == ([other] if other == "dw_wide<16>" else [other] * copies)
 
 
 def operands_below(M, K, b, gib):
@@ -91,3 +93,16 @@ def test_dw_calls_with_the_queried_workspace_are_taken(recorder, b):
             assert "dw_mfma<%d>" % b not in g["names"]
         if not operands_below(M, K, b, 4):
             assert products(g) == ["dw_generic"]
+
+
+@pytest.mark.parametrize("b", [32, 64])
+def test_dw_with_a_pitch_of_dy_that_only_the_wide_tiles_can_address(recorder, b):
+    """Too little to multiply for the wide tiles, but rows of dY so far apart that the 128x128 tiles cannot take them: the
+    matrix cores all the same, alone and in batches."""
+    far = dict(M=1000, K=1000, N=4000, b=b, lddy=1600000)
+    near = dict(far, M=200, lddy=4000)
+    single, pair, both, plain = recorder([{"items": [far]}, batch(far, far), batch(far, near), {"items": [near]}])
+    assert [g["rc"] for g in (single, pair, both, plain)] == [0] * 4
+    assert products(single) == products(pair) == [f"dw_wide<{b}>"]
+    assert sorted(products(both)) == [f"dw_mfma<{b}>", f"dw_wide<{b}>"]
+    assert products(plain) == [f"dw_mfma<{b}>"]
