@@ -305,25 +305,45 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint3
         store_stream(reinterpret_cast<W *>(vrow + ((int64_t)q * S + e) * kBytes), val);
       }
     } else {
-      // The loads of four blocks together, none of them under a condition (each would wait for the one before): past the last
-      // block that block again, beyond the matrix the first vector of the block-row.  ([25088 x 768] bfloat16, 16x16 blocks:
-      // 16.7 -> 14.6 us; [50176 x 1536], 32x32: 45.2 -> 41.2.)
+      // The loads of four blocks together.  A lane with twelve blocks or more issues all four whatever is left (none waits for
+      // a condition): past the last block that block again, beyond the matrix the first vector of the row.  With fewer the
+      // loads that nobody needs show ([50176 x 384] bfloat16, 16x16 blocks, keep 0.25, 5 blocks a lane or fewer: 13.9 us so and
+      // 12.8 under conditions; 64x64, keep 0.9: 14.6 and 13.3), with more the conditions do ([50176 x 3072], 16x16, keep
+      // 0.9: 133 and 146).  One after the other: 13.1, 13.4 and 167.
       constexpr int kInFlight = 4;
-      for (; q0 < (int)nk; q0 += kInFlight * step) {
-        W val[kInFlight];
-        bool in[kInFlight];
+      if (nk >= 12 * step) {
+        for (; q0 < (int)nk; q0 += kInFlight * step) {
+          W val[kInFlight];
+          bool in[kInFlight];
 #pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-          const int q = q0 + u * step < (int)nk ? q0 + u * step : (int)nk - 1;
-          const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * kBytes;
-          in[u] = row_in && cb < kb;
-          val[u] = *reinterpret_cast<const W *>(src + (in[u] ? cb : 0));
+          for (int u = 0; u < kInFlight; ++u) {
+            const int q = q0 + u * step < (int)nk ? q0 + u * step : (int)nk - 1;
+            const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * kBytes;
+            in[u] = row_in && cb < kb;
+            val[u] = *reinterpret_cast<const W *>(src + (in[u] ? cb : 0));
+          }
+#pragma unroll
+          for (int u = 0; u < kInFlight; ++u) {
+            W out = {};
+            if (in[u]) out = val[u];
+            if (q0 + u * step < (int)nk) store_stream(reinterpret_cast<W *>(vrow + ((int64_t)(q0 + u * step) * S + e) * kBytes), out);
+          }
         }
+      } else {
+        for (; q0 < (int)nk; q0 += kInFlight * step) {
+          W val[kInFlight];
 #pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-          W out = {};
-          if (in[u]) out = val[u];
-          if (q0 + u * step < (int)nk) store_stream(reinterpret_cast<W *>(vrow + ((int64_t)(q0 + u * step) * S + e) * kBytes), out);
+          for (int u = 0; u < kInFlight; ++u) {
+            val[u] = W{};
+            const int q = q0 + u * step;
+            if (q < (int)nk) {
+              const int64_t cb = (int64_t)kept_j[q] * bcb + (int64_t)v * kBytes;
+              if (row_in && cb < kb) val[u] = *reinterpret_cast<const W *>(src + cb);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < kInFlight; ++u)
+            if (q0 + u * step < (int)nk) store_stream(reinterpret_cast<W *>(vrow + ((int64_t)(q0 + u * step) * S + e) * kBytes), val[u]);
         }
       }
     }

@@ -1189,6 +1189,32 @@ def test_conversion_with_shared_block_rows(M, K, dtype):
     check_forward(X, 32, 32, 0.5, label="shared block-rows")
 
 
+@pytest.mark.parametrize("br,bc,dtype,nbc", [
+    (16, 16, "bf16", 110), (16, 16, "bf16", 420), (32, 32, "f32", 50), (64, 64, "bf16", 14), (64, 64, "bf16", 50), (9, 8, "f32", 180),
+])
+def test_conversion_of_block_rows_with_any_number_of_kept_blocks(br, bc, dtype, nbc):
+    """Block-rows of 0, 1, 2 ... nbc kept blocks: the copy takes them in one of two forms, four blocks at a time, and each lane
+    ends on a remainder of its own.  The last block-row and block-column are cut; NaN behind the matrix."""
+    nbr, per = nbc + 1, 16 // (2 if dtype == "bf16" else 4)
+    M, K = nbr * br - br // 2, nbc * bc - bc // per // 2 * per
+    X = rand_pair(M, K, 1, dtype, seed=nbc)[0]
+    rng = np.random.default_rng(nbc)
+    mask = np.zeros((nbr, nbc), dtype=np.uint8)
+    for i in range(nbr):
+        mask[i, rng.permutation(nbc)[:i]] = 1
+    mask = mask[rng.permutation(nbr)].reshape(-1)
+    o_rp, o_ci, o_val = oracle.bsr_from_mask(X, br, bc, mask)
+    Xd = torch.full((M + br, K), float("nan"), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)[:M]
+    Xd.copy_(to_dev(X))
+    md = torch.from_numpy(mask).cuda()
+    outs = [B.bsr_compress(Xd, br, bc, md, len(o_ci))]
+    outs += B.bsr_compress_batched(B.CompressBatch([(Xd, br, bc, md, len(o_ci))] * 2))
+    torch.cuda.synchronize()
+    for rp, ci, val in outs:
+        assert np.array_equal(rp.cpu().numpy(), o_rp) and np.array_equal(ci.cpu().numpy(), o_ci)
+        assert to_host(val).tobytes() == o_val.tobytes()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("b", [14, 16, 32, 64])
 @pytest.mark.parametrize("M,K,N,pad,shift", [
