@@ -90,10 +90,32 @@ bool retiling_pays(int64_t M, int64_t K, int64_t N, int br) {
   return general_us > 15.3;
 }
 
+// Parallelism and work of the products of a call, by block size (16, 32, 64: wide_class), since each size has a launch of its
+// own.  The work of one does not carry another ([25088 x 384 x 1536] in 32x32 blocks with [3136 x 384 x 1536] in 16x16, keep
+// 0.5: 62.5 us both wide, 58.5 so; [6272 x 384 x 1536] in 32x32 and 64x64: 51.0 and 42.2).  Half-filled launches of 32x32 and of
+// 64x64 blocks together are better than none ([14600 x 384 x 896] in both: 54.0 wide, 61.6 in 128 x 128 tiles; two each of
+// [50176 x 384 x 384], keep 0.25, 77 and 97): their parallelism counts as one.
+struct WideSums {
+  int64_t par[3] = {0, 0, 0};
+  double work[3] = {0.0, 0.0, 0.0};
+  void add(int64_t M, int64_t K, int64_t N, int br) {
+    par[wide_class(br)] += wide_parallelism(M, K, N, br);
+    work[wide_class(br)] += wide_work(M, K, N, br);
+  }
+  // `mfma`: the 128 x 128 tiles, the other choice, can address the operands
+  bool pays(int br, bool mfma) const {
+    const int c = wide_class(br);
+    return (c == 0 ? par[0] : par[1] + par[2]) >= 128 && (work[c] >= 1.0 || !mfma);
+  }
+  static int wide_class(int br) { return br == 16 ? 0 : br == 32 ? 1 : 2; }
+};
+
 bool use_wide_single(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K, int64_t N,
                      int64_t lddy) {
-  return dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy) && wide_parallelism(M, K, N, br) >= 128 &&
-         (wide_work(M, K, N, br) >= 1.0 || !dw_mfma_supported(dtype, br, bc, values, M, K, N, lddy));
+  if (!dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy)) return false;
+  WideSums sums;
+  sums.add(M, K, N, br);
+  return sums.pays(br, dw_mfma_supported(dtype, br, bc, values, M, K, N, lddy));
 }
 
 }  // namespace
@@ -421,8 +443,7 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
   if (misaligned(ws, 16)) return BSR_ERR_ALIGN;
   std::vector<DwJob> batch, single, wide, narrow;
   batch.reserve(n);
-  int64_t wide_par = 0;
-  double work = 0.0;
+  WideSums sums;
   size_t off = 0;
   for (int i = 0; i < n; ++i) {
     const bsr_matmul_item &it = items[i];
@@ -445,8 +466,7 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
       narrow.push_back(job);
     } else if (dw_wide_supported(dtype, it.br, it.bc, it.values, it.dY, it.M, it.K, it.N, it.lddy)) {
       wide.push_back(job);
-      wide_par += wide_parallelism(it.M, it.K, it.N, it.br);
-      work += wide_work(it.M, it.K, it.N, it.br);
+      sums.add(it.M, it.K, it.N, it.br);
     } else if (dw_mfma_supported(dtype, it.br, it.bc, it.values, it.M, it.K, it.N, it.lddy)) {
       batch.push_back(job);
     } else {
@@ -456,14 +476,12 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
   hipStream_t s = static_cast<hipStream_t>(stream);
   // too few tiles to fill the GPU even with a deep split, or too little to multiply: the 128 x 128 tiles suit those better,
   // where they can address the operands (half the activation that the wide tiles take)
-  if (!wide.empty() && (wide_par < 128 || work < 1.0)) {
-    std::vector<DwJob> stay;
-    for (const DwJob &j : wide) {
-      const bool mfma = dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy);
-      (mfma ? batch : wide_par < 128 ? single : stay).push_back(j);
-    }
-    wide.swap(stay);
+  std::vector<DwJob> stay;
+  for (const DwJob &j : wide) {
+    const bool mfma = dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy);
+    (sums.pays(j.br, mfma) ? stay : mfma ? batch : single).push_back(j);
   }
+  wide.swap(stay);
   // the partial tiles of both kinds of products are added up by one launch behind the two kernels
   std::vector<ReduceJob> reductions;
   int rc = launch_dw_wide_batched(wide.data(), (int)wide.size(), s, &reductions);

@@ -106,3 +106,16 @@ def test_dw_with_a_pitch_of_dy_that_only_the_wide_tiles_can_address(recorder, b)
     assert products(single) == products(pair) == [f"dw_wide<{b}>"]
     assert sorted(products(both)) == [f"dw_mfma<{b}>", f"dw_wide<{b}>"]
     assert products(plain) == [f"dw_mfma<{b}>"]
+
+
+def test_batched_dw_lines_of_the_wide_tiles_go_by_block_size(recorder):
+    """Products of different block sizes don't share a launch, so they don't lend each other work: each size goes where it
+    would go by itself.  32x32 and 64x64 blocks lend each other tiles."""
+    large, little, small = (25088, 384, 1536, 32), (3136, 384, 1536, 16), (6272, 384, 1536, 64)
+    alone = [products(g) for g in recorder([batch(large), batch(little), batch(small)])]
+    assert alone == [["dw_wide<32>"], ["dw_mfma<16>"], ["dw_mfma<64>"]]
+    got, = recorder([batch(large, little, small)])
+    assert got["rc"] == 0 and sorted(products(got)) == sorted(sum(alone, []))
+    half = [(14600, 384, 896, b) for b in (16, 32, 64)]
+    assert [products(g) for g in recorder([batch(h) for h in half])] == [["dw_mfma<16>"], ["dw_mfma<32>"], ["dw_mfma<64>"]]
+    assert sorted(products(recorder([batch(*half)])[0])) == ["dw_mfma<16>", "dw_wide<32>", "dw_wide<64>"]
