@@ -66,15 +66,22 @@ bool use_narrow(int dtype, int br, int bc, const void *values, const void *dY, i
 }
 
 // Work from which a call's products are worth the wide kernel, in units of that: its start, its write-out and its few large
-// workgroups cost more than the 128 x 128 tiles until there is enough to multiply.  ([6272 x 384 x 1536] in 32x32 blocks, keep
-// 0.5: 27.6 us wide, 22.3 in 128 x 128 tiles; [800 x 2048 x 2048] 21.6 and 16.0; [12544 x 768 x 768] 31.6 and 34.3;
-// [25088 x 1536 x 384] 39.6 and 43.1; two products [3136 x 384 x 1536] 29.2 and 24.8, [6272 x 384 x 1536] 31.4 and 32.9.
-// 16x16 blocks, where the wide kernel copies by halves of a piece: [25088 x 1536 x 384] 48.9 and 46.7, [23896 x 880 x 2016]
-// 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87.)  Only where the 128 x 128 tiles can address the operands: the
-// general kernel, the other choice, takes 1.1 .. 9 times as long ([1000 x 1000 x 4000] with a far pitch of dY 277 and 31 us,
-// [4000 x 300000 x 8] 10.1 and 6.3 ms), or as long where there is next to nothing to multiply ([512 x 3072 x 8] 17 and 17,
-// [128 x 6144 x 8] 13 and 15).
-double wide_work(int64_t M, int64_t K, int64_t N, int br) {
+// workgroups cost more than the 128 x 128 tiles until there is enough to multiply.
+// A product of 32x32 or 64x64 blocks on its own (`alone`): 4.2e9 multiply-adds of whole 128 x 128 tiles, which is what the other
+// kernel would spend its time on.  Over 147 shapes of 1e9 .. 1.6e10 multiply-adds at five keeps that is 1.088 times as fast as
+// wide tiles for all (geometric mean), nowhere more than 7 % slower, and 1.5 % from the better kernel each time; a line at 5e9
+// multiply-adds whatever the tiles is up to 22 % slower ([8147 x 152 x 1968], 2.4e9, of whole tiles 4.3e9: 20.9 us wide, 25.5 in
+// 128 x 128 tiles; [12544 x 1536 x 256], keep 0.25: 26.8 and 31.5; on the other side [6272 x 384 x 1536] 27.6 and 22.3,
+// [1095 x 1240 x 2832] 25.8 and 18.7).
+// Several: 5e9 multiply-adds of them all (whole tiles are no better measure there; of 32x32 blocks
+// two products [3136 x 384 x 1536] 29.2 wide and 24.8, [6272 x 384 x 1536] 31.4 and 32.9).
+// 16x16 blocks, where the wide kernel copies by halves of a piece: 2.5e10 multiply-adds ([25088 x 1536 x 384] 48.9 wide and 46.7,
+// [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87).
+// Only where the 128 x 128 tiles can address the operands: the general kernel, the other choice, takes 1.1 .. 9 times as long
+// ([1000 x 1000 x 4000] with a far pitch of dY 277 and 31 us, [4000 x 300000 x 8] 10.1 and 6.3 ms), or as long where there is
+// next to nothing to multiply ([512 x 3072 x 8] 17 and 17, [128 x 6144 x 8] 13 and 15).
+double wide_work(int64_t M, int64_t K, int64_t N, int br, bool alone) {
+  if (br != 16 && alone) return (double)M * (double)(ceil_div(K, 128) * 128) * (double)(ceil_div(N, 128) * 128) / 4.2e9;
   return (double)M * (double)K * (double)N / (br == 16 ? 2.5e10 : 5.0e9);
 }
 
@@ -96,26 +103,30 @@ bool retiling_pays(int64_t M, int64_t K, int64_t N, int br) {
 // 64x64 blocks together are better than none ([14600 x 384 x 896] in both: 54.0 wide, 61.6 in 128 x 128 tiles; two each of
 // [50176 x 384 x 384], keep 0.25, 77 and 97): their parallelism counts as one.
 struct WideSums {
+  int n[3] = {0, 0, 0};
   int64_t par[3] = {0, 0, 0};
-  double work[3] = {0.0, 0.0, 0.0};
+  double work[3] = {0.0, 0.0, 0.0}, work_alone[3] = {0.0, 0.0, 0.0};
   void add(int64_t M, int64_t K, int64_t N, int br) {
-    par[wide_class(br)] += wide_parallelism(M, K, N, br);
-    work[wide_class(br)] += wide_work(M, K, N, br);
+    const int c = wide_class(br);
+    ++n[c];
+    par[c] += wide_parallelism(M, K, N, br);
+    work[c] += wide_work(M, K, N, br, false);
+    work_alone[c] += wide_work(M, K, N, br, true);
   }
   // `mfma`: the 128 x 128 tiles, the other choice, can address the operands
   bool pays(int br, bool mfma) const {
     const int c = wide_class(br);
-    return (c == 0 ? par[0] : par[1] + par[2]) >= 128 && (work[c] >= 1.0 || !mfma);
+    if ((c == 0 ? par[0] : par[1] + par[2]) < 128) return false;
+    return (n[c] == 1 ? work_alone[c] : work[c]) >= 1.0 || !mfma;
   }
   static int wide_class(int br) { return br == 16 ? 0 : br == 32 ? 1 : 2; }
 };
 
-bool use_wide_single(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K, int64_t N,
-                     int64_t lddy) {
-  if (!dw_wide_supported(dtype, br, bc, values, dY, M, K, N, lddy)) return false;
+bool use_wide_single(int dtype, const DwJob &j) {
+  if (!dw_wide_supported(dtype, j.br, j.bc, j.values, j.dY, j.M, j.K, j.N, j.lddy)) return false;
   WideSums sums;
-  sums.add(M, K, N, br);
-  return sums.pays(br, dw_mfma_supported(dtype, br, bc, values, M, K, N, lddy));
+  sums.add(j.M, j.K, j.N, j.br);
+  return sums.pays(j.br, dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy));
 }
 
 }  // namespace
@@ -299,10 +310,8 @@ int bsr_t_dense_matmul(const int32_t *row_ptr, const int32_t *col_idx, const voi
     return BSR_ERR_ALIGN;
   const size_t need = bsr_workspace_bytes(BSR_OP_T_DENSE_MATMUL, M, K, N, br, bc, dtype);
   if (need > 0 && (ws == nullptr || ws_bytes < need)) return BSR_ERR_WORKSPACE;
-  if (use_wide_single(dtype, br, bc, values, dY, M, K, N, lddy)) {
-    const DwJob job{row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate, ws, ws_bytes};
-    return launch_dw_wide(job, static_cast<hipStream_t>(stream));
-  }
+  const DwJob job{row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate, ws, ws_bytes};
+  if (use_wide_single(dtype, job)) return launch_dw_wide(job, static_cast<hipStream_t>(stream));
   if (dw_mfma_supported(dtype, br, bc, values, M, K, N, lddy))
     return launch_dw_mfma(dtype, row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate,
                           ws, ws_bytes, static_cast<hipStream_t>(stream));

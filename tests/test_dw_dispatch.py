@@ -119,3 +119,17 @@ def test_batched_dw_lines_of_the_wide_tiles_go_by_block_size(recorder):
     half = [(14600, 384, 896, b) for b in (16, 32, 64)]
     assert [products(g) for g in recorder([batch(h) for h in half])] == [["dw_mfma<16>"], ["dw_mfma<32>"], ["dw_mfma<64>"]]
     assert sorted(products(recorder([batch(*half)])[0])) == ["dw_mfma<16>", "dw_wide<32>", "dw_wide<64>"]
+
+
+@pytest.mark.parametrize("b", [32, 64])
+def test_dw_line_of_the_wide_tiles_counts_whole_tiles_of_the_other_kernel(recorder, b):
+    """A product on its own goes to the wide tiles by what the 128x128 tiles would multiply, whatever part of a tile dW fills;
+    several by what there is to multiply."""
+    wide = [(8147, 152, 1968), (4062, 416, 2128), (12544, 1536, 256), (9877, 128, 3816), (25088, 384, 1536)]
+    narrow = [(6272, 384, 1536), (800, 2048, 2048), (3677, 760, 1208), (3591, 1952, 224), (1095, 1240, 2832)]
+    assert [products(g) for g in recorder([one(*s, b) for s in wide])] == [[f"dw_wide<{b}>"]] * len(wide)
+    assert [products(g) for g in recorder([batch((*s, b)) for s in wide])] == [[f"dw_wide<{b}>"]] * len(wide)
+    assert [products(g) for g in recorder([one(*s, b) for s in narrow])] == [[f"dw_mfma<{b}>"]] * len(narrow)
+    got = recorder([batch((8147, 152, 1968, b), (8147, 152, 1968, b)), batch((3591, 1952, 224, b), (8147, 152, 2500, b))])
+    assert [products(g) for g in got] == [[f"dw_mfma<{b}>"], [f"dw_mfma<{b}>"]]
+    assert products(recorder([batch((8147, 152, 1968, b), (8147, 152, 2200, b))])[0]) == [f"dw_wide<{b}>"]
