@@ -76,10 +76,16 @@ bool use_narrow(int dtype, int br, int bc, const void *values, const void *dY, i
 // Several: 5e9 multiply-adds of them all (whole tiles are no better measure there; of 32x32 blocks
 // two products [3136 x 384 x 1536] 29.2 wide and 24.8, [6272 x 384 x 1536] 31.4 and 32.9).
 // 16x16 blocks, where the wide kernel copies by halves of a piece: 2.5e10 multiply-adds ([25088 x 1536 x 384] 48.9 wide and 46.7,
-// [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87).
+// [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87), and kFill16 of what the launch has time for
+// (dw_wide_fill): the 128 x 128 tiles waste less where the tiles don't fit dW, and where workgroups of very different length
+// share a launch ([27817 x 408 x 3440], 0.44 filled, keep 0.9: 155 wide and 125; twelve products from [33324 x 352 x 200] to
+// [14904 x 2880 x 112], 0.07 filled, 509 and 153; 0.98 filled, [50176 x 1536 x 384], keep 0.25, 61 and 75).  Over 156 shapes and
+// batches of all sizes at three to five keeps no call is more than 3 % slower so than in 128 x 128 tiles, and all together take
+// 0.97 of the time; without the second condition 1.00, the worst 3.7 times as long.
 // Only where the 128 x 128 tiles can address the operands: the general kernel, the other choice, takes 1.1 .. 9 times as long
 // ([1000 x 1000 x 4000] with a far pitch of dY 277 and 31 us, [4000 x 300000 x 8] 10.1 and 6.3 ms), or as long where there is
 // next to nothing to multiply ([512 x 3072 x 8] 17 and 17, [128 x 6144 x 8] 13 and 15).
+constexpr double kFill16 = 0.67;
 double wide_work(int64_t M, int64_t K, int64_t N, int br, bool alone) {
   if (br != 16 && alone) return (double)M * (double)(ceil_div(K, 128) * 128) * (double)(ceil_div(N, 128) * 128) / 4.2e9;
   return (double)M * (double)K * (double)N / (br == 16 ? 2.5e10 : 5.0e9);
@@ -106,6 +112,7 @@ struct WideSums {
   int n[3] = {0, 0, 0};
   int64_t par[3] = {0, 0, 0};
   double work[3] = {0.0, 0.0, 0.0}, work_alone[3] = {0.0, 0.0, 0.0};
+  bool filled16 = false;
   void add(int64_t M, int64_t K, int64_t N, int br) {
     const int c = wide_class(br);
     ++n[c];
@@ -113,11 +120,15 @@ struct WideSums {
     work[c] += wide_work(M, K, N, br, false);
     work_alone[c] += wide_work(M, K, N, br, true);
   }
+  // Once all are added (`jobs`: the products themselves); then pays() answers.
+  void close(const DwJob *jobs, int count) {
+    if (par[0] >= 128 && work[0] >= 1.0) filled16 = dw_wide_fill(jobs, count, 16) >= kFill16;
+  }
   // `mfma`: the 128 x 128 tiles, the other choice, can address the operands
   bool pays(int br, bool mfma) const {
     const int c = wide_class(br);
     if ((c == 0 ? par[0] : par[1] + par[2]) < 128) return false;
-    return (n[c] == 1 ? work_alone[c] : work[c]) >= 1.0 || !mfma;
+    return ((n[c] == 1 ? work_alone[c] : work[c]) >= 1.0 && (c != 0 || filled16)) || !mfma;
   }
   static int wide_class(int br) { return br == 16 ? 0 : br == 32 ? 1 : 2; }
 };
@@ -126,6 +137,7 @@ bool use_wide_single(int dtype, const DwJob &j) {
   if (!dw_wide_supported(dtype, j.br, j.bc, j.values, j.dY, j.M, j.K, j.N, j.lddy)) return false;
   WideSums sums;
   sums.add(j.M, j.K, j.N, j.br);
+  sums.close(&j, 1);
   return sums.pays(j.br, dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy));
 }
 
@@ -485,6 +497,7 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
   hipStream_t s = static_cast<hipStream_t>(stream);
   // too few tiles to fill the GPU even with a deep split, or too little to multiply: the 128 x 128 tiles suit those better,
   // where they can address the operands (half the activation that the wide tiles take)
+  sums.close(wide.data(), (int)wide.size());
   std::vector<DwJob> stay;
   for (const DwJob &j : wide) {
     const bool mfma = dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy);

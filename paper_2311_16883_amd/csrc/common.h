@@ -210,6 +210,9 @@ int launch_dw_narrow_batched(const DwJob *jobs, int n, hipStream_t s, std::vecto
 bool dw_wide_supported(int dtype, int br, int bc, const void *values, const void *dY, int64_t M, int64_t K,
                        int64_t N, int64_t lddy);
 size_t dw_wide_ws_bytes(int64_t M, int64_t K, int64_t N, int br);
+// Share of the multiply-adds that the compute units have time for in the launches over the products of this block size that dW
+// asks for: what is left goes into parts of tiles beyond dW, compute units without a workgroup and those that wait for others.
+double dw_wide_fill(const DwJob *jobs, int n, int br);
 int launch_dw_wide(const DwJob &j, hipStream_t s);
 int launch_dw_wide_batched(const DwJob *jobs, int n, hipStream_t s, std::vector<ReduceJob> *later = nullptr);
 

@@ -599,6 +599,7 @@ int64_t wide_max_splits(int64_t M, int64_t K, int64_t N, int bs) {
 // split just far enough that what is left over fills one more round.
 struct WidePlan {
   int whole, splits;
+  int64_t rounds_stages;    // stages that a compute unit passes through, one round after the other
 };
 
 // Cost model, in units of one stage: a workgroup costs its stages plus a fixed part (tables,
@@ -610,7 +611,7 @@ WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *m
   int64_t s_max = most[0];
   for (int i = 1; i < m; ++i) s_max = most[i] < s_max ? most[i] : s_max;
   if (s_max < 1) s_max = 1;
-  WidePlan best{0, 1};
+  WidePlan best{0, 1, 0};
   double best_cost = 0;
   bool first = true;
   for (int w = 0; w <= m; ++w) {
@@ -620,14 +621,18 @@ WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *m
       if (i < w) { tiles_a += tiles[i]; stages_a = stages[i] > stages_a ? stages[i] : stages_a; }
       else { tiles_b += tiles[i]; stages_b = stages[i] > stages_b ? stages[i] : stages_b; bytes_b += bytes_out[i]; }
     }
-    const double cost_a = (double)ceil_div(tiles_a, (int64_t)256) * ((double)stages_a + fixed_stages) * us_stage;
+    const int64_t rounds_a = ceil_div(tiles_a, (int64_t)256);
+    const double cost_a = (double)rounds_a * ((double)stages_a + fixed_stages) * us_stage;
     for (int64_t s = 1; s <= (w == m ? 1 : s_max); ++s) {
       double cost = cost_a;
+      int64_t passed = rounds_a * stages_a;
       if (w < m) {
-        cost += (double)ceil_div(tiles_b * s, (int64_t)256) * ((double)ceil_div(stages_b, s) + fixed_stages) * us_stage;
+        const int64_t rounds_b = ceil_div(tiles_b * s, (int64_t)256), each = ceil_div(stages_b, s);
+        cost += (double)rounds_b * ((double)each + fixed_stages) * us_stage;
+        passed += rounds_b * each;
         if (s > 1) cost += 2.0 * (double)s * bytes_b / bytes_per_us;
       }
-      if (first || cost < best_cost) { best_cost = cost; best = WidePlan{w, (int)s}; first = false; }
+      if (first || cost < best_cost) { best_cost = cost; best = WidePlan{w, (int)s, passed}; first = false; }
     }
   }
   return best;
@@ -685,19 +690,24 @@ uint32_t wide_cut(const WideBatch &b, int lo, int hi, uint32_t *begin) {
   return longest;
 }
 
-// One launch of up to kWideBatchMax products of block size BS, and the reduction of those it splits.
-template <int BS>
-int wide_launch(const DwJob *const *jobs, int m, hipStream_t s, std::vector<ReduceJob> *later) {
-  if (m <= 0) return BSR_OK;
+// ... of these products, of block size bs.
+WidePlan wide_plan(const DwJob *const *jobs, int m, int bs) {
   int64_t tiles[kWideBatchMax], stages[kWideBatchMax], most[kWideBatchMax];
   double bytes_out[kWideBatchMax];
   for (int i = 0; i < m; ++i) {
     tiles[i] = wide_tiles(jobs[i]->K, jobs[i]->N);
-    stages[i] = ceil_div(ceil_div(jobs[i]->M, (int64_t)BS) * BS, (int64_t)32);
-    most[i] = wide_max_splits(jobs[i]->M, jobs[i]->K, jobs[i]->N, BS);
+    stages[i] = ceil_div(ceil_div(jobs[i]->M, (int64_t)bs) * bs, (int64_t)32);
+    most[i] = wide_max_splits(jobs[i]->M, jobs[i]->K, jobs[i]->N, bs);
     bytes_out[i] = 4.0 * (double)jobs[i]->K * (double)jobs[i]->N;
   }
-  const WidePlan plan = wide_plan(tiles, stages, most, bytes_out, m);
+  return wide_plan(tiles, stages, most, bytes_out, m);
+}
+
+// One launch of up to kWideBatchMax products of block size BS, and the reduction of those it splits.
+template <int BS>
+int wide_launch(const DwJob *const *jobs, int m, hipStream_t s, std::vector<ReduceJob> *later) {
+  if (m <= 0) return BSR_OK;
+  const WidePlan plan = wide_plan(jobs, m, BS);
   WideBatch b;
   ReduceJob red[kWideBatchMax];
   int nred = 0;
@@ -725,20 +735,26 @@ int wide_launch(const DwJob *const *jobs, int m, hipStream_t s, std::vector<Redu
   return rc;
 }
 
-template <int BS>
-int wide_run_batched(const DwJob *jobs, int n, hipStream_t s, std::vector<ReduceJob> *later) {
+// Calls launch(products, how many) for what goes into each launch: the products of block size bs in their order, as many as fit.
+template <typename F>
+int wide_each_launch(const DwJob *jobs, int n, int bs, F launch) {
   const DwJob *mine[kWideBatchMax];
   int m = 0;
   for (int i = 0; i < n; ++i) {
-    if (jobs[i].br != BS) continue;
+    if (jobs[i].br != bs) continue;
     mine[m++] = &jobs[i];
     if (m == kWideBatchMax) {
-      const int rc = wide_launch<BS>(mine, m, s, later);
+      const int rc = launch(mine, m);
       if (rc != BSR_OK) return rc;
       m = 0;
     }
   }
-  return wide_launch<BS>(mine, m, s, later);
+  return m > 0 ? launch(mine, m) : BSR_OK;
+}
+
+template <int BS>
+int wide_run_batched(const DwJob *jobs, int n, hipStream_t s, std::vector<ReduceJob> *later) {
+  return wide_each_launch(jobs, n, BS, [&](const DwJob *const *mine, int m) { return wide_launch<BS>(mine, m, s, later); });
 }
 
 }  // namespace
@@ -761,6 +777,16 @@ bool dw_wide_supported(int dtype, int br, int bc, const void *values, const void
 size_t dw_wide_ws_bytes(int64_t M, int64_t K, int64_t N, int br) {
   const int64_t s = wide_max_splits(M, K, N, br);
   return s > 1 ? (size_t)s * (size_t)K * (size_t)N * sizeof(float) : 0;
+}
+
+double dw_wide_fill(const DwJob *jobs, int n, int br) {
+  double work = 0.0, passed = 0.0;
+  wide_each_launch(jobs, n, br, [&](const DwJob *const *mine, int m) {
+    for (int i = 0; i < m; ++i) work += (double)mine[i]->M * (double)mine[i]->K * (double)mine[i]->N;
+    passed += (double)wide_plan(mine, m, br).rounds_stages * 256.0 * (32.0 * kTileK * kTileN);
+    return BSR_OK;
+  });
+  return passed > 0.0 ? work / passed : 0.0;
 }
 
 int launch_dw_wide(const DwJob &j, hipStream_t s) {

@@ -133,3 +133,15 @@ def test_dw_line_of_the_wide_tiles_counts_whole_tiles_of_the_other_kernel(record
     got = recorder([batch((8147, 152, 1968, b), (8147, 152, 1968, b)), batch((3591, 1952, 224, b), (8147, 152, 2500, b))])
     assert [products(g) for g in got] == [[f"dw_mfma<{b}>"], [f"dw_mfma<{b}>"]]
     assert products(recorder([batch((8147, 152, 1968, b), (8147, 152, 2200, b))])[0]) == [f"dw_wide<{b}>"]
+
+
+def test_dw_of_16x16_blocks_takes_wide_tiles_where_they_are_filled(recorder):
+    """Alone and in batches: work enough and tiles that fit dW and keep the compute units busy, or the 128x128 tiles."""
+    wide = [(50176, 1536, 384), (12348, 768, 3072), (40000, 1500, 1000)]
+    narrow = [(27817, 408, 3440), (11825, 1576, 1664), (30734, 464, 1816), (6867, 2944, 2528), (25088, 1536, 384)]
+    assert [products(g) for g in recorder([one(*s, 16) for s in wide])] == [["dw_wide<16>"]] * len(wide)
+    assert [products(g) for g in recorder([one(*s, 16) for s in narrow])] == [["dw_mfma<16>"]] * len(narrow)
+    even = batch(*[(4116, 768, 3072, 16)] * 18)
+    uneven = batch((33324, 352, 200, 16), (14904, 2880, 112, 16), (17969, 688, 128, 16), (22727, 1344, 72, 16), (13016, 1824, 2232, 16))
+    many = batch(*[(6272, 384, 1536, 16)] * 30)        # more than one launch holds
+    assert [products(g)[:1] for g in recorder([even, uneven, many])] == [["dw_wide<16>"], ["dw_mfma<16>"], ["dw_wide<16>"]]
