@@ -165,10 +165,13 @@ inline __host__ __device__ bool reduce_by_vectors(const ReduceJob &j) {
 
 inline int64_t reduce_outputs(const ReduceJob &j) { return reduce_by_vectors(j) ? j.K * j.N / 4 : j.K * j.N; }
 
-// Threads that share an output of a product, 1: the simpler kernels.  (While that leaves the chip room, `outs` = outputs of
-// all products of the launch, and each has four splits or more.)
+// Threads that share an output of a product, 1: the simpler kernels do.  (`outs` = outputs of all products of the launch: as
+// many threads as the chip has room for, each with four splits or more.  Beyond kReduceSharedVectors the simpler kernels have
+// enough of them for vectors: whole dW calls of M = 50176 with them and so, [300 x 300] 37.4 and 35.9 us, [1000 x 128] 1.3 %
+// less, [512 x 512] and [768 x 384] 2 % more; entry by entry, [300 x 301], 38.9 and 30.9.)
+constexpr int64_t kReduceSharedVectors = 128 * 256;
 int reduce_groups(const ReduceJob &j, int64_t outs) {
-  if (j.splits < 16) return 1;
+  if (j.splits < 16 || (reduce_by_vectors(j) && outs > kReduceSharedVectors)) return 1;
   int groups = 1;
   while (groups < 16 && outs * groups < 512 * 256 && j.splits >= 8 * groups) groups *= 2;
   return groups;
@@ -305,31 +308,34 @@ int launch_splitk_reduce(const float *partial, int splits, int64_t K, int64_t N,
 int launch_splitk_reduce_batched(const ReduceJob *jobs, int n, hipStream_t s) {
   for (int i0 = 0; i0 < n; i0 += kReduceBatchMax) {
     const int m = n - i0 < kReduceBatchMax ? n - i0 : kReduceBatchMax;
-    ReduceBatch b;
-    SharedReduceBatch c;
-    uint32_t wgs = 0, shared_wgs = 0;
-    int nb = 0, nc = 0;
+    const ReduceJob *const job = jobs + i0;
     int64_t outs = 0;
-    for (int i = 0; i < m; ++i) outs += reduce_outputs(jobs[i0 + i]);
-    for (int i = 0; i < m; ++i) {
-      const ReduceJob &j = jobs[i0 + i];
-      const int groups = reduce_groups(j, outs);
-      if (groups > 1) {
-        c.it[nc] = j;
-        c.groups[nc] = (uint8_t)groups;
-        c.wg_begin[nc++] = shared_wgs;
-        shared_wgs += (uint32_t)shared_reduce_wgs(j, groups);
-        continue;
+    for (int i = 0; i < m; ++i) outs += reduce_outputs(job[i]);
+    bool shared = false;
+    for (int i = 0; i < m; ++i) shared = shared || reduce_groups(job[i], outs) > 1;
+    uint32_t wgs = 0;
+    if (shared) {                     // (one launch for all: a second one costs more than the other kernel saves the rest)
+      SharedReduceBatch c;
+      for (int i = 0; i < m; ++i) {
+        const int groups = reduce_groups(job[i], outs);
+        c.it[i] = job[i];
+        c.groups[i] = (uint8_t)groups;
+        c.wg_begin[i] = wgs;
+        wgs += (uint32_t)shared_reduce_wgs(job[i], groups);
       }
-      b.it[nb] = j;
-      b.wg_begin[nb++] = wgs;
-      const int64_t blocks = ceil_div(ceil_div(j.K * j.N, 4), 256);
-      wgs += (uint32_t)(blocks < 1 ? 1 : (blocks < 2048 ? blocks : 2048));
+      c.wg_begin[m] = wgs;
+      hipLaunchKernelGGL(splitk_reduce_shared_batched_kernel, dim3(wgs), dim3(256), 0, s, c, m);
+    } else {
+      ReduceBatch b;
+      for (int i = 0; i < m; ++i) {
+        b.it[i] = job[i];
+        b.wg_begin[i] = wgs;
+        const int64_t blocks = ceil_div(ceil_div(job[i].K * job[i].N, 4), 256);
+        wgs += (uint32_t)(blocks < 1 ? 1 : (blocks < 2048 ? blocks : 2048));
+      }
+      b.wg_begin[m] = wgs;
+      hipLaunchKernelGGL(splitk_reduce_batched_kernel, dim3(wgs), dim3(256), 0, s, b, m);
     }
-    b.wg_begin[nb] = wgs;
-    c.wg_begin[nc] = shared_wgs;
-    if (nb > 0) hipLaunchKernelGGL(splitk_reduce_batched_kernel, dim3(wgs), dim3(256), 0, s, b, nb);
-    if (nc > 0) hipLaunchKernelGGL(splitk_reduce_shared_batched_kernel, dim3(shared_wgs), dim3(256), 0, s, c, nc);
     const int rc = check_launch();
     if (rc != BSR_OK) return rc;
   }

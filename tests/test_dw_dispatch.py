@@ -35,12 +35,13 @@ def recorder(tmp_path_factory):
 
 
 def kernel_name(mangled):
-    """dw_wide<16>, dw_mfma<16>, dw_generic, reblock, dw_narrow, reduce, from the mangled names."""
+    """dw_wide<16>, dw_mfma<16>, dw_narrow<7>, dw_generic, reblock, reduce, reduce_shared, from the mangled names."""
     for key, name in (("dw_wide_batched_kernel", "dw_wide"), ("dw_mfma_batched_kernel", "dw_mfma"), ("dw_mfma_kernel", "dw_mfma"),
                       ("dw_narrow_batched_kernel", "dw_narrow")):
         if key in mangled:
             return "%s<%s>" % (name, re.search(r"Li(\d+)E", mangled).group(1))
-    for key, name in (("dw_generic_kernel", "dw_generic"), ("reblock_kernel", "reblock"), ("splitk_reduce", "reduce")):
+    for key, name in (("dw_generic_kernel", "dw_generic"), ("reblock_kernel", "reblock"),
+                      ("splitk_reduce_shared", "reduce_shared"), ("splitk_reduce", "reduce")):
         if key in mangled:
             return name
     return mangled
@@ -55,7 +56,11 @@ def batch(*items):
 
 
 def products(got):
-    return [n for n in got["names"] if n != "reduce"]
+    return [n for n in got["names"] if not n.startswith("reduce")]
+
+
+def reductions(got):
+    return [n for n in got["names"] if n.startswith("reduce")]
 
 
 @pytest.mark.parametrize("M,K,N,other", [(4000, 300000, 8, "dw_wide<16>"), (4096, 270000, 8, "dw_wide<16>"),
@@ -145,3 +150,12 @@ def test_dw_of_16x16_blocks_takes_wide_tiles_where_they_are_filled(recorder):
     uneven = batch((33324, 352, 200, 16), (14904, 2880, 112, 16), (17969, 688, 128, 16), (22727, 1344, 72, 16), (13016, 1824, 2232, 16))
     many = batch(*[(6272, 384, 1536, 16)] * 30)        # more than one launch holds
     assert [products(g)[:1] for g in recorder([even, uneven, many])] == [["dw_wide<16>"], ["dw_mfma<16>"], ["dw_wide<16>"]]
+
+
+def test_dw_reductions_are_shared_for_small_matrices_only_and_in_one_launch(recorder):
+    """Threads share an output of many splits while there are few outputs; the products of a launch are added up together."""
+    calls = [one(50176, 196, 196, 14), one(50176, 300, 301, 16), one(50176, 512, 512, 14), one(25088, 384, 768, 32),
+             batch((6272, 384, 384, 14), (25088, 384, 384, 14)), batch((700, 140, 332, 32), (25088, 100, 36, 32)),
+             batch((25088, 384, 1536, 32), (25088, 196, 196, 14), (25088, 196, 196, 14))]
+    assert [reductions(g) for g in recorder(calls)] == [["reduce_shared"], ["reduce_shared"], ["reduce"], ["reduce"], ["reduce"],
+                                                        ["reduce_shared"], ["reduce"]]

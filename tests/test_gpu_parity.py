@@ -1420,6 +1420,30 @@ def test_dw_of_many_splits_of_a_small_matrix(M, K, N, pad):
     assert bool((out[:, N:] == 0.25).all())
 
 
+@pytest.mark.parametrize("N,pad,start", [(33, 0, 0), (36, 0, 0), (36, 1, 0), (36, 0, 1), (1, 2, 0)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_batched_dw_of_many_and_few_splits_of_small_matrices(dtype, N, pad, start):
+    """One reduction for products of many splits and of few, by vectors and entry by entry (N, pitch or start of dW no multiple of
+    four), overwritten and added to.  Tolerance: binary32 accumulation, as in the other parity tests; relative to the 0.25 that is
+    added to where that is larger."""
+    made = []
+    for M, K in ((25000, 100), (3000, 40), (700, 17), (40, 5)):
+        X, dY = rand_pair(M, K, N, dtype, seed=M + N)
+        _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, 16, 16, 0.6)
+        ref = oracle.dw(oracle.mask_dense(X, 16, 16, o_mask), dY)
+        flat = torch.full((start + K * (N + pad),), 0.25, dtype=torch.float32, device="cuda")
+        out = flat[start:].view(K, N + pad)
+        made.append((torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda(), to_dev(o_val), M, K, to_dev(dY), out, ref))
+    problems = [(rp, ci, val, M, K, 16, 16, dY, out[:, :N]) for rp, ci, val, M, K, dY, out, _ in made]
+    for accumulate, base in ((True, 0.25), (False, 0.0)):
+        B.bsr_t_dense_matmul_batched(B.MatmulBatch(problems, accumulate=accumulate))
+        torch.cuda.synchronize()
+        for *_, out, ref in made:
+            scale = max(1.0, base / np.max(np.abs(ref)))
+            assert dw_error(out[:, :N].cpu().numpy() - base, ref) <= DW_TOL["f32"] * scale
+            assert bool((out[:, N:] == 0.25).all())
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("M,K,N,br,bc", [
     (254, 60, 16, 1, 32), (250, 50, 30, 1, 8),        # few and more block-rows than the general kernel should walk
