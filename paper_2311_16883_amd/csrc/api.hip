@@ -141,6 +141,79 @@ bool use_wide_single(int dtype, const DwJob &j) {
   return sums.pays(j.br, dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy));
 }
 
+// Workspace of a product, whatever kernel takes it.  (The wide tiles take activations that the 128 x 128 tiles don't, from 2 GiB
+// up to 4 GiB, and rows of dY further apart.)
+size_t dw_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
+  size_t a = dw_generic_ws_bytes(M, K, N, br, bc), b = 0;
+  if (dw_mfma_supported(dtype, br, bc, nullptr, M, K, N, N)) b = dw_mfma_ws_bytes(dtype, M, K, N, br, bc);
+  else if (dw_reblock_supported(dtype, br, bc, M, K, N, N)) b = dw_reblock_ws_bytes(dtype, M, K, N);
+  if (b > a) a = b;
+  if (dw_wide_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
+    b = dw_wide_ws_bytes(M, K, N, br);
+    if (b > a) a = b;
+  }
+  if (dw_narrow_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
+    b = dw_narrow_ws_bytes(M, K, N, br);
+    if (b > a) a = b;
+  }
+  return align_up(a, 256);
+}
+
+// The products of a batched call (their numbers) by the kernel that takes them; `single`: each by a launch of its own.
+struct DwRoutes {
+  std::vector<int> narrow, wide, mfma, single;
+};
+
+std::vector<DwJob> dw_pick(const std::vector<DwJob> &jobs, const std::vector<int> &which) {
+  std::vector<DwJob> r;
+  r.reserve(which.size());
+  for (const int i : which) r.push_back(jobs[i]);
+  return r;
+}
+
+DwRoutes dw_routes(int dtype, const std::vector<DwJob> &jobs, bool several) {
+  DwRoutes r;
+  WideSums sums;
+  std::vector<int> maybe;
+  for (int i = 0; i < (int)jobs.size(); ++i) {
+    const DwJob &j = jobs[i];
+    if (several && use_narrow(dtype, j.br, j.bc, j.values, j.dY, j.M, j.K, j.N, j.lddy)) {
+      r.narrow.push_back(i);
+    } else if (dw_wide_supported(dtype, j.br, j.bc, j.values, j.dY, j.M, j.K, j.N, j.lddy)) {
+      maybe.push_back(i);
+      sums.add(j.M, j.K, j.N, j.br);
+    } else {
+      (dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy) ? r.mfma : r.single).push_back(i);
+    }
+  }
+  // too few tiles to fill the GPU even with a deep split, or too little to multiply: the 128 x 128 tiles suit those better,
+  // where they can address the operands (half the activation that the wide tiles take)
+  const std::vector<DwJob> candidates = dw_pick(jobs, maybe);
+  sums.close(candidates.data(), (int)candidates.size());
+  for (const int i : maybe) {
+    const DwJob &j = jobs[i];
+    const bool mfma = dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy);
+    (sums.pays(j.br, mfma) ? r.wide : mfma ? r.mfma : r.single).push_back(i);
+  }
+  return r;
+}
+
+// One product, with a workspace of dw_ws_bytes or more.
+int launch_dw(int dtype, const DwJob &j, hipStream_t s) {
+  if (use_wide_single(dtype, j)) return launch_dw_wide(j, s);
+  if (dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy))
+    return launch_dw_mfma(dtype, j.row_ptr, j.col_idx, j.values, j.M, j.K, j.br, j.bc, j.dY, j.N, j.lddy, j.dW, j.lddw, j.accumulate,
+                          j.ws, j.ws_bytes, s);
+  // other block shapes: re-tiled into 32x32 blocks for the matrix-core kernel, unless the
+  // problem is so small that the single launch of the general kernel is the faster way
+  if (retiling_pays(j.M, j.K, j.N, j.br) && dw_reblock_supported(dtype, j.br, j.bc, j.M, j.K, j.N, j.lddy) &&
+      j.ws_bytes >= dw_reblock_ws_bytes(dtype, j.M, j.K, j.N))
+    return launch_dw_reblocked(dtype, j.row_ptr, j.col_idx, j.values, j.M, j.K, j.br, j.bc, j.dY, j.N, j.lddy, j.dW, j.lddw,
+                               j.accumulate, j.ws, j.ws_bytes, s);
+  return launch_dw_generic(j.row_ptr, j.col_idx, j.values, dtype, j.M, j.K, j.br, j.bc, j.dY, j.N, j.lddy, j.dW, j.lddw,
+                           j.accumulate, j.ws, j.ws_bytes, s);
+}
+
 }  // namespace
 }  // namespace bsr
 
@@ -192,26 +265,7 @@ size_t bsr_workspace_bytes(int op, int64_t M, int64_t K, int64_t N, int br, int 
     case BSR_OP_DECOMPRESS: return 0;
     case BSR_OP_T_DENSE_MATMUL:
       if (N < 0) return 0;
-      {
-        size_t a = dw_generic_ws_bytes(M, K, N, br, bc);
-        if (dw_mfma_supported(dtype, br, bc, nullptr, M, K, N, N)) {
-          const size_t b = dw_mfma_ws_bytes(dtype, M, K, N, br, bc);
-          if (b > a) a = b;
-        } else if (dw_reblock_supported(dtype, br, bc, M, K, N, N)) {
-          const size_t b = dw_reblock_ws_bytes(dtype, M, K, N);
-          if (b > a) a = b;
-        }
-        // (the wide tiles take activations that the 128 x 128 tiles don't: from 2 GiB up to 4 GiB)
-        if (dw_wide_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
-          const size_t b = dw_wide_ws_bytes(M, K, N, br);
-          if (b > a) a = b;
-        }
-        if (dw_narrow_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
-          const size_t b = dw_narrow_ws_bytes(M, K, N, br);
-          if (b > a) a = b;
-        }
-        return align_up(a, 256);
-      }
+      return dw_ws_bytes(dtype, M, K, N, br, bc);
     case BSR_OP_AFFINE_SCALE_GRAD: return affine_ws_bytes(M, K, br, bc);
     default: return 0;
   }
@@ -323,18 +377,7 @@ int bsr_t_dense_matmul(const int32_t *row_ptr, const int32_t *col_idx, const voi
   const size_t need = bsr_workspace_bytes(BSR_OP_T_DENSE_MATMUL, M, K, N, br, bc, dtype);
   if (need > 0 && (ws == nullptr || ws_bytes < need)) return BSR_ERR_WORKSPACE;
   const DwJob job{row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate, ws, ws_bytes};
-  if (use_wide_single(dtype, job)) return launch_dw_wide(job, static_cast<hipStream_t>(stream));
-  if (dw_mfma_supported(dtype, br, bc, values, M, K, N, lddy))
-    return launch_dw_mfma(dtype, row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate,
-                          ws, ws_bytes, static_cast<hipStream_t>(stream));
-  // other block shapes: re-tiled into 32x32 blocks for the matrix-core kernel, unless the
-  // problem is so small that the single launch of the general kernel is the faster way
-  if (retiling_pays(M, K, N, br) && dw_reblock_supported(dtype, br, bc, M, K, N, lddy) &&
-      ws_bytes >= dw_reblock_ws_bytes(dtype, M, K, N))
-    return launch_dw_reblocked(dtype, row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw,
-                               accumulate, ws, ws_bytes, static_cast<hipStream_t>(stream));
-  return launch_dw_generic(row_ptr, col_idx, values, dtype, M, K, br, bc, dY, N, lddy, dW, lddw,
-                           accumulate, ws, ws_bytes, static_cast<hipStream_t>(stream));
+  return launch_dw(dtype, job, static_cast<hipStream_t>(stream));
 }
 
 int bsr_affine_scale_grad(const int32_t *row_ptr, const int32_t *col_idx, const void *values, int dtype,
@@ -451,7 +494,7 @@ size_t bsr_t_dense_matmul_batched_workspace_bytes(const bsr_matmul_item *items, 
     const bsr_matmul_item &it = items[i];
     Geometry g;
     if (check_shape(dtype, it.M, it.K, it.K, it.br, it.bc, &g) != BSR_OK || it.N < 0) return 0;
-    total += align_up(bsr_workspace_bytes(BSR_OP_T_DENSE_MATMUL, it.M, it.K, it.N, it.br, it.bc, dtype), 256);
+    total += dw_ws_bytes(dtype, it.M, it.K, it.N, it.br, it.bc);
   }
   return total;
 }
@@ -462,9 +505,8 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
   if (n == 0) return BSR_OK;
   if (items == nullptr) return BSR_ERR_NULL;
   if (misaligned(ws, 16)) return BSR_ERR_ALIGN;
-  std::vector<DwJob> batch, single, wide, narrow;
-  batch.reserve(n);
-  WideSums sums;
+  std::vector<DwJob> jobs;
+  jobs.reserve(n);
   size_t off = 0;
   for (int i = 0; i < n; ++i) {
     const bsr_matmul_item &it = items[i];
@@ -478,43 +520,22 @@ int bsr_t_dense_matmul_batched(const bsr_matmul_item *items, int n, int dtype, v
     if (misaligned(it.values, elem_bytes(dtype)) || misaligned(it.dY, elem_bytes(dtype)) || misaligned(it.dW, 4) ||
         misaligned(it.row_ptr, 4) || misaligned(it.col_idx, 4))
       return BSR_ERR_ALIGN;
-    const size_t need = align_up(bsr_workspace_bytes(BSR_OP_T_DENSE_MATMUL, it.M, it.K, it.N, it.br, it.bc, dtype), 256);
+    const size_t need = dw_ws_bytes(dtype, it.M, it.K, it.N, it.br, it.bc);
     if (need > 0 && (ws == nullptr || off + need > ws_bytes)) return BSR_ERR_WORKSPACE;
-    const DwJob job{it.row_ptr, it.col_idx, it.values, it.M, it.K, it.br, it.bc, it.dY, it.N, it.lddy, it.dW,
-                    it.lddw, it.accumulate, need > 0 ? static_cast<char *>(ws) + off : nullptr, need};
+    jobs.push_back(DwJob{it.row_ptr, it.col_idx, it.values, it.M, it.K, it.br, it.bc, it.dY, it.N, it.lddy, it.dW, it.lddw,
+                         it.accumulate, need > 0 ? static_cast<char *>(ws) + off : nullptr, need});
     off += need;
-    if (n > 1 && use_narrow(dtype, it.br, it.bc, it.values, it.dY, it.M, it.K, it.N, it.lddy)) {
-      narrow.push_back(job);
-    } else if (dw_wide_supported(dtype, it.br, it.bc, it.values, it.dY, it.M, it.K, it.N, it.lddy)) {
-      wide.push_back(job);
-      sums.add(it.M, it.K, it.N, it.br);
-    } else if (dw_mfma_supported(dtype, it.br, it.bc, it.values, it.M, it.K, it.N, it.lddy)) {
-      batch.push_back(job);
-    } else {
-      single.push_back(job);
-    }
   }
+  const DwRoutes r = dw_routes(dtype, jobs, n > 1);
+  const std::vector<DwJob> wide = dw_pick(jobs, r.wide), narrow = dw_pick(jobs, r.narrow), mfma = dw_pick(jobs, r.mfma);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // too few tiles to fill the GPU even with a deep split, or too little to multiply: the 128 x 128 tiles suit those better,
-  // where they can address the operands (half the activation that the wide tiles take)
-  sums.close(wide.data(), (int)wide.size());
-  std::vector<DwJob> stay;
-  for (const DwJob &j : wide) {
-    const bool mfma = dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy);
-    (sums.pays(j.br, mfma) ? stay : mfma ? batch : single).push_back(j);
-  }
-  wide.swap(stay);
   // the partial tiles of both kinds of products are added up by one launch behind the two kernels
   std::vector<ReduceJob> reductions;
   int rc = launch_dw_wide_batched(wide.data(), (int)wide.size(), s, &reductions);
   if (rc == BSR_OK) rc = launch_dw_narrow_batched(narrow.data(), (int)narrow.size(), s, &reductions);
   if (rc == BSR_OK && !reductions.empty()) rc = launch_splitk_reduce_batched(reductions.data(), (int)reductions.size(), s);
-  if (rc == BSR_OK) rc = launch_dw_mfma_batched(dtype, batch.data(), (int)batch.size(), s);
-  for (size_t i = 0; rc == BSR_OK && i < single.size(); ++i) {
-    const DwJob &j = single[i];
-    rc = bsr_t_dense_matmul(j.row_ptr, j.col_idx, j.values, dtype, j.M, j.K, j.br, j.bc, j.dY, j.N, j.lddy, j.dW,
-                            j.lddw, j.accumulate, j.ws, j.ws_bytes, stream);
-  }
+  if (rc == BSR_OK) rc = launch_dw_mfma_batched(dtype, mfma.data(), (int)mfma.size(), s);
+  for (size_t i = 0; rc == BSR_OK && i < r.single.size(); ++i) rc = launch_dw(dtype, jobs[r.single[i]], s);
   return rc;
 }
 

@@ -583,12 +583,20 @@ __global__ __launch_bounds__(kWideThreads) void dw_wide_batched_kernel(WideBatch
 
 int64_t wide_tiles(int64_t K, int64_t N) { return ceil_div(K, kTileK) * ceil_div(N, kTileN); }
 
-// Splits of the contraction the planner may pick (the workspace is sized for them): sixteen, or up to 24 where a product of
-// few tiles would leave compute units without one ([50176 x 1536 x 384], 12 tiles, keep 0.25: 47.9 us in 16
-// splits, 44.9 in 21; in 16x16 blocks 68 and 61; [50176 x 1536 x 256], 8 tiles, keep 0.75: 62.7 and 54.2 in 24).
+// What the planner reckons with: microseconds of a stage, bytes of partial matrices per microsecond.
+constexpr double kStageUs = 0.5, kPartialBytesPerUs = 3.0e6;
+
+// Splits of the contraction the planner may pick: sixteen, or up to 24 where a product of few tiles would leave compute units
+// without one and its contraction is long enough for that to pay ([50176 x 1536 x 384], 12 tiles, keep 0.25: 47.9 us in 16
+// splits, 44.9 in 21; in 16x16 blocks 68 and 61; [50176 x 1536 x 256], 8 tiles, keep 0.75: 62.7 and 54.2 in 24).  More than
+// sixteen, s, save stages * (1/16 - 1/s) stages and cost s - 16 partial matrices, written and read: hence the line.  A
+// workspace holds this many, so it grows with M: one for a whole batch does for a short last one.
 int64_t wide_max_splits(int64_t M, int64_t K, int64_t N, int bs) {
   const int64_t rows = ceil_div(M, bs), fill = 256 / wide_tiles(K, N);
-  const int64_t s = fill < 16 ? 16 : fill < 24 ? fill : 24;
+  const double pays = kStageUs * (double)(rows * bs) / 32.0 * kPartialBytesPerUs / (16.0 * 8.0 * (double)K * (double)N);
+  int64_t s = fill < 24 ? fill : 24;
+  if ((double)s > pays) s = (int64_t)pays;
+  if (s < 16) s = 16;
   return rows < s ? rows : s;
 }
 
@@ -605,16 +613,19 @@ struct WidePlan {
 // Cost model, in units of one stage: a workgroup costs its stages plus a fixed part (tables,
 // first copies, write-out); work is done in rounds of 256 workgroups; a partial tile is
 // written once and read once by the reduction.  Measured orders of magnitude on MI355X;
-// only the choice depends on them.
-WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *most, const double *bytes_out, int m) {
-  const double us_stage = 0.5, fixed_stages = 30.0, bytes_per_us = 3.0e6;
+// only the choice depends on them.  `room`: splits whose partial matrices a product's workspace holds.
+WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *most, const int64_t *room, const double *bytes_out,
+                   int m) {
+  const double fixed_stages = 30.0;
   int64_t s_max = most[0];
   for (int i = 1; i < m; ++i) s_max = most[i] < s_max ? most[i] : s_max;
-  if (s_max < 1) s_max = 1;
   WidePlan best{0, 1, 0};
   double best_cost = 0;
   bool first = true;
   for (int w = 0; w <= m; ++w) {
+    int64_t s_most = w == m ? 1 : s_max;
+    for (int i = w; i < m; ++i) s_most = room[i] < s_most ? room[i] : s_most;
+    if (s_most < 1) s_most = 1;
     int64_t tiles_a = 0, tiles_b = 0, stages_a = 0, stages_b = 0;
     double bytes_b = 0;
     for (int i = 0; i < m; ++i) {
@@ -622,15 +633,15 @@ WidePlan wide_plan(const int64_t *tiles, const int64_t *stages, const int64_t *m
       else { tiles_b += tiles[i]; stages_b = stages[i] > stages_b ? stages[i] : stages_b; bytes_b += bytes_out[i]; }
     }
     const int64_t rounds_a = ceil_div(tiles_a, (int64_t)256);
-    const double cost_a = (double)rounds_a * ((double)stages_a + fixed_stages) * us_stage;
-    for (int64_t s = 1; s <= (w == m ? 1 : s_max); ++s) {
+    const double cost_a = (double)rounds_a * ((double)stages_a + fixed_stages) * kStageUs;
+    for (int64_t s = 1; s <= s_most; ++s) {
       double cost = cost_a;
       int64_t passed = rounds_a * stages_a;
       if (w < m) {
         const int64_t rounds_b = ceil_div(tiles_b * s, (int64_t)256), each = ceil_div(stages_b, s);
-        cost += (double)rounds_b * ((double)each + fixed_stages) * us_stage;
+        cost += (double)rounds_b * ((double)each + fixed_stages) * kStageUs;
         passed += rounds_b * each;
-        if (s > 1) cost += 2.0 * (double)s * bytes_b / bytes_per_us;
+        if (s > 1) cost += 2.0 * (double)s * bytes_b / kPartialBytesPerUs;
       }
       if (first || cost < best_cost) { best_cost = cost; best = WidePlan{w, (int)s, passed}; first = false; }
     }
@@ -692,15 +703,16 @@ uint32_t wide_cut(const WideBatch &b, int lo, int hi, uint32_t *begin) {
 
 // ... of these products, of block size bs.
 WidePlan wide_plan(const DwJob *const *jobs, int m, int bs) {
-  int64_t tiles[kWideBatchMax], stages[kWideBatchMax], most[kWideBatchMax];
+  int64_t tiles[kWideBatchMax], stages[kWideBatchMax], most[kWideBatchMax], room[kWideBatchMax];
   double bytes_out[kWideBatchMax];
   for (int i = 0; i < m; ++i) {
     tiles[i] = wide_tiles(jobs[i]->K, jobs[i]->N);
     stages[i] = ceil_div(ceil_div(jobs[i]->M, (int64_t)bs) * bs, (int64_t)32);
     most[i] = wide_max_splits(jobs[i]->M, jobs[i]->K, jobs[i]->N, bs);
     bytes_out[i] = 4.0 * (double)jobs[i]->K * (double)jobs[i]->N;
+    room[i] = jobs[i]->ws == nullptr ? 0 : (int64_t)(jobs[i]->ws_bytes / (size_t)(4 * jobs[i]->K * jobs[i]->N));
   }
-  return wide_plan(tiles, stages, most, bytes_out, m);
+  return wide_plan(tiles, stages, most, room, bytes_out, m);
 }
 
 // One launch of up to kWideBatchMax products of block size BS, and the reduction of those it splits.

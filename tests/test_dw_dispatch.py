@@ -1,6 +1,7 @@
 """Which kernels a dW call would launch, and with what workspace: the host code runs against a recorder of launches
 (tests/launch_recorder.c), at sizes that need no memory here.  CPU only."""
 import json
+import random
 import re
 import subprocess
 import sys
@@ -159,3 +160,46 @@ def test_dw_reductions_are_shared_for_small_matrices_only_and_in_one_launch(reco
              batch((25088, 384, 1536, 32), (25088, 196, 196, 14), (25088, 196, 196, 14))]
     assert [reductions(g) for g in recorder(calls)] == [["reduce_shared"], ["reduce_shared"], ["reduce"], ["reduce"], ["reduce"],
                                                         ["reduce_shared"], ["reduce"]]
+
+
+def partials(M, K, N, splits):
+    return splits * K * N * 4
+
+
+def test_dw_workspace_of_the_wide_tiles(recorder):
+    """Sixteen splits, more only where the contraction is long enough to be split further: 1.09 GB for the 36 products of
+    ResMLP-S12 at batch 128.  What is enough for a batch is enough for a shorter one and for a part of it."""
+    fc1, fc2, patches = (25088, 384, 1536), (50176, 1536, 384), (49152, 196, 196)
+    for b in (32, 64):
+        got = recorder([one(*fc1, b), one(*fc2, b)])
+        assert [g["ws"] for g in got] == [partials(*fc1, 16), partials(*fc2, 21)]
+        assert [g["kernels"][0] for g in got] == [(f"dw_wide<{b}>", 16 * 12), (f"dw_wide<{b}>", 256)]
+    for b in (16, 32, 64):
+        layers = [x for _ in range(12) for x in ((*patches, 14), (*fc1, b), (25088, 1536, 384, b))]
+        network, part, short = recorder([batch(*layers), batch(*layers[:7]), batch(*[(M // 3, K, N, b) for M, K, N, b in layers])])
+        assert network["rc"] == 0 and network["kernels"][0] == (f"dw_wide<{b}>", 512)   # 21 tile by tile, three split
+        assert network["ws"] == sum(g["ws"] for g in recorder([one(*x) for x in layers])) < 1090 << 20
+        assert part["ws"] < network["ws"] and short["ws"] <= network["ws"]
+        sizes = [g["ws"] for g in recorder([one(M, *shape, b) for shape in ((384, 1536), (1536, 384), (1536, 256), (200, 2000))
+                                            for M in range(196, 196 * 300, 196)])]
+        for k in range(0, len(sizes), 299):
+            assert sizes[k:k + 299] == sorted(sizes[k:k + 299])
+
+
+def test_batched_dw_is_taken_whatever_the_operands_allow(recorder):
+    """The workspace is sized for aligned operands and contiguous rows; products that are neither take other kernels, or split
+    less, and their companions too.  None is refused."""
+    rng = random.Random(3)
+    calls = []
+    for _ in range(300):
+        items = []
+        for _ in range(rng.randint(1, 30 if rng.random() < 0.1 else 5)):
+            M, K, N = (int(2 ** rng.uniform(*r)) for r in ((4, 16), (3, 12), (3, 12)))
+            b = rng.choice((14, 16, 16, 32, 32, 64, 8))
+            unit = rng.choice((1, 8, 8))
+            N = max(unit, N // unit * unit)
+            items.append(dict(M=M, K=K, N=N, b=b, lddy=rng.choice((N, N, N + 8, N + 3, 200000)), lddw=N + rng.choice((0, 1)),
+                              values=(1 << 20) + rng.choice((0, 0, 2)), dY=(1 << 20) + rng.choice((0, 0, 2, 4)),
+                              accumulate=rng.choice((0, 1))))
+        calls.append({"items": items, "batched": True})
+    assert [g["rc"] for g in recorder(calls)] == [0] * len(calls)
