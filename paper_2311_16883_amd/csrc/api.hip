@@ -76,18 +76,21 @@ bool use_narrow(int dtype, int br, int bc, const void *values, const void *dY, i
 // Several: 5e9 multiply-adds of them all (whole tiles are no better measure there; of 32x32 blocks
 // two products [3136 x 384 x 1536] 29.2 wide and 24.8, [6272 x 384 x 1536] 31.4 and 32.9).
 // 16x16 blocks, where the wide kernel copies by halves of a piece: 2.5e10 multiply-adds ([25088 x 1536 x 384] 48.9 wide and 46.7,
-// [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87), and kFill16 of what the launch has time for
-// (dw_wide_fill): the 128 x 128 tiles waste less where the tiles don't fit dW, and where workgroups of very different length
-// share a launch ([27817 x 408 x 3440], 0.44 filled, keep 0.9: 155 wide and 125; twelve products from [33324 x 352 x 200] to
-// [14904 x 2880 x 112], 0.07 filled, 509 and 153; 0.98 filled, [50176 x 1536 x 384], keep 0.25, 61 and 75).  Over 156 shapes and
-// batches of all sizes at three to five keeps no call is more than 3 % slower so than in 128 x 128 tiles, and all together take
-// 0.97 of the time; without the second condition 1.00, the worst 3.7 times as long.
+// [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87), and at least kFill16 times as well filled tiles and
+// compute units as 128 x 128 tiles would be filled (dw_wide_fill): these waste less where the wide tiles don't fit dW, and where
+// workgroups of very different length share a launch ([27817 x 408 x 3440], 0.44 to 0.79, keep 0.9: 155 wide and 125; twelve
+// products from [33324 x 352 x 200] to [14904 x 2880 x 112], 0.07 to 0.9, 509 and 153; but [49224 x 3160 x 264], 0.60 to 0.68,
+// keep 0.1, 84 and 122).  Over 156 shapes and batches of all sizes at three to five keeps no call is more than 3 % slower so than
+// in 128 x 128 tiles, and all together take 0.97 of the time; without this condition 1.00, the worst 3.7 times as long.
 // Only where the 128 x 128 tiles can address the operands: the general kernel, the other choice, takes 1.1 .. 9 times as long
 // ([1000 x 1000 x 4000] with a far pitch of dY 277 and 31 us, [4000 x 300000 x 8] 10.1 and 6.3 ms), or as long where there is
 // next to nothing to multiply ([512 x 3072 x 8] 17 and 17, [128 x 6144 x 8] 13 and 15).
-constexpr double kFill16 = 0.67;
+constexpr double kFill16 = 0.71;
+double whole_tiles_work(int64_t M, int64_t K, int64_t N) {
+  return (double)M * (double)(ceil_div(K, 128) * 128) * (double)(ceil_div(N, 128) * 128);
+}
 double wide_work(int64_t M, int64_t K, int64_t N, int br, bool alone) {
-  if (br != 16 && alone) return (double)M * (double)(ceil_div(K, 128) * 128) * (double)(ceil_div(N, 128) * 128) / 4.2e9;
+  if (br != 16 && alone) return whole_tiles_work(M, K, N) / 4.2e9;
   return (double)M * (double)K * (double)N / (br == 16 ? 2.5e10 : 5.0e9);
 }
 
@@ -112,6 +115,7 @@ struct WideSums {
   int n[3] = {0, 0, 0};
   int64_t par[3] = {0, 0, 0};
   double work[3] = {0.0, 0.0, 0.0}, work_alone[3] = {0.0, 0.0, 0.0};
+  double plain16 = 0.0, whole16 = 0.0;         // multiply-adds, and of whole 128 x 128 tiles
   bool filled16 = false;
   void add(int64_t M, int64_t K, int64_t N, int br) {
     const int c = wide_class(br);
@@ -119,10 +123,14 @@ struct WideSums {
     par[c] += wide_parallelism(M, K, N, br);
     work[c] += wide_work(M, K, N, br, false);
     work_alone[c] += wide_work(M, K, N, br, true);
+    if (c == 0) {
+      plain16 += (double)M * (double)K * (double)N;
+      whole16 += whole_tiles_work(M, K, N);
+    }
   }
   // Once all are added (`jobs`: the products themselves); then pays() answers.
   void close(const DwJob *jobs, int count) {
-    if (par[0] >= 128 && work[0] >= 1.0) filled16 = dw_wide_fill(jobs, count, 16) >= kFill16;
+    if (par[0] >= 128 && work[0] >= 1.0) filled16 = dw_wide_fill(jobs, count, 16) >= kFill16 * plain16 / whole16;
   }
   // `mfma`: the 128 x 128 tiles, the other choice, can address the operands
   bool pays(int br, bool mfma) const {

@@ -142,8 +142,8 @@ def test_dw_line_of_the_wide_tiles_counts_whole_tiles_of_the_other_kernel(record
 
 
 def test_dw_of_16x16_blocks_takes_wide_tiles_where_they_are_filled(recorder):
-    """Alone and in batches: work enough and tiles that fit dW and keep the compute units busy, or the 128x128 tiles."""
-    wide = [(50176, 1536, 384), (12348, 768, 3072), (40000, 1500, 1000)]
+    """Alone and in batches: work enough, and tiles that fit dW and keep the compute units busy not much worse than 128x128 tiles."""
+    wide = [(50176, 1536, 384), (12348, 768, 3072), (40000, 1500, 1000), (49224, 3160, 264)]
     narrow = [(27817, 408, 3440), (11825, 1576, 1664), (30734, 464, 1816), (6867, 2944, 2528), (25088, 1536, 384)]
     assert [products(g) for g in recorder([one(*s, 16) for s in wide])] == [["dw_wide<16>"]] * len(wide)
     assert [products(g) for g in recorder([one(*s, 16) for s in narrow])] == [["dw_mfma<16>"]] * len(narrow)
