@@ -9,6 +9,7 @@ from pathlib import Path
 
 import pytest
 
+import test_gpu_parity as parity
 from paper_2311_16883_amd import binding as B
 
 HERE = Path(__file__).resolve().parent
@@ -203,3 +204,26 @@ def test_batched_dw_is_taken_whatever_the_operands_allow(recorder):
                               accumulate=rng.choice((0, 1))))
         calls.append({"items": items, "batched": True})
     assert [g["rc"] for g in recorder(calls)] == [0] * len(calls)
+
+
+def test_the_gpu_tests_of_the_wide_tiles_reach_them(recorder):
+    """The sizes that the GPU tests give for the wide tiles, and for both sides of their lines, take the kernels they name."""
+    for b in (32, 64):
+        for M, K, N in (parity.WIDE_RAGGED, parity.WIDE_NON_FINITE):
+            got, = recorder([one(M, K, N, b)])
+            assert products(got) == [f"dw_wide<{b}>"]
+    shapes = [s[:4] for s in parity.wide_random_shapes()]
+    assert [products(g) for g in recorder([one(*s) for s in shapes])] == [[f"dw_wide<{s[3]}>"] for s in shapes]
+    assert products(recorder([batch(*shapes)])[0]) == ["dw_wide<32>", "dw_wide<64>"]
+    alone = recorder([one(*c[:4]) for c in parity.LARGE_DW])
+    pairs = recorder([batch(c[:4], c[:4]) for c in parity.LARGE_DW])
+    assert [products(g) for g in alone] == [[f"dw_{c[5]}<{c[3]}>"] for c in parity.LARGE_DW]
+    assert [products(g) for g in pairs] == [[f"dw_{c[6]}<{c[3]}>"] for c in parity.LARGE_DW]
+    for b in (16, 32, 64):                  # split products and such as one workgroup runs whole
+        assert {bool(reductions(g)) for c, g in zip(parity.LARGE_DW, alone) if c[3] == b and c[5] == "wide"} == {False, True}
+    for b in (16, 32, 64):
+        far, near = dict(M=1000, K=1000, N=400, b=b, lddy=1600000), dict(M=1000, K=1000, N=400, b=b)
+        got = recorder([{"items": [far]}, batch(far, near, far)])
+        assert [sorted(products(g)) for g in got] == [[f"dw_wide<{b}>"], [f"dw_mfma<{b}>", f"dw_wide<{b}>"]]
+    tiles, = recorder([batch(*[(16000, 1536, 512, 32)] * 24)])
+    assert tiles["kernels"][0][0] == "dw_wide<32>" and reductions(tiles) == ["reduce"]

@@ -629,11 +629,24 @@ def test_batched_dw_more_items_than_one_launch_holds():
             assert dw_error(first[i], ref) <= DW_TOL_DERIVED, f"item {i}"
 
 
+# Sizes that the wide-tile kernel takes; that it does is checked where the launches are recorded (test_dw_dispatch.py).
+WIDE_RAGGED = (3600, 1500, 1000)
+WIDE_NON_FINITE = (3072, 1536, 1024)
+
+
+def wide_random_shapes():
+    rng = np.random.default_rng(16883)
+    for i in range(8):
+        bs = int(rng.choice([32, 64]))
+        M = int(rng.integers(4800 // bs, 6400 // bs)) * bs + int(rng.integers(0, bs))
+        yield M, int(rng.integers(900, 1300)), 8 * int(rng.integers(100, 130)), bs, float(rng.choice([0.02, 0.25, 0.5, 0.75, 1.0]))
+
+
 @pytest.mark.parametrize("bs", [32, 64])
 def test_dw_wide_tiles_ragged_everything(bs):
-    """bfloat16 products with 32 or more tiles of 384 x 128 go to the kernel with workgroup-wide
-    tiles: rows, columns and output columns that end inside a block, a tile, a 16-byte chunk."""
-    M, K, N = 2000, 1500, 1000
+    """bfloat16 products of enough work go to the kernel with workgroup-wide tiles of 384 x 128: rows, columns and output
+    columns that end inside a block, a tile, a 16-byte chunk."""
+    M, K, N = WIDE_RAGGED
     print(f"[case] wide-tile dW M={M} K={K} N={N} block={bs}", flush=True)
     X, dY = rand_pair(M, K, N, "bf16", seed=bs, dist="gelu")
     o_scores, o_mask, o_rp, o_ci, o_val = oracle.prune(X, bs, bs, 0.5)
@@ -653,19 +666,15 @@ def test_dw_wide_tiles_ragged_everything(bs):
 def test_dw_wide_tiles_random_shapes():
     """Seeded random shapes through the wide-tile kernel, single calls and a batched call: block size 32 or
     64, rows / columns / output columns that end anywhere (N a multiple of 8, as the kernel needs), keep
-    ratios from nearly nothing to everything, dY as a view of a wider matrix, dW with a pitch of its own."""
-    rng = np.random.default_rng(16883)
+    ratios from nearly nothing to everything, dY as a view of a wider matrix, dW with a pitch of its own.  The reference is the
+    binary64 product of the masked matrix."""
     problems, refs, shapes = [], [], []
-    for i in range(8):
-        bs = int(rng.choice([32, 64]))
-        M = int(rng.integers(40 * bs, 90 * bs)) + int(rng.integers(0, bs))
-        K = int(rng.integers(500, 1300))
-        N = 8 * int(rng.integers(40, 80))
-        keep = float(rng.choice([0.02, 0.25, 0.5, 0.75, 1.0]))
+    for i, (M, K, N, bs, keep) in enumerate(wide_random_shapes()):
         print(f"[case] wide-tile dW, random shape {i}: M={M} K={K} N={N} block={bs} keep={keep}", flush=True)
         X, dY = rand_pair(M, K, N, "bf16", seed=7000 + i, dist="gelu" if i % 2 else "normal")
         _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, bs, bs, keep)
-        ref = oracle.dw(oracle.mask_dense(X, bs, bs, o_mask), dY)
+        xhat = torch.from_numpy(synth.to_f64(oracle.mask_dense(X, bs, bs, o_mask))).cuda()
+        ref = (xhat.T @ torch.from_numpy(synth.to_f64(dY)).cuda()).cpu().numpy()
         rp, ci = torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda()
         val = to_dev(o_val.reshape(-1, bs)).reshape(o_val.shape)
         wide = torch.zeros((M, N + 8 * (i % 3)), dtype=torch.bfloat16, device="cuda")
@@ -727,8 +736,8 @@ def test_non_finite_dy_per_block_shape_family(br, bc, dtype, skips, big):
     kept blocks are multiplied inside zero-filled tiles, and a zero of the tile times inf is NaN)."""
     M, N = 448, 48
     K = 210 if bc == 14 else (245 if bc == 5 else 256)
-    if big:                                # enough tiles for the kernel with workgroup-wide tiles
-        M, K, N = 2048, 1536, 1024
+    if big:                                # enough work for the kernel with workgroup-wide tiles
+        M, K, N = WIDE_NON_FINITE
     X, dY = rand_pair(M, K, N, dtype, seed=br * 100 + bc)
     o_scores, o_mask, o_rp, o_ci, o_val = oracle.prune(X, br, bc, 0.5)
     nbr, nbc = -(-M // br), -(-K // bc)
@@ -1367,7 +1376,8 @@ def test_affine_scale_grad_rows_of_a_block(M, K, bc, dtype, br):
 
 def check_large_dw(M, K, N, bs, keep, copies):
     """dW of one shape, `copies` products in a call (1: the single call): entries of a block-row shuffled, rows of dY with a
-    NaN tail.  The reference is the binary64 product of the masked matrix, which pins the oracle too."""
+    NaN tail; once more added to a dW with a pitch of its own.  The reference is the binary64 product of the masked matrix, which
+    pins the oracle too."""
     print(f"[case] large dW M={M} K={K} N={N} block={bs} keep={keep} x{copies}", flush=True)
     rng = np.random.default_rng(M + bs)
     X, dY = rand_pair(M, K, N, "bf16", seed=M + N + bs)
@@ -1379,25 +1389,40 @@ def check_large_dw(M, K, N, bs, keep, copies):
     val = to_dev(np.ascontiguousarray(o_val[order]))
     dYd = torch.full((M, N + 8), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :N]
     dYd.copy_(to_dev(dY))
+    sums = [torch.full((K, N + 3), 0.25, dtype=torch.float32, device="cuda") for _ in range(copies)]
     if copies == 1:
         got = [B.bsr_t_dense_matmul(rp, ci, val, M, K, bs, bs, dYd)]
+        B.bsr_t_dense_matmul(rp, ci, val, M, K, bs, bs, dYd, dW=sums[0][:, :N], accumulate=True)
     else:
         got = B.bsr_t_dense_matmul_batched(B.MatmulBatch([(rp, ci, val, M, K, bs, bs, dYd)] * copies))
+        B.bsr_t_dense_matmul_batched(B.MatmulBatch([(rp, ci, val, M, K, bs, bs, dYd, s[:, :N]) for s in sums], accumulate=True))
     torch.cuda.synchronize()
-    for dW in got:
+    for dW, s in zip(got, sums):
         assert dw_error(dW.cpu().numpy(), ref) <= DW_TOL_DERIVED
+        # (a binary32 sum with 0.25: half a unit in its last place more)
+        assert dw_error(s[:, :N].cpu().numpy().astype(np.float64) - 0.25, ref) <= DW_TOL_DERIVED + 2.0 ** -23 * max(1.0, 0.25 / np.max(np.abs(ref)))
+        assert bool((s[:, N:] == 0.25).all())
+
+
+# M, K, N, block, keep, kernels of one and of two products (checked where the launches are recorded)
+LARGE_DW = [
+    (5001, 1100, 1000, 32, 0.3, "wide", "wide"),      # everything ragged, enough work for the wide tiles
+    (5001, 1100, 1000, 64, 0.3, "wide", "wide"),
+    (2500, 1300, 1280, 32, 0.5, "wide", "wide"),      # just above that amount
+    (3000, 1000, 1280, 64, 0.9, "mfma", "wide"),      # just below (alone) and above (two products)
+    (3000, 1000, 1280, 32, 0.2, "mfma", "wide"),
+    (1003, 5000, 5008, 32, 0.1, "wide", "wide"),      # more tiles than compute units: no splits, dW written by the tiles
+    (1003, 5000, 5008, 64, 0.1, "wide", "wide"),
+    (20003, 410, 3080, 16, 0.3, "mfma", "mfma"),      # 16x16 blocks, ragged; tiles that fit dW badly
+    (20003, 760, 3080, 16, 0.3, "wide", "wide"),      # ... splits of more block-rows than one table holds
+    (9100, 1500, 1000, 16, 0.6, "mfma", "wide"),      # just below and above the amount of work
+    (4583, 1530, 3840, 16, 0.1, "wide", "wide"),      # two splits, an odd number of block-rows in all
+    (1203, 5000, 6136, 16, 0.1, "wide", "wide"),      # no splits
+]
 
 
 @pytest.mark.parametrize("copies", [1, 2])
-@pytest.mark.parametrize("M,K,N,bs,keep", [
-    (5001, 1100, 1000, 32, 0.3),             # everything ragged, enough work for the wide tiles
-    (5001, 1100, 1000, 64, 0.3),
-    (3000, 1300, 1280, 32, 0.5),             # just below (alone) and above (two products) that amount
-    (3000, 1300, 1280, 64, 0.9),
-    (20003, 410, 3080, 16, 0.3),             # 16x16 blocks, ragged; splits of more block-rows than one table holds
-    (9100, 1500, 1000, 16, 0.6),             # just below and above
-    (1003, 5000, 5008, 16, 0.1),             # splits of a few stages, odd numbers of block-rows
-])
+@pytest.mark.parametrize("M,K,N,bs,keep", [c[:5] for c in LARGE_DW])
 def test_dw_on_both_sides_of_the_wide_tiles_amount_of_work(M, K, N, bs, keep, copies):
     check_large_dw(M, K, N, bs, keep, copies)
 
@@ -1488,3 +1513,22 @@ def test_dw_of_more_than_2_gib_of_blocks(b):
     torch.cuda.synchronize()
     for dW in got:
         assert dw_error(dW.cpu().numpy(), ref.cpu().numpy()) <= DW_TOL_DERIVED
+
+
+@pytest.mark.parametrize("b", [16, 32, 64])
+def test_dw_with_rows_of_dy_far_apart(b):
+    """A pitch of dY that only the wide tiles can address, NaN between the rows; alone and in a batch with a product that takes
+    the 128x128 tiles."""
+    M, K, N, pitch = 1000, 1000, 400, 1600000
+    print(f"[case] dW, far pitch, block={b}", flush=True)
+    X, dY = rand_pair(M, K, N, "bf16", seed=b)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, b, b, 0.5)
+    ref = oracle.dw(oracle.mask_dense(X, b, b, o_mask), dY)
+    far = torch.full((M, pitch), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :N]
+    far.copy_(to_dev(dY))
+    bsr = torch.from_numpy(o_rp).cuda(), torch.from_numpy(o_ci).cuda(), to_dev(o_val)
+    got = [B.bsr_t_dense_matmul(*bsr, M, K, b, b, far)]
+    got += B.bsr_t_dense_matmul_batched(B.MatmulBatch([(*bsr, M, K, b, b, d) for d in (far, to_dev(dY), far)]))
+    torch.cuda.synchronize()
+    for dW in got:
+        assert dw_error(dW.cpu().numpy(), ref) <= DW_TOL_DERIVED
