@@ -67,21 +67,21 @@ bool use_narrow(int dtype, int br, int bc, const void *values, const void *dY, i
 
 // Work from which a call's products are worth the wide kernel, in units of that: its start, its write-out and its few large
 // workgroups cost more than the 128 x 128 tiles until there is enough to multiply.
-// A product of 32x32 or 64x64 blocks on its own (`alone`): 4.2e9 multiply-adds of whole 128 x 128 tiles, which is what the other
-// kernel would spend its time on.  Over 147 shapes of 1e9 .. 1.6e10 multiply-adds at five keeps that is 1.088 times as fast as
-// wide tiles for all (geometric mean), nowhere more than 7 % slower, and 1.5 % from the better kernel each time; a line at 5e9
-// multiply-adds whatever the tiles is up to 22 % slower ([8147 x 152 x 1968], 2.4e9, of whole tiles 4.3e9: 20.9 us wide, 25.5 in
-// 128 x 128 tiles; [12544 x 1536 x 256], keep 0.25: 26.8 and 31.5; on the other side [6272 x 384 x 1536] 27.6 and 22.3,
-// [1095 x 1240 x 2832] 25.8 and 18.7).
-// Several: 5e9 multiply-adds of them all (whole tiles are no better measure there; of 32x32 blocks
-// two products [3136 x 384 x 1536] 29.2 wide and 24.8, [6272 x 384 x 1536] 31.4 and 32.9).
-// 16x16 blocks, where the wide kernel copies by halves of a piece: 2.5e10 multiply-adds ([25088 x 1536 x 384] 48.9 wide and 46.7,
-// [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87), and at least kFill16 times as well filled tiles and
-// compute units as 128 x 128 tiles would be filled (dw_wide_fill): these waste less where the wide tiles don't fit dW, and where
-// workgroups of very different length share a launch ([27817 x 408 x 3440], 0.44 to 0.79, keep 0.9: 155 wide and 125; twelve
-// products from [33324 x 352 x 200] to [14904 x 2880 x 112], 0.07 to 0.9, 509 and 153; but [49224 x 3160 x 264], 0.60 to 0.68,
-// keep 0.1, 84 and 122).  Over 156 shapes and batches of all sizes at three to five keeps no call is more than 3 % slower so than
-// in 128 x 128 tiles, and all together take 0.97 of the time; without this condition 1.00, the worst 3.7 times as long.
+// A product of 32x32 or 64x64 blocks on its own (`alone`): 4.06e9 multiply-adds of whole tiles of 128 rows and whole strips of
+// 32 columns of dW, which is what the other kernel would spend its time on.  Over 147 shapes of 1e9 .. 1.6e10 multiply-adds at
+// five keeps that is 1.089 times as fast as wide tiles for all (geometric mean), nowhere more than 7 % slower, and 1.4 % from
+// the better kernel each time; a line at 5e9 multiply-adds whatever the tiles is up to 22 % slower ([8147 x 152 x 1968], 2.4e9,
+// in whole tiles 4.1e9: 20.9 us wide, 25.5 in 128 x 128 tiles; [12544 x 1536 x 256], keep 0.25: 26.8 and 31.5; on the other
+// side [6272 x 384 x 1536] 27.6 and 22.3, [1095 x 1240 x 2832] 25.8 and 18.7, [10098 x 3616 x 32], keep 0.75, 26.0 and 21.2).
+// Several: 5e9 multiply-adds of them all (whole tiles are no better measure there; two products [3136 x 384 x 1536] in 32x32
+// blocks 29.2 wide and 24.8, [6272 x 384 x 1536] 31.4 and 32.9).
+// 16x16 blocks, where the wide kernel copies by halves of a piece: 2.5e10 multiply-adds ([25088 x 1536 x 384] 48.9 wide and
+// 46.7, [23896 x 880 x 2016] 111 and 126, 8 x [6272 x 384 x 1536], keep 0.25, 68 and 87), and tiles and compute units at least
+// kFill16 times as well filled as 128 x 128 tiles would be (dw_wide_fill): these waste less where the wide tiles don't fit dW,
+// and where workgroups of very different length share a launch ([27817 x 408 x 3440], 0.44 to 0.79, keep 0.9: 155 wide and 125;
+// twelve products from [33324 x 352 x 200] to [14904 x 2880 x 112], 0.07 to 0.9, 509 and 153; but [49224 x 3160 x 264], 0.60 to
+// 0.68, keep 0.1, 84 and 122).  Over 156 shapes and batches of all sizes at three to five keeps no call is more than 3 % slower
+// so than in 128 x 128 tiles, and all together take 0.96 of the time; without this condition 1.00, the worst 3.7 times as long.
 // Only where the 128 x 128 tiles can address the operands: the general kernel, the other choice, takes 1.1 .. 9 times as long
 // ([1000 x 1000 x 4000] with a far pitch of dY 277 and 31 us, [4000 x 300000 x 8] 10.1 and 6.3 ms), or as long where there is
 // next to nothing to multiply ([512 x 3072 x 8] 17 and 17, [128 x 6144 x 8] 13 and 15).
@@ -90,7 +90,7 @@ double whole_tiles_work(int64_t M, int64_t K, int64_t N) {
   return (double)M * (double)(ceil_div(K, 128) * 128) * (double)(ceil_div(N, 128) * 128);
 }
 double wide_work(int64_t M, int64_t K, int64_t N, int br, bool alone) {
-  if (br != 16 && alone) return whole_tiles_work(M, K, N) / 4.2e9;
+  if (br != 16 && alone) return (double)M * (double)(ceil_div(K, 128) * 128) * (double)(ceil_div(N, 32) * 32) / 4.06e9;
   return (double)M * (double)K * (double)N / (br == 16 ? 2.5e10 : 5.0e9);
 }
 

@@ -133,7 +133,7 @@ def test_dw_line_of_the_wide_tiles_counts_whole_tiles_of_the_other_kernel(record
     """A product on its own goes to the wide tiles by what the 128x128 tiles would multiply, whatever part of a tile dW fills;
     several by what there is to multiply."""
     wide = [(8147, 152, 1968), (4062, 416, 2128), (12544, 1536, 256), (9877, 128, 3816), (25088, 384, 1536)]
-    narrow = [(6272, 384, 1536), (800, 2048, 2048), (3677, 760, 1208), (3591, 1952, 224), (1095, 1240, 2832)]
+    narrow = [(6272, 384, 1536), (800, 2048, 2048), (3677, 760, 1208), (3591, 1952, 224), (1095, 1240, 2832), (10098, 3616, 32)]
     assert [products(g) for g in recorder([one(*s, b) for s in wide])] == [[f"dw_wide<{b}>"]] * len(wide)
     assert [products(g) for g in recorder([batch((*s, b)) for s in wide])] == [[f"dw_wide<{b}>"]] * len(wide)
     assert [products(g) for g in recorder([one(*s, b) for s in narrow])] == [[f"dw_mfma<{b}>"]] * len(narrow)
