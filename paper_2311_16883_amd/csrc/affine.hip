@@ -11,6 +11,8 @@
 // four rows' loads in flight; a lane keeps binary32 sums for its (up to kAffVecs) vectors of columns and
 // adds rows top to bottom.  Waves, then splits, are added in a fixed order, so the
 // result is reproducible bit for bit.  Pruned blocks are never touched.
+#include <type_traits>
+
 #include "common.h"
 
 namespace bsr {
@@ -24,7 +26,7 @@ constexpr int kAffCols = 64 * kAffVecs;          // block-columns a workgroup's 
 
 // BY_ROWS: the four waves share the rows of a block-row; otherwise (fewer than eight rows) they take every fourth block-row
 // (1x32 blocks, [25088 x 384] bfloat16: 24.0 us, 44.7 with one wave at work).
-template <typename T, int V, bool BY_ROWS>
+template <typename T, int V, bool BY_ROWS, bool REPEAT>
 __global__ __launch_bounds__(256) void affine_dscale_kernel(
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx, const T *__restrict__ values,
     const T *__restrict__ dY, int64_t M, int64_t K, int64_t lddy, int br, int bc, int64_t nbr, int64_t nbc,
@@ -86,16 +88,23 @@ __global__ __launch_bounds__(256) void affine_dscale_kernel(
           // Vectors of several 16-bit elements: kInFlight loads are always issued; past the last row they repeat it, and the
           // sum leaves them out.  (Under a condition of its own each of them waits for the load before: [25088 x 384]
           // bfloat16, 32x32 blocks, keep 0.5, both kernels: 17.0 us so, 12.3 now.  Loads of whole words do not wait, and
-          // repeats cost 1 .. 8 %.)
-          constexpr bool kRepeat = sizeof(T) == 2 && V >= 4;
+          // repeats cost 1 .. 8 %.)  Where three in eight or more would be repeats (REPEAT false) they are loads of native
+          // vectors under their conditions: [50176 x 768], 8x8 blocks, keep 0.9, 45 us with repeats, 36 so; 20x8 44 and 40;
+          // the other way round [25088 x 1536], 9x8, keep 0.25, 25 and 28.
+          constexpr bool kShort = sizeof(T) == 2 && V >= 4, kRepeat = kShort && REPEAT;
+          typedef std::conditional_t<kShort && !REPEAT, Raw<T, V>, Vec<T, V>> Load;
+          auto elem = [](const Load &x, int q) {
+            if constexpr (kShort && !REPEAT) return raw_elem<T, V>(x, q);
+            else return elem_to_float<T>(x.e[q]);
+          };
           for (int r0 = rg; r0 < rows; r0 += 4 * kInFlight) {
-            Vec<T, V> xv[kInFlight], yv[kInFlight];
+            Load xv[kInFlight], yv[kInFlight];
 #pragma unroll
             for (int k = 0; k < kInFlight; ++k) {
               const int r = !kRepeat || r0 + 4 * k < rows ? r0 + 4 * k : rows - 1;
               if (kRepeat || r < rows) {
-                xv[k] = *reinterpret_cast<const Vec<T, V> *>(xs + (int64_t)r * bc);
-                yv[k] = *reinterpret_cast<const Vec<T, V> *>(ys + (int64_t)r * lddy);
+                xv[k] = *reinterpret_cast<const Load *>(xs + (int64_t)r * bc);
+                yv[k] = *reinterpret_cast<const Load *>(ys + (int64_t)r * lddy);
               }
             }
 #pragma unroll
@@ -104,7 +113,7 @@ __global__ __launch_bounds__(256) void affine_dscale_kernel(
               if (kRepeat || in) {
 #pragma unroll
                 for (int q = 0; q < V; ++q) {
-                  const float sum = fmaf(elem_to_float<T>(xv[k].e[q]), elem_to_float<T>(yv[k].e[q]), acc[u][q]);
+                  const float sum = fmaf(elem(xv[k], q), elem(yv[k], q), acc[u][q]);
                   acc[u][q] = kRepeat && !in ? acc[u][q] : sum;
                 }
               }
@@ -192,12 +201,16 @@ int launch_affine_dscale(const int32_t *row_ptr, const int32_t *col_idx, const v
   affine_split(nbr, p.gx, &p.splits, &p.rows_per_split);
   float *partial = static_cast<float *>(ws);
   const dim3 grid((unsigned)p.gx, (unsigned)p.splits);
-#define BSR_AFFINE_(T, V, W)                                                                                 \
-  hipLaunchKernelGGL((affine_dscale_kernel<T, V, W>), grid, dim3(256), 0, s, row_ptr, col_idx,               \
+#define BSR_AFFINE_(T, V, ...)                                                                               \
+  hipLaunchKernelGGL((affine_dscale_kernel<T, V, __VA_ARGS__>), grid, dim3(256), 0, s, row_ptr, col_idx,     \
                      static_cast<const T *>(values), static_cast<const T *>(dY), M, K, lddy, br, bc, nbr,    \
                      nbc, p.rows_per_split, partial)
-#define BSR_AFFINE(T, V) \
-  if (br >= 8) BSR_AFFINE_(T, V, true); else BSR_AFFINE_(T, V, false)
+  // (each wave loads rows four apart, four at a time: sixteen rows a trip)
+  const bool repeat = 10 * (16 * ((br + 15) / 16)) < 16 * br;
+#define BSR_AFFINE(T, V)                                              \
+  if (br < 8) BSR_AFFINE_(T, V, false, true);                         \
+  else if (sizeof(T) != 2 || V < 4 || repeat) BSR_AFFINE_(T, V, true, true); \
+  else BSR_AFFINE_(T, V, true, sizeof(T) != 2 || V < 4)
   if (dtype == BSR_F32) {
     switch (p.v) {
       case 4: BSR_AFFINE(float, 4); break;
