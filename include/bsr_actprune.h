@@ -211,7 +211,8 @@ int bsr_decompress(const int32_t *row_ptr, const int32_t *col_idx,
  * order, so results are reproducible run to run.
  * Block shapes 32x32, 64x64, 16x16 and 14x14 are multiplied as stored.  Any other
  * shape -- 1 x b row segments, b = K, rectangular blocks -- is first re-tiled into
- * 32x32 blocks inside the workspace; the workspace size reported for such a shape
+ * 32x32 blocks inside the workspace, unless the product is small enough for a
+ * kernel that takes any shape; the workspace size reported for such a shape
  * includes that copy (about M*K elements).
  * col_idx may be in any order inside a block-row.
  * Non-finite dY: a 32x32 or 64x64 block that was pruned is never multiplied, so an

@@ -97,9 +97,12 @@ double wide_work(int64_t M, int64_t K, int64_t N, int br, bool alone) {
 // Block shapes without a kernel of their own: whether re-tiling and the matrix cores (two or three launches, 11 .. 19 us at the
 // least) take less time than the general kernel, which walks the block-rows one after the other and multiplies on the
 // vector units, the slower the fewer rows a block has (tall blocks: by the size of the activation alone; [700 x 100 x 300] in 128x16
-// blocks 29 general and 14 re-tiled).  Measured over 60 shapes up to 3000 x 600 x 2000, in us: [2543 x 26 x 60]
-// in 1x32 blocks 63 general and 13 re-tiled, [563 x 19 x 1069] 28 and 15, [412 x 213 x 26] in 7x5 blocks 9 and 19, [209 x 328 x 190]
-// 14 and 21, [522 x 484 x 131] in 8x8 blocks 25 and 16, [158 x 26 x 932] 10 and 14.
+// blocks 29 general and 14 re-tiled).  In us: [2543 x 26 x 60] in 1x32 blocks 63 general and 13 re-tiled, [563 x 19 x 1069] 28
+// and 15, [412 x 213 x 26] in 7x5 blocks 9 and 19, [209 x 328 x 190] 14 and 21, [522 x 484 x 131] in 8x8 blocks 25 and 16,
+// [158 x 26 x 932] 10 and 14.  Short and wide activations in small blocks, whose entries every workgroup of either kernel
+// searches, are no different: [8 x 20000 x 10] in 1x1 blocks 28 and 57, [64 x 8000 x 8] in 2x2 24 and 32.  Of 232 shapes up to
+// 20000 rows, 60000 columns of X and 4000 of dW, 30 take the slower of the two by more than 6 %: few rows in 1x32 or 1x128
+// blocks ([41 x 3277 x 30] 22 and 12) and few in tall ones ([210 x 121 x 23] in 300x4 blocks 50 and 15).
 bool retiling_pays(int64_t M, int64_t K, int64_t N, int br) {
   if (br > 16) return M * K > 65536;
   const double general_us = 9.0 + 0.025 * (double)ceil_div(M, br) + 1e-6 * (double)M * (double)K * (double)N * (0.25 + 0.75 / br);

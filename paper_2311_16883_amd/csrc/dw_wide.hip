@@ -41,7 +41,7 @@
 //  * 16x16 blocks: a piece is two block-columns wide and a stage two block-rows high.  Copied and multiplied are halves of
 //    a piece, 16 rows x 32 columns, that hold a kept block; one copy instruction fetches both blocks of a half, each lane with
 //    its own block's offset, and brings zeros for a pruned block beside a kept one (its offset lies beyond the buffer).
-//    ([50176 x 1536 x 384], keep 0.25: 75 us in 128 x 128 tiles, 67 so; 18 products [4116 x 768 x 3072], keep 0.25: 476, 285.)
+//    ([50176 x 1536 x 384], keep 0.25: 72 us in 128 x 128 tiles, 59 so; 18 products [4116 x 768 x 3072], keep 0.25: 462, 270.)
 //  * The multiplying waves are software-pipelined across the barrier by half a
 //    stage: the fragments of a wave's last two pieces are multiplied after the
 //    next barrier, while the first reads of the next stage are on their way.
@@ -588,7 +588,7 @@ constexpr double kStageUs = 0.5, kPartialBytesPerUs = 3.0e6;
 
 // Splits of the contraction the planner may pick: sixteen, or up to 24 where a product of few tiles would leave compute units
 // without one and its contraction is long enough for that to pay ([50176 x 1536 x 384], 12 tiles, keep 0.25: 47.9 us in 16
-// splits, 44.9 in 21; in 16x16 blocks 68 and 61; [50176 x 1536 x 256], 8 tiles, keep 0.75: 62.7 and 54.2 in 24).  More than
+// splits, 44.8 in 21; [50176 x 1536 x 256], 8 tiles, keep 0.75: 61.9 and 51.9 in 24).  More than
 // sixteen, s, save stages * (1/16 - 1/s) stages and cost s - 16 partial matrices, written and read: hence the line.  A
 // workspace holds this many, so it grows with M: one for a whole batch does for a short last one.
 int64_t wide_max_splits(int64_t M, int64_t K, int64_t N, int bs) {

@@ -126,8 +126,6 @@ static_assert(alignof(LooseVec) == 2 && alignof(LooseBytes) == 1, "no more than 
 // VB of the kernels that move 16-byte vectors whose dense side starts at any element (rows of an odd
 // width, an unaligned view); a vector that crosses the matrix edge goes element by element.
 constexpr int kLoose = 1;
-template <> struct BytesOf<kLoose> { typedef uint4 type; };
-template <> __device__ __forceinline__ uint4 zero_bytes<kLoose>() { return make_uint4(0, 0, 0, 0); }
 template <int VB> constexpr int vector_bytes() { return VB == kLoose ? 16 : VB; }
 
 // Gather: one workgroup per block-row (grid-stride), threads over
