@@ -152,6 +152,38 @@ bool use_wide_single(int dtype, const DwJob &j) {
   return sums.pays(j.br, dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy));
 }
 
+// Whether a product on its own takes the kernel whose waves each gather the kept blocks of one strip, instead of the 128 x 128
+// tiles.  Both sides measured, in us (tiles, so), and both plans' estimates compared.
+// binary32, 14- and 16-wide blocks gain from being
+// skipped one by one (1.05 .. 2.6 times as fast over 36 shapes), up to large activations in 14x14 blocks, whose rows the 128 x 128 tiles
+// load in wider vectors ([13986 x 1877 x 39], 2.6e7 elements: 46 and 31 at keep 0.25, 50 and 47 at 0.5, 54 and 63 at 0.75;
+// [50000 x 784 x 128], keep 0.9: 124 and 139).  32x32 and 64x64 blocks gain wherever
+// the 128 x 128 tiles don't fill the compute units or dW, or there are few stages; where they do, they load less for
+// each multiply-add: of 95 calls at keeps .1 .. .9 [1294 x 1344 x 1440] 53 and 35, estimates 1 : 0.45; [9095 x 1504 x 224]
+// 48.9 and 49.5, 1 : 0.65; [6272 x 384 x 1536] 50 and 55, 1 : 0.72; [12544 x 384 x 1536] 87 and 87, 1 : 0.75.
+// bfloat16, where the matrix cores are fast enough that each strip's own pass over dY counts: small products, 1.3 .. 2.2 times as fast
+// ([256 x 128 x 64] 7.4 and 5.7, [1202 x 152 x 446] 12.7 and 7.1, [705 x 416 x 128] in 14x14 blocks 10.9 and 5.9), the fewer blocks are
+// kept the longer: at keep 0.9 [4415 x 456 x 220] in 14x14 blocks, 4.4e8 multiply-adds, 15.6 and 17.1, [3677 x 760 x 1208] in 32x32
+// blocks 0.88 times as fast (2.2 times at keep 0.1), [585 x 705 x 1871], estimates 1 : 0.64, 0.92 times.  Beyond 1.1e9 multiply-adds only
+// small activations, most of whose time is the launches' ([2006 x 454 x 1472], keep 0.9: 18.9 and 15.7), and rows of dY on odd elements in 32x32 blocks,
+// which the tiles load at half the rate ([9947 x 411 x 1001] 31.6 and 25.0 at keep 0.5, 0.84 times as fast at 0.9, 2.9 times at 0.1;
+// [9232 x 666 x 383] 2.0 times at 0.25; [5530 x 654 x 943] 0.99 times at 0.9; in 64x64 blocks [8117 x 337 x 585], keep 0.9, 0.74 times).
+bool use_direct(int dtype, const DwJob &j) {
+  if (!dw_direct_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return false;
+  if (!dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return true;
+  if (dtype == BSR_F32 && j.bc < 32) return j.bc == 16 || j.M * j.K < 25000000;
+  const double work = (double)j.M * (double)j.K * (double)j.N;
+  double line = 0.69;
+  if (dtype == BSR_BF16) {
+    const bool odd = j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0;
+    if (j.bc < 32) line = work < 4e8 ? 0.69 : 0.0;
+    else if (work < 1.1e9) line = 0.62;
+    else if (odd) line = j.bc == 32 ? 0.72 : 0.0;
+    else line = j.M * j.K < 2000000 ? 0.5 : 0.0;
+  }
+  return line > 0.0 && dw_direct_us(dtype, j.M, j.K, j.N, j.br, j.bc) < line * dw_mfma_us(dtype, j.M, j.K, j.N, j.br);
+}
+
 // Workspace of a product, whatever kernel takes it.  (The wide tiles take activations that the 128 x 128 tiles don't, from 2 GiB
 // up to 4 GiB, and rows of dY further apart.)
 size_t dw_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
@@ -165,6 +197,10 @@ size_t dw_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   }
   if (dw_narrow_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
     b = dw_narrow_ws_bytes(M, K, N, br);
+    if (b > a) a = b;
+  }
+  if (dw_direct_supported(dtype, br, bc, nullptr, M, K, N, N)) {
+    b = dw_direct_ws_bytes(dtype, M, K, N, br, bc);
     if (b > a) a = b;
   }
   return align_up(a, 256);
@@ -188,7 +224,9 @@ DwRoutes dw_routes(int dtype, const std::vector<DwJob> &jobs, bool several) {
   std::vector<int> maybe;
   for (int i = 0; i < (int)jobs.size(); ++i) {
     const DwJob &j = jobs[i];
-    if (several && use_narrow(dtype, j.br, j.bc, j.values, j.dY, j.M, j.K, j.N, j.lddy)) {
+    if (!several && !use_wide_single(dtype, j) && use_direct(dtype, j)) {
+      r.single.push_back(i);
+    } else if (several && use_narrow(dtype, j.br, j.bc, j.values, j.dY, j.M, j.K, j.N, j.lddy)) {
       r.narrow.push_back(i);
     } else if (dw_wide_supported(dtype, j.br, j.bc, j.values, j.dY, j.M, j.K, j.N, j.lddy)) {
       maybe.push_back(i);
@@ -212,6 +250,7 @@ DwRoutes dw_routes(int dtype, const std::vector<DwJob> &jobs, bool several) {
 // One product, with a workspace of dw_ws_bytes or more.
 int launch_dw(int dtype, const DwJob &j, hipStream_t s) {
   if (use_wide_single(dtype, j)) return launch_dw_wide(j, s);
+  if (use_direct(dtype, j)) return launch_dw_direct(dtype, j, s);
   if (dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy))
     return launch_dw_mfma(dtype, j.row_ptr, j.col_idx, j.values, j.M, j.K, j.br, j.bc, j.dY, j.N, j.lddy, j.dW, j.lddw, j.accumulate,
                           j.ws, j.ws_bytes, s);

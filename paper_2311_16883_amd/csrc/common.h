@@ -126,6 +126,8 @@ int launch_dw_generic(const int32_t *row_ptr, const int32_t *col_idx, const void
 bool dw_mfma_supported(int dtype, int br, int bc, const void *values, int64_t M, int64_t K, int64_t N,
                        int64_t lddy);
 size_t dw_mfma_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc);
+// What the plan of a product on its own estimates, in microseconds.
+double dw_mfma_us(int dtype, int64_t M, int64_t K, int64_t N, int br);
 int launch_dw_mfma(int dtype, const int32_t *row_ptr, const int32_t *col_idx, const void *values, int64_t M,
                    int64_t K, int br, int bc, const void *dY, int64_t N, int64_t lddy, float *dW,
                    int64_t lddw, int accumulate, void *ws, size_t ws_bytes, hipStream_t s);
@@ -198,6 +200,12 @@ struct DwJob {
 // dw_mfma.hip: the jobs (all of block shapes and sizes dw_mfma_supported accepts, none with
 // K == 0 or N == 0) with as few launches as their kernel instances allow.
 int launch_dw_mfma_batched(int dtype, const DwJob *jobs, int n, hipStream_t s);
+
+// dw_direct.hip: binary32, 14x14, 16x16, 32x32, 64x64 blocks, no staging: one product per launch.
+bool dw_direct_supported(int dtype, int br, int bc, const void *values, int64_t M, int64_t K, int64_t N, int64_t lddy);
+double dw_direct_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc);      // as its plan estimates it
+size_t dw_direct_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc);
+int launch_dw_direct(int dtype, const DwJob &j, hipStream_t s);
 
 // dw_wide.hip: bfloat16, 16x16 / 32x32 / 64x64 blocks, 384-row tiles fed by global -> LDS copies.
 // dw_narrow.hip: bfloat16, small square blocks, a weight matrix of at most 224 x 224: one workgroup owns all of dW

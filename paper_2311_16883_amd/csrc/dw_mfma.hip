@@ -948,6 +948,17 @@ bool dw_mfma_supported(int dtype, int br, int bc, const void *values, int64_t M,
   return true;
 }
 
+double dw_mfma_us(int dtype, int64_t M, int64_t K, int64_t N, int br) {
+  const bool f32 = dtype == BSR_F32;
+  switch (br) {
+    case 32: return f32 ? make_plan<4, 32, 64>(M, K, N, false).cost : make_plan<2, 32, 64>(M, K, N, false).cost;
+    case 64: return f32 ? make_plan<4, 64, 64>(M, K, N, false).cost : make_plan<2, 64, 64>(M, K, N, false).cost;
+    case 16: return f32 ? make_plan<4, 16, 32>(M, K, N, false).cost : make_plan<2, 16, 64>(M, K, N, false).cost;
+    case 14: return f32 ? make_plan<4, 14, 32>(M, K, N, false).cost : make_plan<2, 14, 64>(M, K, N, false).cost;
+    default: return 0.0;
+  }
+}
+
 size_t dw_mfma_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   (void)bc;
   const bool f32 = dtype == BSR_F32;
