@@ -22,7 +22,8 @@ struct ScoreGeom {
   int gb;    // row groups per block-row
   int rb;    // block-rows handled per pass
   int nchunks;
-  int direct;  // score_direct_body (1; 2: its form for few tall blocks), gb lanes per vector column of a block; nchunks = its workgroups
+  int direct;  // score_direct_body (1; 2: its form for few tall blocks), gb lanes per vector column of a block and vpbt of
+               // these in a block; nchunks = its workgroups
 };
 
 // bx, by, gy: the workgroup's place in its tensor's (chunks x passes) grid.  Threads beyond
@@ -104,25 +105,53 @@ __device__ __forceinline__ void score_body(
 // chain of additions as long as its rows.  rs = 8 .. 64 lanes share a column, a number that follows from the matrix and the
 // block alone (score_geometry), and each keeps two sums, of the even and of the odd elements.  ([4096 x 384] binary32
 // in 256x16 blocks, score and select: 16.0 us through the LDS body, 7.5 so.)
-// wg = index of the workgroup among the ceil(nbr * nbc * (bc / V) * RS / 256) of its tensor.
-template <typename T, int V, int RS>
+// LOOSE: rows that begin at any element, block widths that are no whole vectors, a last block in part: 16 bytes at a time
+// all the same (global loads need no alignment beyond the element's).  What a vector holds beyond its block or the last column is set
+// to zero, a vector that would reach beyond the last element of X ends there and is shifted.  (Score and select, bf16,
+// through 2- and 4-byte loads and the LDS body and so: [41298 x 805] in 14x14 blocks 102 and 32 us, [23394 x 1453] 99 and 32,
+// [10307 x 1071] in 1x32 75 and 28, [30022 x 1153] in 64x64 31 and 24.)
+// wg = index of the workgroup among the ceil(nbr * nbc * vpb * RS / 256) of its tensor.
+template <typename T, int V, int RS, bool LOOSE>
 __device__ __forceinline__ void score_direct_body(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
-    int64_t nbc, int rs, double *__restrict__ scores, uint32_t wg) {
+    int64_t nbc, uint32_t vpb, int rs, double *__restrict__ scores, uint32_t wg) {
+  static_assert(!LOOSE || V * sizeof(T) == 16, "whole vectors of 16 bytes");
   constexpr bool TALL = RS == 0;
   const int lanes = TALL ? rs : RS;
   constexpr int kOwn = TALL ? 2 : kRowClasses / (TALL ? 1 : RS);   // sums a lane keeps: its row classes
-  const uint32_t vpb = (uint32_t)(bc / V);                 // lanes across a block row: a power of two
+  // vpb: lanes across a block row, a power of two
   const uint32_t lpb = vpb * (uint32_t)lanes;              // lanes per block: a power of two, at most 64
   const uint32_t per_row = (uint32_t)nbc * lpb;            // lanes per block-row
   const uint32_t gid = wg * (uint32_t)kScoreThreads + threadIdx.x;
   const uint32_t i = gid / per_row, c = gid - i * per_row;
   const uint32_t j = c / lpb, within = c & (lpb - 1), part = within / vpb, u = within & (vpb - 1);
   const int64_t col = (int64_t)j * bc + (int64_t)u * V;
-  const bool live = (int64_t)i < nbr && col < K;
+  const bool live = (int64_t)i < nbr && col < K && (!LOOSE || (int)u * V < bc);
   const int64_t m0 = (int64_t)i * br;
   const int rows = live ? (int)((M - m0) < br ? (M - m0) : br) : 0;
   const T *p = X + m0 * ldx + col;
+  // LOOSE: the words of a vector that belong to the block, and whether any of the lane's vectors reaches beyond X
+  RawWords<16>::type own = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+  const T *const end = X + (M - 1) * ldx + K;
+  bool near_end = false;
+  if constexpr (LOOSE) {
+    int n = bc - (int)u * V < V ? bc - (int)u * V : V;
+    if (K - col < n) n = (int)(K - col);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int in = n * (int)sizeof(T) - 4 * w;             // bytes of word w inside
+      own[w] = in >= 4 ? 0xFFFFFFFFu : in > 0 ? (1u << (8 * in)) - 1u : 0u;
+    }
+    near_end = rows > 0 && p + (int64_t)(rows - 1) * ldx + V > end;
+  }
+  auto load = [&](const T *at) -> Raw<T, V> {
+    if constexpr (LOOSE) {
+      typedef RawWords<16>::type __attribute__((aligned(2))) Any;
+      return *reinterpret_cast<const Any *>(at);
+    } else {
+      return load_stream(reinterpret_cast<const Raw<T, V> *>(at));
+    }
+  };
   double acc[kOwn];
 #pragma unroll
   for (int k = 0; k < kOwn; ++k) acc[k] = 0.0;
@@ -131,22 +160,44 @@ __device__ __forceinline__ void score_direct_body(
   // a condition came one at a time; score and select of 24 tensors [25088 x 384] took 92 us so, 81 now, of
   // [6000 x 768] in 64x64 blocks 11.9 and 9.8)
   constexpr int kInFlight = 8;
-  for (int r0 = (int)part; r0 < rows; r0 += kInFlight * lanes) {
-    Raw<T, V> v[kInFlight];
+  auto add = [&](Raw<T, V> v, int b) {
+    if constexpr (LOOSE) v &= own;
 #pragma unroll
-    for (int b = 0; b < kInFlight; ++b)
-      if (r0 + b * lanes < rows) v[b] = load_stream(reinterpret_cast<const Raw<T, V> *>(p + (int64_t)(r0 + b * lanes) * ldx));
+    for (int q = 0; q < V; ++q) {
+      const double x = (double)raw_elem<T, V>(v, q);
+      const int k = TALL ? q % 2 : b % kOwn;
+      acc[k] = fma(x, x, acc[k]);
+    }
+  };
+  int first = (int)part;
+  if constexpr (LOOSE) {
+    if (__builtin_expect(near_end, 0)) {                     // one row at a time
+      for (; first < rows; first += kInFlight * lanes) {
 #pragma unroll
-    for (int b = 0; b < kInFlight; ++b) {
-      if (r0 + b * lanes < rows) {
-#pragma unroll
-        for (int q = 0; q < V; ++q) {
-          const double x = (double)raw_elem<T, V>(v[b], q);
-          const int k = TALL ? q % 2 : b % kOwn;
-          acc[k] = fma(x, x, acc[k]);
+        for (int b = 0; b < kInFlight; ++b) {
+          const int r = first + b * lanes;
+          if (r >= rows) continue;
+          const T *const at = p + (int64_t)r * ldx;
+          const int over = at + V > end ? (int)(at + V - end) * (int)sizeof(T) : 0;
+          RawWords<16>::type v = load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(at) - over));
+          uint64_t lo = ((uint64_t)v[1] << 32) | v[0], hi = ((uint64_t)v[3] << 32) | v[2];
+          if (over >= 8) { lo = hi >> (8 * (over - 8)); hi = 0; }
+          else if (over > 0) { lo = (lo >> (8 * over)) | (hi << (64 - 8 * over)); hi >>= 8 * over; }
+          v[0] = (uint32_t)lo; v[1] = (uint32_t)(lo >> 32); v[2] = (uint32_t)hi; v[3] = (uint32_t)(hi >> 32);
+          add(v, b);
+          asm volatile("" ::: "memory");                     // (no loads ahead: their registers would be all lanes')
         }
       }
     }
+  }
+  for (int r0 = first; r0 < rows; r0 += kInFlight * lanes) {
+    Raw<T, V> v[kInFlight];
+#pragma unroll
+    for (int b = 0; b < kInFlight; ++b)
+      if (r0 + b * lanes < rows) v[b] = load(p + (int64_t)(r0 + b * lanes) * ldx);
+#pragma unroll
+    for (int b = 0; b < kInFlight; ++b)
+      if (r0 + b * lanes < rows) add(v[b], b);
   }
 #pragma unroll
   for (int half = kOwn / 2; half >= 1; half /= 2)
@@ -158,27 +209,28 @@ __device__ __forceinline__ void score_direct_body(
   if (live && within == 0) scores[(int64_t)i * nbc + j] = sum;
 }
 
-template <typename T, int V>
+template <typename T, int V, bool LOOSE>
 __device__ __forceinline__ void score_direct(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
     int64_t nbc, const ScoreGeom &g, double *__restrict__ scores, uint32_t wg) {
+  const uint32_t vpb = LOOSE ? (uint32_t)g.vpbt : (uint32_t)(bc / V);
   if (g.direct == 2) {
-    score_direct_body<T, V, 0>(X, M, K, ldx, br, bc, nbr, nbc, g.gb, scores, wg);
+    score_direct_body<T, V, 0, LOOSE>(X, M, K, ldx, br, bc, nbr, nbc, vpb, g.gb, scores, wg);
     return;
   }
   switch (g.gb) {
-    case 1: score_direct_body<T, V, 1>(X, M, K, ldx, br, bc, nbr, nbc, 1, scores, wg); break;
-    case 2: score_direct_body<T, V, 2>(X, M, K, ldx, br, bc, nbr, nbc, 2, scores, wg); break;
-    case 4: score_direct_body<T, V, 4>(X, M, K, ldx, br, bc, nbr, nbc, 4, scores, wg); break;
-    default: score_direct_body<T, V, 8>(X, M, K, ldx, br, bc, nbr, nbc, 8, scores, wg); break;
+    case 1: score_direct_body<T, V, 1, LOOSE>(X, M, K, ldx, br, bc, nbr, nbc, vpb, 1, scores, wg); break;
+    case 2: score_direct_body<T, V, 2, LOOSE>(X, M, K, ldx, br, bc, nbr, nbc, vpb, 2, scores, wg); break;
+    case 4: score_direct_body<T, V, 4, LOOSE>(X, M, K, ldx, br, bc, nbr, nbc, vpb, 4, scores, wg); break;
+    default: score_direct_body<T, V, 8, LOOSE>(X, M, K, ldx, br, bc, nbr, nbc, vpb, 8, scores, wg); break;
   }
 }
 
-template <typename T, int V>
+template <typename T, int V, bool LOOSE>
 __global__ __launch_bounds__(kScoreThreads) void score_kernel(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t nbr,
     int64_t nbc, ScoreGeom g, double *__restrict__ scores) {
-  if (g.direct) score_direct<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g, scores, blockIdx.x);
+  if (LOOSE || g.direct) score_direct<T, V, LOOSE>(X, M, K, ldx, br, bc, nbr, nbc, g, scores, blockIdx.x);
   else score_body<T, V>(X, M, K, ldx, br, bc, nbr, nbc, g, scores, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
@@ -197,14 +249,14 @@ struct ScoreBatch {
   ScoreItem it[kScoreBatchMax];
 };
 
-template <typename T, int V>
+template <typename T, int V, bool LOOSE>
 __global__ __launch_bounds__(kScoreThreads) void score_batched_kernel(ScoreBatch b, int n) {
   int i = 0;
   while (i + 1 < n && blockIdx.x >= b.it[i + 1].wg_begin) ++i;
   const ScoreItem &it = b.it[i];
   const uint32_t local = blockIdx.x - it.wg_begin;
-  if (it.g.direct) {
-    score_direct<T, V>(static_cast<const T *>(it.X), it.M, it.K, it.ldx, it.br, it.bc, it.nbr, it.nbc, it.g, it.scores,
+  if (LOOSE || it.g.direct) {
+    score_direct<T, V, LOOSE>(static_cast<const T *>(it.X), it.M, it.K, it.ldx, it.br, it.bc, it.nbr, it.nbc, it.g, it.scores,
                             local);
     return;
   }
@@ -388,11 +440,13 @@ int run_score_span(const void *X, int64_t M, int64_t K, int bc, const SpanGeom &
 }
 
 // Launch geometry of score_kernel for vectors of V elements in a launch of `tensors` tensors; *gy = passes of
-// the grid.
-ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensors, int64_t *gy_out) {
+// the grid.  loose: of its form for any alignment, which has the direct body only (direct == 0: not for this matrix).
+ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensors, int64_t *gy_out, bool loose = false) {
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
   ScoreGeom g;
-  const int vpb = bc / V;
+  int vpb = bc / V;
+  if (loose)
+    for (vpb = 1; vpb * V < bc;) vpb *= 2;
   g.direct = 0;
   // large matrices take the direct body: rs lanes share a vector column of a block so that the
   // tensor has at least `want` lanes, and every lane still has a few rows.  A tensor on its own wants
@@ -401,7 +455,7 @@ ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensor
   // 128 Ki, 6.8 with 256 Ki, 7.1 with 512 Ki; [25088 x 1536]: 22.4 / 22.8 / 16.7 / 18.7).  Tensors that
   // share a launch fill the chip together, and more lanes a block only cost exchanges there (24 tensors:
   // 188 us with 64 Ki lanes each, 202 with 128 Ki).
-  if (vpb >= 1 && vpb <= 64 && (vpb & (vpb - 1)) == 0 && vpb * V == bc) {
+  if (vpb >= 1 && vpb <= 64 && (vpb & (vpb - 1)) == 0 && (loose || vpb * V == bc)) {
     int64_t want = 262144 / tensors;
     if (want < 65536) want = 65536;
     int rs = 1;
@@ -410,9 +464,12 @@ ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensor
     const bool tall = br >= 128 && rs == kRowClasses && nbr * nbc * vpb * rs < 65536;
     while (tall && nbr * nbc * vpb * rs < 65536 && vpb * rs * 2 <= 64 && rs * 2 * 4 <= br) rs *= 2;
     const int64_t lanes = nbr * nbc * vpb * rs;
-    if (lanes >= 16384 && lanes < (int64_t(1) << 31)) {
+    // (loose, tall blocks: more lanes, or the LDS body, whose row groups share a block, is the faster one; [949 x 1428] in 64x64
+    // blocks, 22080 lanes: score and select 9.3 us there, 11.4 so, [912 x 1299] in 14x14, 24552 lanes: 15.3 and 11.6)
+    if (lanes >= (loose && br >= 64 ? 32768 : 16384) && lanes < (int64_t(1) << 31)) {
       g.direct = tall ? 2 : 1;
-      g.jc = g.vpbt = g.vct = g.rb = 1;
+      g.jc = g.vct = g.rb = 1;
+      g.vpbt = vpb;
       g.gb = rs;
       g.nchunks = (int)ceil_div(lanes, (int64_t)kScoreThreads);
       *gy_out = 1;
@@ -443,27 +500,35 @@ ScoreGeom score_geometry(int V, int64_t M, int64_t K, int br, int bc, int tensor
   return g;
 }
 
-template <typename T, int V>
+template <typename T, int V, bool LOOSE>
 int run_score(const void *X, int64_t M, int64_t K, int64_t ldx, int br, int bc, double *scores,
               hipStream_t s) {
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
   int64_t gy;
-  const ScoreGeom g = score_geometry(V, M, K, br, bc, 1, &gy);
+  const ScoreGeom g = score_geometry(V, M, K, br, bc, 1, &gy, LOOSE);
   dim3 grid((unsigned)g.nchunks, (unsigned)gy, 1);
-  hipLaunchKernelGGL((score_kernel<T, V>), grid, dim3(g.direct ? kScoreThreads : g.vct * g.gb * g.rb), 0, s,
+  hipLaunchKernelGGL((score_kernel<T, V, LOOSE>), grid, dim3(g.direct ? kScoreThreads : g.vct * g.gb * g.rb), 0, s,
                      static_cast<const T *>(X), M, K, ldx, br, bc, nbr, nbc, g, scores);
   return check_launch();
 }
 
-// Which kernel scores a tensor: 0 = score_kernel with vectors of `key` elements,
+// Which kernel scores a tensor: 0 = score_kernel with vectors of `key` elements (kLoose: its form for any alignment),
 // 1 = score_span_kernel with `key`-byte accesses, 2 = score_rows_kernel.
+constexpr int kLoose = 100;
 int score_kind(int dtype, const void *X, int64_t M, int64_t K, int64_t ldx, int br, int bc, SpanGeom *g, int *key) {
+  // (partial sums in LDS: at most 48 KB of binary64 beside the span)
   if (span_geometry(dtype, M, K, ldx, br, bc, X, nullptr, g) &&
       (int64_t)g->rb * br * g->nbc * ((bc + 31) / 32) <= 6144) {
     *key = g->vb;
     return (g->vb == 16 && g->seg_words % 4 == 0) ? 2 : 1;
   }
-  *key = dtype == BSR_F32 ? pick_vector(4, 4, bc, K, ldx, X) : pick_vector(8, 2, bc, K, ldx, X);
+  const int v = dtype == BSR_F32 ? 4 : 8;
+  *key = pick_vector(v, elem_bytes(dtype), bc, K, ldx, X);
+  int64_t gy;
+  if (*key == v || (M - 1) * ldx + K < v || !score_geometry(v, M, K, br, bc, 1, &gy, true).direct) return 0;
+  // (binary32: loads of 4 bytes by consecutive lanes are as good, or better, in the direct body, [40056 x 977] in 32x32 blocks 42 us
+  // and 48 so, but for tall blocks, whose lanes of wider loads make more of a row, [27643 x 69] in 64x64 11.7 and 9.7)
+  if (dtype != BSR_F32 || br >= 64 || !score_geometry(*key, M, K, br, bc, 1, &gy).direct) *key = kLoose;
   return 0;
 }
 
@@ -472,16 +537,18 @@ int launch_generic_batch(const ScoreBatch &b, int n, uint32_t wgs, int v, hipStr
   const dim3 grid(wgs), block(kScoreThreads);
   if (sizeof(T) == 4) {
     switch (v) {
-      case 4: hipLaunchKernelGGL((score_batched_kernel<float, 4>), grid, block, 0, s, b, n); break;
-      case 2: hipLaunchKernelGGL((score_batched_kernel<float, 2>), grid, block, 0, s, b, n); break;
-      default: hipLaunchKernelGGL((score_batched_kernel<float, 1>), grid, block, 0, s, b, n); break;
+      case kLoose: hipLaunchKernelGGL((score_batched_kernel<float, 4, true>), grid, block, 0, s, b, n); break;
+      case 4: hipLaunchKernelGGL((score_batched_kernel<float, 4, false>), grid, block, 0, s, b, n); break;
+      case 2: hipLaunchKernelGGL((score_batched_kernel<float, 2, false>), grid, block, 0, s, b, n); break;
+      default: hipLaunchKernelGGL((score_batched_kernel<float, 1, false>), grid, block, 0, s, b, n); break;
     }
   } else {
     switch (v) {
-      case 8: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 8>), grid, block, 0, s, b, n); break;
-      case 4: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 4>), grid, block, 0, s, b, n); break;
-      case 2: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 2>), grid, block, 0, s, b, n); break;
-      default: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 1>), grid, block, 0, s, b, n); break;
+      case kLoose: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 8, true>), grid, block, 0, s, b, n); break;
+      case 8: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 8, false>), grid, block, 0, s, b, n); break;
+      case 4: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 4, false>), grid, block, 0, s, b, n); break;
+      case 2: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 2, false>), grid, block, 0, s, b, n); break;
+      default: hipLaunchKernelGGL((score_batched_kernel<uint16_t, 1, false>), grid, block, 0, s, b, n); break;
     }
   }
   return check_launch();
@@ -504,31 +571,32 @@ int launch_score(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, in
                  double *scores, hipStream_t s) {
   if (M == 0 || K == 0) return BSR_OK;
   SpanGeom g;
-  // partial sums in LDS: at most 48 KB of binary64 beside the span
-  if (span_geometry(dtype, M, K, ldx, br, bc, X, nullptr, &g) &&
-      (int64_t)g.rb * br * g.nbc * ((bc + 31) / 32) <= 6144)
+  int key;
+  if (score_kind(dtype, X, M, K, ldx, br, bc, &g, &key) != 0)
     return dtype == BSR_F32 ? run_score_span<float>(X, M, K, bc, g, scores, s)
                             : run_score_span<uint16_t>(X, M, K, bc, g, scores, s);
   if (dtype == BSR_F32) {
-    switch (pick_vector(4, 4, bc, K, ldx, X)) {
-      case 4: return run_score<float, 4>(X, M, K, ldx, br, bc, scores, s);
-      case 2: return run_score<float, 2>(X, M, K, ldx, br, bc, scores, s);
-      default: return run_score<float, 1>(X, M, K, ldx, br, bc, scores, s);
+    switch (key) {
+      case kLoose: return run_score<float, 4, true>(X, M, K, ldx, br, bc, scores, s);
+      case 4: return run_score<float, 4, false>(X, M, K, ldx, br, bc, scores, s);
+      case 2: return run_score<float, 2, false>(X, M, K, ldx, br, bc, scores, s);
+      default: return run_score<float, 1, false>(X, M, K, ldx, br, bc, scores, s);
     }
   }
-  switch (pick_vector(8, 2, bc, K, ldx, X)) {
-    case 8: return run_score<uint16_t, 8>(X, M, K, ldx, br, bc, scores, s);
-    case 4: return run_score<uint16_t, 4>(X, M, K, ldx, br, bc, scores, s);
-    case 2: return run_score<uint16_t, 2>(X, M, K, ldx, br, bc, scores, s);
-    default: return run_score<uint16_t, 1>(X, M, K, ldx, br, bc, scores, s);
+  switch (key) {
+    case kLoose: return run_score<uint16_t, 8, true>(X, M, K, ldx, br, bc, scores, s);
+    case 8: return run_score<uint16_t, 8, false>(X, M, K, ldx, br, bc, scores, s);
+    case 4: return run_score<uint16_t, 4, false>(X, M, K, ldx, br, bc, scores, s);
+    case 2: return run_score<uint16_t, 2, false>(X, M, K, ldx, br, bc, scores, s);
+    default: return run_score<uint16_t, 1, false>(X, M, K, ldx, br, bc, scores, s);
   }
 }
 
 int launch_score_batched(const ScoreJob *jobs, int n, int dtype, hipStream_t s) {
   // tensors that take the same kernel instance share launches of up to kScoreBatchMax tensors
-  static const int kKeys[2][4] = {{8, 4, 2, 1}, {16, 8, 4, 0}};
+  static const int kKeys[2][5] = {{kLoose, 8, 4, 2, 1}, {16, 8, 4, 0, 0}};
   for (int kind = 0; kind < 2; ++kind) {
-    for (int ki = 0; ki < 4; ++ki) {
+    for (int ki = 0; ki < 5; ++ki) {
       const int want_key = kKeys[kind][ki];
       if (want_key == 0) continue;
       ScoreBatch gb;
@@ -568,7 +636,7 @@ int launch_score_batched(const ScoreJob *jobs, int n, int dtype, hipStream_t s) 
         if (kind == 0) {
           ScoreItem &it = gb.it[m];
           int64_t gy;
-          it.g = score_geometry(key, j.M, j.K, j.br, j.bc, n, &gy);
+          it.g = score_geometry(key == kLoose ? (dtype == BSR_F32 ? 4 : 8) : key, j.M, j.K, j.br, j.bc, n, &gy, key == kLoose);
           it.X = j.X;
           it.scores = j.scores;
           it.M = j.M; it.K = j.K; it.ldx = j.ldx; it.nbr = nbr; it.nbc = nbc;
