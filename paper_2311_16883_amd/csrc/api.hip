@@ -168,11 +168,17 @@ bool use_wide_single(int dtype, const DwJob &j) {
 // small activations, most of whose time is the launches' ([2006 x 454 x 1472], keep 0.9: 18.9 and 15.7), and rows of dY on odd elements in 32x32 blocks,
 // which the tiles load at half the rate ([9947 x 411 x 1001] 31.6 and 25.0 at keep 0.5, 0.84 times as fast at 0.9, 2.9 times at 0.1;
 // [9232 x 666 x 383] 2.0 times at 0.25; [5530 x 654 x 943] 0.99 times at 0.9; in 64x64 blocks [8117 x 337 x 585], keep 0.9, 0.74 times).
+// Row segments of whole 32 columns: against re-tiling and the tiles, two or three launches, until the entries that every strip's
+// workgroups walk and each strip's own pass over dY count, the sooner the more is kept.  (bfloat16, binary32: [742 x 96 x 2848] in 1x64,
+// keep 0.1, 15.6 and 7.9, 22 and 11; [13177 x 448 x 32] in 1x32 21.8 and 14.6, 32 and 20; [445 x 1152 x 752] in 1x64, keep 0.9, 3.9e8
+// multiply-adds, 15.3 and 12.8, 29 and 23; [1586 x 901 x 342] in 1x32, keep 0.75, 4.9e8, 20.6 and 22.0, 35 and 37;
+// [25088 x 384 x 1536] in 1x32 57 and 89.)
 bool use_direct(int dtype, const DwJob &j) {
   if (!dw_direct_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return false;
+  const double work = (double)j.M * (double)j.K * (double)j.N;
+  if (j.br == 1) return work < 4.2e8;
   if (!dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return true;
   if (dtype == BSR_F32 && j.bc < 32) return j.bc == 16 || j.M * j.K < 25000000;
-  const double work = (double)j.M * (double)j.K * (double)j.N;
   double line = 0.69;
   if (dtype == BSR_BF16) {
     const bool odd = j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0;

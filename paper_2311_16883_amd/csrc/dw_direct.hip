@@ -1,6 +1,6 @@
 // Weight gradient from a BSR activation, one product per launch, without shared tiles in LDS and without a barrier in the main
 // loop: each wave gathers kept blocks and the rows of dY that they meet.  bfloat16 and binary32, 14x14, 16x16, 32x32 and
-// 64x64 blocks.
+// 64x64 blocks, and row segments of whole 32 columns (1x32, 1x64, ...), of which a wave takes 16 kept ones at a time.
 //
 // A workgroup owns one strip of IW rows of dW (all of a block-column, half of a 64-wide one) and IW * NS columns, for a
 // contiguous range of block-rows.  It lists the blocks that this strip keeps in its range, and its W waves take 16-row
@@ -22,6 +22,10 @@
 // bfloat16: a lane's operand is eight (16-wide tiles: four) elements of one column, so a unit goes through a small tile of LDS that belongs to
 // the wave alone and comes back through transposing reads.  Bound by latency ([1202 x 152 x 446] 7.1 us, 12.7 before) and by
 // the loads, 160 rows and columns for each 32 x 128 multiply-adds.
+//
+// Row segments: the rows of a unit are any 16 that keep a segment in this strip, so nothing pruned is multiplied and no re-tiled
+// copy is written ([742 x 96 x 2848] in 1x64 blocks, keep 0.1: 7.9 us, 15.6 re-tiled).  Finding them takes a walk over all entries
+// of the workgroup's rows.
 #include <type_traits>
 
 #include "buffer_access.h"
@@ -38,7 +42,8 @@ typedef __attribute__((ext_vector_type(4))) float v4f;
 typedef __attribute__((ext_vector_type(16))) float v16f;
 
 constexpr uint32_t kDead = 0x80000000u;     // offset in `values` that reads as zero (they stay below 2 GiB)
-constexpr int kMaxRows = 1024;              // block-rows of a split: its list of kept blocks is in LDS
+// block-rows of a split: its list of kept blocks is in LDS
+constexpr int max_rows(int br) { return br == 1 ? 4096 : 1024; }
 constexpr int kUnit = 16;                   // rows of a block that a wave takes at a time
 
 template <int BYTES> struct Words;
@@ -89,6 +94,7 @@ struct Geo {
   static constexpr int KS = 64 / IW;                    // activation rows of one instruction
   static constexpr int STEPS = kUnit / KS;
   static constexpr int UPB = BR > kUnit ? BR / kUnit : 1;   // units of a block
+  static constexpr bool SEGMENTS = BR == 1;             // row segments: a unit is 16 of them; BC stands for a part of 32 columns
   static constexpr int SPB = BC > 32 ? BC / 32 : 1;         // strips of a block-column
   // binary32: columns of a dY load, consecutive ones, and loads of a step; a lane's results are as many consecutive columns
   static constexpr int VQ = E == 2 ? 1 : NS < 4 ? NS : 4;
@@ -99,6 +105,7 @@ struct Geo {
   static constexpr int ABYTES = IW / 2, BLOADS = kUnit * COLS / (64 * 8);
   static constexpr int TILES = E == 2 ? kUnit * (IW + COLS) : 0;
   static_assert(BR <= kUnit || BR % kUnit == 0, "whole units");
+  static_assert(BR != 1 || BC == 32, "parts of segments");
   static_assert(BC <= 16 || BC % 32 == 0, "a strip lies in one block-column");
 };
 
@@ -107,7 +114,7 @@ struct DirectParams {
   const void *values, *dY;
   float *out;
   int64_t M, K, N, lddy, ldo, split_stride, nbr, nbc;
-  int rows_per_split, strips, tiles_n, splits, accumulate;
+  int rows_per_split, strips, tiles_n, splits, accumulate, bc;
 };
 
 // D: units of a wave whose loads are on their way or being multiplied.
@@ -121,10 +128,12 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
   // (results that the waves exchange at a time: 32 KB of them, so that three workgroups of four waves share a compute unit)
   constexpr int kPart = W * R * 256 > 32768 ? 32768 / (W * 256) : R;
   static_assert(R % kPart == 0 && kPart % G::VQ == 0, "whole parts of whole vectors");
-  __shared__ __attribute__((aligned(16))) float sSum[W * kPart * 64 > W * G::TILES / 2 ? W * kPart * 64 : W * G::TILES / 2];
+  constexpr int kSumWords = W * kPart * 64 > W * G::TILES / 2 ? W * kPart * 64 : W * G::TILES / 2;
+  constexpr int kMaxRows = max_rows(BR);
+  __shared__ __attribute__((aligned(16))) float sSum[kSumWords > kMaxRows + 1 ? kSumWords : kMaxRows + 1];
   __shared__ uint2 sUnit[kMaxRows];          // kept blocks of the strip: offset in `values`, first row of dY
-  __shared__ int32_t sAt[kMaxRows];
-  __shared__ int sCount[W];
+  __shared__ int sCount[4 * W];
+  int32_t *const sRow = reinterpret_cast<int32_t *>(sSum);   // (until the main loop)
 
   // XCD x (workgroup id % 8) takes the x-th eighth of the work items, split by split: the tiles of a split read the same
   // rows, which its L2 then fetches once
@@ -133,7 +142,9 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
   if ((int)(blockIdx.x >> 3) >= per_xcd || item >= items) return;
   const int split = item / (prm.strips * prm.tiles_n), tile = item % (prm.strips * prm.tiles_n);
   const int strip = tile % prm.strips, tile_n = tile / prm.strips;
-  const int j = strip / G::SPB, sub = (strip % G::SPB) * 32;      // block-column, first column inside it
+  // block-column, first column inside it
+  const int spb = G::SEGMENTS ? prm.bc / 32 : G::SPB, bc = G::SEGMENTS ? prm.bc : BC;
+  const int j = strip / spb, sub = (strip % spb) * 32;
   const int64_t n0 = (int64_t)tile_n * G::COLS;
   const int64_t i_begin = (int64_t)split * prm.rows_per_split;
   int nrows = prm.rows_per_split;
@@ -144,52 +155,119 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
   const int64_t last = (int64_t)__builtin_amdgcn_readfirstlane(prm.row_ptr[prm.nbr]);
 
   // ---- the strip's kept blocks, in the order of their rows ----
-  for (int e = t; e < nrows; e += kThreads) sAt[e] = -1;
-  int per_row = 1;                           // lanes that share a block-row: a power of two
-  while (per_row < 64 && 2 * per_row * nrows <= kThreads) per_row *= 2;
-  __syncthreads();
-  for (int rr = t / per_row; rr < nrows; rr += kThreads / per_row) {
-    const int32_t p0 = prm.row_ptr[i_begin + rr], p1 = prm.row_ptr[i_begin + rr + 1];
-    constexpr int kTogether = 4;
-    for (int32_t pb = p0 + (t & (per_row - 1)); pb < p1; pb += kTogether * per_row) {
-      int32_t c[kTogether];
-#pragma unroll
-      for (int u = 0; u < kTogether; ++u) c[u] = pb + u * per_row < p1 ? prm.col_idx[pb + u * per_row] : -1;
-#pragma unroll
-      for (int u = 0; u < kTogether; ++u)
-        if (c[u] == j) sAt[rr] = pb + u * per_row;
-    }
-  }
-  __syncthreads();
   int kept = 0;
-  for (int base = 0; base < nrows; base += kThreads) {
-    const int rr = base + t;
-    const int32_t at = rr < nrows ? sAt[rr] : -1;
-    const uint64_t live = __ballot(at >= 0);
-    if (lane == 0) sCount[wave] = __popcll(live);
-    __syncthreads();
-    int before = kept, all = kept;
+  if constexpr (G::SEGMENTS) {
+    // Many rows of few entries: all threads walk the entries together, 16 bytes at a time, and list those of this
+    // block-column; which rows they are in is looked up afterwards.
+    const int32_t *const rp = prm.row_ptr + i_begin;
+    for (int e = t; e <= nrows; e += kThreads) sRow[e] = rp[e];
+    const int32_t e0 = rp[0], e1 = rp[nrows];
+    typedef int32_t __attribute__((ext_vector_type(4), aligned(4))) Entries;
+    constexpr int kTogether = 4;
+    for (int32_t base = e0; base < e1; base += kTogether * 4 * kThreads) {
+      int32_t c[kTogether][4];
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-      before += w < wave ? sCount[w] : 0;
-      all += sCount[w];
+      for (int u = 0; u < kTogether; ++u) {
+        const int32_t e = base + 4 * (u * kThreads + t);
+        if (e + 4 <= e1) {
+          const Entries v = *reinterpret_cast<const Entries *>(prm.col_idx + e);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c[u][q] = v[q];
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c[u][q] = e + q < e1 ? prm.col_idx[e + q] : -1;
+        }
+      }
+      int mine[kTogether];                   // matches of the wave's lanes in front of this one
+      const uint64_t in_front = (1ull << lane) - 1ull;
+#pragma unroll
+      for (int u = 0; u < kTogether; ++u) {
+        int before = 0, all = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint64_t m = __ballot(c[u][q] == j);
+          before += __popcll(m & in_front);
+          all += __popcll(m);
+        }
+        mine[u] = before;
+        if (lane == 0) sCount[u * W + wave] = all;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kTogether; ++u) {
+        int at = kept;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          at += w < wave ? sCount[u * W + w] : 0;
+          kept += sCount[u * W + w];
+        }
+        at += mine[u];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (c[u][q] == j && at < kMaxRows) sUnit[at++].x = (uint32_t)(base + 4 * (u * kThreads + t) + q);
+      }
+      __syncthreads();
     }
-    if (at >= 0) {
-      const int e = before + __popcll(live & ((1ull << lane) - 1ull));
-      sUnit[e] = make_uint2((uint32_t)at * (uint32_t)(BR * BC * E), (uint32_t)(i_begin + rr) * (uint32_t)BR);
+    if (kept > nrows) kept = nrows;          // (a row has a column once)
+    __syncthreads();                         // (sRow, where there is no entry at all)
+    for (int k = t; k < kept; k += kThreads) {
+      const int32_t e = (int32_t)sUnit[k].x;
+      int lo = 0, hi = nrows;                // sRow[lo] <= e < sRow[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (sRow[mid] <= e) lo = mid;
+        else hi = mid;
+      }
+      sUnit[k] = make_uint2((uint32_t)e * (uint32_t)(bc * E), (uint32_t)(i_begin + lo));
     }
-    kept = all;
     __syncthreads();
+  } else {
+    for (int e = t; e < nrows; e += kThreads) sRow[e] = -1;
+    int per_row = 1;                           // lanes that share a block-row: a power of two
+    while (per_row < 64 && 2 * per_row * nrows <= kThreads) per_row *= 2;
+    __syncthreads();
+    for (int rr = t / per_row; rr < nrows; rr += kThreads / per_row) {
+      const int32_t p0 = prm.row_ptr[i_begin + rr], p1 = prm.row_ptr[i_begin + rr + 1];
+      constexpr int kTogether = 4;
+      for (int32_t pb = p0 + (t & (per_row - 1)); pb < p1; pb += kTogether * per_row) {
+        int32_t c[kTogether];
+#pragma unroll
+        for (int u = 0; u < kTogether; ++u) c[u] = pb + u * per_row < p1 ? prm.col_idx[pb + u * per_row] : -1;
+#pragma unroll
+        for (int u = 0; u < kTogether; ++u)
+          if (c[u] == j) sRow[rr] = pb + u * per_row;
+      }
+    }
+    __syncthreads();
+    for (int base = 0; base < nrows; base += kThreads) {
+      const int rr = base + t;
+      const int32_t at = rr < nrows ? sRow[rr] : -1;
+      const uint64_t live = __ballot(at >= 0);
+      if (lane == 0) sCount[wave] = __popcll(live);
+      __syncthreads();
+      int before = kept, all = kept;
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        before += w < wave ? sCount[w] : 0;
+        all += sCount[w];
+      }
+      if (at >= 0) {
+        const int e = before + __popcll(live & ((1ull << lane) - 1ull));
+        sUnit[e] = make_uint2((uint32_t)at * (uint32_t)(BR * BC * E), (uint32_t)(i_begin + rr) * (uint32_t)BR);
+      }
+      kept = all;
+      __syncthreads();
+    }
   }
 
   // ---- main loop ----
   const int64_t stored = last < prm.nbr * prm.nbc ? last : prm.nbr * prm.nbc;
-  const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(prm.values, (uint32_t)stored * (uint32_t)(BR * BC * E));
+  const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(prm.values, (uint32_t)stored * (uint32_t)(BR * bc * E));
   const uint32_t dy_bytes = (uint32_t)(((prm.M - 1) * prm.lddy + prm.N) * E);
   const __amdgpu_buffer_rsrc_t rsrc_b = make_rsrc(prm.dY, dy_bytes);
   const int i = lane % G::IW, kr = lane / G::IW;
   const uint32_t pitch = (uint32_t)prm.lddy * (uint32_t)E;
-  const int units = kept * G::UPB;
+  const int units = G::SEGMENTS ? (kept + kUnit - 1) / kUnit : kept * G::UPB;
 
   typename std::conditional<G::IW == 32, v16f, v4f>::type acc[NS];
 #pragma unroll
@@ -206,6 +284,12 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
     *ea = live ? (uint32_t)__builtin_amdgcn_readfirstlane((int)e.x) + h * (BC * E) : kDead;
     *row = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.y) + h;
     return live;
+  };
+  // (row segments: each lane looks up its own; beyond the last one nothing is read)
+  auto segment_at = [&](int u, int r, bool *live) {
+    const int k = u * kUnit + r;
+    *live = k < kept;
+    return sUnit[*live ? k : 0];
   };
   auto run_units = [&](auto load, auto multiply) {
     if (wave >= units) return;
@@ -231,10 +315,20 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
     BVec b[D][G::STEPS][G::NG];
     run_units(
         [&](int d, int u) {
-          uint32_t ea, row;
-          const bool live = unit_at(u, &ea, &row);
+          uint32_t ea = 0, row = 0;
+          bool live = true;
+          if constexpr (!G::SEGMENTS) live = unit_at(u, &ea, &row);
 #pragma unroll
           for (int s = 0; s < G::STEPS; ++s) {
+            if constexpr (G::SEGMENTS) {
+              const uint2 e = segment_at(u, s * G::KS + kr, &live);
+              a[d][s] = load_words<1>(rsrc_a, live ? e.x + (uint32_t)((sub + i) * 4) : kDead);
+              const uint32_t at = live ? e.y * pitch + (uint32_t)(n0 + G::VQ * i) * 4u : kOutOfRange;
+#pragma unroll
+              for (int g = 0; g < G::NG; ++g)
+                b[d][s][g] = load_words<G::VQ>(rsrc_b, g == 0 || !live ? at : at + (uint32_t)(g * G::IW * G::VQ * 4));
+              continue;
+            }
             // rows beyond a block of 14 belong to the next block-row
             const bool row_ok = BR % kUnit == 0 || (s + 1) * G::KS <= BR || s * G::KS + kr < BR;
             a[d][s] = load_words<1>(rsrc_a, col_ok && row_ok ? ea + a_lane + (uint32_t)(s * G::KS * BC * 4) : kDead);
@@ -270,13 +364,20 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
     const int br = lane / CPR, bcol = lane % CPR * 8;
     run_units(
         [&](int d, int u) {
-          uint32_t ea, row;
-          const bool live = unit_at(u, &ea, &row);
-          a[d] = buffer_load<G::ABYTES>(rsrc_a, a_lane == kDead ? kDead : ea + a_lane);
+          uint32_t ea = 0, row = 0;
+          bool live = true;
+          if constexpr (G::SEGMENTS) {
+            const uint32_t at = segment_at(u, ar, &live).x;
+            a[d] = buffer_load<G::ABYTES>(rsrc_a, live ? at + (uint32_t)((sub + ac) * 2) : kDead);
+          } else {
+            live = unit_at(u, &ea, &row);
+            a[d] = buffer_load<G::ABYTES>(rsrc_a, a_lane == kDead ? kDead : ea + a_lane);
+          }
 #pragma unroll
           for (int it = 0; it < G::BLOADS; ++it) {
             const int r = br + it * (64 / CPR);
-            const bool ok = live && r < (BR < kUnit ? BR : kUnit);
+            if constexpr (G::SEGMENTS) row = segment_at(u, r, &live).y - (uint32_t)r;
+            const bool ok = live && (G::SEGMENTS || r < (BR < kUnit ? BR : kUnit));
             const uint32_t ob = (row + (uint32_t)r) * pitch + (uint32_t)(n0 + bcol) * 2u;
             if constexpr (ODD) {
               const uint32_t end = ob + 16u < dy_bytes ? ob + 16u : dy_bytes;
@@ -352,7 +453,7 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
 #pragma unroll
         for (int q = 0; q < G::VQ; ++q) sum.v[q] += sSum[(w * kPart + v * G::VQ + q) * 64 + lane];
       const int row = G::IW == 32 ? 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) : 4 * (lane >> 4) + r;
-      const int64_t k = (int64_t)j * BC + sub + row, n = n0 + g * G::IW * G::VQ + G::VQ * i;
+      const int64_t k = (int64_t)j * bc + sub + row, n = n0 + g * G::IW * G::VQ + G::VQ * i;
       if ((BC < G::IW && row >= BC) || k >= prm.K) continue;
       float *const dst = o + k * prm.ldo + n;
       if (n + G::VQ <= prm.N) {
@@ -398,8 +499,9 @@ constexpr DirectCosts kCostsBf16 = {2.2, 0.086, 0.05, 0.025, 0.0125, 75.7, 0.4, 
 
 DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
-  const int64_t strips = bc == 64 ? ceil_div(K, 32) : nbc;
-  const int upb = br > kUnit ? br / kUnit : 1, e = elem_bytes(dtype);
+  const int64_t strips = bc > 16 ? ceil_div(K, 32) : nbc;
+  const int kMaxRows = max_rows(br), e = elem_bytes(dtype);
+  const double upb = br > kUnit ? br / kUnit : br == 1 ? 1.0 / kUnit : 1.0;
   const DirectCosts &c = dtype == BSR_F32 ? kCostsF32 : kCostsBf16;
   DirectPlan best{0, 0, 1, (int)(nbr < 1 ? 1 : nbr > kMaxRows ? kMaxRows : nbr)};
   bool any = false;
@@ -408,7 +510,7 @@ DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, 
     const int64_t tiles = strips * ceil_div(N, cols);
     const double unit_us = bc % 32 == 0 ? c.unit32 * (cols / 32) : cols > 64 ? c.unit_wide16 : cols > 32 ? c.unit_mid16 : c.unit_narrow16;
     const double unit_kb = kUnit * e * ((bc < 32 ? bc : 32) + cols) * 1e-3;
-    const int per_cu = v == 0 ? 3 : v == 1 || (e == 4 && bc % 32 != 0) ? 2 : 1;
+    const int per_cu = v == 0 ? (br == 1 ? 2 : 3) : v == 1 || (e == 4 && bc % 32 != 0) ? 2 : 1;
     // (splits beyond four rounds of workgroups gain nothing)
     const int64_t s_min = ceil_div(nbr, (int64_t)kMaxRows), s_full = 1024 * per_cu / tiles + 1;
     int64_t s_max = nbr < 64 ? nbr : 64, rows_before = 0;
@@ -424,7 +526,8 @@ DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, 
         const double on_all = (double)(waves * at_a_time);
         const double mult = unit_us * on_all / 4, load = unit_kb * on_all / c.bytes_per_ns;
         const double busy = mult > load ? mult : load;
-        return c.round + units * (busy > c.on_the_way ? busy : c.on_the_way);
+        // (row segments: every workgroup walks all entries of its rows)
+        return c.round + (br == 1 ? (double)rows * nbc * 2.4e-3 * (double)at_a_time / c.bytes_per_ns : 0.0) + units * (busy > c.on_the_way ? busy : c.on_the_way);
       };
       const int64_t on_a_cu = ceil_div(tiles * splits, (int64_t)256);
       const double us = c.start + (double)(on_a_cu / per_cu) * round_us(per_cu) + (on_a_cu % per_cu ? round_us(on_a_cu % per_cu) : 0.0) +
@@ -461,11 +564,11 @@ template <typename T, int BR, int BC>
 void start_variant(int v, const DirectParams &prm, bool odd, hipStream_t s) {
   constexpr int F = BC % 32 == 0 ? 1 : 2;    // 16-wide tiles: twice as many for the same columns
   if constexpr (sizeof(T) == 4) {
-    if (v == 0) start<T, BR, BC, 4 * F, 4, F == 1 ? 2 : 3, 3>(prm, odd, s);
+    if (v == 0) start<T, BR, BC, 4 * F, 4, F == 1 ? 2 : 3, BR == 1 ? 2 : 3>(prm, odd, s);
     else if (v == 1) start<T, BR, BC, 2 * F, 8, 3, 4>(prm, odd, s);
     else start<T, BR, BC, F, 16, 3, F == 1 ? 4 : 8>(prm, odd, s);
   } else {
-    if (v == 0) start<T, BR, BC, 4 * F, 4, 3, 3>(prm, odd, s);
+    if (v == 0) start<T, BR, BC, 4 * F, 4, 3, BR == 1 ? 2 : 3>(prm, odd, s);
     else if (v == 1) start<T, BR, BC, 2 * F, 8, 4, 4>(prm, odd, s);
     else start<T, BR, BC, F, 16, 4, 4>(prm, odd, s);
   }
@@ -475,6 +578,7 @@ template <typename T>
 int start_shape(int br, int v, const DirectParams &prm, bool odd, hipStream_t s) {
   if (br == 14) start_variant<T, 14, 14>(v, prm, odd, s);
   else if (br == 16) start_variant<T, 16, 16>(v, prm, odd, s);
+  else if (br == 1) start_variant<T, 1, 32>(v, prm, odd, s);
   else if (br == 32) start_variant<T, 32, 32>(v, prm, odd, s);
   else start_variant<T, 64, 64>(v, prm, odd, s);
   return check_launch();
@@ -485,7 +589,8 @@ int start_shape(int br, int v, const DirectParams &prm, bool odd, hipStream_t s)
 // The operands are addressed with 32-bit byte offsets, the activation's below 2 GiB.  (bfloat16: values in whole 16-byte vectors,
 // dY of one vector at least.)
 bool dw_direct_supported(int dtype, int br, int bc, const void *values, int64_t M, int64_t K, int64_t N, int64_t lddy) {
-  if ((dtype != BSR_F32 && dtype != BSR_BF16) || br != bc || (br != 14 && br != 16 && br != 32 && br != 64)) return false;
+  if ((dtype != BSR_F32 && dtype != BSR_BF16) || (br == 1 ? bc % 32 != 0 : br != bc || (br != 14 && br != 16 && br != 32 && br != 64)))
+    return false;
   if (M < 1 || K < 1 || N < 1) return false;
   const int64_t e = elem_bytes(dtype);
   if (ceil_div(M, br) * br * ceil_div(K, bc) * bc * e >= (int64_t(1) << 31)) return false;
@@ -505,7 +610,7 @@ int launch_dw_direct(int dtype, const DwJob &j, hipStream_t s) {
   const DirectPlan p = direct_plan(dtype, j.M, j.K, j.N, j.br, j.bc);
   const size_t need = p.splits > 1 ? (size_t)p.splits * j.K * j.N * sizeof(float) : 0;
   if (need > 0 && (j.ws == nullptr || j.ws_bytes < need)) return BSR_ERR_WORKSPACE;
-  if (p.rows_per_split > kMaxRows) return BSR_ERR_SHAPE;
+  if (p.rows_per_split > max_rows(j.br)) return BSR_ERR_SHAPE;
   const bool split = p.splits > 1;
   DirectParams prm;
   prm.row_ptr = j.row_ptr; prm.col_idx = j.col_idx;
@@ -516,7 +621,8 @@ int launch_dw_direct(int dtype, const DwJob &j, hipStream_t s) {
   prm.split_stride = split ? j.K * j.N : 0;
   prm.nbr = ceil_div(j.M, j.br); prm.nbc = ceil_div(j.K, j.bc);
   prm.rows_per_split = p.rows_per_split;
-  prm.strips = (int)(j.bc == 64 ? ceil_div(j.K, 32) : prm.nbc);
+  prm.bc = j.bc;
+  prm.strips = (int)(j.bc > 16 ? ceil_div(j.K, 32) : prm.nbc);
   prm.tiles_n = (int)ceil_div(j.N, variant_columns(p.variant));
   prm.splits = p.splits;
   prm.accumulate = split ? 0 : j.accumulate;

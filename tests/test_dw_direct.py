@@ -23,6 +23,11 @@ def test_single_products_by_kernel(recorder):  # noqa: F811
         got = recorder(alone + [dict(a, batched=True) for a in alone])
         assert [g["rc"] for g in got] == [0] * len(got)
         assert all(key in g["names"][0] for g in got), got
+    segments = [dict(items=[dict(M=M, K=K, N=N, br=1, bc=bc)], dtype=dtype) for dtype in (f32, bf16)
+                for M, K, N, bc in ((742, 96, 2848, 64), (13177, 448, 32, 32), (25088, 384, 1536, 32), (742, 96, 2848, 48))]
+    got = recorder(segments + [dict(c, batched=True) for c in segments])
+    assert [g["rc"] for g in got] == [0] * 16
+    assert ["dw_direct" in g["names"][0] for g in got] == [True, True, False, False] * 4
     pair = dict(items=one(256, 128, 64, 16)["items"] * 2, batched=True, dtype=f32)
     got = recorder([pair, dict(one(256, 128, 64, 16, values=(1 << 20) + 4), dtype=f32), one(256, 128, 64, 16, values=(1 << 20) + 2)])
     assert ["dw_direct" in g["names"][0] for g in got] == [False, True, False]
@@ -74,3 +79,39 @@ def test_dw_of_blocks_gathered_by_the_waves(M, K, N, keep, dtype, b):
         again = out.cpu().numpy()
         # (at most 64 splits are added one by one, each sum rounded to 2^-24 of no more than the largest result)
         assert dw_error(again[:, :N], 2.0 * got[:, :N].astype(np.float64)) <= 64 * 2.0 ** -24 and (again[:, N:] == 0.25).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bc", [32, 96])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K,N,keep", [
+    (1, 1, 8, 1.0),
+    (37, 130, 33, 0.5),           # rows on odd elements, a segment in part, units in part
+    (4097, 40, 34, 0.7),          # one row more than the list of a split holds
+    (900, 1000, 140, 0.02),       # strips that keep nothing
+    (1200, 700, 257, 1.0),        # every row
+])
+def test_dw_of_row_segments_gathered_by_the_waves(M, K, N, keep, dtype, bc):
+    """As above, in 1 x bc blocks."""
+    rng = np.random.default_rng(M + bc)
+    X, dY = rand_pair(M, K, N, dtype, seed=M + K)
+    _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, 1, bc, keep)
+    ref = oracle.dw(oracle.mask_dense(X, 1, bc, o_mask), dY)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    flat = torch.full((M * (N + 3) + 128,), float("nan"), device="cuda", dtype=dt)
+    vals = torch.full((o_val.size + 64,), float("nan"), device="cuda", dtype=dt)
+    rp = torch.from_numpy(o_rp).cuda()
+    order = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(o_rp[:-1], o_rp[1:])]).astype(np.int64)
+    for pick, shift, pad in ((np.arange(len(o_ci)), 64, 0), (order, 65, 1)):
+        flat.fill_(float("nan"))
+        dYd = flat[shift:].as_strided((M, N), (N + pad, 1))
+        dYd.copy_(to_dev(dY))
+        val = vals[:o_val.size].view(o_val.shape)
+        val.copy_(to_dev(np.ascontiguousarray(o_val[pick]).reshape(-1, bc)).reshape(o_val.shape))
+        ci = torch.from_numpy(np.ascontiguousarray(o_ci[pick])).cuda()
+        got = B.bsr_t_dense_matmul(rp, ci, val, M, K, 1, bc, dYd).cpu().numpy()
+        assert dw_error(got, ref) <= (DW_TOL_DERIVED if dtype == "bf16" else DW_TOL["f32"])
+        dead = np.ones(K, bool)
+        for j in np.unique(o_ci):
+            dead[j * bc:(j + 1) * bc] = False
+        assert not got[dead].any()
