@@ -126,7 +126,12 @@ static_assert(alignof(LooseVec) == 2 && alignof(LooseBytes) == 1, "no more than 
 // VB of the kernels that move 16-byte vectors whose dense side starts at any element (rows of an odd
 // width, an unaligned view); a vector that crosses the matrix edge goes element by element.
 constexpr int kLoose = 1;
-template <int VB> constexpr int vector_bytes() { return VB == kLoose ? 16 : VB; }
+// VB of the gather whose block rows are no whole 16-byte vectors, but one at least: the last vector of a row ends where the row
+// ends and repeats bytes of the one before (two lanes write the same to the same place), on both sides at any element.  14-wide rows
+// of bfloat16 are two such vectors where pieces of 4 or 2 bytes took 7 or 14 ([41298 x 805], keep 0.9: 44 us and 32 so; [20466 x 2669]
+// 66 and 42; binary32, four where 7 of 8 bytes or 14 of 4 were: 83 and 61, 84 and 66).
+constexpr int kTail = 3;
+template <int VB> constexpr int vector_bytes() { return VB == kLoose || VB == kTail ? 16 : VB; }
 
 // Gather: one workgroup per block-row (grid-stride), threads over
 // (kept block, row, vector).  rowb / ldb / kb are in bytes.
@@ -275,17 +280,46 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint3
 
   // ---- copy ----
   constexpr int kBytes = vector_bytes<VB>();
-  const int vpb = (int)(bcb / kBytes);
+  const int vpb = VB == kTail ? (int)((bcb + 15) / 16) : (int)(bcb / kBytes);
   const int S = br * vpb;                                  // vectors per block
   const uint8_t *xrow = X + i * br * ldb;
-  uint8_t *vrow = values + (int64_t)prefix * S * kBytes;
+  const int64_t block_bytes = VB == kTail ? br * bcb : (int64_t)S * kBytes;
+  uint8_t *vrow = values + (int64_t)prefix * block_bytes;
   const int64_t rows_left = M - i * br;
   // Vector (r, v) of the blocks q0, q0 + step, ...
   auto copy_blocks = [&](int q0, int step, int r, int v, int e) {
     typedef typename RawWords<kBytes>::type W;
     const bool row_in = r < rows_left;
     const uint8_t *src = xrow + (row_in ? (int64_t)r * ldb : 0);
-    if constexpr (VB == kLoose) {
+    if constexpr (VB == kTail) {
+      // four loads together, outside the matrix from the block-row's first bytes
+      const int64_t off = (int64_t)v * 16 < bcb - 16 ? (int64_t)v * 16 : bcb - 16;
+      uint8_t *const dst = vrow + (int64_t)r * bcb + off;
+      constexpr int kInFlight = 4;
+      for (; q0 < (int)nk; q0 += kInFlight * step) {
+        W val[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+          const int q = q0 + u * step < (int)nk ? q0 + u * step : (int)nk - 1;
+          const int64_t cb = (int64_t)kept_j[q] * bcb + off;
+          val[u] = reinterpret_cast<const LooseVec *>(row_in && cb + 16 <= kb ? src + cb : xrow)->v;
+        }
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+          const int q = q0 + u * step;
+          if (q >= (int)nk) continue;
+          const int64_t cb = (int64_t)kept_j[q] * bcb + off;
+          W out = val[u];
+          if (!row_in || cb + 16 > kb) {                     // (the last block-column, or below the matrix)
+            out = W{};
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+              if (row_in && cb + 2 * k < kb) out[k >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(src + cb)[k] << (16 * (k & 1));
+          }
+          reinterpret_cast<LooseVec *>(dst + (int64_t)q * block_bytes)->v = out;
+        }
+      }
+    } else if constexpr (VB == kLoose) {
       // (one after the other: the four together take 2 .. 5 % longer)
 #pragma unroll 4
       for (int q = q0; q < (int)nk; q += step) {
@@ -357,6 +391,64 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint3
 template <int VB>
 __global__ __launch_bounds__(256) void compress_kernel(CompressArgs a) {
   compress_body<VB>(a, blockIdx.x);
+}
+
+// Many block-rows of little each (row segments at any alignment): a wave per block-row, whose place row_ptr_kernel has written.
+// It lists 64 block-columns at a time and copies their kept blocks, 64 vectors of 16 bytes at a time.  Bound by the
+// three dependent trips to memory of a row: many short waves.  ([10307 x 1071] bfloat16 in 1x32 blocks: 350000 blocks, 51 us
+// by an index build and a workgroup per block-row copying element by element, 17 with row_ptr and so; [30000 x 601], keep 0.25,
+// 68 and 24.)
+__global__ __launch_bounds__(256) void compress_rows_kernel(CompressArgs a) {
+  typedef RawWords<16>::type W;
+  __shared__ int32_t kept[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 4 + wave;
+  if (i >= a.nbr) return;                                  // (no barrier below)
+  const uint32_t vpb = (uint32_t)((a.bcb + 15) / 16), S = (uint32_t)a.br * vpb;
+  const int64_t block_bytes = a.br * a.bcb, rows_left = a.M - i * a.br;
+  const uint8_t *const xrow = a.X + i * a.br * a.ldb;
+  const uint8_t *const mrow = a.mask + i * a.nbc;
+  int64_t at = a.row_ptr[i];
+  for (int64_t c0 = 0; c0 < a.nbc; c0 += 64) {
+    const int64_t j = c0 + lane;
+    const bool flag = j < a.nbc && mrow[j] != 0;
+    const uint64_t ball = __ballot(flag);
+    const int pos = __popcll(ball & ((1ull << lane) - 1ull));
+    if (flag) {
+      kept[wave][pos] = (int32_t)j;
+      if (at + pos < a.n_keep) a.col_idx[at + pos] = (int32_t)j;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int64_t nk = __popcll(ball);
+    const int64_t next = at + nk;
+    if (next > a.n_keep) nk = a.n_keep > at ? a.n_keep - at : 0;
+    const uint32_t work = (uint32_t)nk * S;
+    for (uint32_t f0 = (uint32_t)lane; f0 < work; f0 += 128) {
+      W val[2];
+      uint8_t *dst[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t f = f0 + 64 * u < work ? f0 + 64 * u : f0;
+        const uint32_t q = f / S, e = f - q * S, r = e / vpb, v = e - r * vpb;
+        const int64_t off = (int64_t)v * 16 < a.bcb - 16 ? (int64_t)v * 16 : a.bcb - 16;
+        const int64_t cb = (int64_t)kept[wave][q] * a.bcb + off;
+        const bool in = (int64_t)r < rows_left;
+        const uint8_t *const src = xrow + (int64_t)r * a.ldb + cb;
+        val[u] = reinterpret_cast<const LooseVec *>(in && cb + 16 <= a.kb ? src : xrow)->v;
+        if (!in || cb + 16 > a.kb) {
+          val[u] = W{};
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (in && cb + 2 * k < a.kb) val[u][k >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(src)[k] << (16 * (k & 1));
+        }
+        dst[u] = a.values + (at + q) * block_bytes + (int64_t)r * a.bcb + off;
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) reinterpret_cast<LooseVec *>(dst[u])->v = val[u];   // (the first one again behind the last)
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    at = next;
+  }
 }
 
 // Several tensors per launch: tensor k owns the workgroups [wg_begin_k, wg_begin_{k+1}).
@@ -903,7 +995,7 @@ size_t compress_ws_bytes(int dtype, int64_t M, int64_t K, int br, int bc) {
 namespace {
 
 // How one tensor is converted: the kernel family, its vector width and its arguments.
-enum { kPackSpan = 0, kPackDirect = 1, kPackOther = 2 };
+enum { kPackSpan = 0, kPackDirect = 1, kPackOther = 2, kPackRows = 3 };
 struct CompressPlan {
   int path, vb;
   bool count_first;          // span path: a first launch counts every workgroup's kept blocks
@@ -940,6 +1032,15 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
                      nbr * nbr * nbc <= (int64_t(1) << 31);
   if (!fused) {
     p.path = kPackOther;
+    // (blocks so small that a wave does not take long for 64 of them)
+    const int64_t rowb = (int64_t)j.bc * e;
+    if (nbr >= 4096 && nbc > 0 && nbr * nbc <= kRowPtrMaxBlocks && rowb >= 16 && j.K * e >= 16 && j.br * ceil_div(rowb, (int64_t)16) <= 64) {
+      p.path = kPackRows;
+      p.wgs = (unsigned)ceil_div(nbr, (int64_t)4);
+      p.direct = CompressArgs{j.keep_mask, static_cast<const uint8_t *>(j.X), j.row_ptr, j.col_idx,
+                              static_cast<uint8_t *>(j.values), j.M, j.K * e, j.ldx * e, rowb, nbr, nbc,
+                              j.n_keep, j.br, 0u, 1, 1u};
+    }
     return p;
   }
   p.path = kPackDirect;
@@ -947,6 +1048,7 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
   // Rows of X that start anywhere, blocks that are whole 16-byte vectors: 16 bytes from where they are
   // ([9947 x 411] bf16, 32x32 blocks: 22 us element by element, 7 us so).
   if (p.vb < 16 && (int64_t)j.bc * e % 16 == 0 && (uintptr_t)j.values % 16 == 0) p.vb = kLoose;
+  else if (p.vb < 16 && (int64_t)j.bc * e >= 16 && j.K * e >= 16) p.vb = kTail;
   // Every workgroup counts the mask in front of its row, wgs * nblocks / 2 bytes out of L2 in all, unless a
   // launch writes row_ptr first (6 to 8 us).  That is the faster way from 256 MB on (mask of 3136 x 96 blocks, 472 MB:
   // 48 us -> 8 + 30 us; 3136 x 48, 236 MB: 70 us either way; 1568 x 48, 59 MB: 35 -> 39 us), if the count is not hidden
@@ -1029,17 +1131,22 @@ int launch_compress(const uint8_t *keep_mask, const void *X, int dtype, int64_t 
     if (rc != BSR_OK) return rc;
     return launch_pack(X, dtype, M, K, ldx, br, bc, row_ptr, col_idx, n_keep, values, s);
   }
-  if (p.rows_first) {
+  if (p.rows_first || p.path == kPackRows) {
     RowPtrBatch<1> b;
     b.it[0] = RowPtrItem{keep_mask, row_ptr, p.direct.nbr, p.direct.nbc};
     const int rc = run_row_ptr<1>(b, 1, p.direct.nbr * p.direct.nbc, s);
     if (rc != BSR_OK) return rc;
     p.direct.have_row_ptr = 1;
   }
+  if (p.path == kPackRows) {
+    hipLaunchKernelGGL(compress_rows_kernel, dim3(p.wgs), dim3(256), 0, s, p.direct);
+    return check_launch();
+  }
 #define BSR_COMPRESS(VB) hipLaunchKernelGGL((compress_kernel<VB>), dim3(p.wgs), dim3(256), 0, s, p.direct)
   switch (p.vb) {
     case 16: BSR_COMPRESS(16); break;
     case kLoose: BSR_COMPRESS(kLoose); break;
+    case kTail: BSR_COMPRESS(kTail); break;
     case 8: BSR_COMPRESS(8); break;
     case 4: BSR_COMPRESS(4); break;
     default: BSR_COMPRESS(2); break;
@@ -1081,7 +1188,7 @@ int launch_decompress(const int32_t *row_ptr, const int32_t *col_idx, const void
 // pass, separate index build) goes through the single-tensor path.  The results are those of the
 // single-tensor calls (bit copies either way).
 int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream_t s) {
-  static const int kVbs[5] = {16, 8, 4, 2, kLoose};
+  static const int kVbs[6] = {16, 8, 4, 2, kLoose, kTail};
   std::vector<CompressPlan> plans((size_t)n);
   int64_t row_wgs = 0;
   for (int i = 0; i < n; ++i) row_wgs += ceil_div(jobs[i].M, jobs[i].br);
@@ -1103,7 +1210,7 @@ int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream
       CompressPlan &p = plans[(size_t)i];
       const CompressJob &j = jobs[i];
       const int64_t nbr = ceil_div(j.M, j.br), nbc = ceil_div(j.K, j.bc);
-      if (p.path == kPackOther || p.wgs == 0 || nbr * nbc > kRowPtrMaxBlocks || (n < 2 && !p.rows_first)) continue;
+      if (p.path == kPackOther || p.path == kPackRows || p.wgs == 0 || nbr * nbc > kRowPtrMaxBlocks || (n < 2 && !p.rows_first)) continue;
       rb.it[m] = RowPtrItem{j.keep_mask, j.row_ptr, nbr, nbc};
       if (nbr * nbc > most) most = nbr * nbc;
       if (p.path == kPackSpan) {
@@ -1122,7 +1229,7 @@ int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream
     if (rc != BSR_OK) return rc;
   }
   for (int path = kPackSpan; path <= kPackDirect; ++path) {
-    for (int vi = 0; vi < 5; ++vi) {
+    for (int vi = 0; vi < 6; ++vi) {
       const int vb = kVbs[vi];
       CompressBatch db;
       CompressSpanBatch sb;
@@ -1141,6 +1248,7 @@ int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream
           switch (vb) {
             case 16: hipLaunchKernelGGL((compress_batched_kernel<16>), dim3(total), dim3(256), 0, s, db, m); break;
             case kLoose: hipLaunchKernelGGL((compress_batched_kernel<kLoose>), dim3(total), dim3(256), 0, s, db, m); break;
+            case kTail: hipLaunchKernelGGL((compress_batched_kernel<kTail>), dim3(total), dim3(256), 0, s, db, m); break;
             case 8: hipLaunchKernelGGL((compress_batched_kernel<8>), dim3(total), dim3(256), 0, s, db, m); break;
             case 4: hipLaunchKernelGGL((compress_batched_kernel<4>), dim3(total), dim3(256), 0, s, db, m); break;
             default: hipLaunchKernelGGL((compress_batched_kernel<2>), dim3(total), dim3(256), 0, s, db, m); break;
@@ -1175,7 +1283,7 @@ int launch_compress_batched(const CompressJob *jobs, int n, int dtype, hipStream
   for (int i = 0; i < n; ++i) {
     const CompressPlan &p = plans[(size_t)i];
     const CompressJob &j = jobs[i];
-    if (p.path == kPackOther || (p.path == kPackSpan && p.count_first)) {
+    if (p.path == kPackOther || p.path == kPackRows || (p.path == kPackSpan && p.count_first)) {
       const int rc = launch_compress(j.keep_mask, j.X, dtype, j.M, j.K, j.ldx, j.br, j.bc, j.n_keep, j.row_ptr,
                                      j.col_idx, j.values, j.ws, s);
       if (rc != BSR_OK) return rc;
