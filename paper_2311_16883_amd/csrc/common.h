@@ -57,6 +57,11 @@ size_t select_ws_bytes(int64_t nblocks);
 int launch_select(const double *scores, int64_t nblocks, int64_t n_keep, uint8_t *keep_mask, void *ws,
                   hipStream_t s);
 
+// scores and selection of a small matrix in one launch (scores: may be null)
+bool score_select_small_supported(int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc);
+int launch_score_select_small(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t n_keep,
+                              double *scores, uint8_t *keep_mask, hipStream_t s);
+
 // several independent selections with as few launches as their sizes allow
 struct SelectJob {
   const double *scores;

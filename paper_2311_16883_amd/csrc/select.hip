@@ -879,12 +879,87 @@ __global__ __launch_bounds__(256) void select_small_kernel(SelectBatch<N> b) {
   select_one_group<256, 4, 8>(it.scores, it.nblocks, it.n_keep, it.mask, sh, bs);
 }
 
+// Small matrices in few blocks: scored and selected by one workgroup, one launch.  Such calls are bound by what a launch costs on the
+// host, about 2.5 us, and by latency on the GPU; a compute unit takes in 128 KB in about 2 us, as long as a second launch.
+// lpb lanes share a block: vpb of them a row of it, in vectors of 16 bytes at any alignment (what a vector holds beyond the block or the
+// last column is set to zero, one that would reach beyond X is put together from its elements), each every lpb / vpb-th row.
+// ([256 x 128] binary32 in 16x16 blocks, 128 KB: 7.5 us in two launches and 6.6 so, back to back; of that the host's part 7.3 and 4.7, and a
+// small training step, whose calls the host issues one by one, is bound by it: 17.8 and 16.7 us.  [1000 x 32] 16.1 and 7.6, [120 x 250] 9.2 and
+// 7.8; where two rounds of lanes are needed it may take longer back to back, [600 x 100] bfloat16 8.3 and 9.3.)
+constexpr int kFusedThreads = 1024;
+template <typename T>
+__global__ __launch_bounds__(kFusedThreads) void score_select_small_kernel(
+    const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, uint32_t nbc, uint32_t nblocks, uint32_t vpb,
+    uint32_t lpb, uint32_t n_keep, double *__restrict__ scores_out, uint8_t *__restrict__ mask) {
+  constexpr int V = 16 / (int)sizeof(T), kInFlight = 8;
+  typedef RawWords<16>::type W;
+  typedef W __attribute__((aligned(2))) Any;
+  __shared__ SelectShared sh;
+  __shared__ BracketShared bs;
+  __shared__ __attribute__((aligned(16))) double score[1024];
+  const uint32_t rs = lpb / vpb;
+  const T *const end = X + (M - 1) * ldx + K;
+  for (uint32_t g0 = 0; g0 < nblocks * lpb; g0 += kFusedThreads) {
+    const uint32_t gid = g0 + threadIdx.x;
+    const uint32_t b = gid / lpb, within = gid & (lpb - 1), part = within / vpb, u = within & (vpb - 1);
+    const uint32_t i = b / nbc, j = b - i * nbc;
+    const int64_t col = (int64_t)j * bc + (int64_t)u * V, m0 = (int64_t)i * br;
+    const bool live = b < nblocks && col < K && (int)u * V < bc;
+    const int rows = live ? (int)(M - m0 < br ? M - m0 : br) : 0;
+    int n = bc - (int)u * V < V ? bc - (int)u * V : V;       // elements of the vector inside the block and the matrix
+    if (K - col < n) n = (int)(K - col);
+    const T *const p = X + m0 * ldx + col;
+    int whole = rows;                                        // rows whose vector does not reach beyond X
+    while (whole > 0 && p + (int64_t)(whole - 1) * ldx + V > end) --whole;
+    W own;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int in = n * (int)sizeof(T) - 4 * w;
+      own[w] = in >= 4 ? 0xFFFFFFFFu : in > 0 ? (1u << (8 * in)) - 1u : 0u;
+    }
+    double acc[2] = {0.0, 0.0};
+    for (int r0 = (int)part; r0 < whole; r0 += kInFlight * (int)rs) {
+      W v[kInFlight];
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k)
+        if (r0 + k * (int)rs < whole) v[k] = *reinterpret_cast<const Any *>(p + (int64_t)(r0 + k * (int)rs) * ldx);
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k) {
+        if (r0 + k * (int)rs < whole) {
+          v[k] &= own;
+#pragma unroll
+          for (int q = 0; q < V; ++q) {
+            const double x = (double)raw_elem<T, V>(v[k], q);
+            acc[q % 2] = fma(x, x, acc[q % 2]);
+          }
+        }
+      }
+    }
+    for (int r = whole; r < rows; ++r) {
+      if ((uint32_t)r % rs != part) continue;
+      for (int q = 0; q < n; ++q) {
+        const double x = (double)elem_to_float<T>(p[(int64_t)r * ldx + q]);
+        acc[q & 1] = fma(x, x, acc[q & 1]);
+      }
+    }
+    double sum = acc[0] + acc[1];
+    for (uint32_t o = lpb / 2; o >= 1; o /= 2) sum += __shfl_xor(sum, (int)o);
+    if (within == 0 && b < nblocks) {
+      score[b] = sum;
+      if (scores_out != nullptr) scores_out[b] = sum;
+    }
+  }
+  __syncthreads();
+  select_one_group<kFusedThreads, 4, kFinishBits>(score, nblocks, n_keep, mask, sh, bs);
+}
+
 __global__ void fill_u8_kernel(uint8_t *p, int64_t n, uint8_t v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
 }
 
+constexpr int64_t kFusedBytes = 128 << 10;   // largest X that score_select_small_kernel takes
 constexpr int64_t kSmallLimit = 12288;     // one workgroup (up to 12 keys per thread)
 constexpr int64_t kRideAlong = 4096;       // smallest tensor that the grid-wide passes of a batched call take along
 
@@ -966,6 +1041,42 @@ int launch_select(const double *scores, int64_t nblocks, int64_t n_keep, uint8_t
     return check_launch();
   }
   return run_select<1>(b, 1, b.it[0].wgs, s);
+}
+
+namespace {
+
+// Lanes across a row of a block (16-byte vectors) and lanes of a block: as many as the workgroup has, or all rows of a block at once.
+void fused_lanes(int64_t nblocks, int br, int64_t row_bytes, uint32_t *vpb, uint32_t *lpb) {
+  *vpb = 1;
+  while ((int64_t)*vpb * 16 < row_bytes) *vpb *= 2;
+  *lpb = *vpb;
+  while (nblocks * *lpb < kFusedThreads && *lpb < 64 && (int64_t)(*lpb / *vpb) < br) *lpb *= 2;
+}
+
+}  // namespace
+
+// (no more lanes than twice the workgroup's: each further round is a trip to memory, [250 x 128] binary32 in 1x32 blocks, 8000 lanes,
+// 14.5 us so and 7.6 in two launches)
+bool score_select_small_supported(int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc) {
+  const int64_t e = elem_bytes(dtype), nblocks = ceil_div(M, br) * ceil_div(K, bc);
+  if (nblocks > 1024 || M * K * e > kFusedBytes || bc * e > 1024 || br >= 128 || ((M - 1) * ldx + K) * e < 16) return false;
+  uint32_t vpb, lpb;
+  fused_lanes(nblocks, br, bc * e, &vpb, &lpb);
+  return nblocks * lpb <= 2 * kFusedThreads;
+}
+
+int launch_score_select_small(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t n_keep,
+                              double *scores, uint8_t *keep_mask, hipStream_t s) {
+  const int64_t nbc = ceil_div(K, bc), nblocks = ceil_div(M, br) * nbc;
+  uint32_t vpb, lpb;
+  fused_lanes(nblocks, br, (int64_t)bc * elem_bytes(dtype), &vpb, &lpb);
+  if (dtype == BSR_F32)
+    hipLaunchKernelGGL((score_select_small_kernel<float>), dim3(1), dim3(kFusedThreads), 0, s, static_cast<const float *>(X), M, K,
+                       ldx, br, bc, (uint32_t)nbc, (uint32_t)nblocks, vpb, lpb, (uint32_t)n_keep, scores, keep_mask);
+  else
+    hipLaunchKernelGGL((score_select_small_kernel<uint16_t>), dim3(1), dim3(kFusedThreads), 0, s, static_cast<const uint16_t *>(X), M,
+                       K, ldx, br, bc, (uint32_t)nbc, (uint32_t)nblocks, vpb, lpb, (uint32_t)n_keep, scores, keep_mask);
+  return check_launch();
 }
 
 int launch_select_grouped(const double *scores, int64_t nbr, int64_t nbc, int64_t group_rows,

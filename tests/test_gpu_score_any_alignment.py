@@ -37,3 +37,34 @@ def test_scores_of_rows_at_any_alignment(M, K, br, bc, pad, dtype):
     torch.cuda.synchronize()
     for s in got + scores:
         assert np.all(np.abs(s.cpu().numpy().reshape(-1) - ref) <= 2.0 ** -52 * br * bc * ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K,br,bc,pad", [
+    (5, 3, 2, 2, 0),              # hardly more than a vector in all
+    (256, 128, 16, 16, 0),        # whole vectors; the largest that one workgroup takes in binary32
+    (100, 321, 14, 14, 0),        # odd rows, vectors beyond blocks and matrix
+    (37, 500, 1, 64, 3),
+    (127, 130, 64, 64, 1),        # few blocks: 64 lanes for each
+    (1000, 31, 7, 5, 0),          # 1001 blocks
+    (64, 512, 100, 256, 0),       # one block-row, less than a block high
+])
+def test_small_matrices_scored_and_selected_by_one_workgroup(M, K, br, bc, pad, dtype):
+    """Scores to the rounding of their sums, masks as the oracle's at keeps from none to all, with and without scores asked for."""
+    X, _ = rand_pair(M, K, 8, dtype, seed=M + K)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    flat = torch.full((M * (K + pad) + 64,), float("nan"), device="cuda", dtype=dt)
+    Xd = flat[33:].as_strided((M, K), (K + pad, 1))
+    Xd.copy_(to_dev(X))
+    last = flat[:(M - 1) * (K + pad) + K].clone().as_strided((M, K), (K + pad, 1))    # nothing behind the last element
+    last.copy_(Xd)
+    for keep in (0.0, 0.03, 0.5, 1.0):
+        ref, o_mask = oracle.prune(X, br, bc, keep)[:2]
+        for x in (Xd, last):
+            mask, scores = B.bsr_score_select(x, br, bc, keep, want_scores=True)
+            alone = B.bsr_score_select(x, br, bc, keep)
+            torch.cuda.synchronize()
+            assert np.all(np.abs(scores.cpu().numpy().reshape(-1) - ref.reshape(-1)) <= 2.0 ** -52 * br * bc * ref.reshape(-1))
+            assert np.array_equal(mask.cpu().numpy().reshape(-1), o_mask.reshape(-1))
+            assert torch.equal(mask, alone)
