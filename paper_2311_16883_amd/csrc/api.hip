@@ -164,7 +164,8 @@ bool use_wide_single(int dtype, const DwJob &j) {
 // bfloat16, where the matrix cores are fast enough that each strip's own pass over dY counts: small products, 1.3 .. 2.2 times as fast
 // ([256 x 128 x 64] 7.4 and 5.7, [1202 x 152 x 446] 12.7 and 7.1, [705 x 416 x 128] in 14x14 blocks 10.9 and 5.9), the fewer blocks are
 // kept the longer: at keep 0.9 [4415 x 456 x 220] in 14x14 blocks, 4.4e8 multiply-adds, 15.6 and 17.1, [3677 x 760 x 1208] in 32x32
-// blocks 0.88 times as fast (2.2 times at keep 0.1), [585 x 705 x 1871], estimates 1 : 0.64, 0.92 times.  Beyond 1.1e9 multiply-adds only
+// blocks 0.88 times as fast (2.2 times at keep 0.1), [585 x 705 x 1871], estimates 1 : 0.64, 0.92 times, [6777 x 1815 x 88] in 64x64 blocks, 1.1e9, with score, select and conversion 49.0 and 57.5.  Beyond
+// 7e8 multiply-adds (1.1e9 where the activation is small) only
 // small activations, most of whose time is the launches' ([2006 x 454 x 1472], keep 0.9: 18.9 and 15.7), and rows of dY on odd elements in 32x32 blocks,
 // which the tiles load at half the rate ([9947 x 411 x 1001] 31.6 and 25.0 at keep 0.5, 0.84 times as fast at 0.9, 2.9 times at 0.1;
 // [9232 x 666 x 383] 2.0 times at 0.25; [5530 x 654 x 943] 0.99 times at 0.9; in 64x64 blocks [8117 x 337 x 585], keep 0.9, 0.74 times).
@@ -183,7 +184,7 @@ bool use_direct(int dtype, const DwJob &j) {
   if (dtype == BSR_BF16) {
     const bool odd = j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0;
     if (j.bc < 32) line = work < 4e8 ? 0.69 : 0.0;
-    else if (work < 1.1e9) line = 0.62;
+    else if (work < (j.M * j.K < 4000000 ? 1.1e9 : 7e8)) line = 0.62;
     else if (odd) line = j.bc == 32 ? 0.72 : 0.0;
     else line = j.M * j.K < 2000000 ? 0.5 : 0.0;
   }
