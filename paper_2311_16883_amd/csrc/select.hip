@@ -58,6 +58,7 @@ constexpr int kGridThreads = 1024;
 constexpr int kBuckets = 256;    // buckets of the grid-wide passes
 constexpr int kMaxGridWgs = 256; // workgroups of the grid-wide passes, at most
 constexpr int kFinishBits = 10;  // digit of the selection among up to kCap candidates: a bin per thread
+constexpr int kRankedAtOnce = 96;   // candidates that are ranked without a radix pass, at most
 constexpr int kFinishKeys = 8;   // of longer lists, candidates per thread that are taken into registers
 
 typedef unsigned __int128 u128;
@@ -819,6 +820,29 @@ __device__ __forceinline__ void select_classify_body(const SelectItem &it, const
     }
     for (int b = t; b < (1 << kFinishBits); b += kGridThreads) sh.hist[b] = 0;
     __syncthreads();
+    // (a few: ranked right away, the comparisons of a candidate with all others shared by kGridThreads / n threads; a radix pass and
+    // the ranking of what it leaves are four barriers and a scan more.  Score and select, with the pass and so: [12544 x 1536] in 32x32
+    // blocks 22.3 and 19.5 us, [49152 x 196] in 14x14 21.7 and 20.7, [1416 x 790] in 1x32 19.2 and 16.0; some 150 candidates, [40827 x 161] in
+    // 1x64, keep 0.1, 24.5 and 26.4)
+    if (n <= (uint32_t)kRankedAtOnce) {
+      const uint32_t parts = (uint32_t)kGridThreads / n, chunk = (n + parts - 1) / parts;
+      const uint32_t part = (uint32_t)t / n, c = (uint32_t)t - part * n;
+      if (part < parts) {
+        const uint64_t k = skey[c];
+        const uint32_t idx = sidx[c];
+        const uint32_t o0 = part * chunk, o1 = o0 + chunk < n ? o0 + chunk : n;
+        uint32_t better = 0;
+#pragma unroll 4
+        for (uint32_t o = o0; o < o1; ++o) {
+          const uint64_t ok = skey[o];
+          better += (ok > k || (ok == k && sidx[o] < idx)) ? 1u : 0u;
+        }
+        if (better) atomicAdd(&sh.hist[c], better);
+      }
+      __syncthreads();
+      if ((uint32_t)t < n) mask[sidx[t]] = sh.hist[t] < it.n_keep - above ? 1 : 0;
+      return;
+    }
     uint64_t ckey[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) ckey[i] = 4u * (uint32_t)t + i < n ? skey[4 * t + i] : 0ull;
