@@ -342,8 +342,9 @@ int bsr_score_select(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx
   const size_t need = score_select_ws(g.nblocks);
   if (ws == nullptr || ws_bytes < need) return BSR_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (score_select_small_supported(dtype, M, K, ldx, br, bc))
-    return launch_score_select_small(X, dtype, M, K, ldx, br, bc, n_keep, scores, keep_mask, s);
+  SmallScore small;
+  if (plan_score_select_small(X, dtype, M, K, ldx, br, bc, n_keep, &small))
+    return launch_score_select_small(small, X, dtype, M, K, ldx, scores, keep_mask, s);
   double *sc = scores != nullptr ? scores : static_cast<double *>(ws);
   rc = launch_score(X, dtype, M, K, ldx, br, bc, sc, s);
   if (rc != BSR_OK) return rc;

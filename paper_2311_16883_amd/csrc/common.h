@@ -43,6 +43,16 @@ void set_hip_error(int e);
 int launch_score(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc,
                  double *scores, hipStream_t s);
 
+// The order in which launch_score adds up a block, where a kernel of few workgroups can keep to it (false: it cannot).  A block is
+// cut into parts: of a slice of `slice` columns the rows a, a + groups, a + 2 groups, ..., added one after the other, each row left to
+// right; its score is the sum of the parts, row group by row group and in these by column.  vec: elements that can be loaded at
+// a time (loose: from any element, else at their natural alignment and all inside the matrix).
+struct ScoreOrder {
+  int groups, slice, slices, vec;
+  bool loose;
+};
+bool score_order(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, ScoreOrder *o);
+
 // several tensors scored with as few launches as their shapes allow
 struct ScoreJob {
   const void *X;
@@ -57,10 +67,18 @@ size_t select_ws_bytes(int64_t nblocks);
 int launch_select(const double *scores, int64_t nblocks, int64_t n_keep, uint8_t *keep_mask, void *ws,
                   hipStream_t s);
 
-// scores and selection of a small matrix in one launch (scores: may be null)
-bool score_select_small_supported(int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc);
-int launch_score_select_small(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t n_keep,
-                              double *scores, uint8_t *keep_mask, hipStream_t s);
+// Scores and selection of a small matrix in one launch (scores: may be null); the plan says whether it is taken.
+struct SmallScore {
+  int br, bc, groups, slice, vec, loose;     // (see ScoreOrder)
+  int vectors, rows, loads;                  // vectors of a slice and rows of a part, at most; vectors that a thread loads
+  uint32_t nblocks, nbc, block_parts, slices;
+  uint32_t per_round, step_i, step_j;        // blocks that a round of threads takes, as block-rows and block-columns
+  uint32_t n_keep;
+  uint32_t magic_nbc, magic_block_parts, magic_slices;   // see span_div
+};
+bool plan_score_select_small(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t n_keep, SmallScore *g);
+int launch_score_select_small(const SmallScore &g, const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, double *scores,
+                              uint8_t *keep_mask, hipStream_t s);
 
 // several independent selections with as few launches as their sizes allow
 struct SelectJob {

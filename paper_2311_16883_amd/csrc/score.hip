@@ -592,6 +592,26 @@ int launch_score(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, in
   }
 }
 
+bool score_order(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, ScoreOrder *o) {
+  SpanGeom sg;
+  int key;
+  const int v = dtype == BSR_F32 ? 4 : 8, kind = score_kind(dtype, X, M, K, ldx, br, bc, &sg, &key);
+  if (kind == 2) {                                           // score_rows_kernel: vectors of 16 bytes, row by row
+    *o = ScoreOrder{br, v, bc / v, v, false};
+    return true;
+  }
+  if (kind == 1) {                                           // score_span_body: pieces of 32 elements, row by row
+    *o = ScoreOrder{br, 32, (int)ceil_div(bc, 32), v, true};
+    return (M - 1) * ldx + K >= v;
+  }
+  if (key == kLoose) return false;
+  int64_t gy;
+  const ScoreGeom g = score_geometry(key, M, K, br, bc, 1, &gy);
+  if (g.direct || g.vpbt * key != bc) return false;
+  *o = ScoreOrder{g.gb, key, g.vpbt, key, false};            // score_body
+  return true;
+}
+
 int launch_score_batched(const ScoreJob *jobs, int n, int dtype, hipStream_t s) {
   // tensors that take the same kernel instance share launches of up to kScoreBatchMax tensors
   static const int kKeys[2][5] = {{kLoose, 8, 4, 2, 1}, {16, 8, 4, 0, 0}};

@@ -905,76 +905,110 @@ __global__ __launch_bounds__(256) void select_small_kernel(SelectBatch<N> b) {
 
 // Small matrices in few blocks: scored and selected by one workgroup, one launch.  Such calls are bound by what a launch costs on the
 // host, about 2.5 us, and by latency on the GPU; a compute unit takes in 128 KB in about 2 us, as long as a second launch.
-// lpb lanes share a block: vpb of them a row of it, in vectors of 16 bytes at any alignment (what a vector holds beyond the block or the
-// last column is set to zero, one that would reach beyond X is put together from its elements), each every lpb / vpb-th row.
-// ([256 x 128] binary32 in 16x16 blocks, 128 KB: 7.5 us in two launches and 6.6 so, back to back; of that the host's part 7.3 and 4.7, and a
-// small training step, whose calls the host issues one by one, is bound by it: 17.8 and 16.7 us.  [1000 x 32] 16.1 and 7.6, [120 x 250] 9.2 and
-// 7.8; where two rounds of lanes are needed it may take longer back to back, [600 x 100] bfloat16 8.3 and 9.3.)
+// The scores are those of launch_score, bit for bit (other calls rank the same matrix by those): a thread adds up one part of a block
+// after the other as ScoreOrder says -- the rows a, a + groups, ... of a slice of columns -- all its loads on their way together, then a
+// thread per block adds its parts in order.  LOOSE: slices of any width at any element, in vectors of 16 bytes; what a vector holds
+// beyond its slice counts as zero, one that would reach beyond X ends there and is shifted.
 constexpr int kFusedThreads = 1024;
-template <typename T>
+constexpr int kFusedLoads = 8;               // vectors that a thread loads, at most
+constexpr int kFusedParts = 9216;            // sums of parts in LDS, a block's an odd number of places from the next one's
+template <typename T, int V, bool LOOSE>
 __global__ __launch_bounds__(kFusedThreads) void score_select_small_kernel(
-    const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, int br, int bc, uint32_t nbc, uint32_t nblocks, uint32_t vpb,
-    uint32_t lpb, uint32_t n_keep, double *__restrict__ scores_out, uint8_t *__restrict__ mask) {
-  constexpr int V = 16 / (int)sizeof(T), kInFlight = 8;
-  typedef RawWords<16>::type W;
-  typedef W __attribute__((aligned(2))) Any;
+    const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, SmallScore g, double *__restrict__ scores_out,
+    uint8_t *__restrict__ mask) {
+  typedef Raw<T, V> W;
+  static_assert(!LOOSE || sizeof(W) == 16, "whole vectors of 16 bytes");
   __shared__ SelectShared sh;
   __shared__ BracketShared bs;
   __shared__ __attribute__((aligned(16))) double score[1024];
-  const uint32_t rs = lpb / vpb;
+  __shared__ double part[kFusedParts];
+  const uint32_t t = threadIdx.x, pitch = g.block_parts | 1u;
   const T *const end = X + (M - 1) * ldx + K;
-  for (uint32_t g0 = 0; g0 < nblocks * lpb; g0 += kFusedThreads) {
-    const uint32_t gid = g0 + threadIdx.x;
-    const uint32_t b = gid / lpb, within = gid & (lpb - 1), part = within / vpb, u = within & (vpb - 1);
-    const uint32_t i = b / nbc, j = b - i * nbc;
-    const int64_t col = (int64_t)j * bc + (int64_t)u * V, m0 = (int64_t)i * br;
-    const bool live = b < nblocks && col < K && (int)u * V < bc;
-    const int rows = live ? (int)(M - m0 < br ? M - m0 : br) : 0;
-    int n = bc - (int)u * V < V ? bc - (int)u * V : V;       // elements of the vector inside the block and the matrix
-    if (K - col < n) n = (int)(K - col);
-    const T *const p = X + m0 * ldx + col;
-    int whole = rows;                                        // rows whose vector does not reach beyond X
-    while (whole > 0 && p + (int64_t)(whole - 1) * ldx + V > end) --whole;
-    W own;
+  // A thread keeps to one part of a block, q = (row group a, slice u), and goes from block to block, g.per_round at a time.
+  const uint32_t b0 = span_div(t, g.block_parts, g.magic_block_parts), q0 = t - b0 * g.block_parts;
+  const uint32_t a = span_div(q0, g.slices, g.magic_slices), u = q0 - a * g.slices;
+  const uint32_t first = b0 < g.per_round ? b0 : g.nblocks;
+  uint32_t i = span_div(first, g.nbc, g.magic_nbc), j = first - i * g.nbc, block = first;
+  const int wide = g.bc - (int)u * g.slice < g.slice ? g.bc - (int)u * g.slice : g.slice;
+  const T *from = nullptr;                   // of the part that is being loaded: first element, rows below it, columns
+  int below = 0, cols = 0, row = 0, vec = 0;
+  auto locate = [&]() {
+    const int m = (int)(i * (uint32_t)g.br + a), col = (int)(j * (uint32_t)g.bc) + (int)u * g.slice;
+    below = (int)M - m < g.br - (int)a ? (int)M - m : g.br - (int)a;
+    cols = (int)K - col < wide ? (int)K - col : wide;
+    if (block >= g.nblocks) below = 0;
+    from = X + (int64_t)m * ldx + col;
+  };
+  locate();
+  uint32_t out = first * pitch + q0;         // place of the part that is being added
+  int added = 0;
+  double acc = 0.0;
+  W v[kFusedLoads];
+  int n[kFusedLoads], over[kFusedLoads];       // elements of a vector that count, bytes by which it was held back
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int in = n * (int)sizeof(T) - 4 * w;
-      own[w] = in >= 4 ? 0xFFFFFFFFu : in > 0 ? (1u << (8 * in)) - 1u : 0u;
+  for (int k = 0; k < kFusedLoads; ++k) {
+    n[k] = over[k] = 0;
+    if (k >= g.loads) continue;
+    const int left = row * g.groups < below ? cols - vec * V : 0;
+    if (left > 0) {
+      const T *const at = from + (int64_t)(row * g.groups) * ldx + vec * V;
+      n[k] = left < V ? left : V;
+      if constexpr (LOOSE) {
+        typedef W __attribute__((aligned(2))) Any;
+        over[k] = at + V > end ? (int)(at + V - end) * (int)sizeof(T) : 0;
+        v[k] = *reinterpret_cast<const Any *>(reinterpret_cast<const char *>(at) - over[k]);
+      } else {
+        v[k] = *reinterpret_cast<const W *>(at);
+      }
     }
-    double acc[2] = {0.0, 0.0};
-    for (int r0 = (int)part; r0 < whole; r0 += kInFlight * (int)rs) {
-      W v[kInFlight];
+    if (++vec == g.vectors) {
+      vec = 0;
+      if (++row == g.rows) {
+        row = 0;
+        block += g.per_round;
+        i += g.step_i;
+        j += g.step_j;
+        if (j >= g.nbc) { j -= g.nbc; ++i; }
+        locate();
+      }
+    }
+  }
 #pragma unroll
-      for (int k = 0; k < kInFlight; ++k)
-        if (r0 + k * (int)rs < whole) v[k] = *reinterpret_cast<const Any *>(p + (int64_t)(r0 + k * (int)rs) * ldx);
-#pragma unroll
-      for (int k = 0; k < kInFlight; ++k) {
-        if (r0 + k * (int)rs < whole) {
-          v[k] &= own;
-#pragma unroll
-          for (int q = 0; q < V; ++q) {
-            const double x = (double)raw_elem<T, V>(v[k], q);
-            acc[q % 2] = fma(x, x, acc[q % 2]);
-          }
+  for (int k = 0; k < kFusedLoads; ++k) {
+    if (k >= g.loads) continue;
+    if (n[k] > 0) {
+      if constexpr (LOOSE) {
+        if (over[k] > 0) {
+          uint64_t lo = ((uint64_t)v[k][1] << 32) | v[k][0], hi = ((uint64_t)v[k][3] << 32) | v[k][2];
+          if (over[k] >= 8) { lo = hi >> (8 * (over[k] - 8)); hi = 0; }
+          else { lo = (lo >> (8 * over[k])) | (hi << (64 - 8 * over[k])); hi >>= 8 * over[k]; }
+          v[k][0] = (uint32_t)lo; v[k][1] = (uint32_t)(lo >> 32); v[k][2] = (uint32_t)hi; v[k][3] = (uint32_t)(hi >> 32);
         }
       }
-    }
-    for (int r = whole; r < rows; ++r) {
-      if ((uint32_t)r % rs != part) continue;
-      for (int q = 0; q < n; ++q) {
-        const double x = (double)elem_to_float<T>(p[(int64_t)r * ldx + q]);
-        acc[q & 1] = fma(x, x, acc[q & 1]);
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const double x = !LOOSE || q < n[k] ? (double)raw_elem<T, V>(v[k], q) : 0.0;
+        acc = fma(x, x, acc);
       }
     }
-    double sum = acc[0] + acc[1];
-    for (uint32_t o = lpb / 2; o >= 1; o /= 2) sum += __shfl_xor(sum, (int)o);
-    if (within == 0 && b < nblocks) {
-      score[b] = sum;
-      if (scores_out != nullptr) scores_out[b] = sum;
+    if (++added == g.rows * g.vectors) {
+      added = 0;
+      if (out < g.nblocks * pitch) part[out] = acc;
+      out += g.per_round * pitch;
+      acc = 0.0;
     }
   }
   __syncthreads();
-  select_one_group<kFusedThreads, 4, kFinishBits>(score, nblocks, n_keep, mask, sh, bs);
+  if (t < g.nblocks) {
+    const double *const mine = part + t * pitch;
+    double sum = 0.0;
+#pragma unroll 8
+    for (uint32_t q = 0; q < g.block_parts; ++q) sum += mine[q];
+    score[t] = sum;
+    if (scores_out != nullptr) scores_out[t] = sum;
+  }
+  __syncthreads();
+  select_one_group<kFusedThreads, 4, kFinishBits>(score, g.nblocks, g.n_keep, mask, sh, bs);
 }
 
 __global__ void fill_u8_kernel(uint8_t *p, int64_t n, uint8_t v) {
@@ -983,7 +1017,6 @@ __global__ void fill_u8_kernel(uint8_t *p, int64_t n, uint8_t v) {
     p[i] = v;
 }
 
-constexpr int64_t kFusedBytes = 128 << 10;   // largest X that score_select_small_kernel takes
 constexpr int64_t kSmallLimit = 12288;     // one workgroup (up to 12 keys per thread)
 constexpr int64_t kRideAlong = 4096;       // smallest tensor that the grid-wide passes of a batched call take along
 
@@ -1067,39 +1100,47 @@ int launch_select(const double *scores, int64_t nblocks, int64_t n_keep, uint8_t
   return run_select<1>(b, 1, b.it[0].wgs, s);
 }
 
-namespace {
-
-// Lanes across a row of a block (16-byte vectors) and lanes of a block: as many as the workgroup has, or all rows of a block at once.
-void fused_lanes(int64_t nblocks, int br, int64_t row_bytes, uint32_t *vpb, uint32_t *lpb) {
-  *vpb = 1;
-  while ((int64_t)*vpb * 16 < row_bytes) *vpb *= 2;
-  *lpb = *vpb;
-  while (nblocks * *lpb < kFusedThreads && *lpb < 64 && (int64_t)(*lpb / *vpb) < br) *lpb *= 2;
+// Which matrices: what a thread has to do for its vectors, next to what another launch takes, and how many blocks there are to rank.
+// (Score and select back to back, two launches and one, in us: of 330 matrices up to 1.4 times the line none is slower so, 1.47 times as
+// fast in the geometric mean -- binary32 [256 x 128] in 16x16 blocks 7.4 and 7.2 (50 by this count; of that the host's part 7.3 and 4.7),
+// [32 x 64] 7.9 and 5.0, bfloat16 [256 x 128] 7.4 and 6.6; beyond, [250 x 250] bfloat16 in 16x16 (96) 7.9 and 9.5, [1000 x 32] binary32 in
+// 8x8 (56) 6.9 and 7.7, [600 x 100] bfloat16 in 32x32 (144) 8.1 and 11.)
+bool plan_score_select_small(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t n_keep, SmallScore *g) {
+  const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
+  if (nbr > 1024 || nbc > 1024 || nbr * nbc > 1024) return false;
+  ScoreOrder o;
+  if (!score_order(X, dtype, M, K, ldx, br, bc, &o)) return false;
+  const int64_t nblocks = nbr * nbc, block_parts = (int64_t)o.groups * o.slices;
+  if (block_parts > kFusedThreads || nblocks * (block_parts | 1) > kFusedParts || M * K >= (int64_t(1) << 30)) return false;
+  const int64_t vectors = ceil_div(o.slice < bc ? o.slice : bc, o.vec), rows = ceil_div(M < br ? M : br, o.groups);
+  const int64_t per_round = kFusedThreads / block_parts;
+  const int64_t loads = ceil_div(nblocks, per_round) * rows * vectors;
+  if (loads > kFusedLoads || loads * (2 + o.vec + (o.loose ? 2 : 0)) * 64 + nblocks > 50 * 64) return false;
+  auto magic = [](int64_t d) { return (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); };
+  *g = SmallScore{br, bc, o.groups, o.slice, o.vec, o.loose, (int)vectors, (int)rows, (int)loads, (uint32_t)nblocks, (uint32_t)nbc,
+                  (uint32_t)block_parts, (uint32_t)o.slices, (uint32_t)per_round, (uint32_t)(per_round / nbc), (uint32_t)(per_round % nbc), (uint32_t)n_keep,
+                  magic(nbc), magic(block_parts), magic(o.slices)};
+  return true;
 }
 
-}  // namespace
-
-// (no more lanes than twice the workgroup's: each further round is a trip to memory, [250 x 128] binary32 in 1x32 blocks, 8000 lanes,
-// 14.5 us so and 7.6 in two launches)
-bool score_select_small_supported(int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc) {
-  const int64_t e = elem_bytes(dtype), nblocks = ceil_div(M, br) * ceil_div(K, bc);
-  if (nblocks > 1024 || M * K * e > kFusedBytes || bc * e > 1024 || br >= 128 || ((M - 1) * ldx + K) * e < 16) return false;
-  uint32_t vpb, lpb;
-  fused_lanes(nblocks, br, bc * e, &vpb, &lpb);
-  return nblocks * lpb <= 2 * kFusedThreads;
-}
-
-int launch_score_select_small(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, int br, int bc, int64_t n_keep,
-                              double *scores, uint8_t *keep_mask, hipStream_t s) {
-  const int64_t nbc = ceil_div(K, bc), nblocks = ceil_div(M, br) * nbc;
-  uint32_t vpb, lpb;
-  fused_lanes(nblocks, br, (int64_t)bc * elem_bytes(dtype), &vpb, &lpb);
-  if (dtype == BSR_F32)
-    hipLaunchKernelGGL((score_select_small_kernel<float>), dim3(1), dim3(kFusedThreads), 0, s, static_cast<const float *>(X), M, K,
-                       ldx, br, bc, (uint32_t)nbc, (uint32_t)nblocks, vpb, lpb, (uint32_t)n_keep, scores, keep_mask);
-  else
-    hipLaunchKernelGGL((score_select_small_kernel<uint16_t>), dim3(1), dim3(kFusedThreads), 0, s, static_cast<const uint16_t *>(X), M,
-                       K, ldx, br, bc, (uint32_t)nbc, (uint32_t)nblocks, vpb, lpb, (uint32_t)n_keep, scores, keep_mask);
+int launch_score_select_small(const SmallScore &g, const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, double *scores,
+                              uint8_t *keep_mask, hipStream_t s) {
+#define BSR_SMALL(T, V, LOOSE)                                                                                                   \
+  hipLaunchKernelGGL((score_select_small_kernel<T, V, LOOSE>), dim3(1), dim3(kFusedThreads), 0, s, static_cast<const T *>(X), M, \
+                     K, ldx, g, scores, keep_mask)
+  if (dtype == BSR_F32) {
+    if (g.loose) BSR_SMALL(float, 4, true);
+    else if (g.vec == 4) BSR_SMALL(float, 4, false);
+    else if (g.vec == 2) BSR_SMALL(float, 2, false);
+    else BSR_SMALL(float, 1, false);
+  } else {
+    if (g.loose) BSR_SMALL(uint16_t, 8, true);
+    else if (g.vec == 8) BSR_SMALL(uint16_t, 8, false);
+    else if (g.vec == 4) BSR_SMALL(uint16_t, 4, false);
+    else if (g.vec == 2) BSR_SMALL(uint16_t, 2, false);
+    else BSR_SMALL(uint16_t, 1, false);
+  }
+#undef BSR_SMALL
   return check_launch();
 }
 

@@ -3,8 +3,9 @@ not share a process with torch, which loads the real runtime).
 
 argv: the recorder, the library.  stdin: a JSON list of calls; stdout: a JSON list of
 {"rc", "ws", "kernels": [[kernel, workgroups], ...]}, ws = what the workspace query returns.
-A call: {"items": [{M, K, N, b or br + bc, lddy, lddw, dY, values, accumulate}, ...], "dtype", "batched"}; addresses are
-numbers that nothing reads.  The workspace passed is exactly the one the query asks for.
+A call: {"items": [{M, K, N, b or br + bc, lddy, lddw, dY, values, accumulate}, ...], "dtype", "batched"} for weight gradients, or
+{"select": {M, K, br, bc, ldx, X}, "dtype"} for bsr_score_select; addresses are numbers that nothing reads.  The workspace passed
+is exactly the one the query asks for.
 """
 import ctypes as C
 import json
@@ -31,8 +32,21 @@ def main():
     lib.bsr_t_dense_matmul_batched_workspace_bytes.restype = size
     lib.bsr_t_dense_matmul_batched_workspace_bytes.argtypes = [p, i32, i32]
     lib.bsr_t_dense_matmul_batched.argtypes = [p, i32, i32, p, size, p]
+    lib.bsr_score_select.argtypes = [p, i32, i64, i64, i64, i32, i32, C.c_double, p, p, p, size, p]
     out = []
+
+    def launched():
+        return [[recorder.recorder_name(i).decode(), recorder.recorder_workgroups(i)] for i in range(recorder.recorder_count())]
+
     for call in json.load(sys.stdin):
+        if "select" in call:
+            a, dtype = call["select"], call.get("dtype", 1)
+            M, K, br, bc = a["M"], a["K"], a["br"], a["bc"]
+            recorder.recorder_reset()
+            ws = lib.bsr_workspace_bytes(0, M, K, 0, br, bc, dtype)
+            rc = lib.bsr_score_select(a.get("X", ADDRESS), dtype, M, K, a.get("ldx", K), br, bc, 0.5, None, ADDRESS, ADDRESS, ws, None)
+            out.append({"rc": rc, "ws": ws, "kernels": launched()})
+            continue
         dtype, items = call.get("dtype", 1), (MatmulItem * len(call["items"]))()
         for a, it in zip(items, call["items"]):
             a.row_ptr = a.col_idx = a.dW = ADDRESS
@@ -49,9 +63,7 @@ def main():
             ws = lib.bsr_workspace_bytes(3, a.M, a.K, a.N, a.br, a.bc, dtype)
             rc = lib.bsr_t_dense_matmul(a.row_ptr, a.col_idx, a.values, dtype, a.M, a.K, a.br, a.bc, a.dY, a.N, a.lddy, a.dW,
                                         a.lddw, a.accumulate, ADDRESS, ws, None)
-        launched = [[recorder.recorder_name(i).decode(), recorder.recorder_workgroups(i)]
-                    for i in range(recorder.recorder_count())]
-        out.append({"rc": rc, "ws": ws, "kernels": launched})
+        out.append({"rc": rc, "ws": ws, "kernels": launched()})
     json.dump(out, sys.stdout)
 
 
