@@ -512,6 +512,29 @@ int run_score(const void *X, int64_t M, int64_t K, int64_t ldx, int br, int bc, 
   return check_launch();
 }
 
+// Whether the form for any alignment is the faster one, where its direct body has lanes enough; `key`: elements of the plain form's
+// vectors, `direct`: which body that form takes.  A block row that is one plain load gains nothing (16 bytes, masked, for the same).  Else
+// it saves loads, the more the lower the blocks: tall ones have lanes enough for loads of 2 or 4 bytes by consecutive lanes, and
+// the LDS body's lanes fit widths of an odd number of vectors well.  Over 3300 pairs of heights 1 .. 128, widths 1 .. 256 and pitches
+// at two sizes of either type.  Score and select, in us, plain and so: bfloat16 [25088 x 1536] in 64x1 blocks 41 and 112,
+// 16x4 33 and 39, 64x5 34 and 43, 64x18 27 and 31; with a pitch of 1537: 128x4 38 and 89, 64x8 32 and 40, 32x8 38 and 37, 32x14 49 and 32;
+// binary32 [25088 x 768]: 64x1 30 and 53, 64x9 36 and 40, 64x30 34 and 37, with a pitch of 769 64x14 41 and 30.
+bool loose_pays(int dtype, int br, int bc, int key, bool direct) {
+  if (key >= bc) return false;
+  const bool spread = key == 1 || bc / key % 2 == 0;         // (rows out of step with the width, not the width itself)
+  if (dtype == BSR_F32) {
+    if (direct) return br >= 64 && bc >= 4;
+    if (br >= 64) return bc >= 10 && spread;
+    return br <= 16 || key == 1 || bc > 6;
+  }
+  if (direct) {
+    if (br > 16) return bc >= (br < 64 ? 8 : 16);
+    return bc >= 8 || (bc == 4 ? key == 1 || br <= 8 : br <= 4);
+  }
+  if (br >= 64) return bc >= 14 && (spread || (key == 2 && bc >= 20));
+  return br <= 16 || (bc >= 5 && key < 4) || bc >= 20;
+}
+
 // Which kernel scores a tensor: 0 = score_kernel with vectors of `key` elements (kLoose: its form for any alignment),
 // 1 = score_span_kernel with `key`-byte accesses, 2 = score_rows_kernel.
 constexpr int kLoose = 100;
@@ -526,9 +549,7 @@ int score_kind(int dtype, const void *X, int64_t M, int64_t K, int64_t ldx, int 
   *key = pick_vector(v, elem_bytes(dtype), bc, K, ldx, X);
   int64_t gy;
   if (*key == v || (M - 1) * ldx + K < v || !score_geometry(v, M, K, br, bc, 1, &gy, true).direct) return 0;
-  // (binary32: loads of 4 bytes by consecutive lanes are as good, or better, in the direct body, [40056 x 977] in 32x32 blocks 42 us
-  // and 48 so, but for tall blocks, whose lanes of wider loads make more of a row, [27643 x 69] in 64x64 11.7 and 9.7)
-  if (dtype != BSR_F32 || br >= 64 || !score_geometry(*key, M, K, br, bc, 1, &gy).direct) *key = kLoose;
+  if (loose_pays(dtype, br, bc, *key, score_geometry(*key, M, K, br, bc, 1, &gy).direct != 0)) *key = kLoose;
   return 0;
 }
 

@@ -11,17 +11,47 @@ from test_dw_dispatch import recorder  # noqa: F401
 from test_gpu_parity import rand_pair, to_dev
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("M,K,br,bc,pad", [
+ANY_ALIGNMENT = [
     (1400, 1301, 14, 14, 0),      # rows on odd elements, blocks of a vector and three quarters
     (1393, 1302, 14, 14, 5),      # a last block-row of seven rows, far rows
     (2050, 2001, 32, 32, 0),      # whole vectors in a block, one column in the last block-column
     (3001, 1003, 64, 64, 3),
     (900, 3007, 1, 100, 0),       # 13 vectors on 16 lanes
     (40000, 3, 2, 2, 0),          # a vector reaches over several rows and, for the last ones, beyond the matrix
-    (5000, 21, 7, 5, 0),
-])
+    (5000, 21, 7, 5, 0),          # too few blocks for these: plain loads
+]
+
+
+def score_form(got):
+    """(elements of a vector, whether at any alignment) of the direct and the LDS body, None for other kernels."""
+    m = re.search(r"12score_kernelI[ft]Li(\d)ELb(\d)", got["names"][0])
+    return m and (int(m[1]), m[2] == "1")
+
+
+def test_scores_by_form(recorder):  # noqa: F811
+    """Blocks whose rows are one aligned load each, and tall narrow ones, are scored by plain loads; what the tests below give for
+    loads at any alignment takes these."""
+    def forms(dtype, shapes):
+        got = recorder([dict(select=dict(M=M, K=K, br=br, bc=bc, ldx=K + pad, X=(1 << 20) + 33 * (2 if dtype else 4)), dtype=dtype) if shift else
+                        dict(select=dict(M=M, K=K, br=br, bc=bc, ldx=K + pad), dtype=dtype) for M, K, br, bc, pad, shift in shapes])
+        assert [g["rc"] for g in got] == [0] * len(got)
+        return [score_form(g) for g in got]
+
+    narrow = [(25088, 1536, br, bc, pad, False) for br, bc in ((16, 4), (128, 4), (16, 2), (64, 1), (1, 1), (4, 1)) for pad in (0, 8)]
+    assert forms(1, narrow) == [(s[3], False) for s in narrow]
+    tall = [(25088, 1536, 64, 8, 1, False), (25088, 1536, 128, 4, 1, False), (25088, 1536, 64, 18, 0, False), (25088, 1536, 32, 3, 0, False)]
+    assert forms(1, tall) == [(1, False), (1, False), (2, False), (1, False)]
+    assert forms(0, [(25088, 768, 64, 1, 0, False), (25088, 768, 128, 2, 4, False), (25088, 768, 64, 30, 0, False)]) == \
+        [(1, False), (2, False), (2, False)]
+    assert forms(1, [(25088, 1533, *s, 0, False) for s in ((14, 14), (16, 6), (32, 32), (1, 32), (2, 4))]) == [(8, True)] * 5
+    below = [(*s, True) for s in ANY_ALIGNMENT]
+    assert forms(1, below) == [(8, True)] * 6 + [(1, False)]
+    assert forms(0, below) == [(4, True), (4, True), (1, False), (4, True), (4, True), (1, False), (1, False)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K,br,bc,pad", ANY_ALIGNMENT)
 def test_scores_of_rows_at_any_alignment(M, K, br, bc, pad, dtype):
     """Against the oracle, to the rounding of sums of br * bc terms in binary64; alone and in a batch, from the first element of
     a buffer, and from one in the middle of NaN (between the rows, too)."""
