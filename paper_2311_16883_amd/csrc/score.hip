@@ -196,8 +196,21 @@ __device__ __forceinline__ void score_direct_body(
     for (int b = 0; b < kInFlight; ++b)
       if (r0 + b * lanes < rows) v[b] = load(p + (int64_t)(r0 + b * lanes) * ldx);
 #pragma unroll
-    for (int b = 0; b < kInFlight; ++b)
-      if (r0 + b * lanes < rows) add(v[b], b);
+    for (int b = 0; b < kInFlight; ++b) {
+      if (r0 + b * lanes >= rows) continue;
+      if constexpr (LOOSE) {
+        add(v[b], b);
+      } else {
+        // (not through the function above: 8 registers more for bfloat16, six waves per SIMD instead of seven.  Score and select of
+        // [25088 x 1536] with a pitch of 1544 in 4x96 blocks 67 us so, 62 without)
+#pragma unroll
+        for (int q = 0; q < V; ++q) {
+          const double x = (double)raw_elem<T, V>(v[b], q);
+          const int k = TALL ? q % 2 : b % kOwn;
+          acc[k] = fma(x, x, acc[k]);
+        }
+      }
+    }
   }
 #pragma unroll
   for (int half = kOwn / 2; half >= 1; half /= 2)
