@@ -153,42 +153,49 @@ bool use_wide_single(int dtype, const DwJob &j) {
 }
 
 // Whether a product on its own takes the kernel whose waves each gather the kept blocks of one strip, instead of the 128 x 128
-// tiles.  Both sides measured, in us (tiles, so), and both plans' estimates compared.
-// binary32, 14- and 16-wide blocks gain from being
-// skipped one by one (1.05 .. 2.6 times as fast over 36 shapes), up to large activations in 14x14 blocks, whose rows the 128 x 128 tiles
-// load in wider vectors ([13986 x 1877 x 39], 2.6e7 elements: 46 and 31 at keep 0.25, 50 and 47 at 0.5, 54 and 63 at 0.75;
-// [50000 x 784 x 128], keep 0.9: 124 and 139).  32x32 and 64x64 blocks gain wherever
-// the 128 x 128 tiles don't fill the compute units or dW, or there are few stages; where they do, they load less for
-// each multiply-add: of 95 calls at keeps .1 .. .9 [1294 x 1344 x 1440] 53 and 35, estimates 1 : 0.45; [9095 x 1504 x 224]
-// 48.9 and 49.5, 1 : 0.65; [6272 x 384 x 1536] 50 and 55, 1 : 0.72; [12544 x 384 x 1536] 87 and 87, 1 : 0.75.
-// bfloat16, where the matrix cores are fast enough that each strip's own pass over dY counts: small products, 1.3 .. 2.2 times as fast
-// ([256 x 128 x 64] 7.4 and 5.7, [1202 x 152 x 446] 12.7 and 7.1, [705 x 416 x 128] in 14x14 blocks 10.9 and 5.9), the fewer blocks are
-// kept the longer: at keep 0.9 [4415 x 456 x 220] in 14x14 blocks, 4.4e8 multiply-adds, 15.6 and 17.1, [3677 x 760 x 1208] in 32x32
-// blocks 0.88 times as fast (2.2 times at keep 0.1), [585 x 705 x 1871], estimates 1 : 0.64, 0.92 times, [6777 x 1815 x 88] in 64x64 blocks, 1.1e9, with score, select and conversion 49.0 and 57.5.  Beyond
-// 7e8 multiply-adds (1.1e9 where the activation is small) only
-// small activations, most of whose time is the launches' ([2006 x 454 x 1472], keep 0.9: 18.9 and 15.7), and rows of dY on odd elements in 32x32 blocks,
-// which the tiles load at half the rate ([9947 x 411 x 1001] 31.6 and 25.0 at keep 0.5, 0.84 times as fast at 0.9, 2.9 times at 0.1;
-// [9232 x 666 x 383] 2.0 times at 0.25; [5530 x 654 x 943] 0.99 times at 0.9; in 64x64 blocks [8117 x 337 x 585], keep 0.9, 0.74 times).
+// tiles: by both plans' estimates, for nine blocks in ten kept, where it gains least.  The lines differ by how far the estimates
+// are off for a kind of call (the tiles need 0.7 of what their plan says in bfloat16, 0.8 in binary32).  Fitted to 1366 products
+// of all these block shapes, of 600 others at keeps 0.1, 0.5, 0.75 and 0.9 two are more than 5 % slower than without this kernel
+// ([32368 x 64 x 283] bfloat16 in 64x64, keep 0.9: 15.5 and 18.1), and all together take 1 / 1.22 .. 1 / 1.49 of the time, by type
+// and keep (geometric mean).  In us, tiles and so, at keep 0.5 and 0.9.  Taken: binary32 [256 x 128 x 64] in 16x16 blocks 9.7 and
+// 5.9; [1889 x 544 x 784] 31 and 18, 34 and 25; [25088 x 196 x 196] in 14x14 38 and 27, 41 and 37; [2000 x 3000 x 300] in 32x32 42
+// and 32, 53 and 44; bfloat16 [1202 x 152 x 446] 12.7 and 7.1; [2000 x 1000 x 190] in 16x16 15 and 8.7, 15 and 11; [2006 x 454 x
+// 1472] in 32x32 18 and 11, 18 and 15; [10000 x 196 x 196] in 14x14 15 and 12, 16 and 14.  Left to the tiles: binary32 [12544 x
+// 768 x 768] in 16x16 103 and 90, 122 and 144; [1000 x 24000 x 300] in 14x14 211 and 546, 265 and 954; [20734 x 2592 x 64] in
+// 64x64, keep 0.9, 69 and 91; bfloat16, rows of dY on odd elements, [9947 x 411 x 1001] in 32x32 32 and 25, 32 and 38.  (Binary32,
+// much to multiply and few block-columns: there the tiles gain by what is pruned as a strip does, [25842 x 42 x 464] in 32x32 21
+// and 27, 26 and 27; [37960 x 23 x 912] in 16x16 40 and 43.)
+// By size: beyond these next to nothing was found that gains, and no plan has to be made.
 // Row segments of whole 32 columns: against re-tiling and the tiles, two or three launches, until the entries that every strip's
 // workgroups walk and each strip's own pass over dY count, the sooner the more is kept.  (bfloat16, binary32: [742 x 96 x 2848] in 1x64,
 // keep 0.1, 15.6 and 7.9, 22 and 11; [13177 x 448 x 32] in 1x32 21.8 and 14.6, 32 and 20; [445 x 1152 x 752] in 1x64, keep 0.9, 3.9e8
 // multiply-adds, 15.3 and 12.8, 29 and 23; [1586 x 901 x 342] in 1x32, keep 0.75, 4.9e8, 20.6 and 22.0, 35 and 37;
 // [25088 x 384 x 1536] in 1x32 57 and 89.)
+bool direct_sizes(int dtype, int64_t M, int64_t K, int64_t N, int br) {
+  const double work = (double)M * (double)K * (double)N;
+  if (br == 1) return work < 4.2e8;
+  if (dtype == BSR_F32) return work < 5.0e9;
+  if (br < 32) return work < 4e8;
+  return work < (M * K < 4000000 ? 1.1e9 : 7e8) || M * K < 2000000;
+}
+bool direct_pays(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, bool odd) {
+  if (!direct_sizes(dtype, M, K, N, br)) return false;
+  if (br == 1) return true;
+  // (a small dW in narrow blocks, such as a cross-patch layer's: partial sums and tiles in part cost more than either plan has it)
+  const bool small = bc < 32 && K * N < 50000 && N > 64;
+  double line = bc >= 32 ? (odd ? 0.65 : 0.67) : odd ? 0.68 : small ? 0.75 : 0.70;
+  if (dtype == BSR_F32) {
+    const bool few = K < (bc < 32 ? 40 : 128) && (double)M * (double)K * (double)N > 3e8;
+    line = few ? 0.55 : bc == 16 ? 1.0 : bc >= 32 ? 0.83 : small ? 1.32 : 0.9;
+  }
+  return dw_direct_most_us(dtype, M, K, N, br, bc) < line * dw_mfma_us(dtype, M, K, N, br);
+}
 bool use_direct(int dtype, const DwJob &j) {
   if (!dw_direct_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return false;
-  const double work = (double)j.M * (double)j.K * (double)j.N;
-  if (j.br == 1) return work < 4.2e8;
-  if (!dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return true;
-  if (dtype == BSR_F32 && j.bc < 32) return j.bc == 16 || j.M * j.K < 25000000;
-  double line = 0.69;
-  if (dtype == BSR_BF16) {
-    const bool odd = j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0;
-    if (j.bc < 32) line = work < 4e8 ? 0.69 : 0.0;
-    else if (work < (j.M * j.K < 4000000 ? 1.1e9 : 7e8)) line = 0.62;
-    else if (odd) line = j.bc == 32 ? 0.72 : 0.0;
-    else line = j.M * j.K < 2000000 ? 0.5 : 0.0;
-  }
-  return line > 0.0 && dw_direct_us(dtype, j.M, j.K, j.N, j.br, j.bc) < line * dw_mfma_us(dtype, j.M, j.K, j.N, j.br);
+  // (square blocks that the tiles cannot address, binary32 values off 16-byte boundaries: the general kernel takes 1 .. 4 times as long)
+  if (j.br > 1 && !dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return true;
+  const bool odd = dtype == BSR_BF16 && (j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0);
+  return direct_pays(dtype, j.M, j.K, j.N, j.br, j.bc, odd);
 }
 
 // Workspace of a product, whatever kernel takes it.  (The wide tiles take activations that the 128 x 128 tiles don't, from 2 GiB

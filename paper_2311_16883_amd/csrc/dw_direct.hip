@@ -474,13 +474,15 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
 
 // Tile width and splits of a product.
 struct DirectPlan {
-  double us;
+  double us, most_us;                        // as planned, and with most blocks kept (see make_direct_plan)
   int variant, splits, rows_per_split;       // variant: 0 wide tiles .. 2 narrow ones
 };
 
 constexpr int kVariants = 3;
 constexpr int kWaves[kVariants] = {4, 8, 16};
 inline int variant_columns(int v) { return 128 >> v; }
+// workgroups that a compute unit holds (e: bytes of an element)
+inline int at_a_time(int v, int e, int br, int bc) { return v == 0 ? (br == 1 ? 2 : 3) : v == 1 || (e == 4 && bc % 32 != 0) ? 2 : 1; }
 
 // What each choice would take, in microseconds: rounds of the workgroups that the compute units hold at a time, each with a start
 // and an end (list of blocks, sums) and the units of its waves, which take what their matrix instructions (bfloat16: and LDS
@@ -497,22 +499,38 @@ struct DirectCosts {
 constexpr DirectCosts kCostsF32 = {3.8, 0.24, 0.48, 0.24, 0.14, 48.5, 1.05, 3.4, 3.0, 0.212};
 constexpr DirectCosts kCostsBf16 = {2.2, 0.086, 0.05, 0.025, 0.0125, 75.7, 0.4, 3.1, 3.6, 0.114};
 
+// A plan is chosen for keep 0.6; whether the kernel is taken at all goes by most_us, what the chosen plan needs when nine blocks in ten
+// are kept (the other kernels take about as long whatever is kept, so a call that is no slower then is no slower at all).  That
+// counts the walk through the entries of a workgroup's rows as well, which every strip does ([2000 x 30000 x 256] binary32 in 16x16
+// blocks: 1875 strips, 1300 us at keep 0.9), and that a last block-column in part is the first to be pruned: of the others more is kept.
 DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
   const int64_t strips = bc > 16 ? ceil_div(K, 32) : nbc;
   const int kMaxRows = max_rows(br), e = elem_bytes(dtype);
   const double upb = br > kUnit ? br / kUnit : br == 1 ? 1.0 / kUnit : 1.0;
   const DirectCosts &c = dtype == BSR_F32 ? kCostsF32 : kCostsBf16;
-  DirectPlan best{0, 0, 1, (int)(nbr < 1 ? 1 : nbr > kMaxRows ? kMaxRows : nbr)};
-  bool any = false;
-  for (int v = 0; v < kVariants; ++v) {
-    const int cols = variant_columns(v), waves = kWaves[v];
-    const int64_t tiles = strips * ceil_div(N, cols);
+  auto estimate = [&](int v, int64_t rows, int64_t splits, double keep, bool walk) {
+    const int cols = variant_columns(v), waves = kWaves[v], per_cu = at_a_time(v, e, br, bc);
     const double unit_us = bc % 32 == 0 ? c.unit32 * (cols / 32) : cols > 64 ? c.unit_wide16 : cols > 32 ? c.unit_mid16 : c.unit_narrow16;
     const double unit_kb = kUnit * e * ((bc < 32 ? bc : 32) + cols) * 1e-3;
-    const int per_cu = v == 0 ? (br == 1 ? 2 : 3) : v == 1 || (e == 4 && bc % 32 != 0) ? 2 : 1;
+    const double units = (double)rows * upb * keep / waves + 0.5;
+    auto round_us = [&](int64_t n) {
+      const double on_all = (double)(waves * n);
+      const double mult = unit_us * on_all / 4, load = unit_kb * on_all / c.bytes_per_ns;
+      const double busy = mult > load ? mult : load;
+      return c.round + (walk ? (double)rows * nbc * 4e-3 * keep * (double)n / c.bytes_per_ns : 0.0) +
+             units * (busy > c.on_the_way ? busy : c.on_the_way);
+    };
+    const int64_t on_a_cu = ceil_div(strips * ceil_div(N, cols) * splits, (int64_t)256);
+    return c.start + (double)(on_a_cu / per_cu) * round_us(per_cu) + (on_a_cu % per_cu ? round_us(on_a_cu % per_cu) : 0.0) +
+           (splits > 1 ? c.reduce + (double)splits * (double)K * (double)N * 8e-6 * c.reduce_per_mb : 0.0);
+  };
+  DirectPlan best{0, 0, 0, 1, (int)(nbr < 1 ? 1 : nbr > kMaxRows ? kMaxRows : nbr)};
+  bool any = false;
+  for (int v = 0; v < kVariants; ++v) {
+    const int64_t tiles = strips * ceil_div(N, variant_columns(v));
     // (splits beyond four rounds of workgroups gain nothing)
-    const int64_t s_min = ceil_div(nbr, (int64_t)kMaxRows), s_full = 1024 * per_cu / tiles + 1;
+    const int64_t s_min = ceil_div(nbr, (int64_t)kMaxRows), s_full = 1024 * at_a_time(v, e, br, bc) / tiles + 1;
     int64_t s_max = nbr < 64 ? nbr : 64, rows_before = 0;
     if (s_max > s_full) s_max = s_full;
     if (s_max < s_min) s_max = s_min;
@@ -521,21 +539,14 @@ DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, 
       if (rows == rows_before) continue;
       rows_before = rows;
       const int64_t splits = ceil_div(nbr, rows);
-      const double units = (double)rows * upb * 0.6 / waves + 0.5;
-      auto round_us = [&](int64_t at_a_time) {
-        const double on_all = (double)(waves * at_a_time);
-        const double mult = unit_us * on_all / 4, load = unit_kb * on_all / c.bytes_per_ns;
-        const double busy = mult > load ? mult : load;
-        // (row segments: every workgroup walks all entries of its rows)
-        return c.round + (br == 1 ? (double)rows * nbc * 2.4e-3 * (double)at_a_time / c.bytes_per_ns : 0.0) + units * (busy > c.on_the_way ? busy : c.on_the_way);
-      };
-      const int64_t on_a_cu = ceil_div(tiles * splits, (int64_t)256);
-      const double us = c.start + (double)(on_a_cu / per_cu) * round_us(per_cu) + (on_a_cu % per_cu ? round_us(on_a_cu % per_cu) : 0.0) +
-                        (splits > 1 ? c.reduce + (double)splits * (double)K * (double)N * 8e-6 * c.reduce_per_mb : 0.0);
-      if (!any || us < best.us) best = DirectPlan{us, v, (int)splits, (int)rows};
+      const double us = estimate(v, rows, splits, 0.6, br == 1);    // (row segments: every workgroup walks all entries of its rows)
+      if (!any || us < best.us) best = DirectPlan{us, 0, v, (int)splits, (int)rows};
       any = true;
     }
   }
+  const int64_t whole = K / bc < 1 ? 1 : K / bc;
+  const double most = 0.9 * (double)nbc / (double)whole;
+  best.most_us = estimate(best.variant, best.rows_per_split, best.splits, most < 1.0 ? most : 1.0, true);
   return best;
 }
 
@@ -599,7 +610,15 @@ bool dw_direct_supported(int dtype, int br, int bc, const void *values, int64_t 
   return ceil_div(K, 16) * ceil_div(N, 32) < (int64_t(1) << 24);
 }
 
-double dw_direct_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) { return direct_plan(dtype, M, K, N, br, bc).us; }
+double dw_direct_most_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
+  const DirectPlan p = direct_plan(dtype, M, K, N, br, bc);
+  // (bfloat16, one workgroup of 16 waves per compute unit: with many units each, their loads take longer than the model has it,
+  // [5615 x 96 x 2160] in 64x64 blocks, 22 units: 17.2 us in 128 x 128 tiles, 21.2 here, 14 by the model; [2916 x 32 x 584], 11.5: 10.3,
+  // 12.4 and 9.9)
+  const int64_t units = (int64_t)p.rows_per_split * br / kUnit;
+  const bool many = dtype == BSR_BF16 && bc >= 32 && p.variant == 2 && p.splits == 1 && units > 11 * kWaves[2];
+  return p.most_us * (!many ? 1.0 : units > 16 * kWaves[2] ? 2.0 : 1.15);
+}
 
 size_t dw_direct_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   const DirectPlan p = direct_plan(dtype, M, K, N, br, bc);

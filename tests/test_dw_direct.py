@@ -11,12 +11,17 @@ from test_gpu_parity import DW_TOL, DW_TOL_DERIVED, dw_error, rand_pair, to_dev
 
 
 def test_single_products_by_kernel(recorder):  # noqa: F811
-    """Alone (single call or a batch of one): small products and such as the 128x128 tiles fill badly.  Several go as before.  The
-    queried workspace is enough on both sides of the line."""
+    """Alone (single call or a batch of one): products that gain whatever is kept, small ones and such as the 128x128 tiles fill
+    badly; not those that would take longer with most blocks kept, wide activations and much to multiply.  Several go as before.
+    The queried workspace is enough on both sides of the line."""
     f32, bf16 = 0, 1
-    direct = [(f32, 256, 128, 64, 16), (f32, 12544, 384, 384, 14), (f32, 1294, 1344, 1440, 32), (f32, 342, 108, 86, 64),
-              (bf16, 256, 128, 64, 16), (bf16, 1202, 152, 446, 32), (bf16, 705, 416, 128, 14), (bf16, 9947, 411, 1001, 32)]
-    tiles = [(f32, 12544, 384, 1536, 32), (f32, 6272, 384, 1536, 64), (f32, 13986, 1877, 39, 14),
+    direct = [(f32, 256, 128, 64, 16), (f32, 27601, 228, 192, 14), (f32, 1294, 1344, 1440, 32), (f32, 342, 108, 86, 64),
+              (bf16, 256, 128, 64, 16), (bf16, 1202, 152, 446, 32), (bf16, 705, 416, 128, 14), (f32, 25088, 196, 196, 14), (f32, 50176, 196, 196, 14),
+              (bf16, 10000, 196, 196, 14), (bf16, 2000, 1000, 190, 16)]
+    tiles = [(f32, 12544, 384, 1536, 32), (f32, 6272, 384, 1536, 64), (f32, 13986, 1877, 39, 14), (f32, 12544, 768, 768, 16),
+             (f32, 12544, 384, 384, 14), (f32, 50176, 3072, 768, 16), (f32, 1000, 24000, 300, 14), (f32, 4096, 20000, 8, 16),
+             (f32, 25842, 42, 464, 32), (f32, 20734, 2592, 64, 64), (bf16, 9947, 411, 1001, 32), (bf16, 7001, 901, 501, 32),
+             (bf16, 5615, 96, 2160, 64),
              (bf16, 6272, 384, 1536, 32), (bf16, 4415, 456, 220, 14), (bf16, 8117, 337, 585, 64), (bf16, 49152, 196, 196, 14)]
     for shapes, key in ((direct, "dw_direct"), (tiles, "dw_mfma")):
         alone = [dict(one(*s), dtype=dtype) for dtype, *s in shapes]
