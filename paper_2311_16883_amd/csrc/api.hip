@@ -103,10 +103,12 @@ double wide_work(int64_t M, int64_t K, int64_t N, int br, bool alone) {
 // searches, are no different: [8 x 20000 x 10] in 1x1 blocks 28 and 57, [64 x 8000 x 8] in 2x2 24 and 32.  Of 232 shapes up to
 // 20000 rows, 60000 columns of X and 4000 of dW, 30 take the slower of the two by more than 6 %: few rows in 1x32 or 1x128
 // blocks ([41 x 3277 x 30] 22 and 12) and few in tall ones ([210 x 121 x 23] in 300x4 blocks 50 and 15).
+double general_us(int64_t M, int64_t K, int64_t N, int br) {
+  return 9.0 + 0.025 * (double)ceil_div(M, br) + 1e-6 * (double)M * (double)K * (double)N * (0.25 + 0.75 / br);
+}
 bool retiling_pays(int64_t M, int64_t K, int64_t N, int br) {
   if (br > 16) return M * K > 65536;
-  const double general_us = 9.0 + 0.025 * (double)ceil_div(M, br) + 1e-6 * (double)M * (double)K * (double)N * (0.25 + 0.75 / br);
-  return general_us > 15.3;
+  return general_us(M, K, N, br) > 15.3;
 }
 
 // Parallelism and work of the products of a call, by block size (16, 32, 64: wide_class), since each size has a launch of its
@@ -166,11 +168,6 @@ bool use_wide_single(int dtype, const DwJob &j) {
 // much to multiply and few block-columns: there the tiles gain by what is pruned as a strip does, [25842 x 42 x 464] in 32x32 21
 // and 27, 26 and 27; [37960 x 23 x 912] in 16x16 40 and 43.)
 // By size: beyond these next to nothing was found that gains, and no plan has to be made.
-// Row segments of whole 32 columns: against re-tiling and the tiles, two or three launches, until the entries that every strip's
-// workgroups walk and each strip's own pass over dY count, the sooner the more is kept.  (bfloat16, binary32: [742 x 96 x 2848] in 1x64,
-// keep 0.1, 15.6 and 7.9, 22 and 11; [13177 x 448 x 32] in 1x32 21.8 and 14.6, 32 and 20; [445 x 1152 x 752] in 1x64, keep 0.9, 3.9e8
-// multiply-adds, 15.3 and 12.8, 29 and 23; [1586 x 901 x 342] in 1x32, keep 0.75, 4.9e8, 20.6 and 22.0, 35 and 37;
-// [25088 x 384 x 1536] in 1x32 57 and 89.)
 bool direct_sizes(int dtype, int64_t M, int64_t K, int64_t N, int br) {
   const double work = (double)M * (double)K * (double)N;
   if (br == 1) return work < 4.2e8;
@@ -178,9 +175,26 @@ bool direct_sizes(int dtype, int64_t M, int64_t K, int64_t N, int br) {
   if (br < 32) return work < 4e8;
   return work < (M * K < 4000000 ? 1.1e9 : 7e8) || M * K < 2000000;
 }
+// Row segments of whole 32 columns, against re-tiling and the tiles, two or three launches, or the general kernel: here, too, by what
+// each needs for nine segments in ten kept (for re-tiling a fit to 624 products, within 15 % of four in five).  Of 780 products at keeps
+// 0.1 .. 0.9 the worst is 8 % slower so than without this kernel.  In us, without and so, keep 0.1, 0.5 and 0.9: bfloat16
+// [40000 x 320 x 32] in 1x32 blocks 32 and 14, 28 and 16, 25 and 19; [1000 x 400 x 1000] 19 and 8.1, 20 and 10, 20 and 14;
+// [1646 x 136 x 3104] in 1x64 19 and 8.8, 19 and 14, 19 and 16; binary32 [5711 x 376 x 78] in 1x128 28 and 16, 28 and 20, 27 and 22.
+// Not: wide activations, whose entries every strip walks, bfloat16 [4096 x 10000 x 8] in 1x32 42 and 43, 51 and 150, 64 and 260;
+// [3000 x 3000 x 46] 26 and 13, 25 and 24, 25 and 32; few rows and a small dW, which the general kernel
+// takes as fast, [24 x 59 x 10] 8 and 9.
+bool segments_pay(int dtype, int64_t M, int64_t K, int64_t N, int bc) {
+  if (M < 64 && K < 1000 && K * N < 20000) return false;
+  const double us = dw_direct_most_us(dtype, M, K, N, 1, bc);
+  // (the general kernel's search among a row's entries: [25 x 2688 x 32] bfloat16 14.6, 9.5 so)
+  if (!retiling_pays(M, K, N, 1)) return us < (dtype == BSR_F32 ? 0.85 : 0.8) * (general_us(M, K, N, 1) + 1.2e-3 * (double)(K < 4000 ? K : 4000));
+  const double mb = (double)M * (double)K * elem_bytes(dtype) * 1e-6;
+  const double other = (5.4 + 0.68 * dw_mfma_us(dtype, M, K, N, 32) + 0.37 * mb) * (K <= 32 ? 0.87 : 1.0);
+  return us < (dtype == BSR_F32 ? 0.95 : 0.92) * other;
+}
 bool direct_pays(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, bool odd) {
   if (!direct_sizes(dtype, M, K, N, br)) return false;
-  if (br == 1) return true;
+  if (br == 1) return segments_pay(dtype, M, K, N, bc);
   // (a small dW in narrow blocks, such as a cross-patch layer's: partial sums and tiles in part cost more than either plan has it)
   const bool small = bc < 32 && K * N < 50000 && N > 64;
   double line = bc >= 32 ? (odd ? 0.65 : 0.67) : odd ? 0.68 : small ? 0.75 : 0.70;

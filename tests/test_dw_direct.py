@@ -29,10 +29,11 @@ def test_single_products_by_kernel(recorder):  # noqa: F811
         assert [g["rc"] for g in got] == [0] * len(got)
         assert all(key in g["names"][0] for g in got), got
     segments = [dict(items=[dict(M=M, K=K, N=N, br=1, bc=bc)], dtype=dtype) for dtype in (f32, bf16)
-                for M, K, N, bc in ((742, 96, 2848, 64), (13177, 448, 32, 32), (25088, 384, 1536, 32), (742, 96, 2848, 48))]
+                for M, K, N, bc in ((742, 96, 2848, 64), (13177, 448, 32, 32), (39, 480, 214, 64), (25088, 384, 1536, 32),
+                                    (742, 96, 2848, 48), (4096, 10000, 8, 32), (500, 20000, 40, 32), (24, 59, 10, 32))]
     got = recorder(segments + [dict(c, batched=True) for c in segments])
-    assert [g["rc"] for g in got] == [0] * 16
-    assert ["dw_direct" in g["names"][0] for g in got] == [True, True, False, False] * 4
+    assert [g["rc"] for g in got] == [0] * 32
+    assert ["dw_direct" in g["names"][0] for g in got] == ([True] * 3 + [False] * 5) * 4
     pair = dict(items=one(256, 128, 64, 16)["items"] * 2, batched=True, dtype=f32)
     got = recorder([pair, dict(one(256, 128, 64, 16, values=(1 << 20) + 4), dtype=f32), one(256, 128, 64, 16, values=(1 << 20) + 2)])
     assert ["dw_direct" in g["names"][0] for g in got] == [False, True, False]
