@@ -183,18 +183,18 @@ bool direct_sizes(int dtype, int64_t M, int64_t K, int64_t N, int br) {
 // Not: wide activations, whose entries every strip walks, bfloat16 [4096 x 10000 x 8] in 1x32 42 and 43, 51 and 150, 64 and 260;
 // [3000 x 3000 x 46] 26 and 13, 25 and 24, 25 and 32; few rows and a small dW, which the general kernel
 // takes as fast, [24 x 59 x 10] 8 and 9.
-bool segments_pay(int dtype, int64_t M, int64_t K, int64_t N, int bc) {
+bool segments_pay(int dtype, int64_t M, int64_t K, int64_t N, int bc, size_t ws_bytes) {
   if (M < 64 && K < 1000 && K * N < 20000) return false;
-  const double us = dw_direct_most_us(dtype, M, K, N, 1, bc);
+  const double us = dw_direct_most_us(dtype, M, K, N, 1, bc, ws_bytes);
   // (the general kernel's search among a row's entries: [25 x 2688 x 32] bfloat16 14.6, 9.5 so)
   if (!retiling_pays(M, K, N, 1)) return us < (dtype == BSR_F32 ? 0.85 : 0.8) * (general_us(M, K, N, 1) + 1.2e-3 * (double)(K < 4000 ? K : 4000));
   const double mb = (double)M * (double)K * elem_bytes(dtype) * 1e-6;
   const double other = (5.4 + 0.68 * dw_mfma_us(dtype, M, K, N, 32) + 0.37 * mb) * (K <= 32 ? 0.87 : 1.0);
   return us < (dtype == BSR_F32 ? 0.95 : 0.92) * other;
 }
-bool direct_pays(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, bool odd) {
+bool direct_pays(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, bool odd, size_t ws_bytes) {
   if (!direct_sizes(dtype, M, K, N, br)) return false;
-  if (br == 1) return segments_pay(dtype, M, K, N, bc);
+  if (br == 1) return segments_pay(dtype, M, K, N, bc, ws_bytes);
   // (a small dW in narrow blocks, such as a cross-patch layer's: partial sums and tiles in part cost more than either plan has it)
   const bool small = bc < 32 && K * N < 50000 && N > 64;
   double line = bc >= 32 ? (odd ? 0.65 : 0.67) : odd ? 0.68 : small ? 0.75 : 0.70;
@@ -202,17 +202,18 @@ bool direct_pays(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, boo
     const bool few = K < (bc < 32 ? 40 : 128) && (double)M * (double)K * (double)N > 3e8;
     line = few ? 0.55 : bc == 16 ? 1.0 : bc >= 32 ? 0.83 : small ? 1.32 : 0.9;
   }
-  return dw_direct_most_us(dtype, M, K, N, br, bc) < line * dw_mfma_us(dtype, M, K, N, br);
+  return dw_direct_most_us(dtype, M, K, N, br, bc, ws_bytes) < line * dw_mfma_us(dtype, M, K, N, br);
 }
 bool use_direct(int dtype, const DwJob &j) {
   if (!dw_direct_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return false;
   // (square blocks that the tiles cannot address, binary32 values off 16-byte boundaries: the general kernel takes 1 .. 4 times as long)
-  if (j.br > 1 && !dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return true;
+  if (j.br > 1 && !dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy))
+    return dw_direct_most_us(dtype, j.M, j.K, j.N, j.br, j.bc, j.ws_bytes) < 1e30;
   const bool odd = dtype == BSR_BF16 && (j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0);
-  return direct_pays(dtype, j.M, j.K, j.N, j.br, j.bc, odd);
+  return direct_pays(dtype, j.M, j.K, j.N, j.br, j.bc, odd, j.ws_bytes);
 }
 
-// Workspace of a product, whatever kernel takes it.  (The wide tiles take activations that the 128 x 128 tiles don't, from 2 GiB
+// Workspace of a product, whatever kernel takes it (the gathering one makes do with what the others need).  (The wide tiles take activations that the 128 x 128 tiles don't, from 2 GiB
 // up to 4 GiB, and rows of dY further apart.)
 size_t dw_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   size_t a = dw_generic_ws_bytes(M, K, N, br, bc), b = 0;
@@ -225,10 +226,6 @@ size_t dw_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   }
   if (dw_narrow_supported(dtype, br, bc, nullptr, nullptr, M, K, N, N)) {
     b = dw_narrow_ws_bytes(M, K, N, br);
-    if (b > a) a = b;
-  }
-  if (dw_direct_supported(dtype, br, bc, nullptr, M, K, N, N)) {
-    b = dw_direct_ws_bytes(dtype, M, K, N, br, bc);
     if (b > a) a = b;
   }
   return align_up(a, 256);
@@ -457,7 +454,7 @@ int bsr_t_dense_matmul(const int32_t *row_ptr, const int32_t *col_idx, const voi
     return BSR_ERR_ALIGN;
   const size_t need = bsr_workspace_bytes(BSR_OP_T_DENSE_MATMUL, M, K, N, br, bc, dtype);
   if (need > 0 && (ws == nullptr || ws_bytes < need)) return BSR_ERR_WORKSPACE;
-  const DwJob job{row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate, ws, ws_bytes};
+  const DwJob job{row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate, ws, need};    // (need: whatever is passed beyond it changes nothing)
   return launch_dw(dtype, job, static_cast<hipStream_t>(stream));
 }
 

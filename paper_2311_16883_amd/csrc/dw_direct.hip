@@ -516,11 +516,12 @@ double segments_us(const DirectPlan &p, int dtype, int64_t tiles, int64_t K, int
          (p.splits > 1 ? c.reduce + c.reduce_mb * (double)p.splits * (double)K * (double)N * 8e-6 : 0.0);
 }
 
+// The splits' sums go where the other kernels for the product have theirs, no more of them than fit (ws_bytes).
 // A plan is chosen for keep 0.6; whether the kernel is taken at all goes by most_us, what the chosen plan needs when nine blocks in ten
 // are kept (the other kernels take about as long whatever is kept, so a call that is no slower then is no slower at all).  That
 // counts the walk through the entries of a workgroup's rows as well, which every strip does ([2000 x 30000 x 256] binary32 in 16x16
 // blocks: 1875 strips, 1300 us at keep 0.9), and that a last block-column in part is the first to be pruned: of the others more is kept.
-DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
+DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes) {
   const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
   const int64_t strips = bc > 16 ? ceil_div(K, 32) : nbc;
   const int kMaxRows = max_rows(br), e = elem_bytes(dtype);
@@ -551,6 +552,8 @@ DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, 
     int64_t s_max = nbr < 64 ? nbr : 64, rows_before = 0;
     if (s_max > s_full) s_max = s_full;
     if (s_max < s_min) s_max = s_min;
+    const int64_t s_room = (int64_t)(ws_bytes / ((size_t)K * N * sizeof(float)));
+    if (s_max > s_room) s_max = s_room > 1 ? s_room : 1;
     for (int64_t s = s_min; s <= s_max; ++s) {
       const int64_t rows = ceil_div(nbr, s);
       if (rows == rows_before) continue;
@@ -561,6 +564,7 @@ DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, 
       any = true;
     }
   }
+  if (!any) return best;                     // (us 0: no plan)
   const int64_t whole = K / bc < 1 ? 1 : K / bc;
   const double most = 0.9 * (double)nbc / (double)whole;
   if (br > 1) best.most_us = estimate(best.variant, best.rows_per_split, best.splits, most < 1.0 ? most : 1.0, true);
@@ -569,10 +573,11 @@ DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, 
 }
 
 // (a call asks for its plan several times: workspace, choice of the kernel, launch)
-DirectPlan direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
-  thread_local struct { int64_t M, K, N; int dtype, br, bc; DirectPlan plan; } last = {0, 0, 0, 0, 0, 0, {}};
-  if (last.M != M || last.K != K || last.N != N || last.dtype != dtype || last.br != br || last.bc != bc)
-    last = {M, K, N, dtype, br, bc, make_direct_plan(dtype, M, K, N, br, bc)};
+DirectPlan direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes) {
+  thread_local struct { int64_t M, K, N; int dtype, br, bc; size_t ws_bytes; DirectPlan plan; } last = {0, 0, 0, 0, 0, 0, 0, {}};
+  if (last.M != M || last.K != K || last.N != N || last.dtype != dtype || last.br != br || last.bc != bc ||
+      last.ws_bytes != ws_bytes)
+    last = {M, K, N, dtype, br, bc, ws_bytes, make_direct_plan(dtype, M, K, N, br, bc, ws_bytes)};
   return last.plan;
 }
 
@@ -628,8 +633,9 @@ bool dw_direct_supported(int dtype, int br, int bc, const void *values, int64_t 
   return ceil_div(K, 16) * ceil_div(N, 32) < (int64_t(1) << 24);
 }
 
-double dw_direct_most_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
-  const DirectPlan p = direct_plan(dtype, M, K, N, br, bc);
+double dw_direct_most_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes) {
+  const DirectPlan p = direct_plan(dtype, M, K, N, br, bc, ws_bytes);
+  if (p.us == 0.0) return 1e30;
   // (bfloat16, one workgroup of 16 waves per compute unit: with many units each, their loads take longer than the model has it,
   // [5615 x 96 x 2160] in 64x64 blocks, 22 units: 17.2 us in 128 x 128 tiles, 21.2 here, 14 by the model; [2916 x 32 x 584], 11.5: 10.3,
   // 12.4 and 9.9)
@@ -638,16 +644,11 @@ double dw_direct_most_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int
   return p.most_us * (!many ? 1.0 : units > 16 * kWaves[2] ? 2.0 : 1.15);
 }
 
-size_t dw_direct_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
-  const DirectPlan p = direct_plan(dtype, M, K, N, br, bc);
-  return p.splits > 1 ? (size_t)p.splits * K * N * sizeof(float) : 0;
-}
-
 int launch_dw_direct(int dtype, const DwJob &j, hipStream_t s) {
-  const DirectPlan p = direct_plan(dtype, j.M, j.K, j.N, j.br, j.bc);
+  const DirectPlan p = direct_plan(dtype, j.M, j.K, j.N, j.br, j.bc, j.ws_bytes);
   const size_t need = p.splits > 1 ? (size_t)p.splits * j.K * j.N * sizeof(float) : 0;
   if (need > 0 && (j.ws == nullptr || j.ws_bytes < need)) return BSR_ERR_WORKSPACE;
-  if (p.rows_per_split > max_rows(j.br)) return BSR_ERR_SHAPE;
+  if (p.us == 0.0 || p.rows_per_split > max_rows(j.br)) return BSR_ERR_SHAPE;
   const bool split = p.splits > 1;
   DirectParams prm;
   prm.row_ptr = j.row_ptr; prm.col_idx = j.col_idx;

@@ -39,6 +39,20 @@ def test_single_products_by_kernel(recorder):  # noqa: F811
     assert ["dw_direct" in g["names"][0] for g in got] == [False, True, False]
 
 
+def test_products_gathered_by_the_waves_need_no_workspace_of_their_own(recorder):  # noqa: F811
+    """The query names what the other kernels need (re-tiled row segments: the copy and its partial sums), whichever takes the
+    product; it is enough on either side of the line."""
+    segments = [((5232, 4516, 6468, 32), 47 << 20), ((5545, 573, 7444, 96), 7 << 20), ((4534, 3042, 3895, 64), 28 << 20)]
+    got = recorder([dict(items=[dict(M=M, K=K, N=N, br=1, bc=bc)]) for (M, K, N, bc), _ in segments])
+    assert [g["rc"] for g in got] == [0] * 3 and all("reblock" in g["names"][0] for g in got)
+    assert all(g["ws"] <= most for g, (_, most) in zip(got, segments)), [g["ws"] for g in got]
+    for dtype in (0, 1):
+        for br, bc in ((14, 14), (16, 16), (32, 32), (1, 32), (1, 96)):
+            for K, N in ((64, 64), (196, 196), (411, 1001), (1500, 24)):
+                got = recorder([dict(items=[dict(M=M, K=K, N=N, br=br, bc=bc)], dtype=dtype) for M in range(100, 30000, 700)])
+                assert [g["rc"] for g in got] == [0] * len(got)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("b", [14, 16, 32, 64])
 @pytest.mark.parametrize("M,K,N,keep,dtype", [
