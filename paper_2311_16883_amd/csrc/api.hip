@@ -183,34 +183,55 @@ bool direct_sizes(int dtype, int64_t M, int64_t K, int64_t N, int br) {
 // Not: wide activations, whose entries every strip walks, bfloat16 [4096 x 10000 x 8] in 1x32 42 and 43, 51 and 150, 64 and 260;
 // [3000 x 3000 x 46] 26 and 13, 25 and 24, 25 and 32; few rows and a small dW, which the general kernel
 // takes as fast, [24 x 59 x 10] 8 and 9.
-bool segments_pay(int dtype, int64_t M, int64_t K, int64_t N, int bc, size_t ws_bytes) {
-  if (M < 64 && K < 1000 && K * N < 20000) return false;
-  const double us = dw_direct_most_us(dtype, M, K, N, 1, bc, ws_bytes);
+double segments_other_us(int dtype, int64_t M, int64_t K, int64_t N) {
+  if (M < 64 && K < 1000 && K * N < 20000) return 0.0;
   // (the general kernel's search among a row's entries: [25 x 2688 x 32] bfloat16 14.6, 9.5 so)
-  if (!retiling_pays(M, K, N, 1)) return us < (dtype == BSR_F32 ? 0.85 : 0.8) * (general_us(M, K, N, 1) + 1.2e-3 * (double)(K < 4000 ? K : 4000));
+  if (!retiling_pays(M, K, N, 1))
+    return (dtype == BSR_F32 ? 0.85 : 0.8) * (general_us(M, K, N, 1) + 1.2e-3 * (double)(K < 4000 ? K : 4000));
   const double mb = (double)M * (double)K * elem_bytes(dtype) * 1e-6;
   const double other = (5.4 + 0.68 * dw_mfma_us(dtype, M, K, N, 32) + 0.37 * mb) * (K <= 32 ? 0.87 : 1.0);
-  return us < (dtype == BSR_F32 ? 0.95 : 0.92) * other;
+  return (dtype == BSR_F32 ? 0.95 : 0.92) * other;
 }
-bool direct_pays(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, bool odd, size_t ws_bytes) {
-  if (!direct_sizes(dtype, M, K, N, br)) return false;
-  if (br == 1) return segments_pay(dtype, M, K, N, bc, ws_bytes);
-  // (a small dW in narrow blocks, such as a cross-patch layer's: partial sums and tiles in part cost more than either plan has it)
-  const bool small = bc < 32 && K * N < 50000 && N > 64;
-  double line = bc >= 32 ? (odd ? 0.65 : 0.67) : odd ? 0.68 : small ? 0.75 : 0.70;
-  if (dtype == BSR_F32) {
-    const bool few = K < (bc < 32 ? 40 : 128) && (double)M * (double)K * (double)N > 3e8;
-    line = few ? 0.55 : bc == 16 ? 1.0 : bc >= 32 ? 0.83 : small ? 1.32 : 0.9;
-  }
-  return dw_direct_most_us(dtype, M, K, N, br, bc, ws_bytes) < line * dw_mfma_us(dtype, M, K, N, br);
+
+// The plan of a product on its own, and the time that the other kernels need for it.  A thread keeps those of its last shapes: a
+// network's layers come by again and again, and a plan costs as much on the host as a third of a launch.
+struct DirectChoice {
+  int64_t M, K, N;
+  size_t ws_bytes;
+  int dtype, br, bc;
+  DirectPlan plan;
+  double other_us;
+};
+constexpr int kKeptChoices = 64;
+const DirectChoice &direct_choice(int dtype, const DwJob &j) {
+  static thread_local DirectChoice kept[kKeptChoices];
+  uint64_t h = (uint64_t)j.M * 0x9E3779B97F4A7C15ull ^ (uint64_t)j.K * 0xC2B2AE3D27D4EB4Full ^ (uint64_t)j.N * 0x165667B19E3779F9ull;
+  h = (h ^ (uint64_t)(j.br + 64 * j.bc + dtype)) * 0x9E3779B97F4A7C15ull;
+  DirectChoice &c = kept[h >> 58];
+  if (c.M != j.M || c.K != j.K || c.N != j.N || c.ws_bytes != j.ws_bytes || c.dtype != dtype || c.br != j.br || c.bc != j.bc)
+    c = DirectChoice{j.M, j.K, j.N, j.ws_bytes, dtype, j.br, j.bc, make_direct_plan(dtype, j.M, j.K, j.N, j.br, j.bc, j.ws_bytes),
+                     j.br == 1 ? segments_other_us(dtype, j.M, j.K, j.N) : dw_mfma_us(dtype, j.M, j.K, j.N, j.br)};
+  return c;
 }
+
 bool use_direct(int dtype, const DwJob &j) {
   if (!dw_direct_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy)) return false;
+  const bool tiles = j.br == 1 || dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy);
+  if (tiles && !direct_sizes(dtype, j.M, j.K, j.N, j.br)) return false;
+  const DirectChoice &c = direct_choice(dtype, j);
+  if (c.plan.us == 0.0) return false;
   // (square blocks that the tiles cannot address, binary32 values off 16-byte boundaries: the general kernel takes 1 .. 4 times as long)
-  if (j.br > 1 && !dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy))
-    return dw_direct_most_us(dtype, j.M, j.K, j.N, j.br, j.bc, j.ws_bytes) < 1e30;
-  const bool odd = dtype == BSR_BF16 && (j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0);
-  return direct_pays(dtype, j.M, j.K, j.N, j.br, j.bc, odd, j.ws_bytes);
+  if (!tiles) return true;
+  if (j.br == 1) return c.plan.most_us < c.other_us;
+  // (a small dW in narrow blocks, such as a cross-patch layer's: partial sums and tiles in part cost more than either plan has it)
+  const bool small = j.bc < 32 && j.K * j.N < 50000 && j.N > 64;
+  const bool odd = j.N % 2 != 0 || j.lddy % 2 != 0 || (uintptr_t)j.dY % 4 != 0;
+  double line = j.bc >= 32 ? (odd ? 0.65 : 0.67) : odd ? 0.68 : small ? 0.75 : 0.70;
+  if (dtype == BSR_F32) {
+    const bool few = j.K < (j.bc < 32 ? 40 : 128) && (double)j.M * (double)j.K * (double)j.N > 3e8;
+    line = few ? 0.55 : j.bc == 16 ? 1.0 : j.bc >= 32 ? 0.83 : small ? 1.32 : 0.9;
+  }
+  return c.plan.most_us < line * c.other_us;
 }
 
 // Workspace of a product, whatever kernel takes it (the gathering one makes do with what the others need).  (The wide tiles take activations that the 128 x 128 tiles don't, from 2 GiB
@@ -275,7 +296,7 @@ DwRoutes dw_routes(int dtype, const std::vector<DwJob> &jobs, bool several) {
 // One product, with a workspace of dw_ws_bytes or more.
 int launch_dw(int dtype, const DwJob &j, hipStream_t s) {
   if (use_wide_single(dtype, j)) return launch_dw_wide(j, s);
-  if (use_direct(dtype, j)) return launch_dw_direct(dtype, j, s);
+  if (use_direct(dtype, j)) return launch_dw_direct(dtype, j, direct_choice(dtype, j).plan, s);
   if (dw_mfma_supported(dtype, j.br, j.bc, j.values, j.M, j.K, j.N, j.lddy))
     return launch_dw_mfma(dtype, j.row_ptr, j.col_idx, j.values, j.M, j.K, j.br, j.bc, j.dY, j.N, j.lddy, j.dW, j.lddw, j.accumulate,
                           j.ws, j.ws_bytes, s);

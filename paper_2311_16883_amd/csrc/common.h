@@ -226,9 +226,12 @@ int launch_dw_mfma_batched(int dtype, const DwJob *jobs, int n, hipStream_t s);
 
 // dw_direct.hip: 14x14, 16x16, 32x32, 64x64 blocks and 1 x 32k row segments, waves that gather kept blocks: one product per launch.
 bool dw_direct_supported(int dtype, int br, int bc, const void *values, int64_t M, int64_t K, int64_t N, int64_t lddy);
-// What its plan needs when nine blocks in ten are kept, in microseconds, with a workspace of that size (1e30: it cannot do with that).
-double dw_direct_most_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes);
-int launch_dw_direct(int dtype, const DwJob &j, hipStream_t s);
+struct DirectPlan {
+  double us, most_us;                        // estimated time, as planned (0: there is no plan) and with nine blocks in ten kept
+  int variant, splits, rows_per_split;
+};
+DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes);
+int launch_dw_direct(int dtype, const DwJob &j, const DirectPlan &p, hipStream_t s);
 
 // dw_wide.hip: bfloat16, 16x16 / 32x32 / 64x64 blocks, 384-row tiles fed by global -> LDS copies.
 // dw_narrow.hip: bfloat16, small square blocks, a weight matrix of at most 224 x 224: one workgroup owns all of dW

@@ -472,12 +472,7 @@ __global__ __launch_bounds__(64 * W, WAVES) void dw_direct_kernel(DirectParams p
   }
 }
 
-// Tile width and splits of a product.
-struct DirectPlan {
-  double us, most_us;                        // as planned, and with most blocks kept (see make_direct_plan)
-  int variant, splits, rows_per_split;       // variant: 0 wide tiles .. 2 narrow ones
-};
-
+// A plan's variant: 0 wide tiles .. 2 narrow ones.
 constexpr int kVariants = 3;
 constexpr int kWaves[kVariants] = {4, 8, 16};
 inline int variant_columns(int v) { return 128 >> v; }
@@ -521,65 +516,89 @@ double segments_us(const DirectPlan &p, int dtype, int64_t tiles, int64_t K, int
 // are kept (the other kernels take about as long whatever is kept, so a call that is no slower then is no slower at all).  That
 // counts the walk through the entries of a workgroup's rows as well, which every strip does ([2000 x 30000 x 256] binary32 in 16x16
 // blocks: 1875 strips, 1300 us at keep 0.9), and that a last block-column in part is the first to be pruned: of the others more is kept.
+// What a variant's workgroups cost, whatever the splits.
+struct VariantCosts {
+  int64_t tiles;
+  double unit_us, unit_kb;
+  int waves, per_cu;
+};
+
+}  // namespace
+
+// (the operands are below 2 GiB: 32-bit counts of block-rows.  A few hundred ns at the most: splits that cost more than the best plan
+// by what they write alone end a variant's turn)
 DirectPlan make_direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes) {
-  const int64_t nbr = ceil_div(M, br), nbc = ceil_div(K, bc);
-  const int64_t strips = bc > 16 ? ceil_div(K, 32) : nbc;
-  const int kMaxRows = max_rows(br), e = elem_bytes(dtype);
+  const uint32_t nbr = (uint32_t)ceil_div(M, br);
+  const int64_t nbc = ceil_div(K, bc), strips = bc > 16 ? ceil_div(K, 32) : nbc;
+  const uint32_t kMaxRows = (uint32_t)max_rows(br);
+  const int e = elem_bytes(dtype);
   const double upb = br > kUnit ? br / kUnit : br == 1 ? 1.0 / kUnit : 1.0;
   const DirectCosts &c = dtype == BSR_F32 ? kCostsF32 : kCostsBf16;
-  auto estimate = [&](int v, int64_t rows, int64_t splits, double keep, bool walk) {
-    const int cols = variant_columns(v), waves = kWaves[v], per_cu = at_a_time(v, e, br, bc);
-    const double unit_us = bc % 32 == 0 ? c.unit32 * (cols / 32) : cols > 64 ? c.unit_wide16 : cols > 32 ? c.unit_mid16 : c.unit_narrow16;
-    const double unit_kb = kUnit * e * ((bc < 32 ? bc : 32) + cols) * 1e-3;
-    const double units = (double)rows * upb * keep / waves + 0.5;
+  const double split_us = (double)K * (double)N * 8e-6 * c.reduce_per_mb;
+  auto costs = [&](int v) {
+    const int cols = variant_columns(v);
+    return VariantCosts{strips * ceil_div(N, cols),
+                        bc % 32 == 0 ? c.unit32 * (cols / 32) : cols > 64 ? c.unit_wide16 : cols > 32 ? c.unit_mid16 : c.unit_narrow16,
+                        kUnit * e * ((bc < 32 ? bc : 32) + cols) * 1e-3, kWaves[v], at_a_time(v, e, br, bc)};
+  };
+  auto estimate = [&](const VariantCosts &vc, uint32_t rows, uint32_t splits, double keep, bool walk) {
+    const double units = (double)rows * upb * keep / vc.waves + 0.5;
     auto round_us = [&](int64_t n) {
-      const double on_all = (double)(waves * n);
-      const double mult = unit_us * on_all / 4, load = unit_kb * on_all / c.bytes_per_ns;
+      const double on_all = (double)(vc.waves * n);
+      const double mult = vc.unit_us * on_all / 4, load = vc.unit_kb * on_all / c.bytes_per_ns;
       const double busy = mult > load ? mult : load;
       return c.round + (walk ? (double)rows * nbc * 4e-3 * keep * (double)n / c.bytes_per_ns : 0.0) +
              units * (busy > c.on_the_way ? busy : c.on_the_way);
     };
-    const int64_t on_a_cu = ceil_div(strips * ceil_div(N, cols) * splits, (int64_t)256);
-    return c.start + (double)(on_a_cu / per_cu) * round_us(per_cu) + (on_a_cu % per_cu ? round_us(on_a_cu % per_cu) : 0.0) +
-           (splits > 1 ? c.reduce + (double)splits * (double)K * (double)N * 8e-6 * c.reduce_per_mb : 0.0);
+    const int64_t on_a_cu = (vc.tiles * splits + 255) >> 8;
+    const int64_t full = vc.per_cu == 1 ? on_a_cu : vc.per_cu == 2 ? on_a_cu >> 1 : on_a_cu / 3, rest = on_a_cu - full * vc.per_cu;
+    return c.start + (full > 0 ? (double)full * round_us(vc.per_cu) : 0.0) + (rest > 0 ? round_us(rest) : 0.0) +
+           (splits > 1 ? c.reduce + (double)splits * split_us : 0.0);
   };
   DirectPlan best{0, 0, 0, 1, (int)(nbr < 1 ? 1 : nbr > kMaxRows ? kMaxRows : nbr)};
   bool any = false;
+  const int64_t s_room = (int64_t)(ws_bytes / ((size_t)K * N * sizeof(float)));
   for (int v = 0; v < kVariants; ++v) {
-    const int64_t tiles = strips * ceil_div(N, variant_columns(v));
+    const VariantCosts vc = costs(v);
     // (splits beyond four rounds of workgroups gain nothing)
-    const int64_t s_min = ceil_div(nbr, (int64_t)kMaxRows), s_full = 1024 * at_a_time(v, e, br, bc) / tiles + 1;
-    int64_t s_max = nbr < 64 ? nbr : 64, rows_before = 0;
+    const uint32_t s_min = (nbr + kMaxRows - 1) / kMaxRows;
+    const int64_t s_full = 1024 * vc.per_cu / vc.tiles + 1;
+    int64_t s_max = nbr < 64 ? nbr : 64;
     if (s_max > s_full) s_max = s_full;
     if (s_max < s_min) s_max = s_min;
-    const int64_t s_room = (int64_t)(ws_bytes / ((size_t)K * N * sizeof(float)));
     if (s_max > s_room) s_max = s_room > 1 ? s_room : 1;
-    for (int64_t s = s_min; s <= s_max; ++s) {
-      const int64_t rows = ceil_div(nbr, s);
+    uint32_t rows_before = 0;
+    for (uint32_t s = s_min; s <= s_max; ++s) {
+      const uint32_t rows = (nbr + s - 1) / s;
       if (rows == rows_before) continue;
       rows_before = rows;
-      const int64_t splits = ceil_div(nbr, rows);
-      const double us = estimate(v, rows, splits, 0.6, br == 1);    // (row segments: every workgroup walks all entries of its rows)
+      const uint32_t splits = (nbr + rows - 1) / rows;
+      if (any && splits > 1 && c.start + c.round + c.reduce + (double)splits * split_us > best.us) break;
+      const double us = estimate(vc, rows, splits, 0.6, br == 1);   // (row segments: every workgroup walks all entries of its rows)
       if (!any || us < best.us) best = DirectPlan{us, 0, v, (int)splits, (int)rows};
       any = true;
     }
   }
   if (!any) return best;                     // (us 0: no plan)
   const int64_t whole = K / bc < 1 ? 1 : K / bc;
-  const double most = 0.9 * (double)nbc / (double)whole;
-  if (br > 1) best.most_us = estimate(best.variant, best.rows_per_split, best.splits, most < 1.0 ? most : 1.0, true);
-  else best.most_us = segments_us(best, dtype, strips * ceil_div(N, variant_columns(best.variant)), K, N, nbc, most < 1.0 ? most : 1.0);
+  double most = 0.9 * (double)nbc / (double)whole;
+  if (most > 1.0) most = 1.0;
+  const VariantCosts vc = costs(best.variant);
+  if (br == 1) {
+    best.most_us = segments_us(best, dtype, vc.tiles, K, N, nbc, most);
+    return best;
+  }
+  best.most_us = estimate(vc, (uint32_t)best.rows_per_split, (uint32_t)best.splits, most, true);
+  // (bfloat16, one workgroup of 16 waves per compute unit: with many units each, their loads take longer than the model has it,
+  // [5615 x 96 x 2160] in 64x64 blocks, 22 units: 17.2 us in 128 x 128 tiles, 21.2 here, 14 by the model; [2916 x 32 x 584], 11.5: 10.3,
+  // 12.4 and 9.9)
+  const int64_t units = (int64_t)best.rows_per_split * br / kUnit;
+  if (dtype == BSR_BF16 && bc >= 32 && best.variant == 2 && best.splits == 1 && units > 11 * kWaves[2])
+    best.most_us *= units > 16 * kWaves[2] ? 2.0 : 1.15;
   return best;
 }
 
-// (a call asks for its plan several times: workspace, choice of the kernel, launch)
-DirectPlan direct_plan(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes) {
-  thread_local struct { int64_t M, K, N; int dtype, br, bc; size_t ws_bytes; DirectPlan plan; } last = {0, 0, 0, 0, 0, 0, 0, {}};
-  if (last.M != M || last.K != K || last.N != N || last.dtype != dtype || last.br != br || last.bc != bc ||
-      last.ws_bytes != ws_bytes)
-    last = {M, K, N, dtype, br, bc, ws_bytes, make_direct_plan(dtype, M, K, N, br, bc, ws_bytes)};
-  return last.plan;
-}
+namespace {
 
 template <typename T, int BR, int BC, int NS, int W, int D, int WAVES>
 void start(const DirectParams &prm, bool odd, hipStream_t s) {
@@ -633,19 +652,7 @@ bool dw_direct_supported(int dtype, int br, int bc, const void *values, int64_t 
   return ceil_div(K, 16) * ceil_div(N, 32) < (int64_t(1) << 24);
 }
 
-double dw_direct_most_us(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc, size_t ws_bytes) {
-  const DirectPlan p = direct_plan(dtype, M, K, N, br, bc, ws_bytes);
-  if (p.us == 0.0) return 1e30;
-  // (bfloat16, one workgroup of 16 waves per compute unit: with many units each, their loads take longer than the model has it,
-  // [5615 x 96 x 2160] in 64x64 blocks, 22 units: 17.2 us in 128 x 128 tiles, 21.2 here, 14 by the model; [2916 x 32 x 584], 11.5: 10.3,
-  // 12.4 and 9.9)
-  const int64_t units = (int64_t)p.rows_per_split * br / kUnit;
-  const bool many = dtype == BSR_BF16 && bc >= 32 && p.variant == 2 && p.splits == 1 && units > 11 * kWaves[2];
-  return p.most_us * (!many ? 1.0 : units > 16 * kWaves[2] ? 2.0 : 1.15);
-}
-
-int launch_dw_direct(int dtype, const DwJob &j, hipStream_t s) {
-  const DirectPlan p = direct_plan(dtype, j.M, j.K, j.N, j.br, j.bc, j.ws_bytes);
+int launch_dw_direct(int dtype, const DwJob &j, const DirectPlan &p, hipStream_t s) {
   const size_t need = p.splits > 1 ? (size_t)p.splits * j.K * j.N * sizeof(float) : 0;
   if (need > 0 && (j.ws == nullptr || j.ws_bytes < need)) return BSR_ERR_WORKSPACE;
   if (p.us == 0.0 || p.rows_per_split > max_rows(j.br)) return BSR_ERR_SHAPE;
