@@ -129,7 +129,7 @@ constexpr int kLoose = 1;
 // VB of the gather whose block rows are no whole 16-byte vectors, but one at least: the last vector of a row ends where the row
 // ends and repeats bytes of the one before (two lanes write the same to the same place), on both sides at any element.  14-wide rows
 // of bfloat16 are two such vectors where pieces of 4 or 2 bytes took 7 or 14 ([41298 x 805], keep 0.9: 44 us and 32 so; [20466 x 2669]
-// 66 and 42; binary32, four where 7 of 8 bytes or 14 of 4 were: 83 and 61, 84 and 66).
+// 66 and 42; binary32, four where 7 of 8 bytes or 14 of 4 were, [41298 x 805] 54 and 44).  Where: tail_pays.
 constexpr int kTail = 3;
 template <int VB> constexpr int vector_bytes() { return VB == kLoose || VB == kTail ? 16 : VB; }
 
@@ -300,7 +300,8 @@ __device__ __forceinline__ void compress_body(const CompressArgs &a, const uint3
         W val[kInFlight];
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
-          const int q = q0 + u * step < (int)nk ? q0 + u * step : (int)nk - 1;
+          const int q = q0 + u * step;
+          if (q >= (int)nk) continue;
           const int64_t cb = (int64_t)kept_j[q] * bcb + off;
           val[u] = reinterpret_cast<const LooseVec *>(row_in && cb + 16 <= kb ? src + cb : xrow)->v;
         }
@@ -1006,6 +1007,18 @@ struct CompressPlan {
   CompressSpanArgs span;
 };
 
+// Whether block rows that are no whole vectors are copied by vectors that end with the row (kTail) rather than in pieces of vb bytes.
+// Two vectors for each thread of a block-row at least: with less to do the pieces are no slower ([41000 x 161] bfloat16 in 7x9 blocks,
+// keep 0.75, 17 us in pieces and 19 so, [20000 x 322] in 3x17 18 and 20; [41000 x 805] in 7x9 74 and 26).  Binary32, whose pieces
+// are 4 or 8 bytes: as long as matrix and result stay in the memory-side cache; out of it the two stores to a line that rows share cost
+// more ([29297 x 1618] in 9x13, keep 0.75, 72 and 95, [20466 x 2669] in 14x14 78 and 89; [41298 x 805] in 14x14 50 and 40); by pieces of
+// 8 bytes where there is more to do only ([45000 x 300] in 14x14, keep 0.25, 14.2 and 15.1, [25088 x 784] 15.1 and 14.7).
+bool tail_pays(const CompressJob &j, int e, int vb) {
+  const int64_t rowb = (int64_t)j.bc * e, vectors = ceil_div(j.K, (int64_t)j.bc) * j.br * ceil_div(rowb, (int64_t)16);
+  if (rowb < 16 || j.K * e < 16 || vectors < 512) return false;
+  return e == 2 || (j.M * j.K * e <= 150000000 && (vb < 8 || vectors >= 2048));
+}
+
 // row_wgs: block-rows of the whole call (what shares the launch)
 CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
   CompressPlan p{};
@@ -1048,7 +1061,7 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
   // Rows of X that start anywhere, blocks that are whole 16-byte vectors: 16 bytes from where they are
   // ([9947 x 411] bf16, 32x32 blocks: 22 us element by element, 7 us so).
   if (p.vb < 16 && (int64_t)j.bc * e % 16 == 0 && (uintptr_t)j.values % 16 == 0) p.vb = kLoose;
-  else if (p.vb < 16 && (int64_t)j.bc * e >= 16 && j.K * e >= 16) p.vb = kTail;
+  else if (p.vb < 16 && tail_pays(j, e, p.vb)) p.vb = kTail;
   // Every workgroup counts the mask in front of its row, wgs * nblocks / 2 bytes out of L2 in all, unless a
   // launch writes row_ptr first (6 to 8 us).  That is the faster way from 256 MB on (mask of 3136 x 96 blocks, 472 MB:
   // 48 us -> 8 + 30 us; 3136 x 48, 236 MB: 70 us either way; 1568 x 48, 59 MB: 35 -> 39 us), if the count is not hidden

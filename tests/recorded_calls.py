@@ -4,7 +4,7 @@ not share a process with torch, which loads the real runtime).
 argv: the recorder, the library.  stdin: a JSON list of calls; stdout: a JSON list of
 {"rc", "ws", "kernels": [[kernel, workgroups], ...]}, ws = what the workspace query returns.
 A call: {"items": [{M, K, N, b or br + bc, lddy, lddw, dY, values, accumulate}, ...], "dtype", "batched"} for weight gradients, or
-{"select": {M, K, br, bc, ldx, X}, "dtype"} for bsr_score_select; addresses are numbers that nothing reads.  The workspace passed
+{"select": {M, K, br, bc, ldx, X}, "dtype"} for bsr_score_select, or {"compress": the same, "dtype"} for bsr_compress; addresses are numbers that nothing reads.  The workspace passed
 is exactly the one the query asks for.
 """
 import ctypes as C
@@ -33,16 +33,23 @@ def main():
     lib.bsr_t_dense_matmul_batched_workspace_bytes.argtypes = [p, i32, i32]
     lib.bsr_t_dense_matmul_batched.argtypes = [p, i32, i32, p, size, p]
     lib.bsr_score_select.argtypes = [p, i32, i64, i64, i64, i32, i32, C.c_double, p, p, p, size, p]
+    lib.bsr_compress.argtypes = [p, i32, i64, i64, i64, i32, i32, p, i64, p, p, p, p, size, p]
     out = []
 
     def launched():
         return [[recorder.recorder_name(i).decode(), recorder.recorder_workgroups(i)] for i in range(recorder.recorder_count())]
 
     for call in json.load(sys.stdin):
-        if "select" in call:
-            a, dtype = call["select"], call.get("dtype", 1)
+        if "select" in call or "compress" in call:
+            a, dtype = call.get("select") or call["compress"], call.get("dtype", 1)
             M, K, br, bc = a["M"], a["K"], a["br"], a["bc"]
             recorder.recorder_reset()
+            if "compress" in call:
+                ws = lib.bsr_workspace_bytes(1, M, K, 0, br, bc, dtype)
+                rc = lib.bsr_compress(a.get("X", ADDRESS), dtype, M, K, a.get("ldx", K), br, bc, ADDRESS, -(-M // br), ADDRESS, ADDRESS,
+                                      ADDRESS, ADDRESS, ws, None)
+                out.append({"rc": rc, "ws": ws, "kernels": launched()})
+                continue
             ws = lib.bsr_workspace_bytes(0, M, K, 0, br, bc, dtype)
             rc = lib.bsr_score_select(a.get("X", ADDRESS), dtype, M, K, a.get("ldx", K), br, bc, 0.5, None, ADDRESS, ADDRESS, ws, None)
             out.append({"rc": rc, "ws": ws, "kernels": launched()})
