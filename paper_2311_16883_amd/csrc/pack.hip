@@ -1045,9 +1045,10 @@ CompressPlan plan_compress(const CompressJob &j, int dtype, int64_t row_wgs) {
                      nbr * nbr * nbc <= (int64_t(1) << 31);
   if (!fused) {
     p.path = kPackOther;
-    // (blocks so small that a wave does not take long for 64 of them)
+    // (blocks so small that a wave does not take long for 64 of them; rows of one block, or two small ones, give a wave next to nothing
+    // to do: [49000 x 30] bfloat16 with a pitch of 31 in 1x64 blocks, keep 0.75, 26 us and 38 so, [49000 x 130] in 1x128 47 and 32)
     const int64_t rowb = (int64_t)j.bc * e;
-    if (nbr >= 4096 && nbc > 0 && nbr * nbc <= kRowPtrMaxBlocks && rowb >= 16 && j.K * e >= 16 && j.br * ceil_div(rowb, (int64_t)16) <= 64) {
+    if (nbr >= 4096 && (nbc >= 3 || (nbc == 2 && j.K * e >= 240)) && nbr * nbc <= kRowPtrMaxBlocks && rowb >= 16 && j.K * e >= 16 && j.br * ceil_div(rowb, (int64_t)16) <= 64) {
       p.path = kPackRows;
       p.wgs = (unsigned)ceil_div(nbr, (int64_t)4);
       p.direct = CompressArgs{j.keep_mask, static_cast<const uint8_t *>(j.X), j.row_ptr, j.col_idx,

@@ -21,6 +21,7 @@ ANY_ALIGNMENT = [
     (9000, 2301, 1, 32, 0, 1.0),       # 72 block-columns, two passes of a wave
     (30000, 71, 1, 32, 1, 0.4),        # (rows apart: binary32 as well)
     (9000, 2301, 1, 32, 2, 1.0),
+    (9000, 61, 1, 128, 1, 0.5),        # many block-rows of one block: a workgroup each
 ]
 
 
@@ -32,11 +33,11 @@ def test_conversions_by_kernel(recorder):  # noqa: F811
         return ["tail" if "compress_kernelILi3E" in g["names"][-1] else "rows" if "compress_rows" in g["names"][-1] else "other" for g in got]
 
     for dtype in (0, 1):
-        assert names(dtype, [(20000, 322, 3, 17, 1), (41000, 161, 7, 9, 1)]) == ["other"] * 2
+        assert names(dtype, [(49000, 30, 1, 64, 1), (49000, 60, 1, 128, 1), (20000, 322, 3, 17, 1), (41000, 161, 7, 9, 1)]) == ["other"] * 4
         assert names(dtype, [(41298, 805, 14, 14, 0), (9170, 1779, 14, 14, 0), (5000, 805, 7, 9, 0)]) == ["tail"] * 3
         assert names(dtype, [(10307, 1071, 1, 32, 1), (30000, 601, 1, 32, 1), (41000, 805, 7, 9, 0)]) == ["rows"] * 3
         span = [] if dtype else [6, 8, 9]     # (contiguous rows of whole words)
-        reached = ["tail"] * 3 + ["other"] + ["tail"] * 2 + ["rows"] * 6
+        reached = ["tail"] * 3 + ["other"] + ["tail"] * 2 + ["rows"] * 6 + ["other"]
         assert names(dtype, ANY_ALIGNMENT) == ["other" if i in span else n for i, n in enumerate(reached)]
     assert names(0, [(29297, 1618, 9, 13, 0), (20466, 2669, 14, 14, 0)]) == ["other"] * 2
     assert names(1, [(29297, 1618, 9, 13, 0), (20466, 2669, 14, 14, 0)]) == ["tail"] * 2
