@@ -1,5 +1,7 @@
 """dW of products on their own whose waves gather the kept blocks: which calls take that kernel (CPU), and its results at the
 edges of its tiles, units, splits and lists."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -68,7 +70,7 @@ def test_products_gathered_by_the_waves_need_no_workspace_of_their_own(recorder)
     (500, 130, 257, 0.3, "bf16"),
     (2500, 40, 66, 0.9, "bf16"),
     (700, 500, 131, 0.6, "bf16"),
-    (500, 40, 2001, 0.4, "bf16"),        # tiles of 128 columns
+    (500, 40, 2001, 0.4, "bf16"),        # many tiles of dY, one column in the last
     (16000, 200, 45, 0.75, "bf16"),      # several splits, and more block-rows than the list of one holds
 ])
 def test_dw_of_blocks_gathered_by_the_waves(M, K, N, keep, dtype, b):
@@ -135,3 +137,74 @@ def test_dw_of_row_segments_gathered_by_the_waves(M, K, N, keep, dtype, bc):
         for j in np.unique(o_ci):
             dead[j * bc:(j + 1) * bc] = False
         assert not got[dead].any()
+
+
+# One product for every form of the kernel that a call of its own can take: element, rows of a block, waves of a workgroup (4: tiles
+# of 128 columns, 8: 64, 16: 32), rows of dY on odd elements, splits; M, K, N, and the columns of a block.
+FORMS = [
+    ("f32", 1, 4, False, False, 23, 893, 586, 96), ("f32", 1, 4, False, True, 1855, 1092, 78, 96),
+    ("f32", 1, 8, False, False, 66, 9, 4, 32), ("f32", 1, 8, False, True, 1259, 12, 4, 32),
+    ("f32", 1, 16, False, False, 267, 33, 4, 32), ("f32", 1, 16, False, True, 17222, 8, 5, 32),
+    ("f32", 14, 4, False, False, 24, 1876, 96, 14), ("f32", 14, 4, False, True, 4453, 394, 68, 14),
+    ("f32", 14, 8, False, False, 23, 1825, 50, 14), ("f32", 14, 8, False, True, 2426, 40, 746, 14),
+    ("f32", 14, 16, False, False, 20, 9, 10, 14), ("f32", 14, 16, False, True, 1422, 11, 6, 14),
+    ("f32", 16, 4, False, False, 28, 720, 348, 16), ("f32", 16, 4, False, True, 2122, 575, 232, 16),
+    ("f32", 16, 8, False, False, 20, 267, 508, 16), ("f32", 16, 8, False, True, 3211, 566, 38, 16),
+    ("f32", 16, 16, False, False, 25, 9, 6, 16), ("f32", 16, 16, False, True, 2448, 8, 6, 16),
+    ("f32", 32, 4, False, False, 28, 810, 624, 32), ("f32", 32, 4, False, True, 5907, 389, 230, 32),
+    ("f32", 32, 8, False, False, 40, 8, 5, 32), ("f32", 32, 8, False, True, 1111, 25, 4, 32),
+    ("f32", 32, 16, False, False, 77, 9, 4, 32), ("f32", 32, 16, False, True, 6520, 11, 4, 32),
+    ("f32", 64, 4, False, False, 20, 576, 1068, 64), ("f32", 64, 8, False, False, 49, 12, 4, 64),
+    ("f32", 64, 8, False, True, 1196, 10, 8, 64), ("f32", 64, 16, False, False, 75, 11, 4, 64),
+    ("f32", 64, 16, False, True, 6216, 16, 4, 64), ("bf16", 1, 4, False, False, 21, 1677, 288, 32),
+    ("bf16", 1, 4, False, True, 3676, 730, 94, 32), ("bf16", 1, 4, True, False, 22, 970, 557, 32),
+    ("bf16", 1, 8, False, False, 21, 79, 2754, 96), ("bf16", 1, 8, False, True, 11449, 9, 380, 32),
+    ("bf16", 1, 8, True, False, 20, 1548, 199, 96), ("bf16", 1, 8, True, True, 3261, 500, 33, 32),
+    ("bf16", 1, 16, False, False, 183, 8, 4, 96), ("bf16", 1, 16, False, True, 4541, 47, 4, 32),
+    ("bf16", 1, 16, True, False, 216, 11, 5, 96), ("bf16", 1, 16, True, True, 5248, 34, 5, 96),
+    ("bf16", 14, 4, False, False, 23, 285, 906, 14), ("bf16", 14, 4, False, True, 7672, 209, 214, 14),
+    ("bf16", 14, 4, True, False, 31, 1961, 95, 14), ("bf16", 14, 8, False, False, 20, 279, 408, 14),
+    ("bf16", 14, 8, False, True, 9722, 15, 228, 14), ("bf16", 14, 8, True, False, 21, 39, 2955, 14),
+    ("bf16", 14, 8, True, True, 12076, 141, 63, 14), ("bf16", 14, 16, False, False, 22, 9, 12, 14),
+    ("bf16", 14, 16, False, True, 3777, 9, 6, 14), ("bf16", 14, 16, True, False, 25, 10, 5, 14),
+    ("bf16", 14, 16, True, True, 5501, 21, 5, 14), ("bf16", 16, 4, False, False, 26, 1136, 194, 16),
+    ("bf16", 16, 4, False, True, 16253, 235, 72, 16), ("bf16", 16, 4, True, False, 21, 124, 2953, 16),
+    ("bf16", 16, 8, False, False, 20, 569, 238, 16), ("bf16", 16, 8, False, True, 8166, 18, 362, 16),
+    ("bf16", 16, 8, True, False, 25, 543, 307, 16), ("bf16", 16, 8, True, True, 7333, 23, 589, 16),
+    ("bf16", 16, 16, False, False, 23, 9, 4, 16), ("bf16", 16, 16, False, True, 5300, 8, 6, 16),
+    ("bf16", 16, 16, True, False, 23, 47, 5, 16), ("bf16", 16, 16, True, True, 10286, 8, 9, 16),
+    ("bf16", 32, 4, False, False, 22, 377, 1372, 32), ("bf16", 32, 4, True, False, 136, 838, 639, 32),
+    ("bf16", 32, 8, False, False, 25, 167, 1546, 32), ("bf16", 32, 8, False, True, 6389, 15, 1172, 32),
+    ("bf16", 32, 8, True, False, 21, 467, 553, 32), ("bf16", 32, 16, False, False, 27, 10, 4, 32),
+    ("bf16", 32, 16, False, True, 7163, 8, 4, 32), ("bf16", 32, 16, True, False, 30, 12, 5, 32),
+    ("bf16", 32, 16, True, True, 13036, 9, 5, 32), ("bf16", 64, 4, False, False, 85, 967, 544, 64),
+    ("bf16", 64, 8, False, False, 23, 229, 1122, 64), ("bf16", 64, 8, False, True, 5211, 16, 944, 64),
+    ("bf16", 64, 8, True, False, 71, 1464, 207, 64), ("bf16", 64, 16, False, False, 24, 11, 6, 64),
+    ("bf16", 64, 16, False, True, 5353, 10, 4, 64), ("bf16", 64, 16, True, False, 23, 13, 7, 64),
+    ("bf16", 64, 16, True, True, 8725, 17, 9, 64),
+]
+
+
+def form_reached(got):
+    m = re.search(r"dw_direct_kernelI([ft])Li(\d+)ELi\d+ELi\d+ELi(\d+)ELi\d+ELi\d+ELb(\d)", got["mangled"][0])
+    return m and ("f32" if m[1] == "f" else "bf16", int(m[2]), int(m[3]), m[4] == "1", len(got["names"]) > 1)
+
+
+def test_the_sizes_above_reach_every_form(recorder):  # noqa: F811
+    got = recorder([dict(items=[dict(M=M, K=K, N=N, br=br, bc=bc)], dtype=0 if dtype == "f32" else 1)
+                    for dtype, br, _, _, _, M, K, N, bc in FORMS])
+    assert [g["rc"] for g in got] == [0] * len(got)
+    assert [form_reached(g) for g in got] == [f[:5] for f in FORMS]
+    every = {("f32", br, waves, False) for br in (1, 14, 16, 32, 64) for waves in (4, 8, 16)}
+    every |= {("bf16", br, waves, odd) for br in (1, 14, 16, 32, 64) for waves in (4, 8, 16) for odd in (False, True)}
+    # (wide tiles of 64x64 blocks beside odd rows: no product was found whose plan has them)
+    assert {f[:4] for f in FORMS} == every - {("bf16", 64, 4, True)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,br,waves,odd,splits,M,K,N,bc", FORMS)
+def test_dw_by_every_form_of_the_gathering_waves(dtype, br, waves, odd, splits, M, K, N, bc):
+    if br == 1:
+        test_dw_of_row_segments_gathered_by_the_waves(M, K, N, 0.6, dtype, bc)
+    else:
+        test_dw_of_blocks_gathered_by_the_waves(M, K, N, 0.6, dtype, br)

@@ -29,6 +29,7 @@ def recorder(tmp_path_factory):
         assert r.returncode == 0, r.stderr
         got = json.loads(r.stdout)
         for g in got:
+            g["mangled"] = [n for n, _ in g["kernels"]]
             g["kernels"] = [(kernel_name(n), w) for n, w in g["kernels"]]
             g["names"] = [n for n, _ in g["kernels"]]
         return got

@@ -1241,8 +1241,9 @@ def test_conversion_of_block_rows_with_any_number_of_kept_blocks(br, bc, dtype, 
 ])
 def test_dw_rows_of_dy_at_any_alignment(M, K, N, pad, shift, b, dtype):
     """dY is read in 16-byte vectors whatever its pitch and start: what a vector holds beyond a row's end, the
-    matrix' end or a 14-wide block must reach no entry of dW.  Its surroundings are NaN here.  Tolerance: binary32
-    accumulation of at most 700 products, as in the other parity tests."""
+    matrix' end or a 14-wide block must reach no entry of dW.  Its surroundings are NaN here.  Alone: gathered by waves; in pairs: the
+    128x128 tiles (which test_gpu_dw_tiles.py has alone).  Tolerance: binary32 accumulation of at most 700 products, as in the other
+    parity tests."""
     X, dY = rand_pair(M, K, N, dtype, seed=M + N + b)
     _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, b, b, 0.6)
     ref = oracle.dw(oracle.mask_dense(X, b, b, o_mask), dY)
@@ -1268,8 +1269,8 @@ def test_dw_rows_of_dy_at_any_alignment(M, K, N, pad, shift, b, dtype):
     (15, 256, 5),                # two block-rows, slots
 ])
 def test_dw_of_14x14_binary32_blocks_without_slots(M, K, N):
-    """Sizes whose plan has no slots, alone and in a call of three: blocks that lie in two tiles, the entries of a
-    block-row in order and shuffled; NaN around values and dY."""
+    """Sizes whose plan has no slots (the last one: gathered by waves alone, slots in the call of three), alone and in a call of
+    three: blocks that lie in two tiles, the entries of a block-row in order and shuffled; NaN around values and dY."""
     rng = np.random.default_rng(M)
     X, dY = rand_pair(M, K, N, "f32", seed=M + K)
     _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, 14, 14, 0.6)
@@ -1294,8 +1295,8 @@ def test_dw_of_14x14_binary32_blocks_without_slots(M, K, N):
 @pytest.mark.parametrize("N,pad", [(131, 1), (77, 1), (130, 2)])
 @pytest.mark.parametrize("br,bc", [(1, 32), (8, 16)])
 def test_dw_of_re_tiled_blocks_with_padded_rows_of_dy(br, bc, N, pad):
-    """Block shapes without a kernel instance reach the same loads of dY through the re-tiling (M * K above the limit of
-    the general kernel); the padding of dY's rows is NaN."""
+    """Rows of dY that are padded with NaN, in block shapes that a call of this size gives to the gathering waves (1x32) and to the
+    general kernel (8x16); sizes that are re-tiled are in test_gpu_dw_tiles.py."""
     M, K = 700, 130
     X, dY = rand_pair(M, K, N, "bf16", seed=M + N + br)
     _, o_mask, o_rp, o_ci, o_val = oracle.prune(X, br, bc, 0.6)
