@@ -209,11 +209,12 @@ int bsr_decompress(const int32_t *row_ptr, const int32_t *col_idx,
  * multiply-add.  This is X^T*dY; torch's nn.Linear.weight.grad is its transpose.
  * The contraction is split over block-rows; partial sums are reduced in a fixed
  * order, so results are reproducible run to run.
- * Block shapes 32x32, 64x64, 16x16 and 14x14 are multiplied as stored.  Any other
- * shape -- 1 x b row segments, b = K, rectangular blocks -- is first re-tiled into
- * 32x32 blocks inside the workspace, unless the product is small enough for a
- * kernel that takes any shape; the workspace size reported for such a shape
- * includes that copy (about M*K elements).
+ * Block shapes 32x32, 64x64, 16x16 and 14x14 are multiplied as stored, and so are
+ * row segments of whole 32 columns (1x32, 1x64, ...) in products on their own that
+ * are faster so.  Any other shape -- row segments else, b = K, rectangular blocks --
+ * is first re-tiled into 32x32 blocks inside the workspace, unless the product is
+ * small enough for a kernel that takes any shape; the workspace size reported for
+ * all of these includes that copy (about M*K elements).
  * col_idx may be in any order inside a block-row.
  * Non-finite dY: a 32x32 or 64x64 block that was pruned is never multiplied, so an
  * inf or NaN of dY reaches only the rows of dW that belong to kept blocks of its

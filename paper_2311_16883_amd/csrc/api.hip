@@ -175,14 +175,14 @@ bool direct_sizes(int dtype, int64_t M, int64_t K, int64_t N, int br) {
   if (br < 32) return work < 4e8;
   return work < (M * K < 4000000 ? 1.1e9 : 7e8) || M * K < 2000000;
 }
-// Row segments of whole 32 columns, against re-tiling and the tiles, two or three launches, or the general kernel: here, too, by what
-// each needs for nine segments in ten kept (for re-tiling a fit to 624 products, within 15 % of four in five).  Of 780 products at keeps
-// 0.1 .. 0.9 the worst is 8 % slower so than without this kernel.  In us, without and so, keep 0.1, 0.5 and 0.9: bfloat16
-// [40000 x 320 x 32] in 1x32 blocks 32 and 14, 28 and 16, 25 and 19; [1000 x 400 x 1000] 19 and 8.1, 20 and 10, 20 and 14;
-// [1646 x 136 x 3104] in 1x64 19 and 8.8, 19 and 14, 19 and 16; binary32 [5711 x 376 x 78] in 1x128 28 and 16, 28 and 20, 27 and 22.
-// Not: wide activations, whose entries every strip walks, bfloat16 [4096 x 10000 x 8] in 1x32 42 and 43, 51 and 150, 64 and 260;
-// [3000 x 3000 x 46] 26 and 13, 25 and 24, 25 and 32; few rows and a small dW, which the general kernel
-// takes as fast, [24 x 59 x 10] 8 and 9.
+// Row segments of whole 32 columns, against re-tiling and the tiles, two or three launches, or the general kernel: here, too, by
+// what each needs for nine segments in ten kept (for re-tiling a fit to 624 products, within 15 % of four in five).  Of 780
+// products at keeps 0.1 .. 0.9 the worst is 8 % slower so than without this kernel.  In us, without and so, keep 0.1, 0.5 and 0.9:
+// bfloat16 [40000 x 320 x 32] in 1x32 blocks 32 and 14, 28 and 16, 25 and 19; [1000 x 400 x 1000] 19 and 8.1, 20 and 10, 20 and
+// 14; [1646 x 136 x 3104] in 1x64 19 and 8.8, 19 and 14, 19 and 16; binary32 [5711 x 376 x 78] in 1x128 28 and 16, 28 and 20, 27
+// and 22. Not: wide activations, whose entries every strip walks, bfloat16 [4096 x 10000 x 8] in 1x32 42 and 43, 51 and 150, 64
+// and 260; [3000 x 3000 x 46] 26 and 13, 25 and 24, 25 and 32; few rows and a small dW, which the general kernel takes as fast,
+// [24 x 59 x 10] 8 and 9.
 double segments_other_us(int dtype, int64_t M, int64_t K, int64_t N) {
   if (M < 64 && K < 1000 && K * N < 20000) return 0.0;
   // (the general kernel's search among a row's entries: [25 x 2688 x 32] bfloat16 14.6, 9.5 so)
@@ -220,7 +220,8 @@ bool use_direct(int dtype, const DwJob &j) {
   if (tiles && !direct_sizes(dtype, j.M, j.K, j.N, j.br)) return false;
   const DirectChoice &c = direct_choice(dtype, j);
   if (c.plan.us == 0.0) return false;
-  // (square blocks that the tiles cannot address, binary32 values off 16-byte boundaries: the general kernel takes 1 .. 4 times as long)
+  // (square blocks that the tiles cannot address, such as binary32 values off 16-byte boundaries: the general kernel takes 1 .. 4
+  // times as long)
   if (!tiles) return true;
   if (j.br == 1) return c.plan.most_us < c.other_us;
   // (a small dW in narrow blocks, such as a cross-patch layer's: partial sums and tiles in part cost more than either plan has it)
@@ -234,8 +235,8 @@ bool use_direct(int dtype, const DwJob &j) {
   return c.plan.most_us < line * c.other_us;
 }
 
-// Workspace of a product, whatever kernel takes it (the gathering one makes do with what the others need).  (The wide tiles take activations that the 128 x 128 tiles don't, from 2 GiB
-// up to 4 GiB, and rows of dY further apart.)
+// Workspace of a product, whatever kernel takes it (the gathering one makes do with what the others need).  (The wide tiles take
+// activations that the 128 x 128 tiles don't, from 2 GiB up to 4 GiB, and rows of dY further apart.)
 size_t dw_ws_bytes(int dtype, int64_t M, int64_t K, int64_t N, int br, int bc) {
   size_t a = dw_generic_ws_bytes(M, K, N, br, bc), b = 0;
   if (dw_mfma_supported(dtype, br, bc, nullptr, M, K, N, N)) b = dw_mfma_ws_bytes(dtype, M, K, N, br, bc);
@@ -475,7 +476,8 @@ int bsr_t_dense_matmul(const int32_t *row_ptr, const int32_t *col_idx, const voi
     return BSR_ERR_ALIGN;
   const size_t need = bsr_workspace_bytes(BSR_OP_T_DENSE_MATMUL, M, K, N, br, bc, dtype);
   if (need > 0 && (ws == nullptr || ws_bytes < need)) return BSR_ERR_WORKSPACE;
-  const DwJob job{row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate, ws, need};    // (need: whatever is passed beyond it changes nothing)
+  // (need, not ws_bytes: what is passed beyond it changes nothing)
+  const DwJob job{row_ptr, col_idx, values, M, K, br, bc, dY, N, lddy, dW, lddw, accumulate, ws, need};
   return launch_dw(dtype, job, static_cast<hipStream_t>(stream));
 }
 

@@ -16,11 +16,12 @@
 // consecutive columns of dY in one instruction and feeds element q to its q-th tile, so that the columns
 // VQ * i + q (i = 0 .. IW - 1) form tile q, and a lane's results are VQ consecutive columns as well.  Per step a wave
 // issues one 4-byte load of the activation, one 16-byte load of dY and four matrix instructions.  Small products are bound by
-// latency (list, loads, sums, each a trip or two to memory: 6 us for [256 x 128 x 64], 9.7 before), large ones by the
-// matrix cores ([21148 x 552 x 685], keep 0.9: 162 us, 171 before) and by what reaches a compute unit, 48 bytes per ns.
+// latency (list, loads, sums, each a trip or two to memory: 6 us for [256 x 128 x 64], 9.7 in 128 x 128 tiles), larger ones by the
+// matrix cores and by what reaches a compute unit, 48 bytes per ns; where most blocks are kept the tiles, which load less for
+// each multiply-add, take those ([12544 x 768 x 768] in 16x16 blocks, keep 0.9: 144 us so, 122 there).
 //
 // bfloat16: a lane's operand is eight (16-wide tiles: four) elements of one column, so a unit goes through a small tile of LDS that belongs to
-// the wave alone and comes back through transposing reads.  Bound by latency ([1202 x 152 x 446] 7.1 us, 12.7 before) and by
+// the wave alone and comes back through transposing reads.  Bound by latency ([1202 x 152 x 446] 7.1 us, 12.7 in the tiles) and by
 // the loads, 160 rows and columns for each 32 x 128 multiply-adds.
 //
 // Row segments: the rows of a unit are any 16 that keep a segment in this strip, so nothing pruned is multiplied and no re-tiled
@@ -482,7 +483,7 @@ inline int at_a_time(int v, int e, int br, int bc) { return v == 0 ? (br == 1 ? 
 // What each choice would take, in microseconds: rounds of the workgroups that the compute units hold at a time, each with a start
 // and an end (list of blocks, sums) and the units of its waves, which take what their matrix instructions (bfloat16: and LDS
 // accesses) need, what their loads need, or what one wave's loads are on their way; and the launch that adds up the
-// splits.  At keep 0.6, since what is kept is not known here; only the choices depend on it.  The constants are a fit to every
+// splits.  Variant and splits are chosen at keep 0.6, since what is kept is not known here.  The constants are a fit to every
 // variant and number of splits at 15 shapes in binary32, from [256 x 128 x 64] to [47739 x 860 x 67], and at 20 in bfloat16, up to
 // [9947 x 411 x 1001] and [49035 x 658 x 32]: what is chosen takes 1.01 (bfloat16 1.03) times as long as the best one in the mean.  What
 // matters most is that the workgroups fill whole rounds: binary32 [12544 x 384 x 1536] in 32x32 blocks 80 us
